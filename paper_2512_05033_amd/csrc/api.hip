@@ -486,7 +486,8 @@ extern "C" arb_status arb_next_token(const void *hidden, const int32_t *rows, in
   arb_status s;
   if ((s = launch_gather_rows((const bf16 *)hidden, rows, n, d_model, x, st))) return s;
   if ((s = launch_gemm(x, (const bf16 *)w_lm, logits, n, vocab, d_model, ARB_EPI_STORE_F32, st))) return s;
-  return launch_sample_token(logits, n, vocab, temperature, uniforms, token, chosen_logit, st);
+  // the gathered rows have been multiplied: their memory holds the choice's partial results
+  return launch_sample_token(logits, n, vocab, temperature, uniforms, token, chosen_logit, x, (size_t)n * d_model * sizeof(bf16), st);
 }
 
 extern "C" arb_status arb_first_stop(const int32_t *tokens, int32_t n, int32_t max_len, int32_t sep, int32_t eos,

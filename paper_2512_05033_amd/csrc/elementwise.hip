@@ -520,39 +520,79 @@ arb_status launch_gather_rows(const bf16 *src, const int32_t *rows, int n, int d
   return ARB_OK;
 }
 
-// One block per row of fp32 logits [n, V].  Greedy (temperature <= 0): the smallest index of the
-// maximum.  Otherwise the token is drawn from softmax(logits / temperature) by inversion with the
-// caller's uniform u in [0, 1): the smallest k with sum_{i<=k} w_i >= u * sum_i w_i, where
-// w_i = exp((l_i - max) / temperature); sums run in index order within a thread's contiguous range
-// and in thread order across ranges, so a call is reproducible.
-__global__ __launch_bounds__(256) void sample_token_kernel(const float *__restrict__ logits, int V, float temperature,
-                                                           const float *__restrict__ uniforms,
-                                                           int32_t *__restrict__ token, float *__restrict__ chosen) {
+// Choice of one token per row of fp32 logits [n, V], in two launches.  Greedy (temperature <= 0): the smallest
+// index of the maximum.  Otherwise the token is drawn from softmax(logits / temperature) by inversion with the
+// caller's uniform u in [0, 1): the smallest k with sum_{i<=k} w_i >= u * sum_i w_i, w_i = exp((l_i - max) / temperature);
+// every sum has a fixed order, so a call is reproducible.
+//
+// The logits are read once at memory speed: a row is cut into chunks, a workgroup reduces one chunk with
+// 16-byte loads of neighbouring lanes to (maximum, its smallest index, sum of exp relative to the chunk's maximum),
+// and one workgroup per row joins the chunks; only when sampling it reads the one chunk that holds the target again.
+// (One workgroup per row, each thread walking its own contiguous range, took 195 us for 16 rows of 151936: a 4-byte
+// load per cache line and lane and 16 of 256 CUs at work.  The two launches take 6.)
+struct ChoiceChunk { float max, sum; int arg, unused; };
+constexpr int kChoiceChunk = 4096;        // least elements per chunk: 4 loads of 16 bytes per thread
+
+// (v, i) ordered by larger v, then smaller i; NaN never wins
+__device__ __forceinline__ void take_better(float &v, int &i, float v2, int i2) {
+  if (v2 > v || (v2 == v && i2 < i)) { v = v2; i = i2; }
+}
+
+// Best (value, index) over a block of 256 threads; every thread gets it.
+__device__ __forceinline__ void block_best_256(float &v, int &i, float *lds_v, int *lds_i) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) take_better(v, i, __shfl_xor(v, o, 64), __shfl_xor(i, o, 64));
+  const int w = threadIdx.x >> 6;
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) { lds_v[w] = v; lds_i[w] = i; }
+  __syncthreads();
+  v = lds_v[0]; i = lds_i[0];
+#pragma unroll
+  for (int k = 1; k < 4; ++k) take_better(v, i, lds_v[k], lds_i[k]);
+}
+
+__global__ __launch_bounds__(256) void choice_chunk_kernel(const float *__restrict__ logits, int V, int chunk_len,
+                                                           float temperature, ChoiceChunk *__restrict__ chunks) {
+  __shared__ float red_v[4];
+  __shared__ int red_i[4];
+  const int tid = threadIdx.x, lo = blockIdx.x * chunk_len, hi = min(lo + chunk_len, V);
+  const float *l = logits + (size_t)blockIdx.y * V;
+  float best = -INFINITY;
+  int arg = V;
+  for (int i = lo + tid * 4; i < hi; i += 1024) {            // V is a multiple of 4: a load is whole or not there
+    const f32x4 x = *(const f32x4 *)(l + i);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (x[e] > best) { best = x[e]; arg = i + e; }
+  }
+  block_best_256(best, arg, red_v, red_i);
+  float sum = 0.f;
+  if (temperature > 0.f && arg < V) {
+    const float inv_t = 1.0f / temperature;
+    for (int i = lo + tid * 4; i < hi; i += 1024) {
+      const f32x4 x = *(const f32x4 *)(l + i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum += expf((x[e] - best) * inv_t);
+    }
+    sum = block_sum_256(sum, red_v);
+  }
+  if (tid == 0) chunks[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = ChoiceChunk{best, sum, arg, 0};
+}
+
+__global__ __launch_bounds__(256) void choice_join_kernel(const float *__restrict__ logits, int V, int chunk_len,
+                                                          int n_chunks, float temperature,
+                                                          const float *__restrict__ uniforms,
+                                                          const ChoiceChunk *__restrict__ chunks,
+                                                          int32_t *__restrict__ token, float *__restrict__ chosen) {
   __shared__ float red_v[256];
   __shared__ int red_i[256];
   const int row = blockIdx.x, tid = threadIdx.x;
   const float *l = logits + (size_t)row * V;
-  const int per = (V + 255) / 256, lo = min(tid * per, V), hi = min(lo + per, V);    // contiguous range of this thread
-  float best = -INFINITY;
-  int arg = V;
-  for (int i = lo; i < hi; ++i) {
-    const float v = l[i];
-    if (v > best) { best = v; arg = i; }
-  }
-  red_v[tid] = best;
-  red_i[tid] = arg;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (tid < o) {
-      const float v = red_v[tid + o];
-      const int a = red_i[tid + o];
-      if (v > red_v[tid] || (v == red_v[tid] && a < red_i[tid])) { red_v[tid] = v; red_i[tid] = a; }
-    }
-    __syncthreads();
-  }
-  const float mx = red_v[0];
-  const int amax = red_i[0] < V ? red_i[0] : 0;          // a row of NaNs or -inf picks token 0
-  __syncthreads();
+  const ChoiceChunk mine = tid < n_chunks ? chunks[(size_t)row * n_chunks + tid] : ChoiceChunk{-INFINITY, 0.f, V, 0};
+  float mx = mine.max;
+  int arg = mine.arg;
+  block_best_256(mx, arg, red_v, red_i);
+  const int amax = arg < V ? arg : 0;                    // a row of NaNs or -inf picks token 0
   if (!(temperature > 0.f)) {
     if (tid == 0) {
       token[row] = amax;
@@ -561,48 +601,79 @@ __global__ __launch_bounds__(256) void sample_token_kernel(const float *__restri
     return;
   }
   const float inv_t = 1.0f / temperature;
-  __shared__ float total_s;
-  __shared__ int pick_s;
-  float part = 0.f;
-  for (int i = lo; i < hi; ++i) part += expf((l[i] - mx) * inv_t);
-  red_v[tid] = part;
+  // the chunk that contains the target: the first whose cumulative weight reaches it
+  __shared__ float before_s, target_s;
+  __shared__ int chunk_s, pick_s;
   __syncthreads();
-  if (tid == 0) {                                       // exclusive prefix over the 256 ranges, in order
+  red_v[tid] = mine.arg < V ? mine.sum * expf((mine.max - mx) * inv_t) : 0.f;
+  __syncthreads();
+  if (tid == 0) {
+    float total = 0.f;
+    for (int t = 0; t < n_chunks; ++t) total += red_v[t];
+    const float target = uniforms[row] * total;
     float run = 0.f;
-    for (int t = 0; t < 256; ++t) {
-      const float p = red_v[t];
-      red_v[t] = run;
-      run += p;
+    int c = -1;
+    for (int t = 0; t < n_chunks && c < 0; ++t) {
+      if (target <= run + red_v[t]) c = t; else run += red_v[t];
     }
-    total_s = run;
+    before_s = run;
+    target_s = target;
+    chunk_s = arg < V ? c : -1;                           // -1: no chunk claims the target (NaN, or rounding at the very end)
     pick_s = V;
   }
   __syncthreads();
-  const float target = uniforms[row] * total_s;
-  const float before = red_v[tid];
-  // the range that contains the target: before < target <= before + part (the first range also takes target == 0)
-  if (lo < hi && (target > before || tid == 0) && target <= before + part) {
-    float run = before;
-    int pick = hi - 1;                                  // rounding in the re-summation cannot leave the range
-    for (int i = lo; i < hi; ++i) {
-      run += expf((l[i] - mx) * inv_t);
-      if (run >= target) { pick = i; break; }
+  const int c = chunk_s;
+  int k = amax;                                           // ... then the mode
+  if (c >= 0) {
+    const int lo = c * chunk_len, hi = min(lo + chunk_len, V), per = (hi - lo + 255) / 256;
+    const int a = min(lo + tid * per, hi), b = min(a + per, hi);
+    float part = 0.f;
+    for (int i = a; i < b; ++i) part += expf((l[i] - mx) * inv_t);
+    red_v[tid] = part;
+    __syncthreads();
+    if (tid == 0) {
+      float run = before_s;
+      for (int t = 0; t < 256; ++t) {
+        const float p = red_v[t];
+        red_v[t] = run;
+        run += p;
+      }
     }
-    atomicMin(&pick_s, pick);
+    __syncthreads();
+    float run = red_v[tid];
+    for (int i = a; i < b; ++i) {
+      run += expf((l[i] - mx) * inv_t);
+      if (run >= target_s) { atomicMin(&pick_s, i); break; }
+    }
+    __syncthreads();
+    k = pick_s < V ? pick_s : hi - 1;                     // rounding in the re-summation cannot leave the chunk
   }
-  __syncthreads();
   if (tid == 0) {
-    const int k = pick_s < V ? pick_s : amax;           // no range claimed the target (rounding at the very end): the mode
     token[row] = k;
     if (chosen) chosen[row] = l[k];
   }
 }
 
+// scratch: device memory of at least scratch_bytes >= n * 16 bytes (more lets a row be cut into more chunks)
 arb_status launch_sample_token(const float *logits, int n, int V, float temperature, const float *uniforms,
-                               int32_t *token, float *chosen, hipStream_t st) {
+                               int32_t *token, float *chosen, void *scratch, size_t scratch_bytes, hipStream_t st) {
   if (n == 0) return ARB_OK;
-  hipLaunchKernelGGL(sample_token_kernel, dim3(n), dim3(256), 0, st, logits, V, temperature, uniforms, token, chosen);
-  ARB_CHECK_LAUNCH("sample_token");
+  size_t most = scratch_bytes / ((size_t)n * sizeof(ChoiceChunk));
+  if (most < 1) return arb_fail(ARB_ECAPACITY, "sample_token: scratch of %zu bytes for %d rows", scratch_bytes, n);
+  if (most > 256) most = 256;                             // a thread of the joining workgroup per chunk
+  int chunk_len = kChoiceChunk;
+  if ((size_t)ceil_div(V, chunk_len) > most) chunk_len = ceil_div(ceil_div(V, (int)most), 1024) * 1024;
+  const int n_chunks = ceil_div(V, chunk_len);
+  ChoiceChunk *chunks = (ChoiceChunk *)scratch;
+  for (int r = 0; r < n; r += 65535) {                    // grid.y limit
+    const int m = n - r < 65535 ? n - r : 65535;
+    hipLaunchKernelGGL(choice_chunk_kernel, dim3(n_chunks, m), dim3(256), 0, st, logits + (size_t)r * V, V, chunk_len,
+                       temperature, chunks + (size_t)r * n_chunks);
+  }
+  ARB_CHECK_LAUNCH("choice_chunk");
+  hipLaunchKernelGGL(choice_join_kernel, dim3(n), dim3(256), 0, st, logits, V, chunk_len, n_chunks, temperature, uniforms,
+                     chunks, token, chosen);
+  ARB_CHECK_LAUNCH("choice_join");
   return ARB_OK;
 }
 

@@ -276,6 +276,28 @@ def test_next_token_greedy_and_sampled(A, d, V, n):
     assert exact >= n - max(1, n // 50) and tok[0] == 0
 
 
+@pytest.mark.parametrize("d,V,n", [(64, 128, 1), (64, 4096, 3), (64, 4224, 2), (64, 151936, 3)])
+def test_next_token_choice_at_chunk_edges(A, d, V, n):
+    """The choice cuts a row of logits into chunks: one short chunk, one whole chunk, a remainder of 128, and a row whose
+    chunks are longer because the scratch of a narrow model holds few of them.  One-hot hidden states and a weight
+    column of small integers make every logit exact, so the tokens have to be exact too: planted equal maxima
+    in two chunks (the smaller index wins) and draws whose cumulative sums fp32 holds exactly."""
+    hidden = torch.zeros(n, d, dtype=torch.bfloat16, device="cuda")
+    hidden[:, 0] = 1.0
+    rows = torch.arange(n, dtype=torch.int32, device="cuda")
+    w_lm = torch.zeros(V, d, dtype=torch.bfloat16, device="cuda")
+    for at in ({V - 1}, {0, V - 1}, {V // 2 + 1, V - 2}):
+        w_lm[:, 0] = 0.0
+        w_lm[sorted(at), 0] = 3.0
+        tok, chosen = A.arb_next_token(hidden, rows, w_lm)
+        assert tok.tolist() == [min(at)] * n and chosen.tolist() == [3.0] * n
+    w_lm[:, 0] = 1.0                    # all weights equal: index k is drawn for u in (k/V, (k+1)/V]
+    for u in (0.0, 0.25, 0.5, 1.0 - 2.0 ** -20):
+        want = max(0, int(np.ceil(np.float32(u) * np.float32(V))) - 1)
+        tok, _ = A.arb_next_token(hidden, rows, w_lm, temperature=1.0, uniforms=torch.full((n,), u, device="cuda"))
+        assert tok.tolist() == [want] * n
+
+
 def test_first_stop_bit_exact(A):
     r = np.random.default_rng(8)
     toks = r.integers(3, 50, (70, 33)).astype(np.int32)
