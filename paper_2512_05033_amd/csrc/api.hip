@@ -286,7 +286,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   // chip; their fp32 products (one per split; a single one when not split: a plain store is cheaper
   // in the GEMM epilogue than a read-modify-write of the stream) are added to the residual stream by
   // the norm kernel that follows.
-  const int so = gemm_residual_splits(T, d, c.n_q_heads * c.head_dim), sd = gemm_residual_splits(T, d, c.d_ffn);
+  int so = gemm_residual_splits(T, d, c.n_q_heads * c.head_dim), sd = gemm_residual_splits(T, d, c.d_ffn);
   // The QKV projection is narrow as well; when its tiles leave half the CUs idle it is split along K
   // into fp32 partial products (in `parts`, free at that point) that rope_append adds up, which also
   // spares q and k a rounding.
@@ -298,6 +298,15 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   // 64-row tiles is as fast, and rope_append reads bf16 instead of partial products (1.5B shape, 1024 tokens: -0.8 %)
   if (ceil_div(T, 64) * (m->qkv_rows() / 128) >= 192) sq = 1;
   if (sq < 2) sq = 1;
+  bool qkv_f32 = sq > 1;
+  // Few tokens: the weight-streaming kernel with its own splits; its QKV products stay in fp32 whatever their number.
+  if (const int few = m->w4 ? 0 : gemm_stream_splits(T, m->qkv_rows(), d)) {
+    sq = few < 8 * d / m->qkv_rows() ? few : 8 * d / m->qkv_rows();
+    qkv_f32 = sq >= 1;
+    if (sq < 1) sq = 1;
+  }
+  if (const int few = m->w4 ? 0 : gemm_stream_splits(T, d, c.n_q_heads * c.head_dim)) so = few;
+  if (const int few = m->w4 ? 0 : gemm_stream_splits(T, d, c.d_ffn)) sd = few;
   // one projection: bf16 weights, or packed 4-bit weights with their group scales
   auto project = [&](const bf16 *a, const bf16 *wt, const bf16 *scale, void *out, int N, int K, int epi, int splits,
                      int part, const bf16 *wt_blocked = nullptr) {
@@ -324,7 +333,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_QKV, st);
-      if (sq > 1)
+      if (qkv_f32)
         s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), w.parts, m->qkv_rows(), d, ARB_EPI_STORE_F32, sq, GEMM_PART_ALL);
       else
         s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), w.qkv, m->qkv_rows(), d, ARB_EPI_STORE_BF16, 1, GEMM_PART_ALL);
@@ -333,7 +342,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     {
       TraceScope t(m, ARB_STAGE_ROPE_APPEND, st);
       // the queries leave the rotary kernel multiplied by log2(e)/sqrt(hd) (in fp32, before their one rounding)
-      s = launch_rope_append(w.qkv, w.parts, sq > 1 ? sq : 0, w.cs, w.tok_slot, (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], T, c.n_q_heads,
+      s = launch_rope_append(w.qkv, w.parts, qkv_f32 ? sq : 0, w.cs, w.tok_slot, (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], T, c.n_q_heads,
                              c.n_kv_heads, c.head_dim, attention_q_scale(c.head_dim), st);
     }
     if (s) return s;

@@ -79,6 +79,7 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
 arb_status launch_pack_k_blocked(const bf16 *W, size_t rows, int K, bf16 *packed, hipStream_t st);
 int gemm_large_cols(int M, int N, int K, int epilogue, int splits);   // in units of 256 columns (128 SwiGLU features)
 int gemm_residual_splits(int M, int N, int K);
+int gemm_stream_splits(int M, int N, int K);   // K splits of an fp32 projection on the few-token kernel; 0: another kernel takes it
 
 // attention.hip
 struct AttnPlan {

@@ -188,6 +188,8 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const bf16 *__restrict__ A
 // MI = 32-row MFMA tiles per wave along M: 2 gives the 128x128 tile (4 stages), 1 a 64x128 tile
 // (6 stages) for launches that would otherwise leave more than half of the CUs without a workgroup,
 // 4 a 256x128 tile (3 stages) for launches that are one well-filled round of such tiles.
+// NT_B: the weights are loaded non-temporal, for launches of a single m-tile, where every weight is used once (8B
+// gate/up at 33 rows 50.3 -> 46.6 us); with several m-tiles they meet in L2 and have to stay there.
 #ifndef ARB_RING_K
 #define ARB_RING_K 64
 #endif
@@ -206,8 +208,9 @@ __device__ __forceinline__ int lds_off_ring(int row, int chunk) {   // element o
 
 // s_waitcnt immediates (vmcnt in bits 3:0 and 15:14, lgkmcnt in 11:8, expcnt 6:4 left at "no wait")
 constexpr int waitcnt_vm_lgkm0(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 0x70; }
+constexpr int waitcnt_vm(int vm) { return waitcnt_vm_lgkm0(vm) | 0xF00; }       // lgkmcnt at "no wait" too
 
-template <int EPI, int MI>
+template <int EPI, int MI, bool NT_B = false>
 __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
                                                    void *__restrict__ Cv, int M, int N, int K, int tiles_m,
                                                    int tiles_n, int tile_n0) {
@@ -282,7 +285,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const bf16 *__restric
   auto dma_b = [&](int s, int kt) {
 #pragma unroll
     for (int i = 0; i < B_LOADS; ++i)
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(b_src[i] + (size_t)kt * RK), LDS_PTR(ARB_ST(s) + RBM * RK + (i * 4 + wave_u) * 512), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(b_src[i] + (size_t)kt * RK), LDS_PTR(ARB_ST(s) + RBM * RK + (i * 4 + wave_u) * 512), 16, 0, NT_B ? 2 : 0);
   };
   // The swizzle term of a fragment row depends on frag_row only, so each operand needs one LDS offset
   // per sub-step; MFMA tile and stage are constant displacements from it.
@@ -619,7 +622,185 @@ __global__ __launch_bounds__(256, 1) void gemm256_kernel(const bf16 *__restrict_
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Weight-streaming kernel for few token rows (M <= 32: drafting token by token, a single short step).
+// Such a launch reads every weight once and multiplies it with next to nothing, so it is bound by how many
+// bytes of weights are in flight (a plain read of this memory reaches 6.2 TB/s, 7.0 with non-temporal loads).
+// A workgroup owns 16 RT weight rows and a K range; its four waves deal the range's chunks of 64 k among
+// themselves and each streams its own chunks, weights and activations, through a private ring of D LDS stages: no
+// barrier until the end, when the four sums are added in LDS (fixed order) and stored.  Loads are direct-to-LDS and
+// cover 8 rows x 128 bytes, i.e. whole cache lines: the same loop with fragments loaded straight into registers (four
+// neighbouring lanes on four different rows) stays at 4.1 TB/s.  Weights are loaded non-temporal: each is used once.
+// 16x16x32 MFMAs with the weights as rows and 16 MT tokens as columns; a lane ends with 4 consecutive features of one
+// token.  Ring depth and rows keep a workgroup at 72 to 80 KB (two per CU) where MT allows.
+// Measured at 16 tokens, weights from memory (against the 64- and 128-row tiles): 1.5B shape QKV 3.6 us (6.6),
+// O 3.4 (6.0), gate/up 15.0 (16.8), down 7.7 (11.0), LM head 88 (100); 8B shape gate/up 41 (49), down 21 (24),
+// LM head 188 (256).
+__device__ __forceinline__ int lds_off_stream(int row, int chunk) {   // 128-byte rows; 16 lanes read one chunk of 16 rows
+  return row * 64 + ((chunk ^ ((row >> 1) & 7)) << 3);
+}
+
+template <int EPI, int MT, int RT, int D>
+__global__ __launch_bounds__(256) void gemm_stream_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
+                                                          void *__restrict__ Cv, int M, int N, int K) {
+  constexpr int W = 4;                                  // waves, each with its own chunks of K and its own ring
+  constexpr int STAGE = (RT + MT) * 1024;               // elements of a wave's stage: 16 RT weight rows, 16 MT token rows
+  constexpr int UNUSED = 8;
+  constexpr int LOADS = 2 * (RT + MT);                  // wave-wide 1 KB loads per stage
+  constexpr bool SWIGLU = EPI == ARB_EPI_SWIGLU_BF16;
+  static_assert(D >= 2 && D <= 4 && (!SWIGLU || RT % 2 == 0), "ring depth, gate/up pairs");
+  // one array per stage (the compiler orders LDS reads against in-flight loads by object)
+  __shared__ __attribute__((aligned(16))) bf16 St0[W * STAGE], St1[W * STAGE], St2[D > 2 ? W * STAGE : UNUSED],
+      St3[D > 3 ? W * STAGE : UNUSED];
+#define ARB_ST(s) ((s) == 0 ? St0 : (s) == 1 ? St1 : (s) == 2 ? St2 : St3)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, quarter = lane >> 4, load_row = lane >> 3;
+
+  // K range of this workgroup in chunks of 64, and this wave's share of it: chunks begin + wave, + W, ...
+  const int nk_all = K / 64;
+  const int kt_begin = (int)((long long)nk_all * blockIdx.y / gridDim.y);
+  const int kt_end = (int)((long long)nk_all * (blockIdx.y + 1) / gridDim.y);
+  const int n = (kt_end - kt_begin - wave + W - 1) / W, last = n - 1;
+
+  const bf16 *w_src[2 * RT], *x_src[2 * MT];
+#pragma unroll
+  for (int i = 0; i < 2 * RT; ++i) {
+    const int r = i * 8 + load_row, t = r >> 4;          // tile-local row, its 16-row MFMA tile
+    // SwiGLU: the first half of the tiles are gate rows, the second half the matching up rows; N = F there
+    const int row = SWIGLU ? blockIdx.x * (RT * 8) + (t % (RT / 2)) * 16 + (r & 15) + (t >= RT / 2 ? N : 0)
+                           : blockIdx.x * (RT * 16) + r;
+    w_src[i] = B + (size_t)row * K + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+  }
+#pragma unroll
+  for (int j = 0; j < 2 * MT; ++j) {
+    const int r = j * 8 + load_row;
+    const int m = r < M ? r : M - 1;                      // rows past M re-read the last one; never stored
+    x_src[j] = A + (size_t)m * K + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+  }
+
+  f32x4 acc[RT][MT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int j = 0; j < MT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  auto load = [&](int s, int it) {                        // `it` past the end: the last chunk again, never used
+    const size_t k = (size_t)(kt_begin + wave + min(it, last) * W) * 64;
+    bf16 *dst = ARB_ST(s) + wave * STAGE;
+#pragma unroll
+    for (int i = 0; i < 2 * RT; ++i)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(w_src[i] + k), LDS_PTR(dst + i * 512), 16, 0, 2 /* nt */);
+#pragma unroll
+    for (int j = 0; j < 2 * MT; ++j)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(x_src[j] + k), LDS_PTR(dst + (2 * RT + j) * 512), 16, 0, 0);
+  };
+  auto multiply = [&](int s) {
+    const bf16 *src = ARB_ST(s) + wave * STAGE;
+    bf16x8 wf[2][RT], xf[2][MT];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int off = lds_off_stream(r16, h * 4 + quarter);     // the swizzle does not change when 16 is added to the row
+#pragma unroll
+      for (int i = 0; i < RT; ++i) wf[h][i] = *(const bf16x8 *)&src[i * 1024 + off];
+#pragma unroll
+      for (int j = 0; j < MT; ++j) xf[h][j] = *(const bf16x8 *)&src[(RT + j) * 1024 + off];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][i], xf[h][j], acc[i][j], 0, 0, 0);
+  };
+  if (n > 0) {
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s) load(s, s);
+    int it = 0;
+    for (; it + D <= n; it += D) {
+#pragma unroll
+      for (int s = 0; s < D; ++s) {
+        load((s + D - 1) % D, it + s + D - 1);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS * (D - 1)));       // this stage has landed; the D - 1 behind it may be in flight
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(s);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __builtin_amdgcn_sched_barrier(0);
+    const int rem = n - it;
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s)
+      if (s < rem) multiply(s);
+  }
+  // Sum of the four waves.  The sums go over stage 0: every load has landed (waited for above) and, past the barrier,
+  // every wave is done reading.
+  __syncthreads();
+  float *red = (float *)St0;
+  static_assert(STAGE * sizeof(bf16) >= RT * MT * 256 * sizeof(float), "the sums fit stage 0");
+#undef ARB_ST
+  constexpr int TILE = 64 * 4;                            // floats of one 16x16 tile, in lane order
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int j = 0; j < MT; ++j) *(f32x4 *)&red[((wave * RT + i) * MT + j) * TILE + lane * 4] = acc[i][j];
+  __syncthreads();
+  auto total = [&](int i, int j, int l) {
+    f32x4 s = *(const f32x4 *)&red[(i * MT + j) * TILE + l * 4];
+#pragma unroll
+    for (int w = 1; w < W; ++w) s += *(const f32x4 *)&red[((w * RT + i) * MT + j) * TILE + l * 4];
+    return s;
+  };
+  // D layout of the 16x16 MFMA: lane holds column lane%16 (token) and rows 4*(lane/16) + {0..3} (features)
+  for (int t = tid; t < (SWIGLU ? RT / 2 : RT) * MT * 64; t += 256) {
+    const int l = t & 63, j = (t >> 6) % MT, i = (t >> 6) / MT;
+    const int m = j * 16 + (l & 15);
+    if (m >= M) continue;
+    const f32x4 s = total(i, j, l);
+    if (SWIGLU) {
+      const f32x4 up = total(i + RT / 2, j, l);
+      bf16x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (bf16)(s[e] * __builtin_amdgcn_rcpf(1.0f + __expf(-s[e])) * up[e]);
+      *(bf16x4 *)((bf16 *)Cv + (size_t)m * N + blockIdx.x * (RT * 8) + i * 16 + (l >> 4) * 4) = o;
+    } else {
+      const size_t at = (size_t)m * N + blockIdx.x * (RT * 16) + i * 16 + (l >> 4) * 4;
+      if (EPI == ARB_EPI_STORE_BF16) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (bf16)s[e];
+        *(bf16x4 *)((bf16 *)Cv + at) = o;
+      } else if (EPI == EPI_PARTIAL_F32) {
+        *(f32x4 *)((float *)Cv + (size_t)blockIdx.y * M * N + at) = s;
+      } else {
+        *(f32x4 *)((float *)Cv + at) += s;
+      }
+    }
+  }
+}
+
 }  // namespace
+
+// Whether a launch runs on the weight-streaming kernel, and in which shape: mt = 16-token tiles, rt = 16-row
+// tiles of weights per workgroup.  rows = weight rows (2 F for SwiGLU).
+//  - Up to 16 tokens it beats the tiled kernels at every size measured (figures at the kernel).  Four row tiles instead
+//    of two pay where there are still two workgroups per CU (LM heads: 88 against 95 us on the 1.5B shape, 188 against
+//    201 on the 8B one; gate/up of the 8B shape 43 against 41).
+//  - From 17 to 32 tokens the activations, which every workgroup reads for itself, weigh as much as half of its weights: it
+//    still wins where the tiled kernels are short of workgroups, i.e. on small matrices (up to 16 M weights: the narrow
+//    projections of the 1.5B shape, whose forward of 20 tokens takes 453 us instead of 523), and on a very large matrix with
+//    a long K (8B LM head 204 against 238 us).  In between the tiled kernels win (1.5B gate/up 16.8 against 18.9 us, LM head 97
+//    against 121; a 4-layer pass of 30 tokens on the 8B shape 550 against 579).
+//  - Beyond, the 64-row tile, which shares the activations through LDS, is as fast or faster (64 tokens on the 8B
+//    shape: a 4-layer pass 506 against 648 us; 37 on the 1.5B shape: 555 both).
+static bool stream_shape(int M, int rows, int K, int *mt, int *rt) {
+  if (M <= 0 || M > 32) return false;
+  const bool wide = rows / 64 >= 512 && rows % 64 == 0;
+  *mt = M <= 16 ? 1 : 2;
+  *rt = wide ? 4 : 2;
+  return M <= 16 || (long long)rows * K <= (16 << 20) || (rows >= 65536 && wide && K >= 4096);
+}
 
 // K splits of a projection with fp32 partial products that runs in 256x256 tiles: few token rows
 // (M a little above a multiple of 128 wastes most of a 128-row tile row) and a long K, where 128x128 tiles would
@@ -650,7 +831,23 @@ int gemm_residual_splits(int M, int N, int K) {
   return s < 1 ? 1 : s;
 }
 
+int gemm_stream_splits(int M, int N, int K) {
+  int mt, rt;
+  if (!stream_shape(M, N, K, &mt, &rt)) return 0;
+  // About one workgroup per CU, two where one split would leave CUs without work; at least six chunks of K per split
+  // (the four waves share them) and at most the eight partial products that the workspace holds.  (1.5B shape, 16
+  // tokens: O 4.8 / 3.9 / 3.4 us with 1 / 2 / 4 splits, down 7.7 / 8.4 with 5 / 8; 8B: QKV 15.7 / 12.6 with 1 / 2,
+  // down 32.9 / 22.2 / 21.7 with 1 / 2 / 4.)
+  const int tiles = N / (16 * rt), nk = K / BK;
+  int s = tiles >= 256 ? 1 : tiles > 128 ? 2 : 256 / tiles;
+  if (s > nk / 6) s = nk / 6;
+  if (s > 8) s = 8;
+  return s < 1 ? 1 : s;
+}
+
 int gemm_large_cols(int M, int N, int K, int epilogue, int splits) {
+  int mt, rt;
+  if (stream_shape(M, epilogue == ARB_EPI_SWIGLU_BF16 ? 2 * N : N, K, &mt, &rt)) return 0;
   // Large tiles run one per CU, so they go in whole rounds of 256: as many n-tile columns as fill whole
   // rounds (all of them when the last round would be at least 80 % full), the remaining columns in
   // 128x128 tiles.  With less than one round of large tiles everything runs in small ones.
@@ -681,6 +878,35 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
   if (splits > 1 && epilogue != ARB_EPI_RESIDUAL_F32 && epilogue != ARB_EPI_STORE_F32)
     return arb_fail(ARB_EINVAL, "gemm: split-K needs an fp32 epilogue (partial products)");
   if (splits < 1 || splits > K / BK) return arb_fail(ARB_EINVAL, "gemm: %d splits of %d K-steps", splits, K / BK);
+  const int rows = epilogue == ARB_EPI_SWIGLU_BF16 ? 2 * N : N;
+  int mt, rt;
+  if (stream_shape(M, rows, K, &mt, &rt)) {
+    if (part == GEMM_PART_LARGE) return ARB_OK;
+    const dim3 sgrid(rows / (16 * rt), splits), sblock(256);
+#define ARB_STREAM(E)                                                                                                 \
+  do {                                                                                                                \
+    if (mt == 1 && rt == 2)                                                                                           \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 1, 2, 3>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+    else if (mt == 1)                                                                                                 \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 1, 4, 2>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+    else if (rt == 2)                                                                                                 \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 2, 2, 4>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+    else                                                                                                              \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 2, 4, 3>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+  } while (0)
+    switch (epilogue) {
+      case ARB_EPI_STORE_BF16: ARB_STREAM(ARB_EPI_STORE_BF16); break;
+      case ARB_EPI_RESIDUAL_F32:
+        if (splits > 1) ARB_STREAM(EPI_PARTIAL_F32); else ARB_STREAM(ARB_EPI_RESIDUAL_F32);
+        break;
+      case ARB_EPI_SWIGLU_BF16: ARB_STREAM(ARB_EPI_SWIGLU_BF16); break;
+      case ARB_EPI_STORE_F32: ARB_STREAM(ARB_EPI_STORE_F32); break;
+      default: return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
+    }
+#undef ARB_STREAM
+    ARB_CHECK_LAUNCH("gemm_stream");
+    return ARB_OK;
+  }
   const int big_cols = gemm_large_cols(M, N, K, epilogue, splits);   // n-tile columns given to the large-tile kernel
   if (big_cols > 0 && part != GEMM_PART_SMALL) {
     const int tm = ceil_div(M, LM);
@@ -709,7 +935,9 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
   if (tiles_n == 0 || part == GEMM_PART_LARGE) return ARB_OK;
   const dim3 block(256);
   const bool ring = tiles_m * tiles_n * splits <= 256;      // at most one workgroup per CU: latency-bound
-  const bool half = tiles_m * tiles_n * splits <= 128;      // not even half of the CUs: 64-row tiles
+  // not even half of the CUs: 64-row tiles; also for at most 64 token rows, of which a 128-row tile would waste half
+  // its loads in flight (gate/up of the 1.5B shape at 33 rows 17.6 -> 16.6 us, of the 8B shape 50 -> 46.6)
+  const bool half = tiles_m * tiles_n * splits <= 128 || M <= 64;      // not even half of the CUs: 64-row tiles
   // More than one round of 128-row tiles that is one well-filled round of 256-row tiles (the split-K down
   // projection): the taller tile reads 0.75 KB of LDS per MFMA instead of 1 KB, needs a third less ingest
   // per flop and runs on the deep-ring kernel.
@@ -721,6 +949,8 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
   do {                                                                                                                \
     if (tall)                                                                                                         \
       hipLaunchKernelGGL((gemm_ring_kernel<E, 4>), grid256, block, 0, st, A, B, C, M, N, K, tm256, tiles_n, tile_n0); \
+    else if (half && M <= 64)                                                                                         \
+      hipLaunchKernelGGL((gemm_ring_kernel<E, 1, true>), grid64, block, 0, st, A, B, C, M, N, K, tm64, tiles_n, tile_n0); \
     else if (half)                                                                                                    \
       hipLaunchKernelGGL((gemm_ring_kernel<E, 1>), grid64, block, 0, st, A, B, C, M, N, K, tm64, tiles_n, tile_n0);   \
     else if (ring)                                                                                                    \

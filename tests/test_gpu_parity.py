@@ -95,6 +95,28 @@ def test_gemm_swiglu(A, M, F, K):
     assert got.shape == (M, F) and rel_err(bf16_np(got), ref) < 5e-3
 
 
+@pytest.mark.parametrize("M", [1, 15, 16, 17, 32, 33])
+@pytest.mark.parametrize("N,K", [(128, 64),        # one chunk of k: three of a workgroup's four waves have none
+                                 (128, 320),       # five chunks, less than a turn of any ring for most waves
+                                 (384, 1600),      # 25 chunks: whole turns of the rings and remainders
+                                 (32768, 192)])    # 64 weight rows per workgroup
+def test_gemm_few_tokens(A, M, N, K):
+    """The weight-streaming kernel at the edges of its token tiles (16, 32; 33 goes to the tiled kernel) and of its
+    rings.  Bounds as for the other GEMM tests: half an ulp of bf16 is 2^-9 of the value, fp32 sums of up to 1600 terms
+    stay far below 1e-5 of the largest."""
+    a, b = rand_bf16((M, K), 1.0, 15), rand_bf16((N, K), 0.05, 16)
+    ref = bf16_np(a) @ bf16_np(b).T
+    assert rel_err(bf16_np(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_BF16)), ref) < 4e-3
+    assert rel_err(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
+    h0 = torch.randn(M, N, device="cuda", dtype=torch.float32)
+    h = h0.clone()
+    A.arb_stage_gemm(a, b, A.ARB_EPI_RESIDUAL_F32, out=h)
+    assert rel_err(h.cpu().numpy(), h0.cpu().numpy().astype(np.float64) + ref) < 1e-5
+    F = N // 2
+    got = A.arb_stage_gemm(a, b, A.ARB_EPI_SWIGLU_BF16)
+    assert rel_err(bf16_np(got), O.silu(ref[:, :F]) * ref[:, F:]) < 5e-3
+
+
 @pytest.mark.parametrize("rows,K", [(1, 32), (130, 96), (17920, 1536)])
 def test_pack_k_blocked_bit_exact(A, rows, K):
     w = rand_bf16((rows, K), 1.0, 21)
