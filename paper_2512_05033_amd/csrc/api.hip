@@ -286,7 +286,15 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   // chip; their fp32 products (one per split; a single one when not split: a plain store is cheaper
   // in the GEMM epilogue than a read-modify-write of the stream) are added to the residual stream by
   // the norm kernel that follows.
-  int so = gemm_residual_splits(T, d, c.n_q_heads * c.head_dim), sd = gemm_residual_splits(T, d, c.d_ffn);
+  // 4-bit weights keep one number of splits for all rows.
+  const int hq = c.n_q_heads * c.head_dim;
+  auto residual_plan = [&](int K) {
+    return m->w4 ? GemmPlan{{{0, T, gemm_residual_splits(T, d, K), false}}, 1} : gemm_plan(T, d, K, true);
+  };
+  const GemmPlan plan_o = residual_plan(hq), plan_d = residual_plan(c.d_ffn);
+  auto parts_of = [&](const GemmPlan &p) {
+    return RowParts{p.seg[0].splits, p.seg[p.n - 1].splits, p.seg[0].rows};
+  };
   // The QKV projection is narrow as well; when its tiles leave half the CUs idle it is split along K
   // into fp32 partial products (in `parts`, free at that point) that rope_append adds up, which also
   // spares q and k a rounding.
@@ -305,17 +313,20 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     qkv_f32 = sq >= 1;
     if (sq < 1) sq = 1;
   }
-  if (const int few = m->w4 ? 0 : gemm_stream_splits(T, d, c.n_q_heads * c.head_dim)) so = few;
-  if (const int few = m->w4 ? 0 : gemm_stream_splits(T, d, c.d_ffn)) sd = few;
-  // one projection: bf16 weights, or packed 4-bit weights with their group scales
-  auto project = [&](const bf16 *a, const bf16 *wt, const bf16 *scale, void *out, int N, int K, int epi, int splits,
-                     int part, const bf16 *wt_blocked = nullptr) {
-    if (!m->w4) return launch_gemm(a, wt, out, T, N, K, epi, st, splits, part, wt_blocked);
+  const GemmPlan plan_q = qkv_f32 ? GemmPlan{{{0, T, sq, false}}, 1} : gemm_plan(T, m->qkv_rows(), d, false);
+  // one projection by its plan: bf16 weights, or packed 4-bit weights with their group scales
+  auto project = [&](const bf16 *a, const bf16 *wt, const bf16 *scale, void *out, int N, int K, int epi, const GemmPlan &p) {
+    if (!m->w4) return launch_gemm_plan(p, a, wt, out, T, N, K, epi, st);
+    return launch_gemm_w4(a, (const uint32_t *)wt, scale, out, T, N, K, epi, st, p.seg[0].splits);
+  };
+  auto gate_up = [&](int l, int part) {
+    if (!m->w4) return launch_gemm(w.x, m->wgu[l], w.act, T, c.d_ffn, d, ARB_EPI_SWIGLU_BF16, st, part,
+                                   m->wgu_blocked.empty() ? nullptr : m->wgu_blocked[l]);
     if (part == GEMM_PART_SMALL) return (arb_status)ARB_OK;            // the 4-bit kernel is one launch
-    return launch_gemm_w4(a, (const uint32_t *)wt, scale, out, T, N, K, epi, st, splits);
+    return launch_gemm_w4(w.x, (const uint32_t *)m->wgu[l], m->sgu[l], w.act, T, c.d_ffn, d, ARB_EPI_SWIGLU_BF16, st, 1);
   };
   auto scale_of = [&](const std::vector<const bf16 *> &v, int l) { return m->w4 ? v[l] : (const bf16 *)nullptr; };
-  int pending = 0;
+  RowParts pending{};
   arb_status s;
   if ((s = launch_token_meta(bt->prefix_lens, bt->cu_step_lens, bt->block_tables, B, T, bt->max_blocks_per_seq,
                              c.kv_block, w.tok_pos, w.tok_slot, st)))
@@ -328,15 +339,13 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
         s = launch_embed_rmsnorm(m->embed, bt->token_ids, m->g_attn[0], c.rms_eps, T, d, w.h, w.x, st);
       else
         s = launch_rmsnorm(w.h, w.parts, pending, m->g_attn[l], c.rms_eps, T, d, w.x, st);
-      pending = 0;
+      pending = RowParts{};
     }
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_QKV, st);
-      if (qkv_f32)
-        s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), w.parts, m->qkv_rows(), d, ARB_EPI_STORE_F32, sq, GEMM_PART_ALL);
-      else
-        s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), w.qkv, m->qkv_rows(), d, ARB_EPI_STORE_BF16, 1, GEMM_PART_ALL);
+      s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), qkv_f32 ? (void *)w.parts : (void *)w.qkv, m->qkv_rows(), d,
+                  qkv_f32 ? ARB_EPI_STORE_F32 : ARB_EPI_STORE_BF16, plan_q);
     }
     if (s) return s;
     {
@@ -355,34 +364,31 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_OPROJ, st);
-      s = project(w.attn, m->wo[l], scale_of(m->so, l), w.parts, d, c.n_q_heads * c.head_dim,
-                  so > 1 ? ARB_EPI_RESIDUAL_F32 : ARB_EPI_STORE_F32, so, GEMM_PART_ALL);
-      pending = so;
+      s = project(w.attn, m->wo[l], scale_of(m->so, l), w.parts, d, hq, ARB_EPI_STORE_F32, plan_o);
+      pending = parts_of(plan_o);
     }
     if (s) return s;
     if ((s = launch_rmsnorm(w.h, w.parts, pending, m->g_mlp[l], c.rms_eps, T, d, w.x, st))) return s;
-    pending = 0;
+    pending = RowParts{};
     {
       TraceScope t(m, ARB_STAGE_GATE_UP, st);
       {
         TraceScope large(m, ARB_STAGE_GATE_UP_LARGE, st);
-        s = project(w.x, m->wgu[l], scale_of(m->sgu, l), w.act, c.d_ffn, d, ARB_EPI_SWIGLU_BF16, 1, GEMM_PART_LARGE,
-                    m->wgu_blocked.empty() ? nullptr : m->wgu_blocked[l]);
+        s = gate_up(l, GEMM_PART_LARGE);
       }
-      if (!s) s = project(w.x, m->wgu[l], scale_of(m->sgu, l), w.act, c.d_ffn, d, ARB_EPI_SWIGLU_BF16, 1, GEMM_PART_SMALL);
+      if (!s) s = gate_up(l, GEMM_PART_SMALL);
     }
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_DOWN, st);
-      s = project(w.act, m->wd[l], scale_of(m->sd, l), w.parts, d, c.d_ffn,
-                  sd > 1 ? ARB_EPI_RESIDUAL_F32 : ARB_EPI_STORE_F32, sd, GEMM_PART_ALL);
-      pending = sd;
+      s = project(w.act, m->wd[l], scale_of(m->sd, l), w.parts, d, c.d_ffn, ARB_EPI_STORE_F32, plan_d);
+      pending = parts_of(plan_d);
     }
     if (s) return s;
   }
   if (h_in) {
     // fold the last projection's partial products into the residual stream, then hand it back
-    if (pending && (s = launch_rmsnorm(w.h, w.parts, pending, m->g_final, c.rms_eps, T, d, w.x, st))) return s;
+    if (pending.head && (s = launch_rmsnorm(w.h, w.parts, pending, m->g_final, c.rms_eps, T, d, w.x, st))) return s;
     ARB_CHECK_HIP(hipMemcpyAsync(h_out, w.h, (size_t)T * d * sizeof(float), hipMemcpyDeviceToDevice, st));
     return ARB_OK;
   }
@@ -545,7 +551,7 @@ extern "C" arb_status arb_stage_gemm(const void *A, const void *B, const void *B
                                      int32_t N, int32_t K, int32_t epilogue, void *stream) {
   if (M == 0) return ARB_OK;
   if (!A || !B || !C) return arb_fail(ARB_EINVAL, "arb_stage_gemm: null pointer");
-  return launch_gemm((const bf16 *)A, (const bf16 *)B, C, M, N, K, epilogue, (hipStream_t)stream, 1, GEMM_PART_ALL,
+  return launch_gemm((const bf16 *)A, (const bf16 *)B, C, M, N, K, epilogue, (hipStream_t)stream, GEMM_PART_ALL,
                      (const bf16 *)B_blocked);
 }
 
@@ -603,7 +609,7 @@ extern "C" arb_status arb_stage_rmsnorm(const float *x, const float *g, float ep
   if (T < 0) return arb_fail(ARB_EINVAL, "arb_stage_rmsnorm: T = %d", T);
   if (T == 0) return ARB_OK;
   if (!x || !g || !out) return arb_fail(ARB_EINVAL, "arb_stage_rmsnorm: null pointer");
-  return launch_rmsnorm(const_cast<float *>(x), nullptr, 0, g, eps, T, d, (bf16 *)out, (hipStream_t)stream);
+  return launch_rmsnorm(const_cast<float *>(x), nullptr, RowParts{}, g, eps, T, d, (bf16 *)out, (hipStream_t)stream);
 }
 
 extern "C" arb_status arb_stage_rope_append(const arb_model *m, void *qkv, void *k_pool, void *v_pool,
@@ -653,7 +659,7 @@ extern "C" arb_status arb_stage_norm_pool_head(const float *h, const float *g_fi
   const size_t need = (size_t)batch->total_tokens * sizeof(float);
   if (!ws || ws_bytes < need) return arb_fail(ARB_ECAPACITY, "arb_stage_norm_pool_head: workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t st = (hipStream_t)stream;
-  if (arb_status s = launch_final_norm_head(h, nullptr, 0, g_final, eps, batch->total_tokens, d, w_head, nullptr, (bf16 *)hidden_out,
+  if (arb_status s = launch_final_norm_head(h, nullptr, RowParts{}, g_final, eps, batch->total_tokens, d, w_head, nullptr, (bf16 *)hidden_out,
                                             (float *)ws, st))
     return s;
   return launch_pool_route((const float *)ws, batch->cu_step_lens, batch->batch, b_head, pool, 0, tau, scores, escalate, st);

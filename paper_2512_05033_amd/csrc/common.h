@@ -67,15 +67,26 @@ static __device__ __forceinline__ void tile_of(int logical, int tiles_m, int til
 // ---- launchers implemented in the kernel files (all asynchronous on `st`) ----
 
 // gemm.hip
-// With splits > 1 (residual and fp32-store epilogues) C is not accumulated into: split s writes its fp32
-// partial product to C + s*M*N and the consumer adds the partials up (the norm kernels for the residual
-// stream, rope_append for q/k/v).
-// A launch is up to two kernels: n-tile columns [0, gemm_large_cols) in 256x256 tiles, the rest in
-// 128x128 tiles; `part` restricts the call to one of them.
-enum { GEMM_PART_ALL = 0, GEMM_PART_LARGE = 1, GEMM_PART_SMALL = 2 };
+// A projection is launched over all rows in one go, or as two segments of rows with kernels of their own (gemm_plan).  A
+// segment split along K stores split i's fp32 partial product to C + i*M*N (its rows of it) and the consumer adds
+// the partials up: the norm kernels for the residual stream, rope_append for q/k/v.
+struct GemmSeg {
+  int row0, rows, splits;
+  bool wide;               // the eight-wave 256x256-tile kernel
+};
+struct GemmPlan {
+  GemmSeg seg[2];
+  int n;
+};
+GemmPlan gemm_plan(int M, int N, int K, bool partials);   // partials: fp32 output that may be split along K
+arb_status launch_gemm_plan(const GemmPlan &plan, const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue,
+                            hipStream_t st);
+// The unsplit projection.  SwiGLU and launches with B_blocked are up to two kernels: n-tile columns
+// [0, gemm_large_cols) in 256x256 tiles, the rest in smaller ones; `part` restricts the call to one of them.
 // B_blocked: optional K-blocked copy of B (launch_pack_k_blocked); the 256x256-tile part of the launch reads it instead of B.
+enum { GEMM_PART_ALL = 0, GEMM_PART_LARGE = 1, GEMM_PART_SMALL = 2 };
 arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, hipStream_t st,
-                       int splits = 1, int part = GEMM_PART_ALL, const bf16 *B_blocked = nullptr);
+                       int part = GEMM_PART_ALL, const bf16 *B_blocked = nullptr);
 arb_status launch_pack_k_blocked(const bf16 *W, size_t rows, int K, bf16 *packed, hipStream_t st);
 int gemm_large_cols(int M, int N, int K, int epilogue, int splits);   // in units of 256 columns (128 SwiGLU features)
 int gemm_residual_splits(int M, int N, int K);
@@ -111,15 +122,19 @@ arb_status launch_rope_table(const int32_t *tok_pos, int total_tokens, int head_
                              hipStream_t st);
 arb_status launch_embed_rmsnorm(const bf16 *embed, const int32_t *token_ids, const float *g, float eps, int T, int d,
                                 float *h, bf16 *x, hipStream_t st);
-// parts/n_parts: fp32 partial products [n_parts, T, d] that are first added to h (and h is updated).
-arb_status launch_rmsnorm(float *h, const float *parts, int n_parts, const float *g, float eps, int T, int d, bf16 *x,
+// The fp32 partial products [*, T, d] of a projection that a norm kernel first adds to h (and h is updated): `head` of
+// them for rows below `row`, `tail` for the others (the segments of a GemmPlan).
+struct RowParts {
+  int head, tail, row;
+};
+arb_status launch_rmsnorm(float *h, const float *parts, RowParts n_parts, const float *g, float eps, int T, int d, bf16 *x,
                           hipStream_t st);
 // parts/n_parts: when n_parts > 0 the projection is read as the sum of fp32 partial products
 // [n_parts, T, (Hq+2Hkv)*hd] instead of from qkv; the rotated q is written to qkv (bf16) either way.
 arb_status launch_rope_append(bf16 *qkv, const float *parts, int n_parts, const f32x2 *cs, const int32_t *tok_slot,
                               bf16 *k_pool, bf16 *v_pool, int T, int n_q_heads, int n_kv_heads, int head_dim,
                               float q_scale, hipStream_t st);
-arb_status launch_final_norm_head(const float *h, const float *parts, int n_parts, const float *g, float eps, int T,
+arb_status launch_final_norm_head(const float *h, const float *parts, RowParts n_parts, const float *g, float eps, int T,
                                   int d, const float *w_head, const float *w_head1, bf16 *hidden_out, float *tok_dot,
                                   hipStream_t st);     // w_head1: class-1 row of a two-class head, else null
 arb_status launch_pool_route(const float *tok_dot, const int32_t *cu_step_lens, int batch, float b_head, int pool,

@@ -135,12 +135,12 @@ arb_status launch_rope_table(const int32_t *tok_pos, int total_tokens, int head_
 // sum-of-squares pass and the scaling pass (d <= 256*8*ROW_VECS).
 #define ROW_VECS 4
 
-// With n_parts > 0 the row is first completed by the split-K partial products of
-// the preceding residual projection: h = h_in + sum_s parts[s] (fixed order), and
-// written back through h_out when that is not null.
+// With partial products the row is first completed by those of the preceding residual projection (their number may
+// differ between its head and its tail rows): h = h_in + sum_s parts[s] (fixed order), and written back through
+// h_out when that is not null.
 template <bool EMBED, bool HEAD>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const float *__restrict__ parts,
-                                                      int n_parts, size_t part_stride,
+                                                      RowParts row_parts, size_t part_stride,
                                                       const bf16 *__restrict__ embed,
                                                       const int32_t *__restrict__ token_ids,
                                                       const float *__restrict__ g, float eps, int d,
@@ -149,6 +149,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const f
                                                       const float *__restrict__ w_head1, float *__restrict__ tok_dot) {
   __shared__ float red[4];
   const int row = blockIdx.x, tid = threadIdx.x;
+  const int n_parts = row < row_parts.row ? row_parts.head : row_parts.tail;
   float v[ROW_VECS][8];
   float ss = 0.f;
 #pragma unroll
@@ -250,13 +251,13 @@ arb_status launch_embed_rmsnorm(const bf16 *embed, const int32_t *token_ids, con
   if (T == 0) return ARB_OK;
   if (arb_status s = check_row_width(d)) return s;
   hipLaunchKernelGGL((rmsnorm_kernel<true, false>), dim3(T), dim3(256), 0, st, (const float *)nullptr,
-                     (const float *)nullptr, 0, (size_t)0, embed, token_ids, g, eps, d, h, x, (const float *)nullptr,
+                     (const float *)nullptr, RowParts{}, (size_t)0, embed, token_ids, g, eps, d, h, x, (const float *)nullptr,
                      (const float *)nullptr, (float *)nullptr);
   ARB_CHECK_LAUNCH("embed_rmsnorm");
   return ARB_OK;
 }
 
-arb_status launch_rmsnorm(float *h, const float *parts, int n_parts, const float *g, float eps, int T, int d, bf16 *x,
+arb_status launch_rmsnorm(float *h, const float *parts, RowParts n_parts, const float *g, float eps, int T, int d, bf16 *x,
                           hipStream_t st) {
   if (T == 0) return ARB_OK;
   if (arb_status s = check_row_width(d)) return s;
@@ -267,7 +268,7 @@ arb_status launch_rmsnorm(float *h, const float *parts, int n_parts, const float
   return ARB_OK;
 }
 
-arb_status launch_final_norm_head(const float *h, const float *parts, int n_parts, const float *g, float eps, int T,
+arb_status launch_final_norm_head(const float *h, const float *parts, RowParts n_parts, const float *g, float eps, int T,
                                   int d, const float *w_head, const float *w_head1, bf16 *hidden_out, float *tok_dot,
                                   hipStream_t st) {
   if (T == 0) return ARB_OK;

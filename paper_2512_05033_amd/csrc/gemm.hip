@@ -14,6 +14,8 @@
 // lane ends up holding gate and up of the same (row, feature).
 #include "common.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int BM = 128, BN = 128, BK = 64;
@@ -26,13 +28,13 @@ __device__ __forceinline__ int lds_off(int row, int chunk) {   // element offset
   return row * BK + ((chunk ^ ((row >> 1) & 7)) << 3);
 }
 
-// fp32 store; in a split-K launch split s stores its partial product to C + s*M*N.
+// fp32 store; in a split-K launch split s stores its partial product to C + s * part_stride.
 constexpr int EPI_PARTIAL_F32 = ARB_EPI_STORE_F32;
 
 template <int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
                                                    void *__restrict__ Cv, int M, int N, int K, int tiles_m,
-                                                   int tiles_n, int tile_n0) {
+                                                   int tiles_n, int tile_n0, size_t part_stride) {
   // One array per operand and stage: the compiler orders LDS reads against in-flight direct-to-LDS
   // loads by object, so separate objects let the reads of one stage overlap the loads into the other.
   __shared__ __attribute__((aligned(16))) bf16 As0[LDS_TILE], As1[LDS_TILE], Bs0[LDS_TILE], Bs1[LDS_TILE];
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const bf16 *__restrict__ A
             if (EPI == ARB_EPI_STORE_BF16) {
               ((bf16 *)Cv)[(size_t)m * N + col] = (bf16)acc[i][j][r];
             } else if (EPI == EPI_PARTIAL_F32) {
-              ((float *)Cv)[((size_t)blockIdx.y * M + m) * N + col] = acc[i][j][r];
+              ((float *)Cv)[blockIdx.y * part_stride + (size_t)m * N + col] = acc[i][j][r];
             } else {
               float *dst = (float *)Cv + (size_t)m * N + col;
               *dst += acc[i][j][r];
@@ -213,7 +215,7 @@ constexpr int waitcnt_vm(int vm) { return waitcnt_vm_lgkm0(vm) | 0xF00; }       
 template <int EPI, int MI, bool NT_B = false>
 __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
                                                    void *__restrict__ Cv, int M, int N, int K, int tiles_m,
-                                                   int tiles_n, int tile_n0) {
+                                                   int tiles_n, int tile_n0, size_t part_stride) {
   constexpr int RBM = 64 * MI;                              // rows of the tile
   constexpr int RING_STAGES = ring_stages(MI);
   constexpr int RING_STAGE_ELEMS = (RBM + BN) * RK;         // A rows then B rows
@@ -401,7 +403,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const bf16 *__restric
             if (EPI == ARB_EPI_STORE_BF16) {
               ((bf16 *)Cv)[(size_t)m * N + col] = (bf16)acc[i][j][r];
             } else if (EPI == EPI_PARTIAL_F32) {
-              ((float *)Cv)[((size_t)blockIdx.y * M + m) * N + col] = acc[i][j][r];
+              ((float *)Cv)[blockIdx.y * part_stride + (size_t)m * N + col] = acc[i][j][r];
             } else {
               float *dst = (float *)Cv + (size_t)m * N + col;
               *dst += acc[i][j][r];
@@ -431,9 +433,11 @@ constexpr int LM = 256, LN = 256, LK = 32;
 constexpr int L_TILE = LM * LK;          // elements per operand and stage
 
 
-// BLOCKED: B is the K-blocked copy of the weights, [K/32][rows][32] (arb_pack_k_blocked): the 16 rows of a
-// wave-wide load of one K step are then 1 KB of consecutive memory, whole cache lines, instead of 16 half lines.
-template <int EPI, bool BLOCKED>
+// B is the K-blocked copy of the weights, [K/32][rows][32] (arb_pack_k_blocked): the 16 rows of a wave-wide load of one
+// K step are then 1 KB of consecutive memory, whole cache lines, instead of 16 half lines.  Launches without such a
+// copy go to the eight-wave kernel below; where there is one, this kernel is still the better one on few token rows
+// (gate/up 1024x2x8192x1536 in 256 tiles 47.4 us against 50.6, 512x2x16384x4096 112 against 119) and within 3 % on many.
+template <int EPI>
 __global__ __launch_bounds__(256, 1) void gemm256_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
                                                          void *__restrict__ Cv, int M, int N, int K, int tiles_m,
                                                          int tiles_n) {
@@ -464,8 +468,7 @@ __global__ __launch_bounds__(256, 1) void gemm256_kernel(const bf16 *__restrict_
   // tile_n*128 + (r/64)*32 + r%32 of the gate (r/32 even) or up (odd) half; N = F there.
   const int b_row0 = EPI == ARB_EPI_SWIGLU_BF16 ? tile_n * 128 + (row0 & 31) + ((row0 >> 5) & 1) * N : tile_n * LN + row0;
   const size_t b_rows = EPI == ARB_EPI_SWIGLU_BF16 ? 2 * (size_t)N : (size_t)N;      // rows of the weight matrix
-  const size_t b_row_pitch = BLOCKED ? 32 : (size_t)K;                                  // elements between rows
-  const size_t b_k_pitch = BLOCKED ? b_rows * 32 : (size_t)LK;                          // elements between K steps
+  const size_t b_row_pitch = 32, b_k_pitch = b_rows * 32;                               // elements between rows, K steps
   const size_t b_step = (size_t)(EPI == ARB_EPI_SWIGLU_BF16 ? 32 : 64) * b_row_pitch;
   const bf16 *b_src = B + (size_t)b_row0 * b_row_pitch + chunk * 8;
 
@@ -477,13 +480,7 @@ __global__ __launch_bounds__(256, 1) void gemm256_kernel(const bf16 *__restrict_
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  // K range of this workgroup (the whole of K unless the launch is split along K), in pairs of steps
-  const int pairs_all = K / (2 * LK);
-  const int kt_begin = 2 * (int)((long long)pairs_all * blockIdx.y / gridDim.y);
-  const int nk = 2 * (int)((long long)pairs_all * (blockIdx.y + 1) / gridDim.y) - kt_begin, last = nk - 1;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) a_src[i] += (size_t)kt_begin * LK;
-  b_src += (size_t)kt_begin * b_k_pitch;
+  const int nk = K / LK, last = nk - 1;
   const int frag_row = lane & 31, frag_half = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
 #define ARB_STAGE(base, s) ((s) == 0 ? base##0 : (s) == 1 ? base##1 : (s) == 2 ? base##2 : base##3)
@@ -610,8 +607,8 @@ __global__ __launch_bounds__(256, 1) void gemm256_kernel(const bf16 *__restrict_
           if (m < M) {
             if (EPI == ARB_EPI_STORE_BF16) {
               ((bf16 *)Cv)[(size_t)m * N + col] = (bf16)acc[i][j][r];
-            } else if (EPI == EPI_PARTIAL_F32) {
-              ((float *)Cv)[((size_t)blockIdx.y * M + m) * N + col] = acc[i][j][r];
+            } else if (EPI == ARB_EPI_STORE_F32) {
+              ((float *)Cv)[(size_t)m * N + col] = acc[i][j][r];
             } else {
               float *dst = (float *)Cv + (size_t)m * N + col;
               *dst += acc[i][j][r];
@@ -619,6 +616,280 @@ __global__ __launch_bounds__(256, 1) void gemm256_kernel(const bf16 *__restrict_
           }
         }
       }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Eight-wave large-tile kernel: the 256x256 tile of row-major operands with two waves per SIMD, so that one wave's
+// MFMAs cover the other's LDS reads, barriers and epilogue.  A wave owns 128x64 of the tile as 4x2 MFMA tiles.  K is
+// walked in steps of 64 (every row piece is a whole 128-byte line, which the 32-wide steps of the kernel above only
+// get from a K-blocked copy) through two LDS stages of four regions: the upper and lower half of every wave's rows
+// (A0, A1) and the two 32-column groups of every wave's columns (B0, B1), 16 KB each.
+//
+// A step is four phases of 8 MFMAs per wave: A0 B0, A0 B1, A1 B1, A1 B0.  A fragment register is read again
+// as soon as its last MFMA has been issued (A1 over A0 in the second phase, the next step's A0 and B0 over A1 and
+// B0 in the fourth), so the fragments need 64 registers beside the 128 accumulators and two waves fit a SIMD.  A
+// region is free once every wave has consumed its fragments, one phase after the phase that reads it; the loads of
+// step t+2 go there at once, six phases (1.5 steps, 96 KB in flight) before they are read.  One barrier per phase hands
+// regions over in both directions: behind it every wave's share of the region read next has landed (counted vmcnt) and every
+// wave is done with the region refilled next.  Fragment reads and their waits are inline assembly: left to the
+// compiler, every read would wait for all direct-to-LDS loads in flight.
+//
+// The rate of a full chip is set by its clock under this load, not by the schedule: 256 tiles with K = 14336 run at
+// 1.34 PFLOP/s (1.6 us per step), 192 at 1.14 (1.3 us per step), so three quarters of a round are 85 % as fast as
+// a whole one, and a launch of 144 tiles already beats smaller tiles that fill the chip.  Measured (before: 128x128
+// tiles): down 8208x1536x8960 193 us (262), O 8208x1536x1536 44 (55), down 3001x4096x14336 293 (407), QKV
+// 2048x6144x4096 89 (125).
+constexpr int W_TM = 256, W_TN = 256;                    // tile
+constexpr int W_REGION = 128 * 64;                        // elements of a region
+
+template <int OFF>
+__device__ __forceinline__ void wide_request_a(unsigned addr, bf16x8 &f0, bf16x8 &f1) {       // two MFMA tiles, 32 rows apart
+  asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4"
+               : "=&v"(f0), "=&v"(f1)
+               : "v"(addr), "n"(OFF), "n"(OFF + 32 * 64 * 2)
+               : "memory");
+}
+template <int OFF>
+__device__ __forceinline__ void wide_request_b(unsigned addr, bf16x8 &f) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(f) : "v"(addr), "n"(OFF) : "memory");
+}
+// at most N of this wave's LDS reads are outstanding; naming the fragments keeps their MFMAs behind the wait
+template <int N>
+__device__ __forceinline__ void wide_await(bf16x8 &f0, bf16x8 &f1, bf16x8 &f2) {
+  asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(f0), "+v"(f1), "+v"(f2) : "n"(N) : "memory");
+}
+
+template <int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_wide_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
+                                                           void *__restrict__ Cv, int M, int N, int K, int tiles_m,
+                                                           int tiles_n, size_t part_stride) {
+  __shared__ __attribute__((aligned(1024))) bf16 Regions[8 * W_REGION];    // A [stage][half], then B [stage][group]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  int tile_m, tile_n;
+  tile_of<4>(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tile_m, tile_n);
+  const int m0 = tile_m * W_TM;
+
+  // K range of this workgroup (the whole of K unless the launch is split along K)
+  const int nk_all = K / 64;
+  const int kt_begin = (int)((long long)nk_all * blockIdx.y / gridDim.y);
+  const int nk = (int)((long long)nk_all * (blockIdx.y + 1) / gridDim.y) - kt_begin, last = nk - 1;
+
+  // This wave brings rows [16 wave, 16 wave + 16) of every region, 8 rows of 128 bytes per wave-wide load; the
+  // 16-byte chunks of a row are swizzled by row/2 on the global side.  Region row r of A half h is tile row
+  // (r/64) 128 + 64 h + r%64; region row r of B group j is column (r/32) 64 + 32 j + r%32 of the tile, or for SwiGLU
+  // feature 32 (r/32) + r%32 of the tile's 128, its gate (j = 0) or up (j = 1) row.
+  constexpr bool SWIGLU = EPI == ARB_EPI_SWIGLU_BF16;
+  const size_t k_bytes = (size_t)K * 2;
+  const char *a_base = (const char *)A + (size_t)m0 * k_bytes + (size_t)kt_begin * 128;
+  const char *b_base = (const char *)B + (size_t)tile_n * (SWIGLU ? 128 : W_TN) * k_bytes + (size_t)kt_begin * 128;
+  unsigned a_off[2][2], b_off[2];                         // byte offsets from the tile's first row, < 256 rows
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = wave * 16 + i * 8 + (lane >> 3);
+    const unsigned chunk = (unsigned)(((lane & 7) ^ ((r >> 1) & 7)) * 16);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      int row = (r >> 6) * 128 + h * 64 + (r & 63);
+      row = row < M - m0 ? row : M - 1 - m0;              // tail rows re-read the last row; never stored
+      a_off[h][i] = (unsigned)(row * k_bytes) + chunk;
+    }
+    b_off[i] = (unsigned)((SWIGLU ? r : (r >> 5) * 64 + (r & 31)) * k_bytes) + chunk;
+  }
+  const size_t b_group = (size_t)(SWIGLU ? N : 32) * k_bytes;         // from group 0 to group 1
+  auto load_a = [&](int s, int h, int kt) {               // steps past the end: the last one again, never multiplied
+    const char *src = a_base + (size_t)(kt < last ? kt : last) * 128;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src + a_off[h][i]), LDS_PTR(Regions + (2 * s + h) * W_REGION + (wave * 2 + i) * 512), 16, 0, 0);
+  };
+  auto load_b = [&](int s, int j, int kt) {
+    const char *src = b_base + (size_t)(kt < last ? kt : last) * 128 + (j ? b_group : 0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src + b_off[i]), LDS_PTR(Regions + (4 + 2 * s + j) * W_REGION + (wave * 2 + i) * 512), 16, 0, 0);
+  };
+
+  f32x16 acc[2][2][2];                                    // [A half][32-row tile][B group]
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[h][i][j][r] = 0.f;
+
+  // LDS byte addresses of this lane's fragments of MFMA step kk in stage 0, half / group 0
+  const int frag_row = lane & 31, frag_half = lane >> 5;
+  unsigned a_addr[4], b_addr[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const unsigned o = (unsigned)(uintptr_t)LDS_PTR(Regions) + 2u * (frag_row * 64 + (((2 * kk + frag_half) ^ ((frag_row >> 1) & 7)) << 3));
+    a_addr[kk] = o + 2u * (wm * 64 * 64);
+    b_addr[kk] = o + 2u * (4 * W_REGION + wn * 32 * 64);
+  }
+  bf16x8 fa[2][4], fb[2][4];
+  auto products = [&](auto h_, auto j_, int kk) {
+    constexpr int h = decltype(h_)::value, j = decltype(j_)::value;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][kk], fb[j][kk], acc[h][i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, 0> zero{};
+  constexpr integral_constant<int, 1> one{};
+  constexpr int RB = W_REGION * 2;                        // bytes of a region
+  // The counted waits: 12 reads (A0, B0) are outstanding on entry of phase 0, 4 (B1) of phase 1, 8 (A1) of phase 2.
+  auto phase0 = [&](auto s_) {                            // A0 B0; reads B1
+    constexpr int S = decltype(s_)::value, OFF = (2 * S + 1) * RB;
+    __builtin_amdgcn_sched_barrier(0);
+    wide_await<9>(fa[0][0], fa[1][0], fb[0][0]); products(zero, zero, 0); wide_request_b<OFF>(b_addr[0], fb[1][0]);
+    wide_await<7>(fa[0][1], fa[1][1], fb[0][1]); products(zero, zero, 1); wide_request_b<OFF>(b_addr[1], fb[1][1]);
+    wide_await<5>(fa[0][2], fa[1][2], fb[0][2]); products(zero, zero, 2); wide_request_b<OFF>(b_addr[2], fb[1][2]);
+    wide_await<3>(fa[0][3], fa[1][3], fb[0][3]); products(zero, zero, 3); wide_request_b<OFF>(b_addr[3], fb[1][3]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto phase1 = [&](auto s_) {                            // A0 B1; reads A1 over A0
+    constexpr int S = decltype(s_)::value, OFF = (2 * S + 1) * RB;
+    __builtin_amdgcn_sched_barrier(0);
+    wide_await<3>(fa[0][0], fa[1][0], fb[1][0]); products(zero, one, 0); wide_request_a<OFF>(a_addr[0], fa[0][0], fa[1][0]);
+    wide_await<4>(fa[0][1], fa[1][1], fb[1][1]); products(zero, one, 1); wide_request_a<OFF>(a_addr[1], fa[0][1], fa[1][1]);
+    wide_await<5>(fa[0][2], fa[1][2], fb[1][2]); products(zero, one, 2); wide_request_a<OFF>(a_addr[2], fa[0][2], fa[1][2]);
+    wide_await<6>(fa[0][3], fa[1][3], fb[1][3]); products(zero, one, 3); wide_request_a<OFF>(a_addr[3], fa[0][3], fa[1][3]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto phase2 = [&]() {                                   // A1 B1
+    __builtin_amdgcn_sched_barrier(0);
+    wide_await<6>(fa[0][0], fa[1][0], fb[1][0]); products(one, one, 0);
+    wide_await<4>(fa[0][1], fa[1][1], fb[1][1]); products(one, one, 1);
+    wide_await<2>(fa[0][2], fa[1][2], fb[1][2]); products(one, one, 2);
+    wide_await<0>(fa[0][3], fa[1][3], fb[1][3]); products(one, one, 3);
+  };
+  auto phase3 = [&](auto s_) {                            // A1 B0; reads the next step's A0 and B0 (stage s_) over them
+    constexpr int S = decltype(s_)::value, OFF = 2 * S * RB;
+    __builtin_amdgcn_sched_barrier(0);
+    products(one, zero, 0); wide_request_a<OFF>(a_addr[0], fa[0][0], fa[1][0]); wide_request_b<OFF>(b_addr[0], fb[0][0]);
+    products(one, zero, 1); wide_request_a<OFF>(a_addr[1], fa[0][1], fa[1][1]); wide_request_b<OFF>(b_addr[1], fb[0][1]);
+    products(one, zero, 2); wide_request_a<OFF>(a_addr[2], fa[0][2], fa[1][2]); wide_request_b<OFF>(b_addr[2], fb[0][2]);
+    products(one, zero, 3); wide_request_a<OFF>(a_addr[3], fa[0][3], fa[1][3]); wide_request_b<OFF>(b_addr[3], fb[0][3]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#define ARB_HANDOVER(vm)                               \
+  do {                                                 \
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(vm));        \
+    __builtin_amdgcn_s_barrier();                      \
+    __builtin_amdgcn_sched_barrier(0);                 \
+  } while (0)
+  // Step t out of stage s.  A region is two loads of this wave.  At the end of phase 0 A1(t) has landed (behind it the four
+  // regions of t+1), of phase 2 A0 and B0 of t+1 (behind: B1 A1 of t+1 and A0 B0 B1 of t+2), of phase 3 B1 of t+1
+  // (behind: A1 of t+1 and the four regions of t+2).
+  auto step = [&](auto s_, int t) {
+    constexpr int S = decltype(s_)::value;
+    phase0(s_);
+    ARB_HANDOVER(8);
+    load_a(S, 0, t + 2);
+    load_b(S, 0, t + 2);
+    phase1(s_);
+    ARB_HANDOVER(63);                                     // nothing new is read in phase 2
+    load_b(S, 1, t + 2);
+    phase2();
+    ARB_HANDOVER(10);
+    load_a(S, 1, t + 2);
+    phase3(integral_constant<int, S ^ 1>{});
+    ARB_HANDOVER(10);
+  };
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {                           // in the order the waits count
+    load_a(s, 0, s); load_b(s, 0, s);
+    __builtin_amdgcn_sched_barrier(0);
+    load_b(s, 1, s);
+    __builtin_amdgcn_sched_barrier(0);
+    load_a(s, 1, s);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  ARB_HANDOVER(12);                                       // A0 and B0 of step 0
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    wide_request_a<0>(a_addr[kk], fa[0][kk], fa[1][kk]);
+    wide_request_b<0>(b_addr[kk], fb[0][kk]);
+  }
+  ARB_HANDOVER(10);                                       // B1 of step 0
+  int t = 0;
+  for (; t + 2 < nk; t += 2) {
+    step(zero, t);
+    step(one, t + 1);
+  }
+  // One or two steps are left, and both stages hold what they need: nothing more is requested, so less may be in flight.
+  // (With an odd number of steps the loop's last loads were clamped repeats.)
+  phase0(zero);
+  ARB_HANDOVER(8);
+  phase1(zero);
+  phase2();
+  if (t + 1 < nk) {
+    ARB_HANDOVER(4);
+    phase3(one);
+    ARB_HANDOVER(2);
+    phase0(one);
+    ARB_HANDOVER(0);
+    phase1(one);
+    phase2();
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) products(one, zero, kk);
+#undef ARB_HANDOVER
+  // every fragment read has returned and every load has landed, in all waves, before the LDS is written again
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  __syncthreads();
+
+  // D layout of the 32x32 MFMA: lane holds column lane%32 and rows 8*(r/4) + 4*(lane/32) + r%4.
+  if (SWIGLU) {
+    // through the LDS, 8 KB per wave, to leave in 16-byte pieces of 64-byte rows (a lane's own elements are 2-byte
+    // pieces of 64 rows); chunks are swizzled by row/4 so that the lane halves write different banks
+    bf16 *C = (bf16 *)Cv, *stage = Regions + wave * 4096;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = h * 64 + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
+          const float gte = acc[h][i][0][r], up = acc[h][i][1][r];
+          stage[row * 32 + (((frag_row >> 3) ^ ((row >> 2) & 3)) << 3) + (frag_row & 7)] =
+              (bf16)(gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up);
+        }
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+      const int row = it * 16 + (lane >> 2), chunk = lane & 3;
+      const bf16x8 v = *(const bf16x8 *)&stage[row * 32 + ((chunk ^ ((row >> 2) & 3)) << 3)];
+      const int m = m0 + wm * 128 + row;
+      if (m < M) *(bf16x8 *)(C + (size_t)m * N + tile_n * 128 + wn * 32 + chunk * 8) = v;
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int col = tile_n * W_TN + wn * 64 + j * 32 + frag_row;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int m = m0 + wm * 128 + h * 64 + i * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
+            if (m < M) {
+              if (EPI == ARB_EPI_STORE_BF16) {
+                ((bf16 *)Cv)[(size_t)m * N + col] = (bf16)acc[h][i][j][r];
+              } else if (EPI == EPI_PARTIAL_F32) {
+                ((float *)Cv)[blockIdx.y * part_stride + (size_t)m * N + col] = acc[h][i][j][r];
+              } else {
+                float *dst = (float *)Cv + (size_t)m * N + col;
+                *dst += acc[h][i][j][r];
+              }
+            }
+          }
+        }
   }
 }
 
@@ -642,7 +913,7 @@ __device__ __forceinline__ int lds_off_stream(int row, int chunk) {   // 128-byt
 
 template <int EPI, int MT, int RT, int D>
 __global__ __launch_bounds__(256) void gemm_stream_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
-                                                          void *__restrict__ Cv, int M, int N, int K) {
+                                                          void *__restrict__ Cv, int M, int N, int K, size_t part_stride) {
   constexpr int W = 4;                                  // waves, each with its own chunks of K and its own ring
   constexpr int STAGE = (RT + MT) * 1024;               // elements of a wave's stage: 16 RT weight rows, 16 MT token rows
   constexpr int UNUSED = 8;
@@ -772,7 +1043,7 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(const bf16 *__restrict
         for (int e = 0; e < 4; ++e) o[e] = (bf16)s[e];
         *(bf16x4 *)((bf16 *)Cv + at) = o;
       } else if (EPI == EPI_PARTIAL_F32) {
-        *(f32x4 *)((float *)Cv + (size_t)blockIdx.y * M * N + at) = s;
+        *(f32x4 *)((float *)Cv + blockIdx.y * part_stride + at) = s;
       } else {
         *(f32x4 *)((float *)Cv + at) += s;
       }
@@ -802,23 +1073,8 @@ static bool stream_shape(int M, int rows, int K, int *mt, int *rt) {
   return M <= 16 || (long long)rows * K <= (16 << 20) || (rows >= 65536 && wide && K >= 4096);
 }
 
-// K splits of a projection with fp32 partial products that runs in 256x256 tiles: few token rows
-// (M a little above a multiple of 128 wastes most of a 128-row tile row) and a long K, where 128x128 tiles would
-// be a single under-filled round (more than 256 of them, so no deep-ring kernel either).  0: not such a launch.
-static int gemm_large_splits(int M, int N, int K) {
-  if (M <= 0 || N <= 0 || N % LN != 0 || K < 2048) return 0;
-  const int tiles_small = ceil_div(M, BM) * (N / BN), tm256 = ceil_div(M, 256);
-  if (tiles_small <= 256 || 512 / tiles_small > 1) return 0;                     // ring kernels / split small tiles
-  if (tm256 * (N / BN) >= 192 && tm256 * (N / BN) <= 256) return 0;              // one round of 256x128 ring tiles
-  const int tiles = ceil_div(M, LM) * (N / LN);
-  int s = 256 / tiles;
-  if (s > K / (16 * LK)) s = K / (16 * LK);                                       // at least 16 steps per split
-  if (s > 8) s = 8;
-  return s >= 2 && tiles * s >= 205 ? s : 0;
-}
-
+// K splits of a projection with fp32 partial products on the tiled kernels
 int gemm_residual_splits(int M, int N, int K) {
-  if (const int s = gemm_large_splits(M, N, K)) return s;
   // as many workgroups as are resident at once (two per CU on 256 CUs) without starting a second
   // round, each keeping at least 4 K-steps; the partials cost 8 bytes of traffic per element and
   // split, so no more splits than that (measured on the 1.5B shape: 5 beats 4 and 6 for K = 8960).
@@ -852,32 +1108,98 @@ int gemm_large_cols(int M, int N, int K, int epilogue, int splits) {
   // rounds (all of them when the last round would be at least 80 % full), the remaining columns in
   // 128x128 tiles.  With less than one round of large tiles everything runs in small ones.
   const int big_n = epilogue == ARB_EPI_SWIGLU_BF16 ? 128 : LN;       // a large n-tile is two small ones
-  if (splits > 1 && (epilogue == ARB_EPI_RESIDUAL_F32 || epilogue == ARB_EPI_STORE_F32) &&
-      splits == gemm_large_splits(M, N, K))
-    return N / LN;                                                     // split-K partial products in large tiles
   if (splits != 1 || M <= 0 || N <= 0 || N % big_n != 0) return 0;
   const int tm = ceil_div(M, LM), tn = N / big_n, total = tm * tn, tail = total % 256;
   if (total < 205) return 0;
   return 5 * tail >= 4 * 256 || tail == 0 ? tn : (total - tail) / tm;
 }
 
-arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, hipStream_t st,
-                       int splits, int part, const bf16 *B_blocked) {
-  if (M == 0) return ARB_OK;
-  if (M < 0 || N <= 0 || K <= 0) return arb_fail(ARB_EINVAL, "gemm: M=%d N=%d K=%d", M, N, K);
-  if (K % BK != 0) return arb_fail(ARB_EUNSUPPORTED, "gemm: K=%d is not a multiple of %d", K, BK);
-  const int tiles_m = ceil_div(M, BM);
-  int tiles_n;
-  if (epilogue == ARB_EPI_SWIGLU_BF16) {
-    if (N % 64 != 0) return arb_fail(ARB_EUNSUPPORTED, "gemm: SwiGLU width %d is not a multiple of 64", N);
-    tiles_n = N / 64;
-  } else {
-    if (N % BN != 0) return arb_fail(ARB_EUNSUPPORTED, "gemm: N=%d is not a multiple of %d", N, BN);
-    tiles_n = N / BN;
+// Time estimates in us for a launch of m rows with fp32 (or bf16) output, from which the planner below chooses.  Both have
+// the form steps x time per step + fixed + what the partial products cost to write here and read in the consumer.  Time
+// per step of 64 k, measured on launches that fill one round of their kernel: 64x128 tiles 0.45, 128x128 one per CU
+// 0.67, two per CU 1.0, 256x128 0.93; 256x256 tiles 1.17 up to half of the CUs, 1.31 at three quarters, 1.59
+// with all (the clock).
+static double traffic_us(int m, int N, int splits, int bytes) { return (double)m * N * bytes * (2 * splits - 1) / 5.0e6; }
+static double tiled_us(int m, int N, int K, int splits, int bytes) {
+  const int t128 = ceil_div(m, BM) * (N / BN) * splits, t64 = ceil_div(m, 64) * (N / BN) * splits,
+            t256 = ceil_div(m, 256) * (N / BN) * splits;
+  double step;
+  if (t128 <= 128 || m <= 64) step = 0.45 * ceil_div(t64, 256);
+  else if (t128 <= 256) step = 0.67;
+  else if (t256 >= 192 && t256 <= 256) step = 0.93;
+  else step = (t128 / 512) * 1.0 + (t128 % 512 == 0 ? 0.0 : t128 % 512 <= 256 ? 0.67 : 0.95);
+  return step * (K / BK) / splits + 5.0 + traffic_us(m, N, splits, bytes);
+}
+static double wide_us(int m, int N, int K, int splits, int bytes) {
+  const double f = ceil_div(m, W_TM) * (N / W_TN) * splits / 256.0;          // at most one round
+  return (f <= 0.5 ? 1.17 : 1.17 + 0.85 * (f - 0.5)) * (K / BK) / splits + 5.0 + traffic_us(m, N, splits, bytes);
+}
+
+// How a projection without the SwiGLU epilogue is launched.  Rows that make up whole rounds of 256 large tiles go to the
+// eight-wave kernel unsplit.  The rows left over (all of them, where there is no whole round) are a launch of their own,
+// because what suits them is another kernel or another split of K: it goes to the eight-wave kernel with the number of
+// splits that fills its round best, or to the tiled kernels, or (a few rows) to the weight-streaming kernel, whichever is
+// estimated to be the fastest.  `partials`: fp32 output that may come as partial products.  (Down 6144x4096x14336:
+// one launch of 384 tiles 635 us; 256 + 128 tiles in two K splits 550.  4943x4096x14336: 619 us in 320 tiles, 568 in
+// 128x128 tiles; 256 + 64 in four splits 465.)
+GemmPlan gemm_plan(int M, int N, int K, bool partials) {
+  GemmPlan p{};
+  int row = 0;
+  const int bytes = partials ? 4 : 2;
+  int mt, rt;
+  if (M > 64 && N % W_TN == 0 && N / W_TN <= 256 && !stream_shape(M, N, K, &mt, &rt)) {
+    const int tn = N / W_TN, per_round = 256 / tn, whole = ceil_div(M, W_TM) / per_round * per_round;
+    if (whole > 0) {
+      row = whole * W_TM < M ? whole * W_TM : M;
+      p.seg[p.n++] = GemmSeg{0, row, 1, true};
+    }
   }
-  if (splits > 1 && epilogue != ARB_EPI_RESIDUAL_F32 && epilogue != ARB_EPI_STORE_F32)
-    return arb_fail(ARB_EINVAL, "gemm: split-K needs an fp32 epilogue (partial products)");
-  if (splits < 1 || splits > K / BK) return arb_fail(ARB_EINVAL, "gemm: %d splits of %d K-steps", splits, K / BK);
+  const int m = M - row;
+  if (m <= 0) return p;
+  GemmSeg rest{row, m, 1, false};
+  if (stream_shape(m, N, K, &mt, &rt)) {
+    if (partials) rest.splits = gemm_stream_splits(m, N, K);
+  } else {
+    if (partials) rest.splits = gemm_residual_splits(m, N, K);
+    double best = tiled_us(m, N, K, rest.splits, bytes);
+    const int tiles = N % W_TN == 0 ? ceil_div(m, W_TM) * (N / W_TN) : 0;
+    for (int s = 1; tiles > 0 && tiles * s <= 256 && s <= (partials ? 8 : 1) && K / BK / s >= 8; ++s) {
+      const double t = wide_us(m, N, K, s, bytes);
+      if (t < best) {
+        best = t;
+        rest.splits = s;
+        rest.wide = true;
+      }
+    }
+  }
+  p.seg[p.n++] = rest;
+  return p;
+}
+
+static arb_status launch_wide(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, hipStream_t st,
+                              int splits, int tiles_n, size_t part_stride) {
+  const int tm = ceil_div(M, W_TM);
+  const dim3 grid(tm * tiles_n, splits), block(512);
+#define ARB_WIDE(E) hipLaunchKernelGGL((gemm_wide_kernel<E>), grid, block, 0, st, A, B, C, M, N, K, tm, tiles_n, part_stride)
+  switch (epilogue) {
+    case ARB_EPI_STORE_BF16: ARB_WIDE(ARB_EPI_STORE_BF16); break;
+    case ARB_EPI_RESIDUAL_F32:
+      if (splits > 1) ARB_WIDE(EPI_PARTIAL_F32); else ARB_WIDE(ARB_EPI_RESIDUAL_F32);
+      break;
+    case ARB_EPI_STORE_F32: ARB_WIDE(ARB_EPI_STORE_F32); break;
+    case ARB_EPI_SWIGLU_BF16: ARB_WIDE(ARB_EPI_SWIGLU_BF16); break;
+    default: return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
+  }
+#undef ARB_WIDE
+  ARB_CHECK_LAUNCH("gemm_wide");
+  return ARB_OK;
+}
+
+// One launch that covers all rows: the weight-streaming kernel, or up to two tiled kernels side by side.
+static arb_status launch_tiles(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, hipStream_t st,
+                               int splits, int part, const bf16 *B_blocked, size_t part_stride) {
+  const int tiles_m = ceil_div(M, BM);
+  int tiles_n = epilogue == ARB_EPI_SWIGLU_BF16 ? N / 64 : N / BN;
   const int rows = epilogue == ARB_EPI_SWIGLU_BF16 ? 2 * N : N;
   int mt, rt;
   if (stream_shape(M, rows, K, &mt, &rt)) {
@@ -886,13 +1208,13 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
 #define ARB_STREAM(E)                                                                                                 \
   do {                                                                                                                \
     if (mt == 1 && rt == 2)                                                                                           \
-      hipLaunchKernelGGL((gemm_stream_kernel<E, 1, 2, 3>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 1, 2, 3>), sgrid, sblock, 0, st, A, B, C, M, N, K, part_stride);      \
     else if (mt == 1)                                                                                                 \
-      hipLaunchKernelGGL((gemm_stream_kernel<E, 1, 4, 2>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 1, 4, 2>), sgrid, sblock, 0, st, A, B, C, M, N, K, part_stride);      \
     else if (rt == 2)                                                                                                 \
-      hipLaunchKernelGGL((gemm_stream_kernel<E, 2, 2, 4>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 2, 2, 4>), sgrid, sblock, 0, st, A, B, C, M, N, K, part_stride);      \
     else                                                                                                              \
-      hipLaunchKernelGGL((gemm_stream_kernel<E, 2, 4, 3>), sgrid, sblock, 0, st, A, B, C, M, N, K);                   \
+      hipLaunchKernelGGL((gemm_stream_kernel<E, 2, 4, 3>), sgrid, sblock, 0, st, A, B, C, M, N, K, part_stride);      \
   } while (0)
     switch (epilogue) {
       case ARB_EPI_STORE_BF16: ARB_STREAM(ARB_EPI_STORE_BF16); break;
@@ -909,26 +1231,22 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
   }
   const int big_cols = gemm_large_cols(M, N, K, epilogue, splits);   // n-tile columns given to the large-tile kernel
   if (big_cols > 0 && part != GEMM_PART_SMALL) {
-    const int tm = ceil_div(M, LM);
-    const dim3 bgrid(tm * big_cols, splits), bblock(256);
-#define ARB_BIG(E)                                                                                                     \
-  do {                                                                                                                 \
-    if (B_blocked)                                                                                                     \
-      hipLaunchKernelGGL((gemm256_kernel<E, true>), bgrid, bblock, 0, st, A, B_blocked, C, M, N, K, tm, big_cols);     \
-    else                                                                                                               \
-      hipLaunchKernelGGL((gemm256_kernel<E, false>), bgrid, bblock, 0, st, A, B, C, M, N, K, tm, big_cols);            \
-  } while (0)
-    switch (epilogue) {
-      case ARB_EPI_STORE_BF16: ARB_BIG(ARB_EPI_STORE_BF16); break;
-      case ARB_EPI_RESIDUAL_F32:
-        if (splits > 1) ARB_BIG(EPI_PARTIAL_F32); else ARB_BIG(ARB_EPI_RESIDUAL_F32);
-        break;
-      case ARB_EPI_STORE_F32: ARB_BIG(ARB_EPI_STORE_F32); break;
-      case ARB_EPI_SWIGLU_BF16: ARB_BIG(ARB_EPI_SWIGLU_BF16); break;
-      default: return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
-    }
+    if (!B_blocked) {
+      if (arb_status s = launch_wide(A, B, C, M, N, K, epilogue, st, splits, big_cols, part_stride)) return s;
+    } else {
+      const int tm = ceil_div(M, LM);
+      const dim3 bgrid(tm * big_cols), bblock(256);
+#define ARB_BIG(E) hipLaunchKernelGGL((gemm256_kernel<E>), bgrid, bblock, 0, st, A, B_blocked, C, M, N, K, tm, big_cols)
+      switch (epilogue) {
+        case ARB_EPI_STORE_BF16: ARB_BIG(ARB_EPI_STORE_BF16); break;
+        case ARB_EPI_RESIDUAL_F32: ARB_BIG(ARB_EPI_RESIDUAL_F32); break;
+        case ARB_EPI_STORE_F32: ARB_BIG(ARB_EPI_STORE_F32); break;
+        case ARB_EPI_SWIGLU_BF16: ARB_BIG(ARB_EPI_SWIGLU_BF16); break;
+        default: return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
+      }
 #undef ARB_BIG
-    ARB_CHECK_LAUNCH("gemm256");
+      ARB_CHECK_LAUNCH("gemm256");
+    }
   }
   const int tile_n0 = big_cols * 2;                   // small n-tiles covered by the large-tile launch
   tiles_n -= tile_n0;
@@ -948,15 +1266,15 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
 #define ARB_SMALL(E)                                                                                                  \
   do {                                                                                                                \
     if (tall)                                                                                                         \
-      hipLaunchKernelGGL((gemm_ring_kernel<E, 4>), grid256, block, 0, st, A, B, C, M, N, K, tm256, tiles_n, tile_n0); \
+      hipLaunchKernelGGL((gemm_ring_kernel<E, 4>), grid256, block, 0, st, A, B, C, M, N, K, tm256, tiles_n, tile_n0, part_stride); \
     else if (half && M <= 64)                                                                                         \
-      hipLaunchKernelGGL((gemm_ring_kernel<E, 1, true>), grid64, block, 0, st, A, B, C, M, N, K, tm64, tiles_n, tile_n0); \
+      hipLaunchKernelGGL((gemm_ring_kernel<E, 1, true>), grid64, block, 0, st, A, B, C, M, N, K, tm64, tiles_n, tile_n0, part_stride); \
     else if (half)                                                                                                    \
-      hipLaunchKernelGGL((gemm_ring_kernel<E, 1>), grid64, block, 0, st, A, B, C, M, N, K, tm64, tiles_n, tile_n0);   \
+      hipLaunchKernelGGL((gemm_ring_kernel<E, 1>), grid64, block, 0, st, A, B, C, M, N, K, tm64, tiles_n, tile_n0, part_stride);   \
     else if (ring)                                                                                                    \
-      hipLaunchKernelGGL((gemm_ring_kernel<E, 2>), grid, block, 0, st, A, B, C, M, N, K, tiles_m, tiles_n, tile_n0);  \
+      hipLaunchKernelGGL((gemm_ring_kernel<E, 2>), grid, block, 0, st, A, B, C, M, N, K, tiles_m, tiles_n, tile_n0, part_stride);  \
     else                                                                                                              \
-      hipLaunchKernelGGL((gemm_kernel<E>), grid, block, 0, st, A, B, C, M, N, K, tiles_m, tiles_n, tile_n0);          \
+      hipLaunchKernelGGL((gemm_kernel<E>), grid, block, 0, st, A, B, C, M, N, K, tiles_m, tiles_n, tile_n0, part_stride);          \
   } while (0)
   switch (epilogue) {
     case ARB_EPI_STORE_BF16: ARB_SMALL(ARB_EPI_STORE_BF16); break;
@@ -970,6 +1288,35 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
 #undef ARB_SMALL
   ARB_CHECK_LAUNCH("gemm");
   return ARB_OK;
+}
+
+arb_status launch_gemm_plan(const GemmPlan &plan, const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue,
+                            hipStream_t st) {
+  const size_t elem = epilogue == ARB_EPI_STORE_BF16 ? sizeof(bf16) : sizeof(float), part_stride = (size_t)M * N;
+  for (int i = 0; i < plan.n; ++i) {
+    const GemmSeg &g = plan.seg[i];
+    const bf16 *a = A + (size_t)g.row0 * K;
+    void *c = (char *)C + (size_t)g.row0 * N * elem;
+    const arb_status s = g.wide ? launch_wide(a, B, c, g.rows, N, K, epilogue, st, g.splits, N / W_TN, part_stride)
+                                : launch_tiles(a, B, c, g.rows, N, K, epilogue, st, g.splits, GEMM_PART_ALL, nullptr, part_stride);
+    if (s) return s;
+  }
+  return ARB_OK;
+}
+
+arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, hipStream_t st, int part,
+                       const bf16 *B_blocked) {
+  if (M == 0) return ARB_OK;
+  if (M < 0 || N <= 0 || K <= 0) return arb_fail(ARB_EINVAL, "gemm: M=%d N=%d K=%d", M, N, K);
+  if (K % BK != 0) return arb_fail(ARB_EUNSUPPORTED, "gemm: K=%d is not a multiple of %d", K, BK);
+  if (epilogue == ARB_EPI_SWIGLU_BF16) {
+    if (N % 64 != 0) return arb_fail(ARB_EUNSUPPORTED, "gemm: SwiGLU width %d is not a multiple of 64", N);
+  } else {
+    if (N % BN != 0) return arb_fail(ARB_EUNSUPPORTED, "gemm: N=%d is not a multiple of %d", N, BN);
+    if (epilogue < 0 || epilogue > ARB_EPI_STORE_F32) return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
+    if (!B_blocked) return launch_gemm_plan(gemm_plan(M, N, K, false), A, B, C, M, N, K, epilogue, st);
+  }
+  return launch_tiles(A, B, C, M, N, K, epilogue, st, 1, part, B_blocked, 0);
 }
 
 // packed[(kb * rows + r) * 32 + j] = W[r][kb * 32 + j]: one thread per 16-byte chunk

@@ -117,6 +117,42 @@ def test_gemm_few_tokens(A, M, N, K):
     assert rel_err(bf16_np(got), O.silu(ref[:, :F]) * ref[:, F:]) < 5e-3
 
 
+@pytest.mark.parametrize("M,N,K", [(4096, 4096, 64), (4000, 4096, 128),      # one round of 256 large tiles, one and two steps of K
+                                   (4097, 4096, 192), (4111, 4096, 320),      # ... and 1 or 15 rows left for another kernel
+                                   (8208, 2048, 256), (2304, 6144, 448)])     # 32 and 10 tile rows per round
+def test_gemm_eight_wave_kernel(A, M, N, K):
+    """Whole rounds of 256x256 tiles, ragged last tile rows, numbers of K steps around the two-stage pipeline's prologue
+    and drain.  Bounds as above."""
+    a, b = rand_bf16((M, K), 1.0, 17), rand_bf16((N, K), 0.05, 18)
+    ref = bf16_np(a) @ bf16_np(b).T
+    assert rel_err(bf16_np(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_BF16)), ref) < 4e-3
+    assert rel_err(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
+    h0 = torch.randn(M, N, device="cuda", dtype=torch.float32)
+    h = h0.clone()
+    A.arb_stage_gemm(a, b, A.ARB_EPI_RESIDUAL_F32, out=h)
+    assert rel_err(h.cpu().numpy(), h0.cpu().numpy().astype(np.float64) + ref) < 1e-5
+
+
+@pytest.mark.parametrize("steps", [[3000, 1200],           # 4096 rows in one round, 104 rows left: other tiles, several splits of K
+                                   [4097, 16],             # 17 rows left for the weight-streaming kernel
+                                   [1300, 250]])           # no whole round: one split launch of large tiles
+def test_layer_in_two_row_segments(A, steps):
+    """A projection whose rows go to two kernels (with their own numbers of partial products, which the norms add up)
+    gives every sequence what it gets when it is alone, i.e. on other kernels.  Each of the two is a bf16 result with an
+    error of the added term well below the stated 2e-2 (0.9 % on this shape), so that is what they may differ by."""
+    m = replace(W.TARGET_8B, n_layers=1, vocab=256)
+    wl, batch = _ragged_batch(m, [0] * len(steps), steps)
+    model = H().make_model(m, W.make_weights(m, 23, "cuda"))
+    ks, vs = W.make_kv_pools(wl, batch, "cuda")
+    h_in = torch.randn(batch.total_tokens, m.d_model, device="cuda", dtype=torch.float32)
+    run = lambda bt, h: A.arb_stage_layers(model, A.KVCache(ks, vs), H().device_batch(bt), 0, 1, h.contiguous()) - h
+    both = run(batch, h_in)
+    for b, (lo, hi) in enumerate(zip(batch.cu_step_lens, batch.cu_step_lens[1:])):
+        alone = run(batch.select([b]), h_in[lo:hi])
+        assert rel_err(both[lo:hi].cpu().numpy(), alone.double().cpu().numpy()) < HIDDEN_TOL
+    model.close()
+
+
 @pytest.mark.parametrize("rows,K", [(1, 32), (130, 96), (17920, 1536)])
 def test_pack_k_blocked_bit_exact(A, rows, K):
     w = rand_bf16((rows, K), 1.0, 21)
