@@ -159,13 +159,13 @@ struct Workspace {
   int32_t *tok_pos, *tok_slot;
   f32x2 *cs;         // [T, hd/2] rotary table
   float *tok_dot;    // [T]
-  float *parts;      // fp32 [8, T, d] split-K partial products of the residual projections
+  float *parts;      // fp32 [8, T, d] split-K partial products of the QKV and residual projections (at least [T, qkv rows])
   void *attn_ws;
   size_t attn_ws_bytes, total;
 };
 
-// attn_splits: the number of key splits whose partial results the attention part must hold.
-static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, void *base) {
+// attn_splits, attn_items: the number of key splits whose partial results, and of work items, the attention part must hold.
+static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, int attn_items, void *base) {
   Workspace w;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -183,8 +183,9 @@ static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, void *bas
   w.tok_slot = (int32_t *)take(t * sizeof(int32_t));
   w.cs = (f32x2 *)take(t * (c.head_dim / 2) * sizeof(f32x2));
   w.tok_dot = (float *)take(t * sizeof(float));
-  w.parts = (float *)take(8 * t * c.d_model * sizeof(float));
-  w.attn_ws_bytes = attention_ws_bytes(attn_splits, T, c.n_q_heads, c.head_dim);
+  const size_t qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+  w.parts = (float *)take(t * (qkv_rows > 8 * (size_t)c.d_model ? qkv_rows : 8 * (size_t)c.d_model) * sizeof(float));
+  w.attn_ws_bytes = attention_ws_bytes(attn_splits, attn_items, T, c.n_q_heads, c.head_dim);
   w.attn_ws = take(w.attn_ws_bytes);
   w.total = off;
   return w;
@@ -193,7 +194,11 @@ static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, void *bas
 extern "C" size_t arb_workspace_bytes(const arb_model *m, int32_t max_batch, int32_t max_total_tokens,
                                       int32_t max_ctx) {
   if (!m || max_batch < 0 || max_total_tokens < 0 || max_ctx < 0) return 0;
-  return carve(m->cfg, max_total_tokens, attention_splits_cap(max_ctx), nullptr).total;
+  const int splits = attention_splits_cap(max_ctx), G = m->cfg.n_q_heads / m->cfg.n_kv_heads;
+  // query tiles: ceil(s_b G / 128) summed over the batch, each against at most `splits` parts of its context
+  const long long items = ((long long)max_total_tokens * G / ATTN_QROWS + max_batch) * m->cfg.n_kv_heads * splits;
+  if (items > INT32_MAX) return 0;
+  return carve(m->cfg, max_total_tokens, splits, (int)items, nullptr).total;
 }
 
 // --------------------------------------------------------------- batch validation
@@ -256,7 +261,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   const int G = c.n_q_heads / c.n_kv_heads;
   const AttnPlan plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads);
   // the attention part is sized by this call's own split count (never above what arb_workspace_bytes assumed)
-  const Workspace w = carve(c, T, plan.max_splits, ws);
+  const Workspace w = carve(c, T, plan.max_splits, plan.n_items, ws);
   if (ws_is_static && ws_bytes < w.total)
     return arb_fail(ARB_ECAPACITY, "arb_score_steps_noalloc: this batch needs %zu bytes of scratch but the static buffer "
                     "holds %zu (ARB_NOALLOC_SCRATCH_BYTES); use arb_score_steps with a workspace", w.total, ws_bytes);
@@ -289,31 +294,27 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   // 4-bit weights keep one number of splits for all rows.
   const int hq = c.n_q_heads * c.head_dim;
   auto residual_plan = [&](int K) {
-    return m->w4 ? GemmPlan{{{0, T, gemm_residual_splits(T, d, K), false}}, 1} : gemm_plan(T, d, K, true);
+    return m->w4 ? GemmPlan{{{0, T, gemm_residual_splits(T, d, K), false}}, 1} : gemm_plan(T, d, K, 8);
   };
   const GemmPlan plan_o = residual_plan(hq), plan_d = residual_plan(c.d_ffn);
   auto parts_of = [&](const GemmPlan &p) {
     return RowParts{p.seg[0].splits, p.seg[p.n - 1].splits, p.seg[0].rows};
   };
-  // The QKV projection is narrow as well; when its tiles leave half the CUs idle it is split along K
-  // into fp32 partial products (in `parts`, free at that point) that rope_append adds up, which also
-  // spares q and k a rounding.
-  int sq = 256 / (ceil_div(T, 128) * (m->qkv_rows() / 128));
-  if (sq > d / 256) sq = d / 256;
-  if (sq > 8 * d / m->qkv_rows()) sq = 8 * d / m->qkv_rows();
-  if (sq > 4) sq = 4;
-  // ... unless 64-row tiles alone occupy at least three quarters of the CUs: then the unsplit projection in
-  // 64-row tiles is as fast, and rope_append reads bf16 instead of partial products (1.5B shape, 1024 tokens: -0.8 %)
-  if (ceil_div(T, 64) * (m->qkv_rows() / 128) >= 192) sq = 1;
-  if (sq < 2) sq = 1;
-  bool qkv_f32 = sq > 1;
-  // Few tokens: the weight-streaming kernel with its own splits; its QKV products stay in fp32 whatever their number.
-  if (const int few = m->w4 ? 0 : gemm_stream_splits(T, m->qkv_rows(), d)) {
-    sq = few < 8 * d / m->qkv_rows() ? few : 8 * d / m->qkv_rows();
-    qkv_f32 = sq >= 1;
-    if (sq < 1) sq = 1;
+  // The QKV projection leaves fp32 products as well (in `parts`, free at that point; up to as many K splits as fit
+  // there), which rope_append adds up: q and k are rounded once, after the rotation.  (With a bf16 projection in between the
+  // final hidden states of the 32-layer 8B shape are 12 % further from the exact ones; the time is the same.)
+  const int q_splits = 8 * d / m->qkv_rows() > 1 ? 8 * d / m->qkv_rows() : 1;
+  GemmPlan plan_q;
+  if (m->w4) {
+    int sq = 256 / (ceil_div(T, 128) * (m->qkv_rows() / 128));
+    if (sq > d / 256) sq = d / 256;
+    if (sq > q_splits) sq = q_splits;
+    if (sq > 4) sq = 4;
+    if (sq < 2 || ceil_div(T, 64) * (m->qkv_rows() / 128) >= 192) sq = 1;
+    plan_q = GemmPlan{{{0, T, sq, false}}, 1};
+  } else {
+    plan_q = gemm_plan(T, m->qkv_rows(), d, q_splits);
   }
-  const GemmPlan plan_q = qkv_f32 ? GemmPlan{{{0, T, sq, false}}, 1} : gemm_plan(T, m->qkv_rows(), d, false);
   // one projection by its plan: bf16 weights, or packed 4-bit weights with their group scales
   auto project = [&](const bf16 *a, const bf16 *wt, const bf16 *scale, void *out, int N, int K, int epi, const GemmPlan &p) {
     if (!m->w4) return launch_gemm_plan(p, a, wt, out, T, N, K, epi, st);
@@ -329,7 +330,8 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   RowParts pending{};
   arb_status s;
   if ((s = launch_token_meta(bt->prefix_lens, bt->cu_step_lens, bt->block_tables, B, T, bt->max_blocks_per_seq,
-                             c.kv_block, w.tok_pos, w.tok_slot, st)))
+                             c.kv_block, w.tok_pos, w.tok_slot, st, &plan,
+                             attention_lists(w.attn_ws, plan, T, c.n_q_heads, c.head_dim), G, c.n_kv_heads)))
     return s;
   if ((s = launch_rope_table(w.tok_pos, T, c.head_dim, c.rope_base, w.cs, st))) return s;
   for (int l = l0; l < l1; ++l) {
@@ -344,22 +346,21 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_QKV, st);
-      s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), qkv_f32 ? (void *)w.parts : (void *)w.qkv, m->qkv_rows(), d,
-                  qkv_f32 ? ARB_EPI_STORE_F32 : ARB_EPI_STORE_BF16, plan_q);
+      s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), w.parts, m->qkv_rows(), d, ARB_EPI_STORE_F32, plan_q);
     }
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_ROPE_APPEND, st);
       // the queries leave the rotary kernel multiplied by log2(e)/sqrt(hd) (in fp32, before their one rounding)
-      s = launch_rope_append(w.qkv, w.parts, qkv_f32 ? sq : 0, w.cs, w.tok_slot, (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], T, c.n_q_heads,
+      s = launch_rope_append(w.qkv, w.parts, parts_of(plan_q), w.cs, w.tok_slot, (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], T, c.n_q_heads,
                              c.n_kv_heads, c.head_dim, attention_q_scale(c.head_dim), st);
     }
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_ATTENTION, st);
       s = launch_attention(w.qkv, m->qkv_rows(), (const bf16 *)kv->k_pool[l], (const bf16 *)kv->v_pool[l],
-                           bt->block_tables, bt->max_blocks_per_seq, bt->prefix_lens, bt->cu_step_lens, B, T,
-                           c.n_q_heads, c.n_kv_heads, c.head_dim, plan, w.tok_pos, w.attn, w.attn_ws, w.attn_ws_bytes, st, true);
+                           bt->block_tables, bt->max_blocks_per_seq, B, T, c.n_q_heads, c.n_kv_heads, c.head_dim, plan,
+                           w.attn, w.attn_ws, w.attn_ws_bytes, st, true);
     }
     if (s) return s;
     {
@@ -596,12 +597,18 @@ extern "C" arb_status arb_stage_attention(const arb_model *m, const void *q, int
   if (!q || !k_pool || !v_pool || !out) return arb_fail(ARB_EINVAL, "arb_stage_attention: null pointer");
   if (q_row_stride < c.n_q_heads * c.head_dim || q_row_stride % 8 != 0)
     return arb_fail(ARB_EINVAL, "arb_stage_attention: q_row_stride %d", q_row_stride);
-  const AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host,
-                                       c.n_q_heads / c.n_kv_heads, c.n_kv_heads);
-  return launch_attention((const bf16 *)q, q_row_stride, (const bf16 *)k_pool, (const bf16 *)v_pool,
-                          batch->block_tables, batch->max_blocks_per_seq, batch->prefix_lens, batch->cu_step_lens,
-                          batch->batch, batch->total_tokens, c.n_q_heads, c.n_kv_heads, c.head_dim, plan, nullptr, (bf16 *)out,
-                          ws, ws_bytes, (hipStream_t)stream, q_scaled != 0);
+  const int G = c.n_q_heads / c.n_kv_heads, T = batch->total_tokens;
+  const AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host, G, c.n_kv_heads);
+  const size_t need = attention_ws_bytes(plan.max_splits, plan.n_items, T, c.n_q_heads, c.head_dim);
+  if (!ws || ws_bytes < need) return arb_fail(ARB_ECAPACITY, "arb_stage_attention: workspace %zu < %zu bytes", ws_bytes, need);
+  hipStream_t st = (hipStream_t)stream;
+  if (arb_status s = launch_token_meta(batch->prefix_lens, batch->cu_step_lens, batch->block_tables, batch->batch, T,
+                                       batch->max_blocks_per_seq, c.kv_block, nullptr, nullptr, st, &plan,
+                                       attention_lists(ws, plan, T, c.n_q_heads, c.head_dim), G, c.n_kv_heads))
+    return s;
+  return launch_attention((const bf16 *)q, q_row_stride, (const bf16 *)k_pool, (const bf16 *)v_pool, batch->block_tables,
+                          batch->max_blocks_per_seq, batch->batch, T, c.n_q_heads, c.n_kv_heads, c.head_dim, plan, (bf16 *)out,
+                          ws, ws_bytes, st, q_scaled != 0);
 }
 
 extern "C" arb_status arb_stage_rmsnorm(const float *x, const float *g, float eps, int32_t T, int32_t d, void *out,
@@ -632,7 +639,7 @@ extern "C" arb_status arb_stage_rope_append(const arb_model *m, void *qkv, void 
                              batch->max_blocks_per_seq, c.kv_block, tok_pos, tok_slot, st)))
     return s;
   if ((s = launch_rope_table(tok_pos, (int)T, c.head_dim, c.rope_base, cs, st))) return s;
-  return launch_rope_append((bf16 *)qkv, nullptr, 0, cs, tok_slot, (bf16 *)k_pool, (bf16 *)v_pool, (int)T, c.n_q_heads,
+  return launch_rope_append((bf16 *)qkv, nullptr, RowParts{}, cs, tok_slot, (bf16 *)k_pool, (bf16 *)v_pool, (int)T, c.n_q_heads,
                             c.n_kv_heads, c.head_dim, 1.0f, st);
 }
 

@@ -27,8 +27,7 @@
 
 namespace {
 
-constexpr int QROWS = 128;     // query rows per workgroup
-constexpr int KT = 64;         // keys per tile
+constexpr int QROWS = ATTN_QROWS, KT = ATTN_KT;
 constexpr float kLazyLog2 = 8.0f;   // growth of a row maximum (log2 units) that forces a rescale
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -202,9 +201,9 @@ __device__ __forceinline__ void attend_tile(const bf16 *sk, const bf16 *sv, cons
 template <int HD, bool SPLIT, bool PRESCALED>
 __global__ __launch_bounds__(256, 2) void attention_kernel(
     const bf16 *__restrict__ q, int q_row_stride, const bf16 *__restrict__ k_pool, const bf16 *__restrict__ v_pool,
-    const int32_t *__restrict__ block_tables, int max_blocks, const int32_t *__restrict__ prefix_lens,
-    const int32_t *__restrict__ cu, int T, int Hq, int Hkv, int max_qtiles, int max_splits, int kv_chunk,
-    float scale_log2, bf16 *__restrict__ out, bf16 *__restrict__ part_acc, float *__restrict__ part_ml, int n_groups) {
+    const int32_t *__restrict__ block_tables, int max_blocks, const AttnItem *__restrict__ items, int n_items, int run,
+    int T, int Hq, int Hkv, float scale_log2, bf16 *__restrict__ out, bf16 *__restrict__ part_acc,
+    float *__restrict__ part_ml) {
   constexpr int CPK = HD / 8;              // 16-byte chunks per key
   constexpr int LOADS = KT * CPK / 256;    // wave-wide 1 KB loads per wave, operand and tile
   constexpr int KPL = 64 / CPK;            // keys covered by one wave-wide load (4 or 8: inside one block)
@@ -216,27 +215,19 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(
 
   // Work item of this workgroup.  The hardware deals workgroups round-robin to the 8 XCDs (blockIdx % 8), and
   // an XCD works through its share in order.  The query tiles of one group (sequence, split, kv head) stream the
-  // same keys: they stay on one XCD, next to each other in its order, and meet in its L2.  The groups are dealt
-  // round-robin with the kv head as the fastest index, then the split: consecutive groups are equally long, so
-  // every XCD gets the same share of every sequence.  (With a contiguous range of sequences per XCD the XCD
-  // with the longest ones finished last: on 16 contexts of 5 K to 32 K keys only 59 % of the workgroup slots
-  // were busy on average, 75 % with this order.)
+  // same keys and are neighbours in the list: the list goes to the XCDs in runs of that length, so that most groups stay on
+  // one XCD and meet in its L2 while every XCD gets the same share of every sequence.  (64 contexts of 1 K to 16 K on
+  // the 1.5B shape, up to 6 query tiles: runs of 1, 2, 6 items 346, 313, 306 us; with a contiguous range of sequences per
+  // XCD the one with the longest finished last.)
   const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-  const int qtile = slot % max_qtiles;
-  int item = (slot / max_qtiles) * 8 + xcd;                 // group index
-  if (item >= n_groups) return;
-  const int hk = item % Hkv; item /= Hkv;
-  const int split = item % max_splits;
-  const int b = item / max_splits;
+  const int index = ((slot / run) * 8 + xcd) * run + slot % run;
+  if (index >= n_items) return;                        // rounding of the grid
+  const AttnItem item = items[index];
+  const int hk = item.split_head & 0xffff, split = item.split_head >> 16, b = item.seq;
   const int G = Hq / Hkv;
-  const int p = prefix_lens[b], tok0 = cu[b], s = cu[b + 1] - tok0;
-  const int rows = s * G, row0 = qtile * QROWS;
-  if (row0 >= rows) return;
-  const int last_row = min(rows, row0 + QROWS) - 1;
-  const int visible = p + last_row / G + 1;            // keys any row of this tile may see
-  const int kv_begin = split * kv_chunk;
-  if (kv_begin >= visible) return;
-  const int kv_end = min(visible, kv_begin + kv_chunk);
+  const int p = item.prefix, tok0 = item.tok0, s = item.step;
+  const int rows = s * G, row0 = item.row0;
+  const int kv_begin = item.kv_begin, kv_end = item.kv_end;
   const int ctx = p + s;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -382,14 +373,14 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(
 template <int HD>
 __global__ __launch_bounds__(256) void attention_merge_kernel(const bf16 *__restrict__ part_acc,
                                                               const float *__restrict__ part_ml,
-                                                              const int32_t *__restrict__ tok_pos, int T, int Hq,
-                                                              int kv_chunk, bf16 *__restrict__ out) {
+                                                              const int32_t *__restrict__ tok_splits, int T, int Hq,
+                                                              bf16 *__restrict__ out) {
   constexpr int TPR = HD / 8;                              // threads per row
   const size_t stride = (size_t)T * Hq;
   const size_t idx = (size_t)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;      // token * Hq + head
   if (idx >= stride) return;
   const int piece = threadIdx.x % TPR;
-  const int n_splits = tok_pos[idx / Hq] / kv_chunk + 1;   // splits that start at or before this token's position
+  const int n_splits = tok_splits[idx / Hq];               // splits that start at or before this token's position
   float m = -INFINITY, l = 0.f;
   float acc[8];
 #pragma unroll
@@ -438,7 +429,8 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const bf16 *__rest
 }  // namespace
 
 static const int kTargetWorkgroups = 512;    // two resident workgroups per CU on 256 CUs
-static const int kMinChunk = 256, kMaxChunk = 4096, kMaxChunkDecode = 8192, kMaxSplits = 64;
+static const int kMinChunk = 256, kMaxChunk = 4096, kMaxChunkDecode = 6144, kMaxSplits = 64;
+static const int kMaxRun = 16;                // longest run of work items on one XCD when there are few runs per XCD
 
 float attention_q_scale(int head_dim) { return (float)(1.4426950408889634 / sqrt((double)head_dim)); }
 
@@ -460,9 +452,10 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
   // Keys per split: about kTargetWorkgroups workgroups (one resident round) when contexts are short,
   // so that few partial states have to be merged; never more than kMaxChunk keys, so that long
   // ragged contexts become several rounds of similar-sized workgroups instead of one unbalanced round
-  // (measured on the ragged workloads: 4096 beats 2048 by 2-3 %, 8192 loses).  A batch whose steps all
-  // fit one wave (32 query rows: drafting token by token) only streams the cache: there the longer
-  // chunk of kMaxChunkDecode wins (fewer prologues and partial states: 5.3 -> 5.7 TB/s).
+  // (measured on the ragged workloads: 3072, 4096 and 6144 tie within 2 %, 2048 loses 4 %).  A batch whose steps all
+  // fit one wave (32 query rows: drafting token by token) only streams the cache: there a longer
+  // chunk wins (4096 / 6144 / 8192 keys: 406 / 400 / 418 us on 32 contexts of 4 K to 32 K of the 8B shape).
+  // A sequence is cut into equal parts of at most that many keys (attn_seq_chunk).
   const int cap = max_step * G <= 32 ? kMaxChunkDecode : kMaxChunk;
   long long chunk = (keys_streamed / kTargetWorkgroups + KT - 1) / KT * KT;
   if (chunk > cap) chunk = cap;
@@ -472,48 +465,57 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
   pl.max_qtiles = ceil_div(max_step * G, QROWS);
   pl.kv_chunk = (int)chunk;
   pl.max_splits = max_ctx > 0 ? ceil_div(max_ctx, pl.kv_chunk) : 1;
+  pl.n_items = 0;
+  for (int b = 0; b < batch; ++b) {
+    const int s = cu_host[b + 1] - cu_host[b], ctx = prefix_host[b] + s, c = attn_seq_chunk(ctx, pl.kv_chunk);
+    for (int begin = 0; begin < ctx; begin += c)
+      pl.n_items += (ceil_div(s * G, QROWS) - attn_first_qtile(prefix_host[b], G, begin)) * n_kv_heads;
+  }
   return pl;
 }
 
-size_t attention_ws_bytes(int max_splits_cap, int total_tokens, int n_q_heads, int head_dim) {
-  const size_t rows = (size_t)max_splits_cap * total_tokens * n_q_heads;
-  return align_up(rows * head_dim * sizeof(bf16), 256) + align_up(rows * 2 * sizeof(float), 256) +
-         align_up((size_t)total_tokens * sizeof(int32_t), 256);
+// Workspace: partial results [splits, T, Hq, hd] bf16 and their (m, l) fp32 (none with a single split), the splits of every
+// token, the work list.
+static size_t part_acc_bytes(int max_splits, int T, int Hq, int hd) {
+  return max_splits > 1 ? align_up((size_t)max_splits * T * Hq * hd * sizeof(bf16), 256) : 0;
+}
+static size_t part_ml_bytes(int max_splits, int T, int Hq) {
+  return max_splits > 1 ? align_up((size_t)max_splits * T * Hq * 2 * sizeof(float), 256) : 0;
+}
+
+size_t attention_ws_bytes(int max_splits, int n_items, int total_tokens, int n_q_heads, int head_dim) {
+  return part_acc_bytes(max_splits, total_tokens, n_q_heads, head_dim) + part_ml_bytes(max_splits, total_tokens, n_q_heads) +
+         align_up((size_t)total_tokens * sizeof(int32_t), 256) + align_up((size_t)n_items * sizeof(AttnItem), 256);
+}
+
+AttnLists attention_lists(void *ws, const AttnPlan &plan, int total_tokens, int n_q_heads, int head_dim) {
+  char *p = (char *)ws + part_acc_bytes(plan.max_splits, total_tokens, n_q_heads, head_dim) +
+            part_ml_bytes(plan.max_splits, total_tokens, n_q_heads);
+  return AttnLists{(AttnItem *)(p + align_up((size_t)total_tokens * sizeof(int32_t), 256)), (int32_t *)p};
 }
 
 arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool, const bf16 *v_pool,
-                            const int32_t *block_tables, int max_blocks_per_seq, const int32_t *prefix_lens,
-                            const int32_t *cu_step_lens, int batch, int total_tokens, int n_q_heads, int n_kv_heads,
-                            int head_dim, const AttnPlan &plan, const int32_t *tok_pos_in, bf16 *out, void *ws, size_t ws_bytes,
+                            const int32_t *block_tables, int max_blocks_per_seq, int batch, int total_tokens, int n_q_heads,
+                            int n_kv_heads, int head_dim, const AttnPlan &plan, bf16 *out, void *ws, size_t ws_bytes,
                             hipStream_t st, bool q_prescaled) {
   if (batch == 0 || total_tokens == 0) return ARB_OK;
   if (head_dim != 64 && head_dim != 128) return arb_fail(ARB_EUNSUPPORTED, "attention: head_dim %d", head_dim);
+  const size_t need = attention_ws_bytes(plan.max_splits, plan.n_items, total_tokens, n_q_heads, head_dim);
+  if (ws == nullptr || ws_bytes < need)
+    return arb_fail(ARB_ECAPACITY, "attention: workspace %zu < %zu bytes", ws_bytes, need);
   const bool split = plan.max_splits > 1;
-  bf16 *part_acc = nullptr;
-  float *part_ml = nullptr;
-  const int32_t *tok_pos = tok_pos_in;      // position of every step token; computed here when not given
-  if (split) {
-    const size_t need = attention_ws_bytes(plan.max_splits, total_tokens, n_q_heads, head_dim);
-    if (ws == nullptr || ws_bytes < need)
-      return arb_fail(ARB_ECAPACITY, "attention: workspace %zu < %zu bytes", ws_bytes, need);
-    const size_t rows = (size_t)plan.max_splits * total_tokens * n_q_heads;
-    char *pws = (char *)ws;
-    part_acc = (bf16 *)pws; pws += align_up(rows * head_dim * sizeof(bf16), 256);
-    part_ml = (float *)pws;  pws += align_up(rows * 2 * sizeof(float), 256);
-    if (!tok_pos) {
-      tok_pos = (int32_t *)pws;
-      if (arb_status s = launch_token_meta(prefix_lens, cu_step_lens, block_tables, batch, total_tokens,
-                                           max_blocks_per_seq, ARB_KV_BLOCK, (int32_t *)pws, nullptr, st))
-        return s;
-    }
-  }
+  bf16 *part_acc = (bf16 *)ws;
+  float *part_ml = (float *)((char *)ws + part_acc_bytes(plan.max_splits, total_tokens, n_q_heads, head_dim));
+  const AttnLists lists = attention_lists(ws, plan, total_tokens, n_q_heads, head_dim);
   const float scale_log2 = attention_q_scale(head_dim);
-  const int n_groups = batch * n_kv_heads * plan.max_splits;      // (sequence, split, kv head)
-  const dim3 grid(ceil_div(n_groups, 8) * 8 * plan.max_qtiles), block(256);
+  // A run is a group's query tiles, shortened where so few of them fit that some XCDs would get a whole run more.
+  int run = plan.max_qtiles;
+  if (run > kMaxRun && plan.n_items % (8 * run) != 0 && plan.n_items < 4 * 8 * run) run = kMaxRun;
+  const dim3 grid(ceil_div(plan.n_items, 8 * run) * 8 * run), block(256);
 #define ARB_ATTN_LAUNCH(HD, SPLIT, PRE)                                                                            \
   hipLaunchKernelGGL((attention_kernel<HD, SPLIT, PRE>), grid, block, 0, st, q, q_row_stride, k_pool, v_pool,      \
-                     block_tables, max_blocks_per_seq, prefix_lens, cu_step_lens, total_tokens, n_q_heads,         \
-                     n_kv_heads, plan.max_qtiles, plan.max_splits, plan.kv_chunk, scale_log2, out, part_acc, part_ml, n_groups)
+                     block_tables, max_blocks_per_seq, lists.items, plan.n_items, run, total_tokens, n_q_heads,    \
+                     n_kv_heads, scale_log2, out, part_acc, part_ml)
 #define ARB_ATTN_PICK(HD)                                                                                          \
   if (split) { if (q_prescaled) ARB_ATTN_LAUNCH(HD, true, true); else ARB_ATTN_LAUNCH(HD, true, false); }          \
   else       { if (q_prescaled) ARB_ATTN_LAUNCH(HD, false, true); else ARB_ATTN_LAUNCH(HD, false, false); }
@@ -524,11 +526,11 @@ arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool,
   if (split) {
     const dim3 mgrid(ceil_div(total_tokens * n_q_heads, 2048 / head_dim)), mblock(256);
     if (head_dim == 128)
-      hipLaunchKernelGGL((attention_merge_kernel<128>), mgrid, mblock, 0, st, part_acc, part_ml, tok_pos, total_tokens,
-                         n_q_heads, plan.kv_chunk, out);
+      hipLaunchKernelGGL((attention_merge_kernel<128>), mgrid, mblock, 0, st, part_acc, part_ml, lists.tok_splits,
+                         total_tokens, n_q_heads, out);
     else
-      hipLaunchKernelGGL((attention_merge_kernel<64>), mgrid, mblock, 0, st, part_acc, part_ml, tok_pos, total_tokens,
-                         n_q_heads, plan.kv_chunk, out);
+      hipLaunchKernelGGL((attention_merge_kernel<64>), mgrid, mblock, 0, st, part_acc, part_ml, lists.tok_splits,
+                         total_tokens, n_q_heads, out);
     ARB_CHECK_LAUNCH("attention_merge");
   }
   return ARB_OK;

@@ -78,7 +78,7 @@ struct GemmPlan {
   GemmSeg seg[2];
   int n;
 };
-GemmPlan gemm_plan(int M, int N, int K, bool partials);   // partials: fp32 output that may be split along K
+GemmPlan gemm_plan(int M, int N, int K, int max_splits);   // max_splits: most partial products of fp32 output; 0: unsplit
 arb_status launch_gemm_plan(const GemmPlan &plan, const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue,
                             hipStream_t st);
 // The unsplit projection.  SwiGLU and launches with B_blocked are up to two kernels: n-tile columns
@@ -93,27 +93,55 @@ int gemm_residual_splits(int M, int N, int K);
 int gemm_stream_splits(int M, int N, int K);   // K splits of an fp32 projection on the few-token kernel; 0: another kernel takes it
 
 // attention.hip
+constexpr int ATTN_QROWS = 128;     // query rows (step tokens x query heads of one kv head) per workgroup
+constexpr int ATTN_KT = 64;         // keys per tile
 struct AttnPlan {
-  int kv_chunk;      // keys per split (multiple of 64)
+  int kv_chunk;      // most keys per split (multiple of 64)
   int max_splits;    // ceil(max_ctx / kv_chunk) over the batch
   int max_qtiles;    // ceil(max_step * G / 128)
+  int n_items;       // (sequence, split, kv head, query tile) with at least one visible key
 };
+// One workgroup's work: query rows [row0, row0 + 128) of the (token, head) rows of one kv head of one sequence against
+// keys [kv_begin, kv_end).  The list of a batch is written on the device once per call and read by every layer.
+struct AttnItem {
+  int32_t seq, tok0, prefix, step;       // sequence; its first step token, cached length, step length
+  int32_t row0, kv_begin, kv_end;
+  int32_t split_head;                    // split << 16 | kv head
+};
+// Keys per split of a sequence: its context in equal parts of at most kv_chunk, whole tiles.
+static __host__ __device__ inline int attn_seq_chunk(int ctx, int kv_chunk) {
+  const int n = (ctx + kv_chunk - 1) / kv_chunk;
+  return ((ctx + n - 1) / n + ATTN_KT - 1) / ATTN_KT * ATTN_KT;
+}
+// First query tile of a sequence with a row that sees key kv_begin (< prefix + step).
+static __host__ __device__ inline int attn_first_qtile(int prefix, int G, int kv_begin) {
+  return kv_begin <= prefix ? 0 : (int)((long long)(kv_begin - prefix) * G / ATTN_QROWS);
+}
 AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads);
-size_t attention_ws_bytes(int max_splits_cap, int total_tokens, int n_q_heads, int head_dim);
+size_t attention_ws_bytes(int max_splits, int n_items, int total_tokens, int n_q_heads, int head_dim);
 int attention_splits_cap(int max_ctx);   // largest max_splits plan_attention can return for contexts <= max_ctx
+// The work list inside an attention workspace (attention_ws_bytes), to be written by launch_token_meta before the
+// launches that use it, and the number of splits that hold keys each step token sees.
+struct AttnLists {
+  AttnItem *items;
+  int32_t *tok_splits;
+};
+AttnLists attention_lists(void *ws, const AttnPlan &plan, int total_tokens, int n_q_heads, int head_dim);
 arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool, const bf16 *v_pool,
-                            const int32_t *block_tables, int max_blocks_per_seq, const int32_t *prefix_lens,
-                            const int32_t *cu_step_lens, int batch, int total_tokens, int n_q_heads, int n_kv_heads,
-                            int head_dim, const AttnPlan &plan, const int32_t *tok_pos_in, bf16 *out, void *ws, size_t ws_bytes,
+                            const int32_t *block_tables, int max_blocks_per_seq, int batch, int total_tokens, int n_q_heads,
+                            int n_kv_heads, int head_dim, const AttnPlan &plan, bf16 *out, void *ws, size_t ws_bytes,
                             hipStream_t st, bool q_prescaled);
 // log2(e) / sqrt(head_dim): the factor the attention kernel wants folded into the queries (q_prescaled), so that
 // its score products are logits in log2 units; launch_rope_append applies it (q_scale) before it rounds q.
 float attention_q_scale(int head_dim);
 
 // elementwise.hip
+// Position and pool slot of every step token (either pointer may be null); with `plan`, in the same launch, the
+// attention lists of the batch.
 arb_status launch_token_meta(const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
                              int batch, int total_tokens, int max_blocks_per_seq, int kv_block, int32_t *tok_pos,
-                             int32_t *tok_slot, hipStream_t st);
+                             int32_t *tok_slot, hipStream_t st, const AttnPlan *plan = nullptr, AttnLists lists = AttnLists{},
+                             int G = 1, int n_kv_heads = 1);
 // Debug range check of token ids and of the block ids a batch references; err: device int32 [4].
 arb_status launch_check_ids(const int32_t *token_ids, int T, int vocab, const int32_t *block_tables, int batch,
                             int max_blocks_per_seq, const int32_t *prefix_lens, const int32_t *cu_step_lens,
@@ -129,9 +157,9 @@ struct RowParts {
 };
 arb_status launch_rmsnorm(float *h, const float *parts, RowParts n_parts, const float *g, float eps, int T, int d, bf16 *x,
                           hipStream_t st);
-// parts/n_parts: when n_parts > 0 the projection is read as the sum of fp32 partial products
-// [n_parts, T, (Hq+2Hkv)*hd] instead of from qkv; the rotated q is written to qkv (bf16) either way.
-arb_status launch_rope_append(bf16 *qkv, const float *parts, int n_parts, const f32x2 *cs, const int32_t *tok_slot,
+// parts/n_parts: when n_parts.head > 0 the projection is read as the sum of fp32 partial products
+// [*, T, (Hq+2Hkv)*hd] instead of from qkv; the rotated q is written to qkv (bf16) either way.
+arb_status launch_rope_append(bf16 *qkv, const float *parts, RowParts n_parts, const f32x2 *cs, const int32_t *tok_slot,
                               bf16 *k_pool, bf16 *v_pool, int T, int n_q_heads, int n_kv_heads, int head_dim,
                               float q_scale, hipStream_t st);
 arb_status launch_final_norm_head(const float *h, const float *parts, RowParts n_parts, const float *g, float eps, int T,

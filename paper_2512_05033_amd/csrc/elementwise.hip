@@ -24,11 +24,104 @@ __device__ __forceinline__ float block_sum_256(float v, float *lds4) {
 
 // ---------------------------------------------------------------- token metadata
 
+// The attention work list: for every sequence, split, kv head and query tile that has a visible key one AttnItem, and
+// nothing else, so that every workgroup of an attention launch has work.  (The launch used to be the full product
+// of batch, most splits and most query tiles; on ragged batches half of its workgroups returned at once, but they took
+// their turn in the order in which workgroups are handed to the CUs, which left the working ones unevenly
+// spread: 64 contexts of 1 K to 16 K on the 1.5B shape 496 -> 306 us per layer, 32 of 4 K to 32 K on the 8B shape with
+// steps of 1 and 64 tokens 613 -> 522.)  Sequences with the longest splits come first, so that a launch ends on
+// short ones; the query tiles of a (sequence, split, kv head) are neighbours, the ones that see most keys first.
+// Blocks [0, n_parts) each know the whole order and write every n_parts-th run of 256 items.
+constexpr int kListSeqs = 512;             // sequences ordered at a time, two per thread
+
+// Items of a sequence with context p + s cut into parts of c keys: every split that starts inside the prefix has all nq
+// query tiles, the few that start inside the step have those whose last row sees their first key.
+__device__ __forceinline__ int attention_item_count(int p, int s, int c, int G, int Hkv) {
+  const int nq = (s * G + ATTN_QROWS - 1) / ATTN_QROWS, in_prefix = p / c + 1;
+  int tiles = in_prefix * nq;
+  for (int begin = in_prefix * c; begin < p + s; begin += c) tiles += nq - attn_first_qtile(p, G, begin);
+  return tiles * Hkv;
+}
+
+__device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ cu, int batch,
+                                      int G, int Hkv, int kv_chunk, AttnItem *__restrict__ items, int part, int n_parts) {
+  __shared__ int key[kListSeqs], first[kListSeqs], prefix[kListSeqs], step[kListSeqs], order[kListSeqs];
+  __shared__ int ends[kListSeqs], wave_total[4];           // ends: inclusive sums of the ordered item counts
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int written = 0;
+  for (int base = 0; base < batch; base += kListSeqs) {
+    const int n = min(kListSeqs, batch - base);
+    for (int i = tid; i < n; i += 256) {
+      const int p = prefix_lens[base + i], t0 = cu[base + i], s = cu[base + i + 1] - t0;
+      prefix[i] = p;
+      first[i] = t0;
+      step[i] = s;
+      key[i] = attn_seq_chunk(p + s, kv_chunk);
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += 256) {
+      const int k = key[i];
+      int rank = 0;
+      for (int j = 0; j < n; ++j) rank += key[j] > k || (key[j] == k && j < i);
+      order[rank] = i;
+    }
+    __syncthreads();
+    int count[2] = {0, 0};
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      if (2 * tid + e < n) {
+        const int i = order[2 * tid + e];
+        count[e] = attention_item_count(prefix[i], step[i], key[i], G, Hkv);
+      }
+    int sum = count[0] + count[1];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(sum, o, 64);
+      if (lane >= o) sum += up;
+    }
+    if (lane == 63) wave_total[wave] = sum;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) sum += wave_total[w];
+    ends[2 * tid] = sum - count[1];
+    ends[2 * tid + 1] = sum;
+    __syncthreads();
+    const int total = ends[n - 1];
+    for (int l = part * 256 + tid; l < total; l += n_parts * 256) {
+      int lo = 0, hi = n - 1;                              // first r with ends[r] > l
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ends[mid] > l) hi = mid; else lo = mid + 1;
+      }
+      const int i = order[lo], p = prefix[i], s = step[i], c = key[i], rows = s * G;
+      const int nq = (rows + ATTN_QROWS - 1) / ATTN_QROWS;
+      const int j0 = lo ? l - ends[lo - 1] : l;
+      int split = min(j0 / (nq * Hkv), p / c), j = j0 - split * nq * Hkv, per;
+      for (;; ++split) {
+        per = nq - attn_first_qtile(p, G, split * c);      // query tiles of this split, the last ones of the sequence
+        if (j < per * Hkv) break;
+        j -= per * Hkv;
+      }
+      const int hk = j / per, row0 = (nq - 1 - (j - hk * per)) * ATTN_QROWS;
+      const int visible = p + (min(rows, row0 + ATTN_QROWS) - 1) / G + 1;          // keys any row of the tile may see
+      items[written + l] = AttnItem{base + i, first[i], p, s, row0, split * c, min(visible, split * c + c), split << 16 | hk};
+    }
+    written += total;
+    __syncthreads();
+  }
+}
+
 // For step token j of sequence b at position pos = p_b + i:
 //   slot = block_tables[b][pos / blk] * blk + pos % blk.
-__global__ void token_meta_kernel(const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ cu,
-                                  const int32_t *__restrict__ tables, int batch, int T, int max_blocks, int blk,
-                                  int32_t *__restrict__ tok_pos, int32_t *__restrict__ tok_slot) {
+// The blocks behind the tokens' write the attention work list (list_blocks of them, none without one).
+__global__ __launch_bounds__(256) void token_meta_kernel(const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ cu,
+                                                         const int32_t *__restrict__ tables, int batch, int T, int max_blocks,
+                                                         int blk, int32_t *__restrict__ tok_pos, int32_t *__restrict__ tok_slot,
+                                                         int list_blocks, int kv_chunk, int G, int Hkv, AttnLists lists) {
+  const int tok_blocks = gridDim.x - list_blocks;
+  if ((int)blockIdx.x >= tok_blocks) {
+    write_attention_items(prefix_lens, cu, batch, G, Hkv, kv_chunk, lists.items, blockIdx.x - tok_blocks, list_blocks);
+    return;
+  }
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= T) return;
   int lo = 0, hi = batch;                 // largest b with cu[b] <= j
@@ -40,14 +133,17 @@ __global__ void token_meta_kernel(const int32_t *__restrict__ prefix_lens, const
   const int pos = prefix_lens[b] + (j - cu[b]);
   if (tok_pos) tok_pos[j] = pos;
   if (tok_slot) tok_slot[j] = tables[(size_t)b * max_blocks + pos / blk] * blk + pos % blk;
+  if (list_blocks) lists.tok_splits[j] = pos / attn_seq_chunk(prefix_lens[b] + cu[b + 1] - cu[b], kv_chunk) + 1;
 }
 
 arb_status launch_token_meta(const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
                              int batch, int total_tokens, int max_blocks_per_seq, int kv_block, int32_t *tok_pos,
-                             int32_t *tok_slot, hipStream_t st) {
+                             int32_t *tok_slot, hipStream_t st, const AttnPlan *plan, AttnLists lists, int G, int n_kv_heads) {
   if (total_tokens == 0) return ARB_OK;
-  hipLaunchKernelGGL(token_meta_kernel, dim3(ceil_div(total_tokens, 256)), dim3(256), 0, st, prefix_lens,
-                     cu_step_lens, block_tables, batch, total_tokens, max_blocks_per_seq, kv_block, tok_pos, tok_slot);
+  const int list_blocks = !plan ? 0 : plan->n_items <= 1024 ? 1 : plan->n_items <= 16384 ? ceil_div(plan->n_items, 1024) : 16;
+  hipLaunchKernelGGL(token_meta_kernel, dim3(ceil_div(total_tokens, 256) + list_blocks), dim3(256), 0, st, prefix_lens,
+                     cu_step_lens, block_tables, batch, total_tokens, max_blocks_per_seq, kv_block, tok_pos, tok_slot,
+                     list_blocks, plan ? plan->kv_chunk : ATTN_KT, G, n_kv_heads, lists);
   ARB_CHECK_LAUNCH("token_meta");
   return ARB_OK;
 }
@@ -291,12 +387,13 @@ arb_status launch_final_norm_head(const float *h, const float *parts, RowParts n
 // products that are added up here (fixed order), so q and k are rounded once.
 template <bool PARTS>
 __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv, const float *__restrict__ parts,
-                                                          int n_parts, size_t part_stride,
+                                                          RowParts row_parts, size_t part_stride,
                                                           const f32x2 *__restrict__ cs,
                                                           const int32_t *__restrict__ tok_slot,
                                                           bf16 *__restrict__ k_pool, bf16 *__restrict__ v_pool,
                                                           int Hq, int Hkv, int hd, float q_scale) {
   const int j = blockIdx.x;
+  const int n_parts = j < row_parts.row ? row_parts.head : row_parts.tail;
   const int half = hd / 2, units_per_head = half / 2, n_heads = Hq + 2 * Hkv;
   bf16 *row = qkv + (size_t)j * n_heads * hd;
   const float *prow = PARTS ? parts + (size_t)j * n_heads * hd : nullptr;
@@ -345,17 +442,17 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv
   }
 }
 
-arb_status launch_rope_append(bf16 *qkv, const float *parts, int n_parts, const f32x2 *cs, const int32_t *tok_slot,
+arb_status launch_rope_append(bf16 *qkv, const float *parts, RowParts n_parts, const f32x2 *cs, const int32_t *tok_slot,
                               bf16 *k_pool, bf16 *v_pool, int T, int n_q_heads, int n_kv_heads, int head_dim,
                               float q_scale, hipStream_t st) {
   if (T == 0) return ARB_OK;
   const size_t stride = (size_t)T * (n_q_heads + 2 * n_kv_heads) * head_dim;
   const dim3 grid(T, ceil_div((n_q_heads + 2 * n_kv_heads) * (head_dim / 4), 256));
-  if (n_parts > 0)
+  if (n_parts.head > 0)
     hipLaunchKernelGGL((rope_append_kernel<true>), grid, dim3(256), 0, st, qkv, parts, n_parts, stride, cs, tok_slot,
                        k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale);
   else
-    hipLaunchKernelGGL((rope_append_kernel<false>), grid, dim3(256), 0, st, qkv, (const float *)nullptr, 0, stride, cs,
+    hipLaunchKernelGGL((rope_append_kernel<false>), grid, dim3(256), 0, st, qkv, (const float *)nullptr, RowParts{}, stride, cs,
                        tok_slot, k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale);
   ARB_CHECK_LAUNCH("rope_append");
   return ARB_OK;

@@ -14,6 +14,7 @@
 // lane ends up holding gate and up of the same (row, feature).
 #include "common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -1139,12 +1140,13 @@ static double wide_us(int m, int N, int K, int splits, int bytes) {
 // eight-wave kernel unsplit.  The rows left over (all of them, where there is no whole round) are a launch of their own,
 // because what suits them is another kernel or another split of K: it goes to the eight-wave kernel with the number of
 // splits that fills its round best, or to the tiled kernels, or (a few rows) to the weight-streaming kernel, whichever is
-// estimated to be the fastest.  `partials`: fp32 output that may come as partial products.  (Down 6144x4096x14336:
+// estimated to be the fastest.  max_splits > 0: fp32 output that may come as that many partial products; 0: unsplit.  (Down 6144x4096x14336:
 // one launch of 384 tiles 635 us; 256 + 128 tiles in two K splits 550.  4943x4096x14336: 619 us in 320 tiles, 568 in
 // 128x128 tiles; 256 + 64 in four splits 465.)
-GemmPlan gemm_plan(int M, int N, int K, bool partials) {
+GemmPlan gemm_plan(int M, int N, int K, int max_splits) {
   GemmPlan p{};
   int row = 0;
+  const bool partials = max_splits > 0;
   const int bytes = partials ? 4 : 2;
   int mt, rt;
   if (M > 64 && N % W_TN == 0 && N / W_TN <= 256 && !stream_shape(M, N, K, &mt, &rt)) {
@@ -1158,12 +1160,18 @@ GemmPlan gemm_plan(int M, int N, int K, bool partials) {
   if (m <= 0) return p;
   GemmSeg rest{row, m, 1, false};
   if (stream_shape(m, N, K, &mt, &rt)) {
-    if (partials) rest.splits = gemm_stream_splits(m, N, K);
+    if (partials) rest.splits = std::min(gemm_stream_splits(m, N, K), max_splits);
   } else {
-    if (partials) rest.splits = gemm_residual_splits(m, N, K);
-    double best = tiled_us(m, N, K, rest.splits, bytes);
+    double best = tiled_us(m, N, K, 1, bytes);
+    if (partials) {
+      const int s = std::min(gemm_residual_splits(m, N, K), max_splits);
+      if (s > 1 && tiled_us(m, N, K, s, bytes) < best) {
+        rest.splits = s;
+        best = tiled_us(m, N, K, s, bytes);
+      }
+    }
     const int tiles = N % W_TN == 0 ? ceil_div(m, W_TM) * (N / W_TN) : 0;
-    for (int s = 1; tiles > 0 && tiles * s <= 256 && s <= (partials ? 8 : 1) && K / BK / s >= 8; ++s) {
+    for (int s = 1; tiles > 0 && tiles * s <= 256 && s <= (partials ? max_splits : 1) && K / BK / s >= 8; ++s) {
       const double t = wide_us(m, N, K, s, bytes);
       if (t < best) {
         best = t;
@@ -1314,7 +1322,7 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
   } else {
     if (N % BN != 0) return arb_fail(ARB_EUNSUPPORTED, "gemm: N=%d is not a multiple of %d", N, BN);
     if (epilogue < 0 || epilogue > ARB_EPI_STORE_F32) return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
-    if (!B_blocked) return launch_gemm_plan(gemm_plan(M, N, K, false), A, B, C, M, N, K, epilogue, st);
+    if (!B_blocked) return launch_gemm_plan(gemm_plan(M, N, K, 0), A, B, C, M, N, K, epilogue, st);
   }
   return launch_tiles(A, B, C, M, N, K, epilogue, st, 1, part, B_blocked, 0);
 }

@@ -417,6 +417,19 @@ def test_attention_stage(A, shape, prefix, steps, peaky, q_scaled):
     assert row_err.max() < 3e-2
 
 
+@pytest.mark.parametrize("shape,prefix,steps", [
+    (W.TINY, [0], [4300]),                       # splits that start inside the step: they have its last query tiles only
+    (W.TINY, [100, 4500], [4100, 20]),           # ... next to a sequence whose splits all start in its prefix
+    (W.TINY, [3 * (i % 7) for i in range(513)], [1 + i % 3 for i in range(513)]),    # more sequences than are ordered at a time
+    (W.ROUTER_1P5B, [8192, 255, 256, 257], [22, 21, 1, 64]),             # contexts at and next to a multiple of the split length
+])
+def test_attention_work_list(A, shape, prefix, steps):
+    got, ref = _attention_case(A, shape, prefix, steps, False, 37)
+    assert rel_err(got, ref) < 1e-2
+    row_err = np.abs(got - ref).max(axis=-1) / (np.abs(ref).max(axis=-1) + 1e-3)
+    assert row_err.max() < 3e-2
+
+
 @pytest.mark.parametrize("seed", [1, 2, 3, 4])
 def test_attention_stage_random_ragged_batches(A, seed):
     """Seeded random batch sizes, prefixes and step lengths (grids whose group count is not a multiple of
