@@ -294,7 +294,8 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   // 4-bit weights keep one number of splits for all rows.
   const int hq = c.n_q_heads * c.head_dim;
   auto residual_plan = [&](int K) {
-    return m->w4 ? GemmPlan{{{0, T, gemm_residual_splits(T, d, K), false}}, 1} : gemm_plan(T, d, K, 8);
+    if (!m->w4) return gemm_plan(T, d, K, 8);
+    return GemmPlan{{{0, T, T <= 32 ? gemm_residual_splits(T, d, K) : gemm_w4_splits(T, d, K, 8), false}}, 1};
   };
   const GemmPlan plan_o = residual_plan(hq), plan_d = residual_plan(c.d_ffn);
   auto parts_of = [&](const GemmPlan &p) {
@@ -310,7 +311,8 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (sq > d / 256) sq = d / 256;
     if (sq > q_splits) sq = q_splits;
     if (sq > 4) sq = 4;
-    if (sq < 2 || ceil_div(T, 64) * (m->qkv_rows() / 128) >= 192) sq = 1;
+    if (sq < 1) sq = 1;
+    if (T > 32) sq = gemm_w4_splits(T, m->qkv_rows(), d, q_splits);
     plan_q = GemmPlan{{{0, T, sq, false}}, 1};
   } else {
     plan_q = gemm_plan(T, m->qkv_rows(), d, q_splits);

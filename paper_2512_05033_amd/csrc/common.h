@@ -38,6 +38,10 @@ arb_status arb_fail(arb_status st, const char *fmt, ...);
 static inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// First of the n steps of K that part i of `parts` owns, in 32 bits (n is at most 2^24, parts at most 64): a 64-bit
+// division is 130 instructions, which a workgroup of few steps first has to fetch.
+static __device__ __forceinline__ int split_point(int n, unsigned i, unsigned parts) { return (int)((unsigned)n * i / parts); }
+
 // ---- tile order shared by the GEMM kernels ----
 
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Give
@@ -186,3 +190,4 @@ arb_status launch_pack_steps(const int32_t *steps, int S, const int32_t *rows, c
 arb_status launch_w4_quantize(const bf16 *W, int N, int K, uint32_t *packed, bf16 *scales, int bits, hipStream_t st);
 arb_status launch_gemm_w4(const bf16 *A, const uint32_t *Bq, const bf16 *Bscale, void *C, int M, int N, int K,
                           int epilogue, hipStream_t st, int splits = 1);
+int gemm_w4_splits(int M, int N, int K, int max_splits);   // K splits of an fp32 projection on the tile kernels

@@ -12,12 +12,16 @@
 // of the bf16 kernel's.  Up to 32 rows a weight-streaming kernel runs instead (below).
 #include "common.h"
 
+#include <math.h>
+
+#include <type_traits>
+
 namespace {
 
 constexpr int BM = 128, BN = 128, BK = 64, GROUP = 128;
 constexpr int LDS_TILE = BM * BK;
+constexpr double kTallStepUs = 1.22, kPairStepUs = 1.34, kSingleStepUs = 0.8;     // measured, see w4_tile_us
 constexpr int kSkinnyRows = 32;     // up to this many activation rows the weight-streaming kernel runs
-constexpr int kSkinnyAhead = 3;     // groups of packed weights a wave of that kernel has in flight
 
 #define GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
@@ -147,7 +151,10 @@ __device__ __forceinline__ void w4_tile_epilogue(const f32x16 (&acc)[2][2], void
 // eight requests made since the tile of the next step stay in flight: loads complete in order, so everything older
 // has landed.  A register that a load in flight will write is named by the wait that covers it (and by a last wait
 // behind the loop): the compiler then neither reads it earlier nor gives it to another value.
-// What bounds it now is the expansion (exact: two integer instructions, a subtraction and half a conversion per
+// Two heights: 128 rows (WM = 2, four waves, two workgroups per CU) and 256 (WM = 4, eight waves, one per CU).  The taller tile
+// expands every weight for twice the rows; what bounds it is the LDS (64x64 per wave: 16 KB of fragment reads per wave and
+// step, as many clocks as the MFMAs, plus the stages' writes).  8B gate/up at 484 rows: 174 us in 128-row tiles, 160 in 256-row ones.
+// What bounds the 128-row tile is the expansion (exact: two integer instructions, a subtraction and half a conversion per
 // weight; without it the 8B gate/up shape at 128 rows takes 41 instead of 59 us, without the MFMAs 56).  The
 // conversion-free expansion of the few-token kernel was tried here too (with the row sums from a third MFMA per
 // row block and, in a second version, two accumulator sets so that the fold of a group runs between the MFMAs of
@@ -159,7 +166,7 @@ __device__ __forceinline__ void w4_request_frags(unsigned a_addr, unsigned b_add
   asm volatile("ds_read_b128 %0, %4 offset:%6\n\tds_read_b128 %1, %4 offset:%7\n\t"
                "ds_read_b128 %2, %5 offset:%8\n\tds_read_b128 %3, %5 offset:%9"
                : "=&v"(fa0), "=&v"(fa1), "=&v"(fb0), "=&v"(fb1)
-               : "v"(a_addr), "v"(b_addr), "n"(AOFF), "n"(AOFF + 32 * BK * 2), "n"(BOFF), "n"(BOFF + 32 * BK * 2)
+               : "v"(a_addr + (AOFF & ~0xFFFF)), "v"(b_addr), "n"(AOFF & 0xFFFF), "n"((AOFF & 0xFFFF) + 32 * BK * 2), "n"(BOFF), "n"(BOFF + 32 * BK * 2)
                : "memory");
 }
 // the requested fragments have landed (and every LDS write of this wave is done); naming them keeps their readers behind
@@ -167,21 +174,24 @@ __device__ __forceinline__ void w4_await_frags(bf16x8 &fa0, bf16x8 &fa1, bf16x8 
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(fa0), "+v"(fa1), "+v"(fb0), "+v"(fb1) : : "memory");
 }
 
-template <int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict__ A, const uint32_t *__restrict__ Bq,
+template <int EPI, int WM>
+__global__ __launch_bounds__(128 * WM, 2) void gemm_w4_kernel(const bf16 *__restrict__ A, const uint32_t *__restrict__ Bq,
                                                       const bf16 *__restrict__ Bscale, void *__restrict__ Cv, int M,
                                                       int N, int K, int tiles_m, int tiles_n) {
   constexpr int NA = 3, AHEAD_W = 6;                    // activation stages; steps the packed weights are ahead
+  constexpr int WAVES = 2 * WM, ROWS = 64 * WM;          // waves (wm, wn) of 64 x 64; tile rows
+  constexpr int A_TILE = ROWS * BK;                      // elements of an activation stage
+  constexpr int WORDS = 8 / WM;                          // packed words a thread expands per step: 128 rows of 8 over 128 WM threads
   // Two objects: the activation ring only ever sees direct-to-LDS loads and the assembly's reads, so the stores of
   // expanded weights into the other one are not ordered behind loads in flight.
-  __shared__ __attribute__((aligned(16))) bf16 Ring[NA * LDS_TILE], Bs[2 * LDS_TILE];
+  __shared__ __attribute__((aligned(16))) bf16 Ring[NA * A_TILE], Bs[2 * LDS_TILE];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   int tile_m, tile_n;
-  constexpr int TILE_GROUP = 4;
+  constexpr int TILE_GROUP = 8 / WM;
   tile_of<TILE_GROUP>(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, tile_m, tile_n);
-  const int m0 = tile_m * BM;
+  const int m0 = tile_m * ROWS;
   const int frag_row = lane & 31, frag_half = lane >> 5;
 
   // weight row of tile-local B row r.  SwiGLU: wave column r/64, MFMA tile (r%64)/32 (0 = gate, 1 = up),
@@ -195,20 +205,20 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict_
   };
 
   const int ng_all = K / GROUP;
-  const int g_begin = (int)((long long)ng_all * blockIdx.y / gridDim.y);
-  const int ng = (int)((long long)ng_all * (blockIdx.y + 1) / gridDim.y) - g_begin;
+  const int g_begin = split_point(ng_all, blockIdx.y, gridDim.y);
+  const int ng = split_point(ng_all, blockIdx.y + 1, gridDim.y) - g_begin;
   const int nk = 2 * ng, last = nk - 1;
 
   const bf16 *a_src[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int c = tid + 256 * i, row = c >> 3, chunk = (c & 7) ^ ((row >> 1) & 7);
+    const int c = tid + 64 * WAVES * i, row = c >> 3, chunk = (c & 7) ^ ((row >> 1) & 7);
     int am = m0 + row;
     am = am < M ? am : M - 1;                            // tail rows re-read the last row; never stored
     a_src[i] = A + (size_t)am * K + (size_t)g_begin * GROUP + chunk * 8;
   }
-  const int b_row = tid >> 1, b_half = tid & 1;
-  const uint32_t *bq_src = Bq + (size_t)weight_row(b_row) * (K / 8) + (size_t)g_begin * (GROUP / 8) + b_half * 4;
+  const int b_row = tid / WM, b_word = tid % WM * WORDS;  // a thread's weights: WORDS words of one row
+  const uint32_t *bq_src = Bq + (size_t)weight_row(b_row) * (K / 8) + (size_t)g_begin * (GROUP / 8) + b_word;
   const bf16 *sc_src[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) sc_src[j] = Bscale + (size_t)weight_row(wn * 64 + j * 32 + frag_row) * (K / GROUP) + g_begin;
@@ -218,22 +228,24 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict_
     kt = kt < last ? kt : last;                          // past the range: a valid step, never read
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(a_src[i] + (size_t)kt * BK), LDS_PTR(Ring + stage * LDS_TILE + (i * 4 + wave_u) * 512), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(a_src[i] + (size_t)kt * BK), LDS_PTR(Ring + stage * A_TILE + (i * WAVES + wave_u) * 512), 16, 0, 0);
   };
-  u32x4 wq[AHEAD_W];                                     // packed weights of steps kt+1 .. kt+6, slot = step % 6
+  typedef uint32_t words_t __attribute__((ext_vector_type(WORDS)));
+  words_t wq[AHEAD_W];                                     // packed weights of steps kt+1 .. kt+6, slot = step % 6
   unsigned sc[3][2];                                     // scales (bf16 bits) of three groups, slot = group % 3
   auto load_w = [&](int slot, int kt) {
     kt = kt < last ? kt : last;
-    asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(wq[slot]) : "v"(bq_src + (size_t)kt * (BK / 8)) : "memory");
+    if constexpr (WM == 2) asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(wq[slot]) : "v"(bq_src + (size_t)kt * (BK / 8)) : "memory");
+    else asm volatile("global_load_dwordx2 %0, %1, off" : "=&v"(wq[slot]) : "v"(bq_src + (size_t)kt * (BK / 8)) : "memory");
   };
   auto load_sc = [&](int slot, int g) {
     g = g < ng ? g : ng - 1;
     asm volatile("global_load_ushort %0, %1, off" : "=&v"(sc[slot][0]) : "v"(sc_src[0] + g) : "memory");
     asm volatile("global_load_ushort %0, %1, off" : "=&v"(sc[slot][1]) : "v"(sc_src[1] + g) : "memory");
   };
-  auto store_b = [&](int buf, const u32x4 &w) {
+  auto store_b = [&](int buf, const words_t &w) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) *(bf16x8 *)&Bs[buf * LDS_TILE + lds_off(b_row, b_half * 4 + c)] = expand_nibbles(w[c]);
+    for (int c = 0; c < WORDS; ++c) *(bf16x8 *)&Bs[buf * LDS_TILE + lds_off(b_row, b_word + c)] = expand_nibbles(w[c]);
   };
 
   // byte addresses of this lane's fragments of MFMA step kk in stage 0: the row block's first row; the second row
@@ -252,6 +264,9 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict_
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = tmp[i][j][r] = 0.f;
+  f32x16 zero;                                           // a group's sums start from the MFMA's own zero operand
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
 
   // Request order of the prologue = that of the loop: (tile, weights[, scales]) per step, the scales on even steps.
 #pragma unroll
@@ -276,14 +291,14 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict_
   // register set (u % 6) and scale set are fixed per position.
   auto step = [&](auto u_, int kt) {
     constexpr int U = decltype(u_)::value;
-    constexpr int SA = (U % NA) * LDS_TILE * 2, SB = (U % 2) * LDS_TILE * 2;
+    constexpr int SA = (U % NA) * A_TILE * 2, SB = (U % 2) * LDS_TILE * 2;
     dma_a((U + 2) % NA, kt + 2);                         // into the stage step kt-1 was read from
     asm volatile("" ::: "memory");
     load_w(U % AHEAD_W, kt + AHEAD_W);                   // that set went into LDS during step kt-1
     if (U % 2 == 0) load_sc((U / 2 + 2) % 3, (kt >> 1) + 2);
     asm volatile("" ::: "memory");
     w4_request_frags<SA, SB>(a_addr[0], b_addr[0], fa[0][0], fa[0][1], fb[0][0], fb[0][1]);
-    const u32x4 &next_w = wq[(U + 1) % AHEAD_W];
+    const words_t &next_w = wq[(U + 1) % AHEAD_W];
     bf16 *next_b = Bs + ((U + 1) % 2) * LDS_TILE;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
@@ -294,13 +309,16 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict_
       // the MFMAs stay behind the request (left alone, the scheduler moves them up and the wave then waits out the
       // LDS latency of every request with nothing to do)
       __builtin_amdgcn_sched_barrier(0);
-      // a quarter of the next step's weights per MFMA step: expanded and stored while the matrix pipe runs
-      *(bf16x8 *)&next_b[lds_off(b_row, b_half * 4 + kk)] = expand_nibbles(next_w[kk]);
+      // a share of the next step's weights per MFMA step: expanded and stored while the matrix pipe runs
+      if (kk * WORDS % 4 == 0) {
+        constexpr int PER = 4 / WORDS;
+        *(bf16x8 *)&next_b[lds_off(b_row, b_word + kk / PER)] = expand_nibbles(next_w[kk / PER]);
+      }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          tmp[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk & 1][i], fb[kk & 1][j], tmp[i][j], 0, 0, 0);
+          tmp[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk & 1][i], fb[kk & 1][j], U % 2 == 0 && kk == 0 ? zero : tmp[i][j], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (U % 2 == 1) {                                    // end of a group
@@ -311,8 +329,6 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict_
         for (int r = 0; r < 16; ++r) {
           acc[i][0][r] = fmaf(tmp[i][0][r], s0, acc[i][0][r]);
           acc[i][1][r] = fmaf(tmp[i][1][r], s1, acc[i][1][r]);
-          tmp[i][0][r] = 0.f;
-          tmp[i][1][r] = 0.f;
         }
     }
     // The tile of step kt+1 was requested at the top of step kt-1; since then: that step's weights, this step's
@@ -344,211 +360,242 @@ __global__ __launch_bounds__(256, 2) void gemm_w4_kernel(const bf16 *__restrict_
 }
 
 
-// Few tokens (M <= 32: drafting token by token): the product is bound by streaming the packed weights once,
-// so there is no tile of A to share.  A workgroup owns 64 weight rows (SwiGLU: 32 gate rows and the 32 up
-// rows of the same features) and a K range; its four waves take the 128-wide groups of that range in turn and
-// each multiplies whole groups: a lane fetches the 32 + 32 bytes of its two weight rows (one per 32-row
-// block) and of a group half straight from memory, kSkinnyAhead groups ahead, expands them in registers and
-// feeds them to the MFMAs as the column operand, against activation fragments from a tile of the wave's own in
-// LDS (MR rows x 128, direct-to-LDS loads NS - 1 groups ahead; fetched straight into registers, 16 bytes per
-// lane from up to 32 rows, the time grew with the number of rows).  What bounds a wave is the chain of round
-// trips to memory, one per group it cannot request early enough: with the activations one group ahead the 8B
-// gate/up shape took 30 us whatever the expansion cost (three versions of it) and even with all weights
-// resident in L2; hence the deeper ring where the tile is small (16 rows: four stages).  Within a group lane
-// half h owns k = 64 h .. 64 h + 63, eight per MFMA step: the contraction order is free as long as both operands
-// agree.  The four partial results meet in LDS for the epilogue.  Arithmetic as in the tile kernel: integer
-// weights in the MFMAs (here 24 + q, see expand_nibbles_plus24), one fp32 multiply by the group's scale per group.
-template <int EPI, int MR, int NS>
-__global__ __launch_bounds__(256, 2) void gemm_w4_skinny_kernel(const bf16 *__restrict__ A, const uint32_t *__restrict__ Bq,
+// Few tokens (M <= 32: drafting token by token): the product only has to stream the packed weights once.  A workgroup
+// owns 128 weight rows (SwiGLU: 64 gate rows and the 64 up rows of the same features) and a K range, walked in chunks
+// of 256 k, i.e. whole 128-byte lines of packed weights, through a ring of D LDS stages filled by direct-to-LDS loads
+// (non-temporal: each weight is used once).  The activations of a chunk are shared by the workgroup; they are four times
+// as wide as the weights, so a wave that fetched its own would read as many bytes of them as of weights.  Eight waves,
+// two per SIMD: wave (b, g) multiplies rows 32 b.. with group g of the chunk's two, so that expansion and MFMAs of
+// different waves overlap; the two group sums meet in LDS at the end.
+// 16x16x32 MFMAs, tokens as rows and weights as columns: a lane ends with 4 tokens of one weight row and needs one
+// scale per row tile and group.  Within a group lane quarter q owns k = 32 q ..
+// 32 q + 31: one 16-byte LDS read of packed weights feeds four MFMAs (the contraction order is free as long as both
+// operands agree).  Weights enter the MFMAs as 24 + q (expand_nibbles_plus24); the sums start from -24 sum_k a_k,
+// computed once per group for both row tiles by MFMAs against the constant.  One fp32 multiply by the group's scale per
+// group, as in the tile kernel.
+// Measured at 16 tokens, 8B shape, weights from memory (before: 32x32 MFMAs, half empty; weights straight to registers in half
+// lines; activations and scales per wave): gate/up 26.1 -> 18.5 us (3.3 TB/s), O and down in 8 splits 16.8 -> 10.9 on
+// average, QKV in 4 splits 12.2 -> 8.2.  What is left is the start of so short a launch and, per chunk, the expansion.
+// Every wait is counted by hand: loads complete in order, so with the loads of D - 2 later chunks in flight the stage
+// read next has landed, and its scales, requested before it (those of a later chunk only make the wait longer); the barrier makes that true of every wave's share, and tells that the stage refilled next has been
+// read.  The loop is not unrolled over the ring: a workgroup runs 2 to 16 turns, and code that runs once is fetched from memory.
+// s_waitcnt immediate that waits for vector memory only (vmcnt in bits 3:0 and 15:14, the other counts at "no wait")
+constexpr int vmcnt_imm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 0xF70; }
+
+template <int OFF>
+__device__ __forceinline__ void w4s_read(unsigned addr, u32x4 &f) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(f) : "v"(addr), "n"(OFF) : "memory");
+}
+// two 16-row tiles: their scales, then their packed weights
+__device__ __forceinline__ void w4s_read_scales(unsigned addr0, unsigned addr1, unsigned &s0, unsigned &s1) {
+  asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3" : "=&v"(s0), "=&v"(s1) : "v"(addr0), "v"(addr1) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void w4s_await(u32x4 &f0, u32x4 &f1) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(f0), "+v"(f1) : "n"(N) : "memory");
+}
+__device__ __forceinline__ void w4s_await_tiles(unsigned &s0, unsigned &s1, u32x4 &f0, u32x4 &f1) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(s0), "+v"(s1), "+v"(f0), "+v"(f1) : : "memory");
+}
+
+template <int EPI, int MT, int D>
+__global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__restrict__ A, const uint32_t *__restrict__ Bq,
                                                                 const bf16 *__restrict__ Bscale, void *__restrict__ Cv,
                                                                 int M, int N, int K) {
-  static_assert((MR == 16 && NS == 4) || (MR == 32 && NS == 2), "64 KB of stages");
-  constexpr int NW = kSkinnyAhead + 1;                 // register sets of packed weights
-  static_assert(NW % NS == 0 && NW >= NS, "one unrolled ring for both");
-  constexpr int WAVE_TILE = MR * GROUP;                // elements of a wave's activation tile
-  // One array per stage, so that reads of one are not ordered behind the loads in flight into another.  After the
-  // loop the first arrays hold the partial results: per wave [row block][accumulator register][lane] floats (8 KB).
-  __shared__ __attribute__((aligned(16))) bf16 St0[4 * WAVE_TILE], St1[4 * WAVE_TILE], St2[NS > 2 ? 4 * WAVE_TILE : 8],
-      St3[NS > 2 ? 4 * WAVE_TILE : 8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, half = lane >> 5;
-  const int tile = blockIdx.x;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int ng_all = K / GROUP;
-  const int g_begin = (int)((long long)ng_all * blockIdx.y / gridDim.y);
-  const int g_end = (int)((long long)ng_all * (blockIdx.y + 1) / gridDim.y);
-  const uint32_t *bq[2];
-  const bf16 *sc[2];
+  constexpr int RT = 2;                                  // 16-row tiles of weights per wave
+  constexpr int W_BYTES = 128 * 128, X_BYTES = MT * 16 * 512, STAGE = W_BYTES + X_BYTES;
+  constexpr int S_CHUNKS = 4, S_BLOCK = 128 * 32;        // chunks whose scales are fetched together; 32 bytes per row
+  constexpr int LOADS = 2 + MT;                          // per wave and chunk: weights, activations
+  constexpr bool SWIGLU = EPI == ARB_EPI_SWIGLU_BF16;
+  static_assert(D >= 3 && D <= 6 && D * STAGE + 3 * S_BLOCK <= 160 * 1024 && (D - 2) * LOADS <= 63 && D * STAGE >= 4 * RT * MT * 1024, "ring");
+  // the chunks of a ring, at most six, lie in at most three scale blocks
+  __shared__ __attribute__((aligned(1024))) char Ring[D * STAGE + 3 * S_BLOCK];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = lane & 15, quarter = lane >> 4, block = wave & 3, grp = wave >> 2;
+
+  // this workgroup's chunks; a last chunk of one group (K an odd multiple of 128) reads that group twice and uses it once
+  const int ng_all = K / GROUP, nc_all = (ng_all + 1) / 2;
+  const int c_begin = split_point(nc_all, blockIdx.y, gridDim.y);
+  const int n = split_point(nc_all, blockIdx.y + 1, gridDim.y) - c_begin, last = n - 1;
+
+  auto weight_row = [&](int r) {                         // r < 128: 32-row block of a wave, 16-row tile, row
+    if (SWIGLU) return (int)blockIdx.x * 64 + (r >> 5) * 16 + (r & 15) + ((r & 16) ? N : 0);
+    return (int)blockIdx.x * 128 + r;
+  };
+  // Loads of 1 KB: 8 weight rows of 8 pieces (16 bytes), or 2 activation rows of 32.  The pieces of a row are swizzled
+  // on the global side so that the fragment reads (16 rows, one piece) cover all banks.  Addresses are a uniform base
+  // (every load stays inside one 16-row tile) and a 32-bit lane offset.
+  const char *w_base[2];
+  unsigned w_off[2], w_off_half[2], x_off[MT], x_off_half[MT];           // _half: the second group's pieces read the first's
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = EPI == ARB_EPI_SWIGLU_BF16 ? (j ? N : 0) + tile * 32 + col : tile * 64 + j * 32 + col;
-    bq[j] = Bq + (size_t)row * (K / 8) + half * 8;
-    sc[j] = Bscale + (size_t)row * (K / GROUP);
+  for (int i = 0; i < 2; ++i) {
+    const int r0 = (wave * 2 + i) * 8, piece = (lane & 7) ^ (4 * i + (lane >> 4));
+    w_base[i] = (const char *)(Bq + (size_t)weight_row(r0) * (K / 8));
+    w_off[i] = (lane >> 3) * (unsigned)(K / 2) + piece * 16;
+    w_off_half[i] = (lane >> 3) * (unsigned)(K / 2) + (piece & 3) * 16;
   }
-  auto stage = [&](int st) -> bf16 * {
-    return (st == 0 ? St0 : st == 1 ? St1 : st == 2 ? St2 : St3) + wave_u * WAVE_TILE;
-  };
-  // A direct-to-LDS load moves four activation rows of the group (4 x 256 bytes, 16 lanes each); a row's sixteen
-  // 16-byte chunks land XORed with the row number so that the fragment reads (16 rows, one chunk) are free of
-  // bank conflicts.  Rows past M re-read the last row: they only feed output rows that are never stored.
-  const int dma_row = lane >> 4, dma_slot = lane & 15;
-  auto dma_a = [&](int g, int st) {
-    g = g < g_end ? g : g_end - 1;                       // past the range: a valid group, not used
-    bf16 *dst = stage(st);
 #pragma unroll
-    for (int j = 0; j < MR / 4; ++j) {
-      const int r = 4 * j + dma_row;
-      const bf16 *src = A + (size_t)(r < M ? r : M - 1) * K + (size_t)g * GROUP + ((dma_slot ^ (r & 15)) << 3);
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src), LDS_PTR(dst + j * 512), 16, 0, 0);
+  for (int j = 0; j < MT; ++j) {
+    const int r = (wave + 8 * j) * 2 + (lane >> 5), piece = (lane & 31) ^ (r & 15);
+    const unsigned row = (unsigned)(r < M ? r : M - 1) * (unsigned)(K * 2);         // rows past M re-read the last one; never stored
+    x_off[j] = row + piece * 16;
+    x_off_half[j] = row + (piece & 15) * 16;
+  }
+  // Scales are fetched for four chunks at a time, eight dwords of a row (the eight scales may start in the middle of the
+  // first): two bytes per row and chunk would cost the address unit as many cache lines as the weights.  Dwords are aligned; an
+  // array that starts in the middle of one counts from that dword's start.  Past the row they hold others, not used; past
+  // the array's last dword that one is read again.
+  const size_t sc_shift = ((uintptr_t)Bscale & 2) / 2;
+  const char *sc_base = (const char *)((uintptr_t)Bscale & ~(uintptr_t)3);
+  const size_t sc_last = ((size_t)(SWIGLU ? 2 * (size_t)N : (size_t)N) * ng_all + sc_shift - 1) >> 1;
+  auto first_scale = [&](int r) { return (size_t)weight_row(r) * ng_all + sc_shift + 2 * c_begin; };
+  size_t sc_dword[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) sc_dword[i] = (first_scale((wave * 2 + i) * 8 + (lane >> 3)) >> 1) + (lane & 7);
+  auto load_scales = [&](int block_of_chunks) {
+    char *dst = Ring + D * STAGE + block_of_chunks % 3 * S_BLOCK;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      size_t at = sc_dword[i] + block_of_chunks * S_CHUNKS;
+      at = at < sc_last ? at : sc_last;
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(sc_base + at * 4), LDS_PTR(dst + (wave * 2 + i) * 256), 4, 0, 0);
     }
   };
-  // Fragments of the eight MFMA steps of a group: this lane's row (rows past the tile repeat it), chunks 8 half + i.
-  // They are read by inline assembly with its own wait: for LDS reads that it can see, the compiler makes the wave
-  // wait for every load in flight whenever it cannot tell their stage from the one a direct-to-LDS load is filling
-  // (here: in two of four groups), which puts a round trip to memory into each of those groups.
-  const int frag_row = col & (MR - 1);
-  unsigned frag_off[8];
+  auto load = [&](int s, int it) {                       // `it` past the end: the last chunk again, never used
+    if (it % S_CHUNKS == 0 && it < n) load_scales(it / S_CHUNKS);
+    const int c = c_begin + (it < last ? it : last);
+    const bool half = 2 * c + 1 >= ng_all;               // a chunk of one group
+    char *dst = Ring + s * STAGE;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) frag_off[i] = (unsigned)(frag_row * GROUP + (((half * 8 + i) ^ (frag_row & 15)) << 3)) * 2u;
-  auto read_frags = [&](int st, bf16x8 (&fa)[8]) {
-    const unsigned base = (unsigned)(uintptr_t)LDS_PTR(stage(st));
-    asm volatile(
-        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
-        "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(fa[0]), "=&v"(fa[1]), "=&v"(fa[2]), "=&v"(fa[3]), "=&v"(fa[4]), "=&v"(fa[5]), "=&v"(fa[6]), "=&v"(fa[7])
-        : "v"(base + frag_off[0]), "v"(base + frag_off[1]), "v"(base + frag_off[2]), "v"(base + frag_off[3]),
-          "v"(base + frag_off[4]), "v"(base + frag_off[5]), "v"(base + frag_off[6]), "v"(base + frag_off[7])
-        : "memory");
+    for (int i = 0; i < 2; ++i)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(w_base[i] + (size_t)c * 128 + (half ? w_off_half[i] : w_off[i])),
+                                       LDS_PTR(dst + (wave * 2 + i) * 1024), 16, 0, 2 /* nt */);
+#pragma unroll
+    for (int j = 0; j < MT; ++j)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR((const char *)A + (size_t)c * 512 + (half ? x_off_half[j] : x_off[j])),
+                                       LDS_PTR(dst + W_BYTES + (wave + 8 * j) * 1024), 16, 0, 0);
   };
 
-  f32x16 acc[2], tmp[2], asum;                         // asum: the activations' own sum over the group, per output row
+  // LDS addresses of this lane's fragments in stage 0: row tile 0 of the weights; word w of the activations' token tile 0
+  const unsigned ring = (unsigned)(uintptr_t)LDS_PTR(Ring);
+  const unsigned w_addr = ring + (block * 32 + c16) * 128 + (((4 * grp + quarter) ^ (c16 >> 1)) << 4);
+  unsigned x_addr[4];
+  unsigned s_addr[RT], high[RT];                         // address of a scale's dword in block 0, chunk 0; is it the upper half
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = tmp[0][r] = tmp[1][r] = asum[r] = 0.f;
+  for (int i = 0; i < RT; ++i) {
+    const int r = block * 32 + i * 16 + c16;
+    const unsigned h = (unsigned)(first_scale(r) & 1) + grp;
+    s_addr[i] = ring + D * STAGE + r * 32 + (h >> 1) * 4;
+    high[i] = h & 1;
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w) x_addr[w] = ring + W_BYTES + c16 * 512 + (((16 * grp + 4 * quarter + w) ^ c16) << 4);
 
-  // The packed weights of a group and, with them, their scales (loads complete in order, so a scale fetched when
-  // it is needed would make the wave wait for everything requested before it).  Requested by inline assembly: the
-  // compiler then keeps no account of them, and the one counted wait in front of a group is the only wait there
-  // is; for loads that it issues itself it falls back to waiting for all of them wherever it loses count (across
-  // the loop's back edge: once per turn).  A set is read only behind the counted wait that covers it.
-  struct Fetched { u32x4 w[2][2]; unsigned s[2]; };
-  auto load_w = [&](int g, Fetched &f) {
-    g = g < g_end ? g : g_end - 1;
+  f32x4 acc[RT][MT];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint32_t *src = bq[j] + (size_t)g * 16;
-      asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(f.w[j][0]) : "v"(src) : "memory");
-      asm volatile("global_load_dwordx4 %0, %1, off offset:16" : "=&v"(f.w[j][1]) : "v"(src) : "memory");
-      asm volatile("global_load_ushort %0, %1, off" : "=&v"(f.s[j]) : "v"(sc[j] + g) : "memory");
-    }
-  };
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int j = 0; j < MT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 minus24;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) minus24[e] = (bf16)-24.0f;
 
-  // The n-th group of a wave uses weight set n % NW and stage n % NS; the loop is unrolled over NW groups so that
-  // both are fixed per position.  In front of group n the wave requests the tile of group n + NS - 1 and then the
-  // weights of group n + NW - 1 (6 loads); the prologue issues the same requests in the same order.
-  const int g_first = g_begin + wave_u;
-  if (g_first < g_end) {
-    Fetched f[NW];
 #pragma unroll
-    for (int d = 0; d < NW - NS; ++d) load_w(g_first + 4 * d, f[d]);
+  for (int s = 0; s < D - 1; ++s)
+    if (n > 0) load(s, s);
+  int s = 0;
+  for (int it = 0; it < n; ++it) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((D - 2) * LOADS));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    load(s == 0 ? D - 1 : s - 1, it + D - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const unsigned stage = s * STAGE;
+    s = s + 1 == D ? 0 : s + 1;
+    if (2 * (c_begin + it) + grp >= ng_all) continue;    // the missing second group of the last chunk
+    u32x4 wf[RT], xf[MT][4];
+    unsigned sc[RT];
 #pragma unroll
-    for (int k = 0; k < NS - 1; ++k) {
-      asm volatile("" ::: "memory");       // the compiler keeps the order of the requests: the counted wait relies on it
-      dma_a(g_first + 4 * k, k);
-      asm volatile("" ::: "memory");
-      load_w(g_first + 4 * (NW - NS + k), f[NW - NS + k]);
+    for (int w = 0; w < 4; ++w) {
+      w4s_read<0>(x_addr[w] + stage, xf[0][w]);
+      if (MT == 2) w4s_read<16 * 512>(x_addr[w] + stage, xf[MT - 1][w]);
     }
-    bf16x8 ones;
+    const unsigned sc_at = it / S_CHUNKS % 3 * S_BLOCK + it % S_CHUNKS * 4;
+    w4s_read_scales(s_addr[0] + sc_at, s_addr[1] + sc_at, sc[0], sc[1]);
+    w4s_read<0>(w_addr + stage, wf[0]);
+    w4s_read<16 * 128>(w_addr + stage, wf[1]);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (bf16)1.0f;
-    for (int base = g_first; base < g_end; base += 4 * NW) {
+    for (int j = 0; j < MT; ++j) {
+      w4s_await<4>(xf[j][0], xf[j][1]);
+      w4s_await<4>(xf[j][2], xf[j][3]);
+    }
+    f32x4 base[MT];
 #pragma unroll
-      for (int u = 0; u < NW; ++u) {
-        const int gg = base + 4 * u;
-        if (gg >= g_end) break;
-        // What this group reads must have landed: its tile, requested NS - 1 groups ago, and its weights, requested
-        // NW - 1 groups ago, i.e. earlier than the tile (NW > NS) or right behind it (NW == NS).  Every group since
-        // has requested MR / 4 + 6 loads, and loads complete in order, so: at most 6 outstanding (the weights that
-        // followed the tile, NW > NS = 2), or at most (NS - 2) (MR / 4 + 6) = 20 (NW == NS = 4).  The wave reads
-        // only its own tile, so no barrier is needed.
-        static_assert((NS == 2 && NW > NS) || (NS == 4 && NW == NS && (NS - 2) * (MR / 4 + 6) == 20), "the counted waits below");
-        // (the wait names the registers of the set it covers, so that the compiler keeps their readers behind it)
-        Fetched &got = f[u];
-#define ARB_W4_COVERED "+v"(got.w[0][0]), "+v"(got.w[0][1]), "+v"(got.w[1][0]), "+v"(got.w[1][1]), "+v"(got.s[0]), "+v"(got.s[1])
-        if (NS == 2) asm volatile("s_waitcnt vmcnt(6)" : ARB_W4_COVERED : : "memory");
-        else asm volatile("s_waitcnt vmcnt(20)" : ARB_W4_COVERED : : "memory");
-#undef ARB_W4_COVERED
-        dma_a(gg + 4 * (NS - 1), (u + NS - 1) % NS);
-        asm volatile("" ::: "memory");
-        load_w(gg + 4 * (NW - 1), f[(u + NW - 1) % NW]);
-        asm volatile("" ::: "memory");
-        const Fetched &cur = f[u];
-        const float s0 = __uint_as_float(cur.s[0] << 16), s1 = __uint_as_float(cur.s[1] << 16);     // bf16 -> fp32
-        bf16x8 frags[8];
-        read_frags(u % NS, frags);
+    for (int j = 0; j < MT; ++j) {
+      base[j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const bf16x8 fa = frags[i];
-          tmp[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, expand_nibbles_plus24(cur.w[0][i >> 2][i & 3]), tmp[0], 0, 0, 0);
-          tmp[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, expand_nibbles_plus24(cur.w[1][i >> 2][i & 3]), tmp[1], 0, 0, 0);
-          asum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, ones, asum, 0, 0, 0);
-        }
+      for (int w = 0; w < 4; ++w)
+        base[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xf[j][w]), minus24, base[j], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    w4s_await_tiles(sc[0], sc[1], wf[0], wf[1]);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[0][r] = fmaf(fmaf(-24.f, asum[r], tmp[0][r]), s0, acc[0][r]);
-          acc[1][r] = fmaf(fmaf(-24.f, asum[r], tmp[1][r]), s1, acc[1][r]);
-          tmp[0][r] = 0.f;
-          tmp[1][r] = 0.f;
-          asum[r] = 0.f;
-        }
+    for (int i = 0; i < RT; ++i) {
+      f32x4 sum[MT];
+#pragma unroll
+      for (int j = 0; j < MT; ++j) sum[j] = base[j];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const bf16x8 q = expand_nibbles_plus24(wf[i][w]);
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+          sum[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xf[j][w]), q, sum[j], 0, 0, 0);
       }
+      const float scale = __uint_as_float(high[i] ? sc[i] & 0xFFFF0000u : sc[i] << 16);
+#pragma unroll
+      for (int j = 0; j < MT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j][e] = fmaf(sum[j][e], scale, acc[i][j][e]);
     }
-    // The clamped requests past the range: their registers stay named until they have landed (a register the compiler
-    // takes for dead it hands to something else, and a load that lands in it afterwards overwrites that).
-#pragma unroll
-    for (int d = 0; d < NW; ++d)
-      asm volatile("s_waitcnt vmcnt(0)"
-                   : "+v"(f[d].w[0][0]), "+v"(f[d].w[0][1]), "+v"(f[d].w[1][0]), "+v"(f[d].w[1][1]), "+v"(f[d].s[0]), "+v"(f[d].s[1])
-                   : : "memory");
   }
-
-  __syncthreads();                                       // every wave is done with its stage reads (and loads)
-  // partial results of wave w: 8 KB each, four of them in the first array (32-row tiles) or two per array
-  auto part = [&](int w) -> float * {
-    return MR == 32 ? (float *)St0 + w * 2048 : (float *)(w < 2 ? St0 : St1) + (w & 1) * 2048;
-  };
-  {
-    float *mine = part(wave_u);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  // the two group sums of a row block meet in LDS: every load has landed and, past the barrier, every stage has been read
+  __syncthreads();
+  f32x4 *red = (f32x4 *)Ring;
+  if (grp == 1) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mine[(j * 16 + r) * 64 + lane] = acc[j][r];
+      for (int j = 0; j < MT; ++j) red[((block * RT + i) * MT + j) * 64 + lane] = acc[i][j];
   }
   __syncthreads();
-  // D layout of the 32x32 MFMA: lane holds column lane%32 (a weight row) and rows (tokens) 8*(r/4) + 4*(lane/32) + r%4.
+  if (grp == 1) return;
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int idx = tid + 256 * p, r = idx >> 6, L = idx & 63;
-    const int m = 8 * (r >> 2) + 4 * (L >> 5) + (r & 3), c = L & 31;
-    float v[2];
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int at = (j * 16 + r) * 64 + L;
-      v[j] = (part(0)[at] + part(1)[at]) + (part(2)[at] + part(3)[at]);
-    }
-    if (m >= M) continue;
-    if (EPI == ARB_EPI_SWIGLU_BF16) {
-      ((bf16 *)Cv)[(size_t)m * N + tile * 32 + c] = (bf16)(v[0] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0])) * v[1]);
-    } else {
+    for (int j = 0; j < MT; ++j) acc[i][j] += red[((block * RT + i) * MT + j) * 64 + lane];
+  // D layout of the 16x16 MFMA: lane holds column lane%16 (a weight row) and rows (tokens) 4*(lane/16) + {0..3}
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const size_t at = (size_t)m * N + tile * 64 + j * 32 + c;
-        if (EPI == ARB_EPI_STORE_BF16) ((bf16 *)Cv)[at] = (bf16)v[j];
-        else if (EPI == EPI_PARTIAL_F32) ((float *)Cv)[(size_t)blockIdx.y * M * N + at] = v[j];
-        else ((float *)Cv)[at] += v[j];
+  for (int j = 0; j < MT; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int m = j * 16 + 4 * quarter + e;
+      if (m >= M) continue;
+      if (SWIGLU) {
+        const float gte = acc[0][j][e], up = acc[1][j][e];
+        ((bf16 *)Cv)[(size_t)m * N + blockIdx.x * 64 + block * 16 + c16] = (bf16)(gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up);
+      } else {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+          const size_t at = (size_t)m * N + blockIdx.x * 128 + block * 32 + i * 16 + c16;
+          if (EPI == ARB_EPI_STORE_BF16) ((bf16 *)Cv)[at] = (bf16)acc[i][j][e];
+          else if (EPI == EPI_PARTIAL_F32) ((float *)Cv)[(size_t)blockIdx.y * M * N + at] = acc[i][j][e];
+          else ((float *)Cv)[at] += acc[i][j][e];
+        }
       }
     }
-  }
 }
 
 }  // namespace
@@ -563,6 +610,31 @@ arb_status launch_w4_quantize(const bf16 *W, int N, int K, uint32_t *packed, bf1
   else hipLaunchKernelGGL(w4_quantize_kernel<3>, grid, block, 0, st, W, N, K, packed, scales);
   ARB_CHECK_LAUNCH("w4_quantize");
   return ARB_OK;
+}
+
+// Time estimates in us of the two tile kernels, from which the number of K splits and the kernel are chosen: steps of 64 k
+// times the time per step measured with one workgroup per CU, or with two (128-row tiles; 256-row tiles only fit once),
+// and what fp32 partial products cost to write here and read in the consumer.
+static double w4_tile_us(int M, int tiles_n, int K, int splits, bool tall) {
+  const int wgs = ceil_div(M, tall ? 2 * BM : BM) * tiles_n * splits, steps = 2 * ceil_div(K / GROUP, splits);
+  double step;
+  if (tall) step = ceil_div(wgs, 256) * kTallStepUs;
+  else step = wgs / 512 * kPairStepUs + (wgs % 512 == 0 ? 0.0 : wgs % 512 <= 256 ? kSingleStepUs : kPairStepUs);
+  return step * steps + 5.0 + (double)M * tiles_n * BN * 4 * (2 * splits - 2) / 5.0e6;
+}
+static bool w4_tall(int M, int tiles_n, int K, int splits) {
+  return M > BM && w4_tile_us(M, tiles_n, K, splits, true) < w4_tile_us(M, tiles_n, K, splits, false);
+}
+
+int gemm_w4_splits(int M, int N, int K, int max_splits) {
+  int best = 1;
+  double best_us = 0.0;
+  for (int s = 1; s <= max_splits && (s == 1 || K / GROUP / s >= 4); ++s) {
+    double us = w4_tile_us(M, N / BN, K, s, false);
+    if (M > BM) us = fmin(us, w4_tile_us(M, N / BN, K, s, true));
+    if (s == 1 || us < best_us) { best = s; best_us = us; }
+  }
+  return best;
 }
 
 arb_status launch_gemm_w4(const bf16 *A, const uint32_t *Bq, const bf16 *Bscale, void *C, int M, int N, int K,
@@ -582,15 +654,19 @@ arb_status launch_gemm_w4(const bf16 *A, const uint32_t *Bq, const bf16 *Bscale,
   if (splits > 1 && epilogue != ARB_EPI_RESIDUAL_F32 && epilogue != ARB_EPI_STORE_F32)
     return arb_fail(ARB_EINVAL, "gemm_w4: split-K needs an fp32 epilogue (partial products)");
   if (splits < 1 || splits > K / GROUP) return arb_fail(ARB_EINVAL, "gemm_w4: %d splits of %d groups", splits, K / GROUP);
-  const bool skinny = M <= kSkinnyRows;                // few tokens: the weight-streaming kernel, 64 weight rows per workgroup
-  const dim3 grid(skinny ? (epilogue == ARB_EPI_SWIGLU_BF16 ? N / 32 : N / 64) : tiles_m * tiles_n, splits), block(256);
+  const bool skinny = M <= kSkinnyRows;                // few tokens: the weight-streaming kernel
+  const bool tall = !skinny && w4_tall(M, tiles_n, K, splits);
+  const int tall_m = ceil_div(M, 2 * BM);
+  const dim3 grid((tall ? tall_m : tiles_m) * tiles_n, splits), block(skinny || tall ? 512 : 256);
 #define ARB_W4(E)                                                                                                    \
   do {                                                                                                               \
     if (skinny && M <= 16)                                                                                           \
-      hipLaunchKernelGGL((gemm_w4_skinny_kernel<E, 16, 4>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);          \
+      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 1, 6>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);          \
     else if (skinny)                                                                                                 \
-      hipLaunchKernelGGL((gemm_w4_skinny_kernel<E, 32, 2>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);          \
-    else hipLaunchKernelGGL((gemm_w4_kernel<E>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K, tiles_m, tiles_n);   \
+      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 2, 4>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);          \
+    else if (tall)                                                                                                   \
+      hipLaunchKernelGGL((gemm_w4_kernel<E, 4>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K, tall_m, tiles_n);    \
+    else hipLaunchKernelGGL((gemm_w4_kernel<E, 2>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K, tiles_m, tiles_n); \
   } while (0)
   switch (epilogue) {
     case ARB_EPI_STORE_BF16: ARB_W4(ARB_EPI_STORE_BF16); break;
