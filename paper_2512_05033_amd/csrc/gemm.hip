@@ -80,8 +80,8 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const bf16 *__restrict__ A
 
   // K range of this workgroup (the whole of K unless the launch is split along K)
   const int nk_all = K / BK;
-  const int kt_begin = (int)((long long)nk_all * blockIdx.y / gridDim.y);
-  const int nk = (int)((long long)nk_all * (blockIdx.y + 1) / gridDim.y) - kt_begin;
+  const int kt_begin = split_point(nk_all, blockIdx.y, gridDim.y);
+  const int nk = split_point(nk_all, blockIdx.y + 1, gridDim.y) - kt_begin;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     a_src[i] += (size_t)kt_begin * BK;
@@ -271,8 +271,8 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(const bf16 *__restric
 
   // K range of this workgroup (the whole of K unless the launch is split along K)
   const int nk_all = K / RK;
-  const int kt_begin = (int)((long long)nk_all * blockIdx.y / gridDim.y);
-  const int nk = (int)((long long)nk_all * (blockIdx.y + 1) / gridDim.y) - kt_begin, last = nk - 1;
+  const int kt_begin = split_point(nk_all, blockIdx.y, gridDim.y);
+  const int nk = split_point(nk_all, blockIdx.y + 1, gridDim.y) - kt_begin, last = nk - 1;
 #pragma unroll
   for (int i = 0; i < A_LOADS; ++i) a_src[i] += (size_t)kt_begin * RK;
 #pragma unroll
@@ -674,8 +674,8 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(const bf16 *__restric
 
   // K range of this workgroup (the whole of K unless the launch is split along K)
   const int nk_all = K / 64;
-  const int kt_begin = (int)((long long)nk_all * blockIdx.y / gridDim.y);
-  const int nk = (int)((long long)nk_all * (blockIdx.y + 1) / gridDim.y) - kt_begin, last = nk - 1;
+  const int kt_begin = split_point(nk_all, blockIdx.y, gridDim.y);
+  const int nk = split_point(nk_all, blockIdx.y + 1, gridDim.y) - kt_begin, last = nk - 1;
 
   // This wave brings rows [16 wave, 16 wave + 16) of every region, 8 rows of 128 bytes per wave-wide load; the
   // 16-byte chunks of a row are swizzled by row/2 on the global side.  Region row r of A half h is tile row
@@ -895,6 +895,131 @@ __global__ __launch_bounds__(512, 2) void gemm_wide_kernel(const bf16 *__restric
 }
 
 // ---------------------------------------------------------------------------------------------
+// Up to 64 token rows beyond the few that the weight-streaming kernel takes (a short step of one sequence): 64 rows by 64
+// weight rows per workgroup.  Such a launch streams the weights once and is bound by how evenly and how deeply the CUs
+// pull them in; with 128 weight rows per workgroup the projections of the 1.5B shape left half of the CUs idle
+// (QKV, O and down 72 to 96 workgroups, gate/up 140).  K is walked in steps of 64 through a ring of D stages of 16 KB,
+// direct-to-LDS, weights non-temporal; five stages let two workgroups share a CU, nine fill it with one.  A wave multiplies
+// 32 rows by all 64 columns (for SwiGLU 32 features' gate and up rows) over half of a step's k; the two halves are added in
+// LDS at the end.  Reads, waits and loads are ordered by hand as in the eight-wave kernel above: with the loads of D - 2
+// later steps in flight the stage read next has landed, behind the barrier for all waves, and the one refilled next has been read.
+template <int EPI, int D>
+__global__ __launch_bounds__(256) void gemm_narrow_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
+                                                          void *__restrict__ Cv, int M, int N, int K, size_t part_stride) {
+  constexpr int STAGE = 16384, LOADS = 4;                 // bytes: 64 A rows, 64 B rows of 128; loads per wave and step
+  constexpr bool SWIGLU = EPI == ARB_EPI_SWIGLU_BF16;
+  __shared__ __attribute__((aligned(1024))) char Ring[D * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, kh = wave >> 1, frag_row = lane & 31, frag_half = lane >> 5;
+
+  const int nk_all = K / 64;
+  const int kt_begin = split_point(nk_all, blockIdx.y, gridDim.y);
+  const int n = split_point(nk_all, blockIdx.y + 1, gridDim.y) - kt_begin, last = n - 1;
+
+  // A load fills 8 rows of 8 pieces (16 bytes); this wave's rows are 8 wave + lane/8 and 32 more.  Pieces are swizzled by
+  // row/2 on the global side.  Addresses: a uniform base and a 32-bit lane offset.
+  const int row = wave * 8 + (lane >> 3);
+  const unsigned k_bytes = (unsigned)K * 2, piece = ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+  unsigned a_off[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) a_off[i] = (unsigned)min(row + 32 * i, M - 1) * k_bytes + piece;      // rows past M: never stored
+  const unsigned b_off = (unsigned)row * k_bytes + piece;
+  const char *a_base = (const char *)A + (size_t)kt_begin * 128;
+  const char *b_base = (const char *)B + (size_t)blockIdx.x * (SWIGLU ? 32 : 64) * k_bytes + (size_t)kt_begin * 128;
+  const size_t b_upper = (size_t)(SWIGLU ? N : 32) * k_bytes;          // from the tile's first 32 weight rows to the others
+  auto load = [&](int s, int it) {                        // past the end: the last step again, never multiplied
+    const size_t k = (size_t)(it < last ? it : last) * 128;
+    char *dst = Ring + s * STAGE + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(b_base + k + (i ? b_upper : 0) + b_off), LDS_PTR(dst + 8192 + i * 4096), 16, 0, 2 /* nt */);
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(a_base + k + a_off[i]), LDS_PTR(dst + i * 4096), 16, 0, 0);
+    }
+  };
+
+  f32x16 acc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+
+  // LDS offsets of this lane's fragments of its two MFMA steps
+  unsigned a_addr[2], b_addr[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const unsigned o = (unsigned)(uintptr_t)LDS_PTR(Ring) + frag_row * 128 + (((2 * (2 * kh + u) + frag_half) ^ ((frag_row >> 1) & 7)) << 4);
+    a_addr[u] = o + wm * 4096;
+    b_addr[u] = o + 8192;
+  }
+#pragma unroll
+  for (int s = 0; s < D - 1; ++s) load(s, s);
+  int s = 0;
+  for (int it = 0; it < n; ++it) {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((D - 2) * LOADS));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    load(s == 0 ? D - 1 : s - 1, it + D - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const unsigned stage = s * STAGE;
+    bf16x8 fa[2], fb[2][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      wide_request_b<0>(a_addr[u] + stage, fa[u]);
+      wide_request_a<0>(b_addr[u] + stage, fb[u][0], fb[u][1]);       // 32 rows of 128 bytes apart
+    }
+    wide_await<3>(fa[0], fb[0][0], fb[0][1]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[0], fb[0][j], acc[j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    wide_await<0>(fa[1], fb[1][0], fb[1][1]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[1], fb[1][j], acc[j], 0, 0, 0);
+    s = s + 1 == D ? 0 : s + 1;
+  }
+  // every load has landed and, past the barrier, every stage has been read
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(0));
+  __syncthreads();
+  f32x4 *red = (f32x4 *)Ring;
+  if (kh == 1) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        red[((wm * 2 + j) * 4 + q) * 64 + lane] = f32x4{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+  }
+  __syncthreads();
+  if (kh == 1) return;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = red[((wm * 2 + j) * 4 + q) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[j][4 * q + e] += v[e];
+    }
+  // D layout of the 32x32 MFMA: lane holds column lane%32 and rows 8*(r/4) + 4*(lane/32) + r%4.
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = wm * 32 + 8 * (r >> 2) + 4 * frag_half + (r & 3);
+    if (m >= M) continue;
+    if (SWIGLU) {
+      const float gte = acc[0][r], up = acc[1][r];
+      ((bf16 *)Cv)[(size_t)m * N + blockIdx.x * 32 + frag_row] = (bf16)(gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const size_t at = (size_t)m * N + blockIdx.x * 64 + j * 32 + frag_row;
+        if (EPI == ARB_EPI_STORE_BF16) ((bf16 *)Cv)[at] = (bf16)acc[j][r];
+        else if (EPI == EPI_PARTIAL_F32) ((float *)Cv)[blockIdx.y * part_stride + at] = acc[j][r];
+        else ((float *)Cv)[at] += acc[j][r];
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Weight-streaming kernel for few token rows (M <= 32: drafting token by token, a single short step).
 // Such a launch reads every weight once and multiplies it with next to nothing, so it is bound by how many
 // bytes of weights are in flight (a plain read of this memory reaches 6.2 TB/s, 7.0 with non-temporal loads).
@@ -930,8 +1055,8 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(const bf16 *__restrict
 
   // K range of this workgroup in chunks of 64, and this wave's share of it: chunks begin + wave, + W, ...
   const int nk_all = K / 64;
-  const int kt_begin = (int)((long long)nk_all * blockIdx.y / gridDim.y);
-  const int kt_end = (int)((long long)nk_all * (blockIdx.y + 1) / gridDim.y);
+  const int kt_begin = split_point(nk_all, blockIdx.y, gridDim.y);
+  const int kt_end = split_point(nk_all, blockIdx.y + 1, gridDim.y);
   const int n = (kt_end - kt_begin - wave + W - 1) / W, last = n - 1;
 
   const bf16 *w_src[2 * RT], *x_src[2 * MT];
@@ -1109,7 +1234,7 @@ int gemm_large_cols(int M, int N, int K, int epilogue, int splits) {
   // rounds (all of them when the last round would be at least 80 % full), the remaining columns in
   // 128x128 tiles.  With less than one round of large tiles everything runs in small ones.
   const int big_n = epilogue == ARB_EPI_SWIGLU_BF16 ? 128 : LN;       // a large n-tile is two small ones
-  if (splits != 1 || M <= 0 || N <= 0 || N % big_n != 0) return 0;
+  if (splits != 1 || M <= 64 || N <= 0 || N % big_n != 0) return 0;
   const int tm = ceil_div(M, LM), tn = N / big_n, total = tm * tn, tail = total % 256;
   if (total < 205) return 0;
   return 5 * tail >= 4 * 256 || tail == 0 ? tn : (total - tail) / tm;
@@ -1235,6 +1360,34 @@ static arb_status launch_tiles(const bf16 *A, const bf16 *B, void *C, int M, int
     }
 #undef ARB_STREAM
     ARB_CHECK_LAUNCH("gemm_stream");
+    return ARB_OK;
+  }
+  // At most 64 token rows: 64 weight rows per workgroup where 128 of them would leave half of the CUs idle, or would make
+  // more than one round of one workgroup per CU (two of these share a CU).  Measured at 37 tokens against 64x128 tiles: down
+  // of the 1.5B shape (96 workgroups of 128 weight rows) 12.7 -> 9.8 us, QKV and O (96, 72) 6.3 -> 6.2 and 6.1 -> 6.0, LM head
+  // (1187, in large tiles before) 117 -> 106, of the 8B shape 248 -> 213.  In between 128 weight rows stay the better
+  // ones: gate/up (140) 16.3 against 18.5.
+  const int wgs128 = rows / BN * splits;
+  if (M <= 64 && (wgs128 <= 128 || wgs128 > 256)) {
+    if (part == GEMM_PART_LARGE) return ARB_OK;
+    const dim3 ngrid(rows / 64, splits), nblock(256);
+    const bool one = rows / 64 * splits <= 256;           // one workgroup per CU: the deep ring
+#define ARB_NARROW(E)                                                                                                    \
+  do {                                                                                                                   \
+    if (one) hipLaunchKernelGGL((gemm_narrow_kernel<E, 9>), ngrid, nblock, 0, st, A, B, C, M, N, K, part_stride);         \
+    else hipLaunchKernelGGL((gemm_narrow_kernel<E, 5>), ngrid, nblock, 0, st, A, B, C, M, N, K, part_stride);             \
+  } while (0)
+    switch (epilogue) {
+      case ARB_EPI_STORE_BF16: ARB_NARROW(ARB_EPI_STORE_BF16); break;
+      case ARB_EPI_RESIDUAL_F32:
+        if (splits > 1) ARB_NARROW(EPI_PARTIAL_F32); else ARB_NARROW(ARB_EPI_RESIDUAL_F32);
+        break;
+      case ARB_EPI_SWIGLU_BF16: ARB_NARROW(ARB_EPI_SWIGLU_BF16); break;
+      case ARB_EPI_STORE_F32: ARB_NARROW(ARB_EPI_STORE_F32); break;
+      default: return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
+    }
+#undef ARB_NARROW
+    ARB_CHECK_LAUNCH("gemm_narrow");
     return ARB_OK;
   }
   const int big_cols = gemm_large_cols(M, N, K, epilogue, splits);   // n-tile columns given to the large-tile kernel
