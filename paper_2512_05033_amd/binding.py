@@ -230,7 +230,10 @@ class DeviceBatch:
         self.cu_host = np.ascontiguousarray(cu_step_lens, dtype=np.int32)
         tables = np.ascontiguousarray(block_tables, dtype=np.int32)
         to = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(device)
-        self.prefix, self.cu, self.tables = to(self.prefix_host), to(self.cu_host), to(tables)
+        # one copy for the three arrays: each copy waits for the stream (a decoding loop makes a batch per token)
+        parts = [self.prefix_host, self.cu_host, tables]
+        packed = to(np.concatenate([a.reshape(-1) for a in parts])).split([a.size for a in parts])
+        self.prefix, self.cu, self.tables = (t.view(a.shape) for t, a in zip(packed, parts))
         if isinstance(token_ids, torch.Tensor):           # already on the device (tokens chosen by arb_next_token)
             self.tokens = _dev(token_ids, torch.int32)
         else:

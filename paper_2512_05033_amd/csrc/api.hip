@@ -331,16 +331,20 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   auto scale_of = [&](const std::vector<const bf16 *> &v, int l) { return m->w4 ? v[l] : (const bf16 *)nullptr; };
   RowParts pending{};
   arb_status s;
-  if ((s = launch_token_meta(bt->prefix_lens, bt->cu_step_lens, bt->block_tables, B, T, bt->max_blocks_per_seq,
-                             c.kv_block, w.tok_pos, w.tok_slot, st, &plan,
-                             attention_lists(w.attn_ws, plan, T, c.n_q_heads, c.head_dim), G, c.n_kv_heads)))
-    return s;
-  if ((s = launch_rope_table(w.tok_pos, T, c.head_dim, c.rope_base, w.cs, st))) return s;
+  const AttnLists lists = attention_lists(w.attn_ws, plan, T, c.n_q_heads, c.head_dim);
+  if (h_in) {                                              // otherwise the first norm's launch does this too
+    if ((s = launch_token_meta(bt->prefix_lens, bt->cu_step_lens, bt->block_tables, B, T, bt->max_blocks_per_seq,
+                               c.kv_block, w.tok_pos, w.tok_slot, st, &plan, lists, G, c.n_kv_heads)))
+      return s;
+    if ((s = launch_rope_table(w.tok_pos, T, c.head_dim, c.rope_base, w.cs, st))) return s;
+  }
   for (int l = l0; l < l1; ++l) {
     {
       TraceScope t(m, ARB_STAGE_NORM, st);
       if (l == 0 && !h_in)
-        s = launch_embed_rmsnorm(m->embed, bt->token_ids, m->g_attn[0], c.rms_eps, T, d, w.h, w.x, st);
+        s = launch_open_pass(m->embed, bt->token_ids, m->g_attn[0], c.rms_eps, T, d, w.h, w.x, bt->prefix_lens, bt->cu_step_lens,
+                             bt->block_tables, B, bt->max_blocks_per_seq, c.kv_block, w.tok_slot, c.rope_base, c.head_dim, w.cs,
+                             plan, lists, G, c.n_kv_heads, st);
       else
         s = launch_rmsnorm(w.h, w.parts, pending, m->g_attn[l], c.rms_eps, T, d, w.x, st);
       pending = RowParts{};

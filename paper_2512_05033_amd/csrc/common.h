@@ -152,8 +152,12 @@ arb_status launch_check_ids(const int32_t *token_ids, int T, int vocab, const in
                             int kv_block, int n_blocks, int32_t *err, hipStream_t st);
 arb_status launch_rope_table(const int32_t *tok_pos, int total_tokens, int head_dim, float rope_base, f32x2 *cs,
                              hipStream_t st);
-arb_status launch_embed_rmsnorm(const bf16 *embed, const int32_t *token_ids, const float *g, float eps, int T, int d,
-                                float *h, bf16 *x, hipStream_t st);
+// The first launch of a pass that starts from token ids: h = the embeddings, x = their norm, and what launch_token_meta and
+// launch_rope_table write (slots, rotary table, the attention work list).
+arb_status launch_open_pass(const bf16 *embed, const int32_t *token_ids, const float *g, float eps, int T, int d, float *h,
+                            bf16 *x, const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
+                            int batch, int max_blocks_per_seq, int kv_block, int32_t *tok_slot, float rope_base, int head_dim,
+                            f32x2 *cs, const AttnPlan &plan, AttnLists lists, int G, int n_kv_heads, hipStream_t st);
 // The fp32 partial products [*, T, d] of a projection that a norm kernel first adds to h (and h is updated): `head` of
 // them for rows below `row`, `tail` for the others (the segments of a GemmPlan).
 struct RowParts {

@@ -112,38 +112,55 @@ __device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, c
 
 // For step token j of sequence b at position pos = p_b + i:
 //   slot = block_tables[b][pos / blk] * blk + pos % blk.
-// The blocks behind the tokens' write the attention work list (list_blocks of them, none without one).
-__global__ __launch_bounds__(256) void token_meta_kernel(const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ cu,
-                                                         const int32_t *__restrict__ tables, int batch, int T, int max_blocks,
-                                                         int blk, int32_t *__restrict__ tok_pos, int32_t *__restrict__ tok_slot,
-                                                         int list_blocks, int kv_chunk, int G, int Hkv, AttnLists lists) {
-  const int tok_blocks = gridDim.x - list_blocks;
-  if ((int)blockIdx.x >= tok_blocks) {
-    write_attention_items(prefix_lens, cu, batch, G, Hkv, kv_chunk, lists.items, blockIdx.x - tok_blocks, list_blocks);
-    return;
-  }
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= T) return;
-  int lo = 0, hi = batch;                 // largest b with cu[b] <= j
+struct TokenMeta {
+  const int32_t *prefix_lens, *cu, *tables;
+  int batch, max_blocks, blk;
+  int32_t *tok_pos, *tok_slot;
+  int list_blocks, kv_chunk, G, Hkv;       // blocks of the launch that write the attention work list (0: there is none)
+  AttnLists lists;
+};
+
+// -> the token's position; with `write` also stores what the later kernels read about it
+__device__ __forceinline__ int token_meta(const TokenMeta &t, int j, bool write) {
+  int lo = 0, hi = t.batch;               // largest b with cu[b] <= j
   while (hi - lo > 1) {
     const int mid = (lo + hi) >> 1;
-    if (cu[mid] <= j) lo = mid; else hi = mid;
+    if (t.cu[mid] <= j) lo = mid; else hi = mid;
   }
-  const int b = lo;
-  const int pos = prefix_lens[b] + (j - cu[b]);
-  if (tok_pos) tok_pos[j] = pos;
-  if (tok_slot) tok_slot[j] = tables[(size_t)b * max_blocks + pos / blk] * blk + pos % blk;
-  if (list_blocks) lists.tok_splits[j] = pos / attn_seq_chunk(prefix_lens[b] + cu[b + 1] - cu[b], kv_chunk) + 1;
+  const int b = lo, prefix = t.prefix_lens[b], t0 = t.cu[b], pos = prefix + (j - t0);
+  if (write) {
+    if (t.tok_pos) t.tok_pos[j] = pos;
+    if (t.tok_slot) t.tok_slot[j] = t.tables[(size_t)b * t.max_blocks + pos / t.blk] * t.blk + pos % t.blk;
+    if (t.list_blocks) t.lists.tok_splits[j] = pos / attn_seq_chunk(prefix + t.cu[b + 1] - t0, t.kv_chunk) + 1;
+  }
+  return pos;
+}
+
+// The first list_blocks blocks write the attention work list.
+__global__ __launch_bounds__(256) void token_meta_kernel(TokenMeta t, int T) {
+  if ((int)blockIdx.x < t.list_blocks) {
+    write_attention_items(t.prefix_lens, t.cu, t.batch, t.G, t.Hkv, t.kv_chunk, t.lists.items, blockIdx.x, t.list_blocks);
+    return;
+  }
+  const int j = (blockIdx.x - t.list_blocks) * 256 + threadIdx.x;
+  if (j < T) token_meta(t, j, true);
+}
+
+static TokenMeta token_meta_args(const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
+                                 int batch, int max_blocks_per_seq, int kv_block, int32_t *tok_pos, int32_t *tok_slot,
+                                 const AttnPlan *plan, AttnLists lists, int G, int n_kv_heads) {
+  const int list_blocks = !plan ? 0 : plan->n_items <= 1024 ? 1 : plan->n_items <= 16384 ? ceil_div(plan->n_items, 1024) : 16;
+  return TokenMeta{prefix_lens, cu_step_lens, block_tables, batch, max_blocks_per_seq, kv_block, tok_pos, tok_slot,
+                   list_blocks, plan ? plan->kv_chunk : ATTN_KT, G, n_kv_heads, lists};
 }
 
 arb_status launch_token_meta(const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
                              int batch, int total_tokens, int max_blocks_per_seq, int kv_block, int32_t *tok_pos,
                              int32_t *tok_slot, hipStream_t st, const AttnPlan *plan, AttnLists lists, int G, int n_kv_heads) {
   if (total_tokens == 0) return ARB_OK;
-  const int list_blocks = !plan ? 0 : plan->n_items <= 1024 ? 1 : plan->n_items <= 16384 ? ceil_div(plan->n_items, 1024) : 16;
-  hipLaunchKernelGGL(token_meta_kernel, dim3(ceil_div(total_tokens, 256) + list_blocks), dim3(256), 0, st, prefix_lens,
-                     cu_step_lens, block_tables, batch, total_tokens, max_blocks_per_seq, kv_block, tok_pos, tok_slot,
-                     list_blocks, plan ? plan->kv_chunk : ATTN_KT, G, n_kv_heads, lists);
+  const TokenMeta t = token_meta_args(prefix_lens, cu_step_lens, block_tables, batch, max_blocks_per_seq, kv_block, tok_pos,
+                                      tok_slot, plan, lists, G, n_kv_heads);
+  hipLaunchKernelGGL(token_meta_kernel, dim3(ceil_div(total_tokens, 256) + t.list_blocks), dim3(256), 0, st, t, total_tokens);
   ARB_CHECK_LAUNCH("token_meta");
   return ARB_OK;
 }
@@ -203,16 +220,19 @@ arb_status launch_check_ids(const int32_t *token_ids, int T, int vocab, const in
 
 // cs[j][t] = (cos, sin) of pos_j * base^(-2t/hd), evaluated in fp64 so that the
 // fp32 table is correctly rounded even at positions of tens of thousands.
+__device__ __forceinline__ f32x2 rope_cos_sin(int pos, int t, int half, double log2_base) {
+  const double inv_freq = exp2(-(double)t / (double)half * log2_base);
+  double s, c;
+  sincos((double)pos * inv_freq, &s, &c);
+  return f32x2{(float)c, (float)s};
+}
+
 __global__ void rope_table_kernel(const int32_t *__restrict__ tok_pos, int T, int half, double log2_base,
                                   f32x2 *__restrict__ cs) {
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= T * half) return;
   const int j = idx / half, t = idx - j * half;
-  const double inv_freq = exp2(-(double)t / (double)half * log2_base);
-  const double ang = (double)tok_pos[j] * inv_freq;
-  double s, c;
-  sincos(ang, &s, &c);
-  cs[idx] = f32x2{(float)c, (float)s};
+  cs[idx] = rope_cos_sin(tok_pos[j], t, half, log2_base);
 }
 
 arb_status launch_rope_table(const int32_t *tok_pos, int total_tokens, int head_dim, float rope_base, f32x2 *cs,
@@ -227,14 +247,26 @@ arb_status launch_rope_table(const int32_t *tok_pos, int total_tokens, int head_
 
 // ------------------------------------------------------------------------ RMSNorm
 
-// One block of 256 threads per row; a row is held in registers between the
-// sum-of-squares pass and the scaling pass (d <= 256*8*ROW_VECS).
-#define ROW_VECS 4
+// One block of 256 threads per row; a row is held in registers between the sum-of-squares pass and the scaling
+// pass: VECS groups of eight elements per thread (1, 2 or 4, the fewest that hold the row, so that the registers of
+// a narrow row do not cost resident waves).  With few rows the kernel is one chain of memory round trips; the gains are
+// asked for together with the row, not behind the reduction (16 rows of 1536: 4.2 -> 3.5 us).
+#define ROW_VECS 4         // the most
 
 // With partial products the row is first completed by those of the preceding residual projection (their number may
 // differ between its head and its tail rows): h = h_in + sum_s parts[s] (fixed order), and written back through
 // h_out when that is not null.
-template <bool EMBED, bool HEAD>
+// The EMBED launch opens a pass: the row is a token's embedding, and the block also finds the token's position and pool
+// slot and its row of the rotary table; its first blocks write the attention work list.  (Three launches before, all of
+// them short chains of dependent loads: together 9 to 20 us of a pass, and the gaps between them.)
+struct PassOpening {
+  TokenMeta meta;
+  double log2_base;
+  int half;                  // head_dim / 2
+  f32x2 *cs;
+};
+
+template <bool EMBED, bool HEAD, int VECS>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const float *__restrict__ parts,
                                                       RowParts row_parts, size_t part_stride,
                                                       const bf16 *__restrict__ embed,
@@ -242,16 +274,29 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const f
                                                       const float *__restrict__ g, float eps, int d,
                                                       float *h_out, bf16 *__restrict__ x_out,
                                                       const float *__restrict__ w_head,
-                                                      const float *__restrict__ w_head1, float *__restrict__ tok_dot) {
+                                                      const float *__restrict__ w_head1, float *__restrict__ tok_dot,
+                                                      PassOpening opening) {
   __shared__ float red[4];
-  const int row = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
+  int row = blockIdx.x;
+  if (EMBED) {
+    const TokenMeta &m = opening.meta;
+    if (row < m.list_blocks) {
+      write_attention_items(m.prefix_lens, m.cu, m.batch, m.G, m.Hkv, m.kv_chunk, m.lists.items, row, m.list_blocks);
+      return;
+    }
+    row -= m.list_blocks;
+  }
   const int n_parts = row < row_parts.row ? row_parts.head : row_parts.tail;
-  float v[ROW_VECS][8];
+  float v[VECS][8];
+  f32x4 gain[VECS][2];
   float ss = 0.f;
 #pragma unroll
-  for (int it = 0; it < ROW_VECS; ++it) {
+  for (int it = 0; it < VECS; ++it) {
     const int c = (it * 256 + tid) * 8;
     if (c < d) {
+      gain[it][0] = *(const f32x4 *)(g + c);
+      gain[it][1] = *(const f32x4 *)(g + c + 4);
       if (EMBED) {
         const bf16x8 e = *(const bf16x8 *)(embed + (size_t)token_ids[row] * d + c);
 #pragma unroll
@@ -302,14 +347,18 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const f
       for (int k = 0; k < 8; ++k) ss += v[it][k] * v[it][k];
     }
   }
+  if (EMBED) {
+    const int pos = token_meta(opening.meta, row, tid == 0);
+    for (int t = tid; t < opening.half; t += 256) opening.cs[(size_t)row * opening.half + t] = rope_cos_sin(pos, t, opening.half, opening.log2_base);
+  }
   ss = block_sum_256(ss, red);
   const float r = 1.0f / sqrtf(ss / (float)d + eps);
   float dot = 0.f;
 #pragma unroll
-  for (int it = 0; it < ROW_VECS; ++it) {
+  for (int it = 0; it < VECS; ++it) {
     const int c = (it * 256 + tid) * 8;
     if (c < d) {
-      const f32x4 g0 = *(const f32x4 *)(g + c), g1 = *(const f32x4 *)(g + c + 4);
+      const f32x4 g0 = gain[it][0], g1 = gain[it][1];
       float y[8];
 #pragma unroll
       for (int k = 0; k < 4; ++k) { y[k] = v[it][k] * r * g0[k]; y[4 + k] = v[it][4 + k] * r * g1[k]; }
@@ -336,20 +385,33 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const f
   }
 }
 
+// launches rmsnorm_kernel<EMBED, HEAD, VECS> for rows of d elements
+#define ARB_LAUNCH_NORM(EMBED, HEAD, GRID, ...)                                                                            \
+  do {                                                                                                                    \
+    if (d <= 2048) hipLaunchKernelGGL((rmsnorm_kernel<EMBED, HEAD, 1>), dim3(GRID), dim3(256), 0, st, __VA_ARGS__);        \
+    else if (d <= 4096) hipLaunchKernelGGL((rmsnorm_kernel<EMBED, HEAD, 2>), dim3(GRID), dim3(256), 0, st, __VA_ARGS__);   \
+    else hipLaunchKernelGGL((rmsnorm_kernel<EMBED, HEAD, ROW_VECS>), dim3(GRID), dim3(256), 0, st, __VA_ARGS__);           \
+  } while (0)
+
 static arb_status check_row_width(int d) {
   if (d <= 0 || d % 8 != 0 || d > 256 * 8 * ROW_VECS)
     return arb_fail(ARB_EUNSUPPORTED, "row width %d: need a multiple of 8 up to %d", d, 256 * 8 * ROW_VECS);
   return ARB_OK;
 }
 
-arb_status launch_embed_rmsnorm(const bf16 *embed, const int32_t *token_ids, const float *g, float eps, int T, int d,
-                                float *h, bf16 *x, hipStream_t st) {
+arb_status launch_open_pass(const bf16 *embed, const int32_t *token_ids, const float *g, float eps, int T, int d, float *h,
+                            bf16 *x, const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
+                            int batch, int max_blocks_per_seq, int kv_block, int32_t *tok_slot, float rope_base, int head_dim,
+                            f32x2 *cs, const AttnPlan &plan, AttnLists lists, int G, int n_kv_heads, hipStream_t st) {
   if (T == 0) return ARB_OK;
   if (arb_status s = check_row_width(d)) return s;
-  hipLaunchKernelGGL((rmsnorm_kernel<true, false>), dim3(T), dim3(256), 0, st, (const float *)nullptr,
+  const PassOpening o{token_meta_args(prefix_lens, cu_step_lens, block_tables, batch, max_blocks_per_seq, kv_block, nullptr,
+                                      tok_slot, &plan, lists, G, n_kv_heads),
+                      log2((double)rope_base), head_dim / 2, cs};
+  ARB_LAUNCH_NORM(true, false, T + o.meta.list_blocks, (const float *)nullptr,
                      (const float *)nullptr, RowParts{}, (size_t)0, embed, token_ids, g, eps, d, h, x, (const float *)nullptr,
-                     (const float *)nullptr, (float *)nullptr);
-  ARB_CHECK_LAUNCH("embed_rmsnorm");
+                     (const float *)nullptr, (float *)nullptr, o);
+  ARB_CHECK_LAUNCH("open_pass");
   return ARB_OK;
 }
 
@@ -357,9 +419,9 @@ arb_status launch_rmsnorm(float *h, const float *parts, RowParts n_parts, const 
                           hipStream_t st) {
   if (T == 0) return ARB_OK;
   if (arb_status s = check_row_width(d)) return s;
-  hipLaunchKernelGGL((rmsnorm_kernel<false, false>), dim3(T), dim3(256), 0, st, (const float *)h, parts, n_parts,
+  ARB_LAUNCH_NORM(false, false, T, (const float *)h, parts, n_parts,
                      (size_t)T * d, (const bf16 *)nullptr, (const int32_t *)nullptr, g, eps, d, h, x,
-                     (const float *)nullptr, (const float *)nullptr, (float *)nullptr);
+                     (const float *)nullptr, (const float *)nullptr, (float *)nullptr, PassOpening{});
   ARB_CHECK_LAUNCH("rmsnorm");
   return ARB_OK;
 }
@@ -370,9 +432,9 @@ arb_status launch_final_norm_head(const float *h, const float *parts, RowParts n
   if (T == 0) return ARB_OK;
   if (arb_status s = check_row_width(d)) return s;
   // the residual stream is not needed after the last norm, so the completed row is not written back
-  hipLaunchKernelGGL((rmsnorm_kernel<false, true>), dim3(T), dim3(256), 0, st, h, parts, n_parts, (size_t)T * d,
+  ARB_LAUNCH_NORM(false, true, T, h, parts, n_parts, (size_t)T * d,
                      (const bf16 *)nullptr, (const int32_t *)nullptr, g, eps, d, (float *)nullptr, hidden_out, w_head,
-                     w_head1, tok_dot);
+                     w_head1, tok_dot, PassOpening{});
   ARB_CHECK_LAUNCH("final_norm_head");
   return ARB_OK;
 }
@@ -409,10 +471,22 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv
     float a[2], b[2];
     if (PARTS) {
       a[0] = a[1] = b[0] = b[1] = 0.f;
-      for (int p = 0; p < n_parts; ++p) {
-        const float *ps = prow + p * part_stride + head * hd;
-        const f32x2 pa = *(const f32x2 *)(ps + t), pb = *(const f32x2 *)(ps + t + half);
-        a[0] += pa[0]; a[1] += pa[1]; b[0] += pb[0]; b[1] += pb[1];
+      // up to eight partial products are asked for together (a loop over a run-time count waits for each before it asks
+      // for the next: 16 tokens of the 1.5B shape, 4 partial products, 3.9 -> 3.4 us); the sums keep the fixed order
+      const float *p0 = prow + head * hd + t;
+      for (int p = 0; p < n_parts; p += 8) {
+        f32x2 pa[8], pb[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (p + i < n_parts) {
+            pa[i] = *(const f32x2 *)(p0 + (p + i) * part_stride);
+            pb[i] = *(const f32x2 *)(p0 + (p + i) * part_stride + half);
+          }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (p + i < n_parts) {
+            a[0] += pa[i][0]; a[1] += pa[i][1]; b[0] += pb[i][0]; b[1] += pb[i][1];
+          }
       }
     } else {
       const bf16x2 va = *(const bf16x2 *)(src + t), vb = *(const bf16x2 *)(src + t + half);
