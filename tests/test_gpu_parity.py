@@ -852,6 +852,20 @@ def test_w4_gemm(A, M, N, K, epi):
         assert got.shape == (M, N) and rel_err(got, O.silu(ref[:, :N]) * ref[:, N:]) < 5e-3
 
 
+@pytest.mark.parametrize("M", [1, 16, 17, 32])
+@pytest.mark.parametrize("K", [128, 256, 640, 1024, 1408, 1664, 3200])
+def test_w4_few_tokens_at_chunk_edges(A, M, K):
+    """The streaming kernel walks K in chunks of two groups through a ring of 4 or 6: a single group, odd numbers of
+    groups (half a last chunk), fewer chunks than the ring holds, whole turns and every remainder."""
+    N = 256
+    a, w = rand_bf16((M, K), 1.0, 56), rand_bf16((N, K), 0.05, 57)
+    packed, scales = A.arb_w4_quantize(w)
+    ref = bf16_np(a) @ O.w4_dequantize(*O.w4_quantize(W.bf16_bits(w))).T
+    assert rel_err(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
+    got = bf16_np(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_SWIGLU_BF16))
+    assert got.shape == (M, N // 2) and rel_err(got, O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
+
+
 @pytest.mark.parametrize("few_tokens,bits", [(False, 4), (True, 4), (True, 3)])
 def test_quantized_draft_forward_matches_the_oracle_on_dequantized_weights(A, few_tokens, bits):
     """The whole forward with 4-bit projection weights (C2's shape, 2 layers, so that split-K, SwiGLU
@@ -881,20 +895,6 @@ def test_quantized_draft_forward_matches_the_oracle_on_dequantized_weights(A, fe
 
 @pytest.mark.parametrize("n,S,vocab", [(5, 7, 6), (700, 12, 9), (64, 1, 3)])
 def test_step_advance_and_pack_follow_first_stop(A, n, S, vocab):
-@pytest.mark.parametrize("M", [1, 16, 17, 32])
-@pytest.mark.parametrize("K", [128, 256, 640, 1024, 1408, 1664, 3200])
-def test_w4_few_tokens_at_chunk_edges(A, M, K):
-    """The streaming kernel walks K in chunks of two groups through a ring of 4 or 6: a single group, odd numbers of
-    groups (half a last chunk), fewer chunks than the ring holds, whole turns and every remainder."""
-    N = 256
-    a, w = rand_bf16((M, K), 1.0, 56), rand_bf16((N, K), 0.05, 57)
-    packed, scales = A.arb_w4_quantize(w)
-    ref = bf16_np(a) @ O.w4_dequantize(*O.w4_quantize(W.bf16_bits(w))).T
-    assert rel_err(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
-    got = bf16_np(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_SWIGLU_BF16))
-    assert got.shape == (M, N // 2) and rel_err(got, O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
-
-
     """Token columns fed one iteration at a time: every step must end where the oracle's first_stop puts its end
     (separator, eos, or max_len), hold exactly those tokens, and drop out of the open list from then on; the
     packed ragged list must be the concatenation of the steps."""
