@@ -470,10 +470,10 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv
     bf16 *src = row + head * hd;
     float a[2], b[2];
     if (PARTS) {
-      a[0] = a[1] = b[0] = b[1] = 0.f;
       // up to eight partial products are asked for together (a loop over a run-time count waits for each before it asks
       // for the next: 16 tokens of the 1.5B shape, 4 partial products, 3.9 -> 3.4 us); the sums keep the fixed order
       const float *p0 = prow + head * hd + t;
+      a[0] = a[1] = b[0] = b[1] = 0.f;
       for (int p = 0; p < n_parts; p += 8) {
         f32x2 pa[8], pb[8];
 #pragma unroll
