@@ -153,7 +153,7 @@ struct TraceScope {
 struct Workspace {
   float *h;          // fp32 [T, d] residual stream
   bf16 *x;           // bf16 [T, d] normed activations
-  bf16 *qkv;         // bf16 [T, (Hq+2Hkv)*hd]
+  bf16 *q;           // bf16 [T, Hq*hd] rotated queries
   bf16 *attn;        // bf16 [T, Hq*hd]
   bf16 *act;         // bf16 [T, F]
   int32_t *tok_pos, *tok_slot;
@@ -176,7 +176,7 @@ static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, int attn_
   const size_t t = (size_t)T;
   w.h = (float *)take(t * c.d_model * sizeof(float));
   w.x = (bf16 *)take(t * c.d_model * sizeof(bf16));
-  w.qkv = (bf16 *)take(t * (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * sizeof(bf16));
+  w.q = (bf16 *)take(t * c.n_q_heads * c.head_dim * sizeof(bf16));
   w.attn = (bf16 *)take(t * c.n_q_heads * c.head_dim * sizeof(bf16));
   w.act = (bf16 *)take(t * c.d_ffn * sizeof(bf16));
   w.tok_pos = (int32_t *)take(t * sizeof(int32_t));
@@ -259,9 +259,15 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (!kv->k_pool[l] || !kv->v_pool[l]) return arb_fail(ARB_EINVAL, "null kv pool in layer %d", l);
   const int T = bt->total_tokens, B = bt->batch, d = c.d_model;
   const int G = c.n_q_heads / c.n_kv_heads;
-  const AttnPlan plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads);
+  AttnPlan plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads);
   // the attention part is sized by this call's own split count (never above what arb_workspace_bytes assumed)
-  const Workspace w = carve(c, T, plan.max_splits, plan.n_items, ws);
+  Workspace w = carve(c, T, plan.max_splits, plan.n_items, ws);
+  // The static buffer is the only scratch whose size does not follow from the batch: there a batch with many splits takes
+  // longer ones rather than be refused.
+  while (ws_is_static && ws_bytes < w.total && plan.max_splits > 1) {
+    plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads, 2 * plan.kv_chunk);
+    w = carve(c, T, plan.max_splits, plan.n_items, ws);
+  }
   if (ws_is_static && ws_bytes < w.total)
     return arb_fail(ARB_ECAPACITY, "arb_score_steps_noalloc: this batch needs %zu bytes of scratch but the static buffer "
                     "holds %zu (ARB_NOALLOC_SCRATCH_BYTES); use arb_score_steps with a workspace", w.total, ws_bytes);
@@ -358,13 +364,13 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     {
       TraceScope t(m, ARB_STAGE_ROPE_APPEND, st);
       // the queries leave the rotary kernel multiplied by log2(e)/sqrt(hd) (in fp32, before their one rounding)
-      s = launch_rope_append(w.qkv, w.parts, parts_of(plan_q), w.cs, w.tok_slot, (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], T, c.n_q_heads,
+      s = launch_rope_append(w.q, w.parts, parts_of(plan_q), w.cs, w.tok_slot, (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], T, c.n_q_heads,
                              c.n_kv_heads, c.head_dim, attention_q_scale(c.head_dim), st);
     }
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_ATTENTION, st);
-      s = launch_attention(w.qkv, m->qkv_rows(), (const bf16 *)kv->k_pool[l], (const bf16 *)kv->v_pool[l],
+      s = launch_attention(w.q, hq, (const bf16 *)kv->k_pool[l], (const bf16 *)kv->v_pool[l],
                            bt->block_tables, bt->max_blocks_per_seq, B, T, c.n_q_heads, c.n_kv_heads, c.head_dim, plan,
                            w.attn, w.attn_ws, w.attn_ws_bytes, st, true);
     }
@@ -606,15 +612,15 @@ extern "C" arb_status arb_stage_attention(const arb_model *m, const void *q, int
   const int G = c.n_q_heads / c.n_kv_heads, T = batch->total_tokens;
   const AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host, G, c.n_kv_heads);
   const size_t need = attention_ws_bytes(plan.max_splits, plan.n_items, T, c.n_q_heads, c.head_dim);
-  if (!ws || ws_bytes < need) return arb_fail(ARB_ECAPACITY, "arb_stage_attention: workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t st = (hipStream_t)stream;
-  if (arb_status s = launch_token_meta(batch->prefix_lens, batch->cu_step_lens, batch->block_tables, batch->batch, T,
-                                       batch->max_blocks_per_seq, c.kv_block, nullptr, nullptr, st, &plan,
-                                       attention_lists(ws, plan, T, c.n_q_heads, c.head_dim), G, c.n_kv_heads))
-    return s;
+  if (ws && ws_bytes >= need)                              // with one split a call needs no scratch; then there is no work list
+    if (arb_status s = launch_token_meta(batch->prefix_lens, batch->cu_step_lens, batch->block_tables, batch->batch, T,
+                                         batch->max_blocks_per_seq, c.kv_block, nullptr, nullptr, st, &plan,
+                                         attention_lists(ws, plan, T, c.n_q_heads, c.head_dim), G, c.n_kv_heads))
+      return s;
   return launch_attention((const bf16 *)q, q_row_stride, (const bf16 *)k_pool, (const bf16 *)v_pool, batch->block_tables,
                           batch->max_blocks_per_seq, batch->batch, T, c.n_q_heads, c.n_kv_heads, c.head_dim, plan, (bf16 *)out,
-                          ws, ws_bytes, st, q_scaled != 0);
+                          ws, ws_bytes, st, q_scaled != 0, batch->prefix_lens, batch->cu_step_lens);
 }
 
 extern "C" arb_status arb_stage_rmsnorm(const float *x, const float *g, float eps, int32_t T, int32_t d, void *out,

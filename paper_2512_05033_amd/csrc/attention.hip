@@ -201,9 +201,9 @@ __device__ __forceinline__ void attend_tile(const bf16 *sk, const bf16 *sv, cons
 template <int HD, bool SPLIT, bool PRESCALED>
 __global__ __launch_bounds__(256, 2) void attention_kernel(
     const bf16 *__restrict__ q, int q_row_stride, const bf16 *__restrict__ k_pool, const bf16 *__restrict__ v_pool,
-    const int32_t *__restrict__ block_tables, int max_blocks, const AttnItem *__restrict__ items, int n_items, int run,
-    int T, int Hq, int Hkv, float scale_log2, bf16 *__restrict__ out, bf16 *__restrict__ part_acc,
-    float *__restrict__ part_ml) {
+    const int32_t *__restrict__ block_tables, int max_blocks, const int32_t *__restrict__ prefix_lens,
+    const int32_t *__restrict__ cu, int max_qtiles, const AttnItem *__restrict__ items, int n_items, int run, int T,
+    int Hq, int Hkv, float scale_log2, bf16 *__restrict__ out, bf16 *__restrict__ part_acc, float *__restrict__ part_ml) {
   constexpr int CPK = HD / 8;              // 16-byte chunks per key
   constexpr int LOADS = KT * CPK / 256;    // wave-wide 1 KB loads per wave, operand and tile
   constexpr int KPL = 64 / CPK;            // keys covered by one wave-wide load (4 or 8: inside one block)
@@ -222,9 +222,17 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(
   const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
   const int index = ((slot / run) * 8 + xcd) * run + slot % run;
   if (index >= n_items) return;                        // rounding of the grid
-  const AttnItem item = items[index];
-  const int hk = item.split_head & 0xffff, split = item.split_head >> 16, b = item.seq;
   const int G = Hq / Hkv;
+  AttnItem item;
+  if (!SPLIT && items == nullptr) {                     // no scratch for a list: the product of sequences, heads and most query tiles
+    const int seq = index / (Hkv * max_qtiles), rest = index - seq * Hkv * max_qtiles;
+    const int p0 = prefix_lens[seq], t0 = cu[seq], len = cu[seq + 1] - t0, r0 = rest % max_qtiles * QROWS;
+    if (r0 >= len * G) return;
+    item = AttnItem{seq, t0, p0, len, r0, 0, p0 + (min(len * G, r0 + QROWS) - 1) / G + 1, rest / max_qtiles};
+  } else {
+    item = items[index];
+  }
+  const int hk = item.split_head & 0xffff, split = item.split_head >> 16, b = item.seq;
   const int p = item.prefix, tok0 = item.tok0, s = item.step;
   const int rows = s * G, row0 = item.row0;
   const int kv_begin = item.kv_begin, kv_end = item.kv_end;
@@ -440,7 +448,7 @@ int attention_splits_cap(int max_ctx) {
   return n < kMaxSplits ? n : kMaxSplits;
 }
 
-AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads) {
+AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int least_chunk) {
   long long keys_streamed = 0;          // sum over (sequence, kv head, query tile) of the context length
   int max_ctx = 0, max_step = 0;
   for (int b = 0; b < batch; ++b) {
@@ -461,6 +469,7 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
   if (chunk > cap) chunk = cap;
   if (chunk < kMinChunk) chunk = kMinChunk;
   while (max_ctx > chunk * kMaxSplits) chunk += KT;
+  if (chunk < least_chunk) chunk = least_chunk;
   AttnPlan pl;
   pl.max_qtiles = ceil_div(max_step * G, QROWS);
   pl.kv_chunk = (int)chunk;
@@ -497,25 +506,26 @@ AttnLists attention_lists(void *ws, const AttnPlan &plan, int total_tokens, int 
 arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool, const bf16 *v_pool,
                             const int32_t *block_tables, int max_blocks_per_seq, int batch, int total_tokens, int n_q_heads,
                             int n_kv_heads, int head_dim, const AttnPlan &plan, bf16 *out, void *ws, size_t ws_bytes,
-                            hipStream_t st, bool q_prescaled) {
+                            hipStream_t st, bool q_prescaled, const int32_t *prefix_lens, const int32_t *cu_step_lens) {
   if (batch == 0 || total_tokens == 0) return ARB_OK;
   if (head_dim != 64 && head_dim != 128) return arb_fail(ARB_EUNSUPPORTED, "attention: head_dim %d", head_dim);
   const size_t need = attention_ws_bytes(plan.max_splits, plan.n_items, total_tokens, n_q_heads, head_dim);
-  if (ws == nullptr || ws_bytes < need)
+  const bool split = plan.max_splits > 1, listed = ws != nullptr && ws_bytes >= need;
+  if (!listed && (split || !prefix_lens || !cu_step_lens))
     return arb_fail(ARB_ECAPACITY, "attention: workspace %zu < %zu bytes", ws_bytes, need);
-  const bool split = plan.max_splits > 1;
+  const int n_items = listed ? plan.n_items : batch * n_kv_heads * plan.max_qtiles;
   bf16 *part_acc = (bf16 *)ws;
   float *part_ml = (float *)((char *)ws + part_acc_bytes(plan.max_splits, total_tokens, n_q_heads, head_dim));
-  const AttnLists lists = attention_lists(ws, plan, total_tokens, n_q_heads, head_dim);
+  const AttnLists lists = listed ? attention_lists(ws, plan, total_tokens, n_q_heads, head_dim) : AttnLists{};
   const float scale_log2 = attention_q_scale(head_dim);
   // A run is a group's query tiles, shortened where so few of them fit that some XCDs would get a whole run more.
   int run = plan.max_qtiles;
-  if (run > kMaxRun && plan.n_items % (8 * run) != 0 && plan.n_items < 4 * 8 * run) run = kMaxRun;
-  const dim3 grid(ceil_div(plan.n_items, 8 * run) * 8 * run), block(256);
+  if (run > kMaxRun && n_items % (8 * run) != 0 && n_items < 4 * 8 * run) run = kMaxRun;
+  const dim3 grid(ceil_div(n_items, 8 * run) * 8 * run), block(256);
 #define ARB_ATTN_LAUNCH(HD, SPLIT, PRE)                                                                            \
   hipLaunchKernelGGL((attention_kernel<HD, SPLIT, PRE>), grid, block, 0, st, q, q_row_stride, k_pool, v_pool,      \
-                     block_tables, max_blocks_per_seq, lists.items, plan.n_items, run, total_tokens, n_q_heads,    \
-                     n_kv_heads, scale_log2, out, part_acc, part_ml)
+                     block_tables, max_blocks_per_seq, prefix_lens, cu_step_lens, plan.max_qtiles, lists.items,     \
+                     n_items, run, total_tokens, n_q_heads, n_kv_heads, scale_log2, out, part_acc, part_ml)
 #define ARB_ATTN_PICK(HD)                                                                                          \
   if (split) { if (q_prescaled) ARB_ATTN_LAUNCH(HD, true, true); else ARB_ATTN_LAUNCH(HD, true, false); }          \
   else       { if (q_prescaled) ARB_ATTN_LAUNCH(HD, false, true); else ARB_ATTN_LAUNCH(HD, false, false); }

@@ -121,7 +121,8 @@ static __host__ __device__ inline int attn_seq_chunk(int ctx, int kv_chunk) {
 static __host__ __device__ inline int attn_first_qtile(int prefix, int G, int kv_begin) {
   return kv_begin <= prefix ? 0 : (int)((long long)(kv_begin - prefix) * G / ATTN_QROWS);
 }
-AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads);
+// least_chunk: keys per split are at least that many (less scratch)
+AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int least_chunk = 0);
 size_t attention_ws_bytes(int max_splits, int n_items, int total_tokens, int n_q_heads, int head_dim);
 int attention_splits_cap(int max_ctx);   // largest max_splits plan_attention can return for contexts <= max_ctx
 // The work list inside an attention workspace (attention_ws_bytes), to be written by launch_token_meta before the
@@ -134,7 +135,7 @@ AttnLists attention_lists(void *ws, const AttnPlan &plan, int total_tokens, int 
 arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool, const bf16 *v_pool,
                             const int32_t *block_tables, int max_blocks_per_seq, int batch, int total_tokens, int n_q_heads,
                             int n_kv_heads, int head_dim, const AttnPlan &plan, bf16 *out, void *ws, size_t ws_bytes,
-                            hipStream_t st, bool q_prescaled);
+                            hipStream_t st, bool q_prescaled, const int32_t *prefix_lens = nullptr, const int32_t *cu_step_lens = nullptr);
 // log2(e) / sqrt(head_dim): the factor the attention kernel wants folded into the queries (q_prescaled), so that
 // its score products are logits in log2 units; launch_rope_append applies it (q_scale) before it rounds q.
 float attention_q_scale(int head_dim);
@@ -192,6 +193,6 @@ arb_status launch_pack_steps(const int32_t *steps, int S, const int32_t *rows, c
 
 // gemm_w4.hip: 4-bit weights (offset-binary nibbles, eight k per uint32, bf16 scale per row and 128 k)
 arb_status launch_w4_quantize(const bf16 *W, int N, int K, uint32_t *packed, bf16 *scales, int bits, hipStream_t st);
+int gemm_w4_splits(int M, int N, int K, int max_splits);   // K splits of an fp32 projection on the tile kernels
 arb_status launch_gemm_w4(const bf16 *A, const uint32_t *Bq, const bf16 *Bscale, void *C, int M, int N, int K,
                           int epilogue, hipStream_t st, int splits = 1);
-int gemm_w4_splits(int M, int N, int K, int max_splits);   // K splits of an fp32 projection on the tile kernels

@@ -446,18 +446,19 @@ arb_status launch_final_norm_head(const float *h, const float *parts, RowParts n
 // by the token's table row ((a, b) -> (a cos - b sin, b cos + a sin)), writes q
 // (bf16) to the qkv row and k, v (bf16) to the token's slot of the pool
 // [n_blocks, Hkv, 16, hd].  With PARTS the projection comes as fp32 split-K partial
-// products that are added up here (fixed order), so q and k are rounded once.
+// products that are added up here (fixed order), so q and k are rounded once; a row of qkv then only holds
+// the query heads.  row_heads: heads per row of qkv.
 template <bool PARTS>
 __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv, const float *__restrict__ parts,
                                                           RowParts row_parts, size_t part_stride,
                                                           const f32x2 *__restrict__ cs,
                                                           const int32_t *__restrict__ tok_slot,
                                                           bf16 *__restrict__ k_pool, bf16 *__restrict__ v_pool,
-                                                          int Hq, int Hkv, int hd, float q_scale) {
+                                                          int Hq, int Hkv, int hd, float q_scale, int row_heads) {
   const int j = blockIdx.x;
   const int n_parts = j < row_parts.row ? row_parts.head : row_parts.tail;
   const int half = hd / 2, units_per_head = half / 2, n_heads = Hq + 2 * Hkv;
-  bf16 *row = qkv + (size_t)j * n_heads * hd;
+  bf16 *row = qkv + (size_t)j * row_heads * hd;
   const float *prow = PARTS ? parts + (size_t)j * n_heads * hd : nullptr;
   const int slot = tok_slot[j];
   const size_t blk = slot / ARB_KV_BLOCK, off = slot % ARB_KV_BLOCK;
@@ -524,10 +525,10 @@ arb_status launch_rope_append(bf16 *qkv, const float *parts, RowParts n_parts, c
   const dim3 grid(T, ceil_div((n_q_heads + 2 * n_kv_heads) * (head_dim / 4), 256));
   if (n_parts.head > 0)
     hipLaunchKernelGGL((rope_append_kernel<true>), grid, dim3(256), 0, st, qkv, parts, n_parts, stride, cs, tok_slot,
-                       k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale);
+                       k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale, n_q_heads);
   else
     hipLaunchKernelGGL((rope_append_kernel<false>), grid, dim3(256), 0, st, qkv, (const float *)nullptr, RowParts{}, stride, cs,
-                       tok_slot, k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale);
+                       tok_slot, k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale, n_q_heads + 2 * n_kv_heads);
   ARB_CHECK_LAUNCH("rope_append");
   return ARB_OK;
 }

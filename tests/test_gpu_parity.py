@@ -430,6 +430,18 @@ def test_attention_work_list(A, shape, prefix, steps):
     assert row_err.max() < 3e-2
 
 
+@pytest.mark.parametrize("shape,prefix,steps", [(W.ROUTER_1P5B, [0, 200, 17], [150, 20, 1]), (W.TINY, [3, 0], [1, 70])])
+def test_attention_stage_of_one_split_needs_no_scratch(A, shape, prefix, steps):
+    m, model = _stage_model(A, shape, 43)
+    wl, batch = _ragged_batch(m, prefix, steps, 43)
+    db = H().device_batch(batch)
+    ks, vs = W.make_kv_pools(wl, batch, "cuda")
+    q = rand_bf16((batch.total_tokens, m.qkv_rows), 1.0, 44)
+    want = A.arb_stage_attention(model, q, ks[0], vs[0], db)
+    got = A.arb_stage_attention(model, q, ks[0], vs[0], db, ws=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(got, want)                       # the same work in another order of workgroups
+
+
 @pytest.mark.parametrize("seed", [1, 2, 3, 4])
 def test_attention_stage_random_ragged_batches(A, seed):
     """Seeded random batch sizes, prefixes and step lengths (grids whose group count is not a multiple of

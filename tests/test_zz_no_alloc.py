@@ -72,3 +72,34 @@ def test_noalloc_rejects_what_does_not_fit(A):
         A.arb_score_steps_noalloc(sess.model, sess.kv, sess.dbatch, 0.0, scores=scores, escalate=esc)
     assert e.value.status == A.ARB_ECAPACITY and "ARB_NOALLOC_SCRATCH_BYTES" in str(e.value)
     torch.cuda.synchronize()
+
+
+def test_noalloc_fits_many_long_contexts_by_longer_splits(A):
+    """Several hundred one-token steps against 100000 cached tokens each (the sequences share one prefix's blocks): with the
+    planned 17 splits per context the work list and the partial results do not fit the array together."""
+    import harness
+    w = W.scaled(W.C2, n_layers=1, batch=1)
+    m, ctx, blk = w.model, 100000, 16
+    splits, rows = 17, (m.n_q_heads + 2 * m.n_kv_heads) * m.head_dim
+    # everything but the work list, per token
+    token = (4 * m.d_model + 2 * m.d_model + 2 * rows + 4 * m.n_q_heads * m.head_dim // 2 + 2 * m.d_ffn + 8 +
+             8 * (m.head_dim // 2) + 4 + 32 * m.d_model + splits * m.n_q_heads * (2 * m.head_dim + 8))
+    B = (A.NOALLOC_SCRATCH_BYTES - 16 * 256) // token
+    n_shared = (ctx - 1) // blk
+    tables = np.empty((B, n_shared + 1), np.int32)
+    tables[:, :n_shared] = np.arange(n_shared)
+    tables[:, n_shared] = n_shared + np.arange(B)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    pool = lambda: [torch.empty(n_shared + B, m.n_kv_heads, blk, m.head_dim, dtype=torch.bfloat16, device="cuda").normal_(0, 0.8, generator=gen)]
+    kv = A.KVCache(pool(), pool())
+    model = harness.make_model(m, W.make_weights(m, 3, "cuda"))
+    db = A.DeviceBatch(np.full(B, ctx - 1, np.int32), np.arange(B + 1, dtype=np.int32), tables,
+                       np.arange(B, dtype=np.int32) * 7)
+    assert model.workspace_bytes(B, B, ctx) > A.NOALLOC_SCRATCH_BYTES
+    s_ref, _, h_ref = A.arb_score_steps(model, kv, db, 0.0, want_hidden=True)
+    scores = torch.empty(B, device="cuda"); esc = torch.empty(B, dtype=torch.uint8, device="cuda")
+    hidden = torch.empty_like(h_ref)
+    A.arb_score_steps_noalloc(model, kv, db, 0.0, scores=scores, escalate=esc, hidden=hidden)
+    # other splits of the keys: other roundings of the partial results to bf16
+    err = (hidden.float() - h_ref.float()).norm() / h_ref.float().norm()
+    assert err < 1e-2 and (scores - s_ref).abs().max() < 1e-2
