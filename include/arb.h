@@ -129,7 +129,8 @@ typedef struct {
  * and a new step of s_b = cu_step_lens[b+1] - cu_step_lens[b] >= 1 tokens whose
  * ids are token_ids[cu_step_lens[b] .. cu_step_lens[b+1]).  The two length arrays
  * are given twice: on the device for the kernels, on the host for validation and
- * launch sizing.  Block-table contents are trusted (not range-checked). */
+ * launch sizing.  The two copies have to agree (where they do not, results are undefined; the attention
+ * work list stays within its memory).  Block-table contents are trusted (not range-checked). */
 typedef struct {
   int32_t batch, total_tokens, max_blocks_per_seq;
   const int32_t *token_ids;          /* device [total_tokens] */

@@ -235,6 +235,7 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(
   const int hk = item.split_head & 0xffff, split = item.split_head >> 16, b = item.seq;
   const int p = item.prefix, tok0 = item.tok0, s = item.step;
   const int rows = s * G, row0 = item.row0;
+  if (row0 >= rows) return;                            // an empty item
   const int kv_begin = item.kv_begin, kv_end = item.kv_end;
   const int ctx = p + s;
 

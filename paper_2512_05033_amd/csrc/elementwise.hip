@@ -32,6 +32,9 @@ __device__ __forceinline__ float block_sum_256(float v, float *lds4) {
 // steps of 1 and 64 tokens 613 -> 522.)  Sequences with the longest splits come first, so that a launch ends on
 // short ones; the query tiles of a (sequence, split, kv head) are neighbours, the ones that see most keys first.
 // Blocks [0, n_parts) each know the whole order and write every n_parts-th run of 256 items.
+// The launch is sized by the host's copy of the lengths and the list is written from the device's.  Where the two disagree
+// nothing is written or read out of range: the list ends at n_items, places that no item claims hold an empty one (its
+// workgroup returns), and splits beyond the max_splits that the partial results have room for are empty too.
 constexpr int kListSeqs = 512;             // sequences ordered at a time, two per thread
 
 // Items of a sequence with context p + s cut into parts of c keys: every split that starts inside the prefix has all nq
@@ -44,7 +47,8 @@ __device__ __forceinline__ int attention_item_count(int p, int s, int c, int G, 
 }
 
 __device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ cu, int batch,
-                                      int G, int Hkv, int kv_chunk, AttnItem *__restrict__ items, int part, int n_parts) {
+                                      int G, int Hkv, int kv_chunk, int max_splits, AttnItem *__restrict__ items,
+                                      int n_items, int part, int n_parts) {
   __shared__ int key[kListSeqs], first[kListSeqs], prefix[kListSeqs], step[kListSeqs], order[kListSeqs];
   __shared__ int ends[kListSeqs], wave_total[4];           // ends: inclusive sums of the ordered item counts
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -52,11 +56,11 @@ __device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, c
   for (int base = 0; base < batch; base += kListSeqs) {
     const int n = min(kListSeqs, batch - base);
     for (int i = tid; i < n; i += 256) {
-      const int p = prefix_lens[base + i], t0 = cu[base + i], s = cu[base + i + 1] - t0;
+      const int p = max(prefix_lens[base + i], 0), t0 = cu[base + i], s = max(cu[base + i + 1] - t0, 0);
       prefix[i] = p;
       first[i] = t0;
       step[i] = s;
-      key[i] = attn_seq_chunk(p + s, kv_chunk);
+      key[i] = s > 0 ? attn_seq_chunk(p + s, kv_chunk) : ATTN_KT;        // without a step: no items
     }
     __syncthreads();
     for (int i = tid; i < n; i += 256) {
@@ -85,7 +89,7 @@ __device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, c
     ends[2 * tid] = sum - count[1];
     ends[2 * tid + 1] = sum;
     __syncthreads();
-    const int total = ends[n - 1];
+    const int total = min(ends[n - 1], n_items - written);
     for (int l = part * 256 + tid; l < total; l += n_parts * 256) {
       int lo = 0, hi = n - 1;                              // first r with ends[r] > l
       while (lo < hi) {
@@ -103,11 +107,14 @@ __device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, c
       }
       const int hk = j / per, row0 = (nq - 1 - (j - hk * per)) * ATTN_QROWS;
       const int visible = p + (min(rows, row0 + ATTN_QROWS) - 1) / G + 1;          // keys any row of the tile may see
-      items[written + l] = AttnItem{base + i, first[i], p, s, row0, split * c, min(visible, split * c + c), split << 16 | hk};
+      items[written + l] = split < max_splits
+                               ? AttnItem{base + i, first[i], p, s, row0, split * c, min(visible, split * c + c), split << 16 | hk}
+                               : AttnItem{};
     }
     written += total;
     __syncthreads();
   }
+  for (int l = written + part * 256 + tid; l < n_items; l += n_parts * 256) items[l] = AttnItem{};
 }
 
 // For step token j of sequence b at position pos = p_b + i:
@@ -116,7 +123,7 @@ struct TokenMeta {
   const int32_t *prefix_lens, *cu, *tables;
   int batch, max_blocks, blk;
   int32_t *tok_pos, *tok_slot;
-  int list_blocks, kv_chunk, G, Hkv;       // blocks of the launch that write the attention work list (0: there is none)
+  int list_blocks, kv_chunk, max_splits, n_items, G, Hkv;       // blocks of the launch that write the attention work list (0: there is none)
   AttnLists lists;
 };
 
@@ -131,7 +138,7 @@ __device__ __forceinline__ int token_meta(const TokenMeta &t, int j, bool write)
   if (write) {
     if (t.tok_pos) t.tok_pos[j] = pos;
     if (t.tok_slot) t.tok_slot[j] = t.tables[(size_t)b * t.max_blocks + pos / t.blk] * t.blk + pos % t.blk;
-    if (t.list_blocks) t.lists.tok_splits[j] = pos / attn_seq_chunk(prefix + t.cu[b + 1] - t0, t.kv_chunk) + 1;
+    if (t.list_blocks) t.lists.tok_splits[j] = min(pos / attn_seq_chunk(prefix + t.cu[b + 1] - t0, t.kv_chunk) + 1, t.max_splits);
   }
   return pos;
 }
@@ -139,7 +146,8 @@ __device__ __forceinline__ int token_meta(const TokenMeta &t, int j, bool write)
 // The first list_blocks blocks write the attention work list.
 __global__ __launch_bounds__(256) void token_meta_kernel(TokenMeta t, int T) {
   if ((int)blockIdx.x < t.list_blocks) {
-    write_attention_items(t.prefix_lens, t.cu, t.batch, t.G, t.Hkv, t.kv_chunk, t.lists.items, blockIdx.x, t.list_blocks);
+    write_attention_items(t.prefix_lens, t.cu, t.batch, t.G, t.Hkv, t.kv_chunk, t.max_splits, t.lists.items, t.n_items, blockIdx.x,
+                          t.list_blocks);
     return;
   }
   const int j = (blockIdx.x - t.list_blocks) * 256 + threadIdx.x;
@@ -151,7 +159,8 @@ static TokenMeta token_meta_args(const int32_t *prefix_lens, const int32_t *cu_s
                                  const AttnPlan *plan, AttnLists lists, int G, int n_kv_heads) {
   const int list_blocks = !plan ? 0 : plan->n_items <= 1024 ? 1 : plan->n_items <= 16384 ? ceil_div(plan->n_items, 1024) : 16;
   return TokenMeta{prefix_lens, cu_step_lens, block_tables, batch, max_blocks_per_seq, kv_block, tok_pos, tok_slot,
-                   list_blocks, plan ? plan->kv_chunk : ATTN_KT, G, n_kv_heads, lists};
+                   list_blocks, plan ? plan->kv_chunk : ATTN_KT, plan ? plan->max_splits : 1, plan ? plan->n_items : 0, G,
+                   n_kv_heads, lists};
 }
 
 arb_status launch_token_meta(const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
@@ -282,7 +291,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const f
   if (EMBED) {
     const TokenMeta &m = opening.meta;
     if (row < m.list_blocks) {
-      write_attention_items(m.prefix_lens, m.cu, m.batch, m.G, m.Hkv, m.kv_chunk, m.lists.items, row, m.list_blocks);
+      write_attention_items(m.prefix_lens, m.cu, m.batch, m.G, m.Hkv, m.kv_chunk, m.max_splits, m.lists.items, m.n_items, row,
+                            m.list_blocks);
       return;
     }
     row -= m.list_blocks;

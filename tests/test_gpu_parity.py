@@ -4,6 +4,7 @@ the same seeded inputs.  Tolerances: hidden states max|d|/max|ref| <= 2e-2
 multiple of the bf16-operand floor the oracle measures on the same sample), router
 scores |d| <= 1e-2, decisions identical unless |score - tau| < 1e-2, slot
 indices and untouched cache contents bit-exact."""
+import re
 from dataclasses import replace
 
 import numpy as np
@@ -428,6 +429,35 @@ def test_attention_work_list(A, shape, prefix, steps):
     assert rel_err(got, ref) < 1e-2
     row_err = np.abs(got - ref).max(axis=-1) / (np.abs(ref).max(axis=-1) + 1e-3)
     assert row_err.max() < 3e-2
+
+
+@pytest.mark.parametrize("host_prefix,device_prefix", [([1000, 300, 900], [200, 100, 900]),      # fewer keys on the device
+                                                       ([600, 100, 0], [1000, 300, 900])])       # more keys and splits
+def test_attention_work_list_where_host_and_device_lengths_disagree(A, host_prefix, device_prefix):
+    """The launch and the workspace are sized by the host's lengths, the work list is written from the device's.  The
+    contract has them equal; where they are not, nothing outside the workspace may be written and no stale word of it
+    taken for work.  With fewer keys on the device the list still holds every piece of work, so the result is theirs.
+    (The workspace has exactly the size that the call asks for and ends in front of a canary; it starts out as -1s,
+    which as a work item would point far outside of every buffer.)"""
+    m, model = _stage_model(A, W.TINY, 61)
+    steps = [20, 5, 1]
+    longest = [max(p) for p in zip(host_prefix, device_prefix)]
+    wl, batch = _ragged_batch(m, longest, steps, 61)          # blocks for the longer of the two
+    ks, vs = W.make_kv_pools(wl, batch, "cuda")
+    q = rand_bf16((batch.total_tokens, m.qkv_rows), 1.0, 62)
+    batch_of = lambda prefix: A.DeviceBatch(np.array(prefix, np.int32), batch.cu_step_lens, batch.block_tables, batch.token_ids)
+    db = batch_of(device_prefix)
+    db.prefix_host[:] = host_prefix
+    with pytest.raises(A.ArbError) as e:                      # host check: nothing is launched
+        A.arb_stage_attention(model, q, ks[0], vs[0], db, ws=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    need = int(re.search(r"workspace 16 < (\d+) bytes", str(e.value)).group(1))
+    buf = torch.full((need + 4096,), 255, dtype=torch.uint8, device="cuda")
+    got = A.arb_stage_attention(model, q, ks[0], vs[0], db, ws=buf[:need])
+    torch.cuda.synchronize()
+    assert (buf[need:] == 255).all()
+    if all(h >= d for h, d in zip(host_prefix, device_prefix)):
+        want = A.arb_stage_attention(model, q, ks[0], vs[0], batch_of(device_prefix))
+        assert rel_err(bf16_np(got), bf16_np(want)) < 1e-2    # other splits of the keys: bf16 roundings of the partial results
 
 
 @pytest.mark.parametrize("shape,prefix,steps", [(W.ROUTER_1P5B, [0, 200, 17], [150, 20, 1]), (W.TINY, [3, 0], [1, 70])])
