@@ -165,7 +165,7 @@ struct Workspace {
 };
 
 // attn_splits, attn_items: the number of key splits whose partial results, and of work items, the attention part must hold.
-static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, int attn_items, void *base) {
+static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, size_t attn_items, void *base) {
   Workspace w;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -196,9 +196,8 @@ extern "C" size_t arb_workspace_bytes(const arb_model *m, int32_t max_batch, int
   if (!m || max_batch < 0 || max_total_tokens < 0 || max_ctx < 0) return 0;
   const int splits = attention_splits_cap(max_ctx), G = m->cfg.n_q_heads / m->cfg.n_kv_heads;
   // query tiles: ceil(s_b G / 128) summed over the batch, each against at most `splits` parts of its context
-  const long long items = ((long long)max_total_tokens * G / ATTN_QROWS + max_batch) * m->cfg.n_kv_heads * splits;
-  if (items > INT32_MAX) return 0;
-  return carve(m->cfg, max_total_tokens, splits, (int)items, nullptr).total;
+  const size_t items = ((size_t)max_total_tokens * G / ATTN_QROWS + max_batch) * m->cfg.n_kv_heads * splits;
+  return carve(m->cfg, max_total_tokens, splits, items, nullptr).total;
 }
 
 // --------------------------------------------------------------- batch validation
@@ -262,11 +261,11 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   AttnPlan plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads);
   // the attention part is sized by this call's own split count (never above what arb_workspace_bytes assumed)
   Workspace w = carve(c, T, plan.max_splits, plan.n_items, ws);
-  // The static buffer is the only scratch whose size does not follow from the batch: there a batch with many splits takes
-  // longer ones rather than be refused.
-  while (ws_is_static && ws_bytes < w.total && plan.max_splits > 1) {
-    plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads, 2 * plan.kv_chunk);
-    w = carve(c, T, plan.max_splits, plan.n_items, ws);
+  // Scratch that has no room for the attention work list (the static buffer's size does not follow from the batch) is used
+  // without one: the workgroups find their work themselves, and the results are the same.
+  if (ws_bytes < w.total) {
+    plan.n_items = 0;
+    w = carve(c, T, plan.max_splits, 0, ws);
   }
   if (ws_is_static && ws_bytes < w.total)
     return arb_fail(ARB_ECAPACITY, "arb_score_steps_noalloc: this batch needs %zu bytes of scratch but the static buffer "
@@ -372,7 +371,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
       TraceScope t(m, ARB_STAGE_ATTENTION, st);
       s = launch_attention(w.q, hq, (const bf16 *)kv->k_pool[l], (const bf16 *)kv->v_pool[l],
                            bt->block_tables, bt->max_blocks_per_seq, B, T, c.n_q_heads, c.n_kv_heads, c.head_dim, plan,
-                           w.attn, w.attn_ws, w.attn_ws_bytes, st, true);
+                           w.attn, w.attn_ws, w.attn_ws_bytes, bt->prefix_lens, bt->cu_step_lens, st, true);
     }
     if (s) return s;
     {
@@ -610,17 +609,19 @@ extern "C" arb_status arb_stage_attention(const arb_model *m, const void *q, int
   if (q_row_stride < c.n_q_heads * c.head_dim || q_row_stride % 8 != 0)
     return arb_fail(ARB_EINVAL, "arb_stage_attention: q_row_stride %d", q_row_stride);
   const int G = c.n_q_heads / c.n_kv_heads, T = batch->total_tokens;
-  const AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host, G, c.n_kv_heads);
-  const size_t need = attention_ws_bytes(plan.max_splits, plan.n_items, T, c.n_q_heads, c.head_dim);
+  AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host, G, c.n_kv_heads);
   hipStream_t st = (hipStream_t)stream;
-  if (ws && ws_bytes >= need)                              // with one split a call needs no scratch; then there is no work list
+  if (!ws || ws_bytes < attention_ws_bytes(plan.max_splits, plan.n_items, T, c.n_q_heads, c.head_dim)) plan.n_items = 0;
+  const size_t need = plan.max_splits > 1 || plan.n_items > 0 ? attention_ws_bytes(plan.max_splits, plan.n_items, T, c.n_q_heads, c.head_dim) : 0;
+  if (need > 0 && (!ws || ws_bytes < need)) return arb_fail(ARB_ECAPACITY, "attention: workspace %zu < %zu bytes", ws_bytes, need);
+  if (need > 0)                                            // with one split a call needs no scratch
     if (arb_status s = launch_token_meta(batch->prefix_lens, batch->cu_step_lens, batch->block_tables, batch->batch, T,
                                          batch->max_blocks_per_seq, c.kv_block, nullptr, nullptr, st, &plan,
                                          attention_lists(ws, plan, T, c.n_q_heads, c.head_dim), G, c.n_kv_heads))
       return s;
   return launch_attention((const bf16 *)q, q_row_stride, (const bf16 *)k_pool, (const bf16 *)v_pool, batch->block_tables,
                           batch->max_blocks_per_seq, batch->batch, T, c.n_q_heads, c.n_kv_heads, c.head_dim, plan, (bf16 *)out,
-                          ws, ws_bytes, st, q_scaled != 0, batch->prefix_lens, batch->cu_step_lens);
+                          ws, ws_bytes, batch->prefix_lens, batch->cu_step_lens, st, q_scaled != 0);
 }
 
 extern "C" arb_status arb_stage_rmsnorm(const float *x, const float *g, float eps, int32_t T, int32_t d, void *out,

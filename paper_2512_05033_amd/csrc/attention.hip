@@ -202,7 +202,8 @@ template <int HD, bool SPLIT, bool PRESCALED>
 __global__ __launch_bounds__(256, 2) void attention_kernel(
     const bf16 *__restrict__ q, int q_row_stride, const bf16 *__restrict__ k_pool, const bf16 *__restrict__ v_pool,
     const int32_t *__restrict__ block_tables, int max_blocks, const int32_t *__restrict__ prefix_lens,
-    const int32_t *__restrict__ cu, int max_qtiles, const AttnItem *__restrict__ items, int n_items, int run, int T,
+    const int32_t *__restrict__ cu, int max_qtiles, int max_splits, int kv_chunk, const AttnItem *__restrict__ items,
+    int n_items, int run, int T,
     int Hq, int Hkv, float scale_log2, bf16 *__restrict__ out, bf16 *__restrict__ part_acc, float *__restrict__ part_ml) {
   constexpr int CPK = HD / 8;              // 16-byte chunks per key
   constexpr int LOADS = KT * CPK / 256;    // wave-wide 1 KB loads per wave, operand and tile
@@ -224,11 +225,17 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(
   if (index >= n_items) return;                        // rounding of the grid
   const int G = Hq / Hkv;
   AttnItem item;
-  if (!SPLIT && items == nullptr) {                     // no scratch for a list: the product of sequences, heads and most query tiles
-    const int seq = index / (Hkv * max_qtiles), rest = index - seq * Hkv * max_qtiles;
+  if (items == nullptr) {
+    // No room for a list: the product of sequences, most splits, heads and most query tiles; a workgroup whose place holds
+    // no visible key returns.  The items, and with them the results, are the list's, bit for bit.
+    const int hq = Hkv * max_qtiles, group = index / hq, rest = index - group * hq;
+    const int seq = SPLIT ? group / max_splits : group, part = SPLIT ? group - seq * max_splits : 0;
     const int p0 = prefix_lens[seq], t0 = cu[seq], len = cu[seq + 1] - t0, r0 = rest % max_qtiles * QROWS;
     if (r0 >= len * G) return;
-    item = AttnItem{seq, t0, p0, len, r0, 0, p0 + (min(len * G, r0 + QROWS) - 1) / G + 1, rest / max_qtiles};
+    const int chunk = SPLIT ? attn_seq_chunk(p0 + len, kv_chunk) : p0 + len, begin = part * chunk;
+    const int visible = p0 + (min(len * G, r0 + QROWS) - 1) / G + 1;          // keys any row of the tile may see
+    if (begin >= visible) return;
+    item = AttnItem{seq, t0, p0, len, r0, begin, min(visible, begin + chunk), part << 16 | rest / max_qtiles};
   } else {
     item = items[index];
   }
@@ -449,7 +456,7 @@ int attention_splits_cap(int max_ctx) {
   return n < kMaxSplits ? n : kMaxSplits;
 }
 
-AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int least_chunk) {
+AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads) {
   long long keys_streamed = 0;          // sum over (sequence, kv head, query tile) of the context length
   int max_ctx = 0, max_step = 0;
   for (int b = 0; b < batch; ++b) {
@@ -470,7 +477,6 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
   if (chunk > cap) chunk = cap;
   if (chunk < kMinChunk) chunk = kMinChunk;
   while (max_ctx > chunk * kMaxSplits) chunk += KT;
-  if (chunk < least_chunk) chunk = least_chunk;
   AttnPlan pl;
   pl.max_qtiles = ceil_div(max_step * G, QROWS);
   pl.kv_chunk = (int)chunk;
@@ -485,7 +491,7 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
 }
 
 // Workspace: partial results [splits, T, Hq, hd] bf16 and their (m, l) fp32 (none with a single split), the splits of every
-// token, the work list.
+// token, the work list (none with n_items == 0).
 static size_t part_acc_bytes(int max_splits, int T, int Hq, int hd) {
   return max_splits > 1 ? align_up((size_t)max_splits * T * Hq * hd * sizeof(bf16), 256) : 0;
 }
@@ -493,31 +499,31 @@ static size_t part_ml_bytes(int max_splits, int T, int Hq) {
   return max_splits > 1 ? align_up((size_t)max_splits * T * Hq * 2 * sizeof(float), 256) : 0;
 }
 
-size_t attention_ws_bytes(int max_splits, int n_items, int total_tokens, int n_q_heads, int head_dim) {
+size_t attention_ws_bytes(int max_splits, size_t n_items, int total_tokens, int n_q_heads, int head_dim) {
   return part_acc_bytes(max_splits, total_tokens, n_q_heads, head_dim) + part_ml_bytes(max_splits, total_tokens, n_q_heads) +
-         align_up((size_t)total_tokens * sizeof(int32_t), 256) + align_up((size_t)n_items * sizeof(AttnItem), 256);
+         align_up((size_t)total_tokens * sizeof(int32_t), 256) + align_up(n_items * sizeof(AttnItem), 256);
 }
 
 AttnLists attention_lists(void *ws, const AttnPlan &plan, int total_tokens, int n_q_heads, int head_dim) {
   char *p = (char *)ws + part_acc_bytes(plan.max_splits, total_tokens, n_q_heads, head_dim) +
             part_ml_bytes(plan.max_splits, total_tokens, n_q_heads);
-  return AttnLists{(AttnItem *)(p + align_up((size_t)total_tokens * sizeof(int32_t), 256)), (int32_t *)p};
+  return AttnLists{plan.n_items > 0 ? (AttnItem *)(p + align_up((size_t)total_tokens * sizeof(int32_t), 256)) : nullptr, (int32_t *)p};
 }
 
 arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool, const bf16 *v_pool,
                             const int32_t *block_tables, int max_blocks_per_seq, int batch, int total_tokens, int n_q_heads,
                             int n_kv_heads, int head_dim, const AttnPlan &plan, bf16 *out, void *ws, size_t ws_bytes,
-                            hipStream_t st, bool q_prescaled, const int32_t *prefix_lens, const int32_t *cu_step_lens) {
+                            const int32_t *prefix_lens, const int32_t *cu_step_lens, hipStream_t st, bool q_prescaled) {
   if (batch == 0 || total_tokens == 0) return ARB_OK;
   if (head_dim != 64 && head_dim != 128) return arb_fail(ARB_EUNSUPPORTED, "attention: head_dim %d", head_dim);
   const size_t need = attention_ws_bytes(plan.max_splits, plan.n_items, total_tokens, n_q_heads, head_dim);
-  const bool split = plan.max_splits > 1, listed = ws != nullptr && ws_bytes >= need;
-  if (!listed && (split || !prefix_lens || !cu_step_lens))
+  const bool split = plan.max_splits > 1, listed = plan.n_items > 0;
+  if ((split || listed) && (!ws || ws_bytes < need))
     return arb_fail(ARB_ECAPACITY, "attention: workspace %zu < %zu bytes", ws_bytes, need);
-  const int n_items = listed ? plan.n_items : batch * n_kv_heads * plan.max_qtiles;
+  const int n_items = listed ? plan.n_items : batch * plan.max_splits * n_kv_heads * plan.max_qtiles;
   bf16 *part_acc = (bf16 *)ws;
   float *part_ml = (float *)((char *)ws + part_acc_bytes(plan.max_splits, total_tokens, n_q_heads, head_dim));
-  const AttnLists lists = listed ? attention_lists(ws, plan, total_tokens, n_q_heads, head_dim) : AttnLists{};
+  const AttnLists lists = split || listed ? attention_lists(ws, plan, total_tokens, n_q_heads, head_dim) : AttnLists{};
   const float scale_log2 = attention_q_scale(head_dim);
   // A run is a group's query tiles, shortened where so few of them fit that some XCDs would get a whole run more.
   int run = plan.max_qtiles;
@@ -525,8 +531,8 @@ arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool,
   const dim3 grid(ceil_div(n_items, 8 * run) * 8 * run), block(256);
 #define ARB_ATTN_LAUNCH(HD, SPLIT, PRE)                                                                            \
   hipLaunchKernelGGL((attention_kernel<HD, SPLIT, PRE>), grid, block, 0, st, q, q_row_stride, k_pool, v_pool,      \
-                     block_tables, max_blocks_per_seq, prefix_lens, cu_step_lens, plan.max_qtiles, lists.items,     \
-                     n_items, run, total_tokens, n_q_heads, n_kv_heads, scale_log2, out, part_acc, part_ml)
+                     block_tables, max_blocks_per_seq, prefix_lens, cu_step_lens, plan.max_qtiles, plan.max_splits,  \
+                     plan.kv_chunk, lists.items, n_items, run, total_tokens, n_q_heads, n_kv_heads, scale_log2, out, part_acc, part_ml)
 #define ARB_ATTN_PICK(HD)                                                                                          \
   if (split) { if (q_prescaled) ARB_ATTN_LAUNCH(HD, true, true); else ARB_ATTN_LAUNCH(HD, true, false); }          \
   else       { if (q_prescaled) ARB_ATTN_LAUNCH(HD, false, true); else ARB_ATTN_LAUNCH(HD, false, false); }

@@ -103,7 +103,7 @@ struct AttnPlan {
   int kv_chunk;      // most keys per split (multiple of 64)
   int max_splits;    // ceil(max_ctx / kv_chunk) over the batch
   int max_qtiles;    // ceil(max_step * G / 128)
-  int n_items;       // (sequence, split, kv head, query tile) with at least one visible key
+  int n_items;       // (sequence, split, kv head, query tile) with at least one visible key; 0: no work list (no room for it)
 };
 // One workgroup's work: query rows [row0, row0 + 128) of the (token, head) rows of one kv head of one sequence against
 // keys [kv_begin, kv_end).  The list of a batch is written on the device once per call and read by every layer.
@@ -121,12 +121,11 @@ static __host__ __device__ inline int attn_seq_chunk(int ctx, int kv_chunk) {
 static __host__ __device__ inline int attn_first_qtile(int prefix, int G, int kv_begin) {
   return kv_begin <= prefix ? 0 : (int)((long long)(kv_begin - prefix) * G / ATTN_QROWS);
 }
-// least_chunk: keys per split are at least that many (less scratch)
-AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int least_chunk = 0);
-size_t attention_ws_bytes(int max_splits, int n_items, int total_tokens, int n_q_heads, int head_dim);
+AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads);
+size_t attention_ws_bytes(int max_splits, size_t n_items, int total_tokens, int n_q_heads, int head_dim);
 int attention_splits_cap(int max_ctx);   // largest max_splits plan_attention can return for contexts <= max_ctx
 // The work list inside an attention workspace (attention_ws_bytes), to be written by launch_token_meta before the
-// launches that use it, and the number of splits that hold keys each step token sees.
+// launches that use it (null: the plan has none), and the number of splits that hold keys each step token sees.
 struct AttnLists {
   AttnItem *items;
   int32_t *tok_splits;
@@ -135,7 +134,7 @@ AttnLists attention_lists(void *ws, const AttnPlan &plan, int total_tokens, int 
 arb_status launch_attention(const bf16 *q, int q_row_stride, const bf16 *k_pool, const bf16 *v_pool,
                             const int32_t *block_tables, int max_blocks_per_seq, int batch, int total_tokens, int n_q_heads,
                             int n_kv_heads, int head_dim, const AttnPlan &plan, bf16 *out, void *ws, size_t ws_bytes,
-                            hipStream_t st, bool q_prescaled, const int32_t *prefix_lens = nullptr, const int32_t *cu_step_lens = nullptr);
+                            const int32_t *prefix_lens, const int32_t *cu_step_lens, hipStream_t st, bool q_prescaled);
 // log2(e) / sqrt(head_dim): the factor the attention kernel wants folded into the queries (q_prescaled), so that
 // its score products are logits in log2 units; launch_rope_append applies it (q_scale) before it rounds q.
 float attention_q_scale(int head_dim);

@@ -138,7 +138,7 @@ __device__ __forceinline__ int token_meta(const TokenMeta &t, int j, bool write)
   if (write) {
     if (t.tok_pos) t.tok_pos[j] = pos;
     if (t.tok_slot) t.tok_slot[j] = t.tables[(size_t)b * t.max_blocks + pos / t.blk] * t.blk + pos % t.blk;
-    if (t.list_blocks) t.lists.tok_splits[j] = min(pos / attn_seq_chunk(prefix + t.cu[b + 1] - t0, t.kv_chunk) + 1, t.max_splits);
+    if (t.lists.tok_splits) t.lists.tok_splits[j] = min(pos / attn_seq_chunk(prefix + t.cu[b + 1] - t0, t.kv_chunk) + 1, t.max_splits);
   }
   return pos;
 }
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void token_meta_kernel(TokenMeta t, int T) {
 static TokenMeta token_meta_args(const int32_t *prefix_lens, const int32_t *cu_step_lens, const int32_t *block_tables,
                                  int batch, int max_blocks_per_seq, int kv_block, int32_t *tok_pos, int32_t *tok_slot,
                                  const AttnPlan *plan, AttnLists lists, int G, int n_kv_heads) {
-  const int list_blocks = !plan ? 0 : plan->n_items <= 1024 ? 1 : plan->n_items <= 16384 ? ceil_div(plan->n_items, 1024) : 16;
+  const int list_blocks = !plan || plan->n_items == 0 ? 0 : plan->n_items <= 1024 ? 1 : plan->n_items <= 16384 ? ceil_div(plan->n_items, 1024) : 16;
   return TokenMeta{prefix_lens, cu_step_lens, block_tables, batch, max_blocks_per_seq, kv_block, tok_pos, tok_slot,
                    list_blocks, plan ? plan->kv_chunk : ATTN_KT, plan ? plan->max_splits : 1, plan ? plan->n_items : 0, G,
                    n_kv_heads, lists};

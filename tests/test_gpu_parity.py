@@ -431,13 +431,22 @@ def test_attention_work_list(A, shape, prefix, steps):
     assert row_err.max() < 3e-2
 
 
+def _least_attention_scratch(A, model, q, k, v, db):
+    """Bytes without which a call on a batch with several key splits is refused (a host check: nothing is launched)."""
+    with pytest.raises(A.ArbError) as e:
+        A.arb_stage_attention(model, q, k, v, db, ws=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    assert e.value.status == A.ARB_ECAPACITY
+    return int(re.search(r"workspace 16 < (\d+) bytes", str(e.value)).group(1))
+
+
+@pytest.mark.parametrize("listed", [False, True])
 @pytest.mark.parametrize("host_prefix,device_prefix", [([1000, 300, 900], [200, 100, 900]),      # fewer keys on the device
                                                        ([600, 100, 0], [1000, 300, 900])])       # more keys and splits
-def test_attention_work_list_where_host_and_device_lengths_disagree(A, host_prefix, device_prefix):
-    """The launch and the workspace are sized by the host's lengths, the work list is written from the device's.  The
+def test_attention_where_host_and_device_lengths_disagree(A, host_prefix, device_prefix, listed):
+    """The launch and the workspace are sized by the host's lengths, the work is found from the device's.  The
     contract has them equal; where they are not, nothing outside the workspace may be written and no stale word of it
-    taken for work.  With fewer keys on the device the list still holds every piece of work, so the result is theirs.
-    (The workspace has exactly the size that the call asks for and ends in front of a canary; it starts out as -1s,
+    taken for work.  With fewer keys on the device every piece of work is still there, so the result is theirs.
+    (The workspace has exactly the size that the call needs and ends in front of a canary; it starts out as -1s,
     which as a work item would point far outside of every buffer.)"""
     m, model = _stage_model(A, W.TINY, 61)
     steps = [20, 5, 1]
@@ -448,9 +457,10 @@ def test_attention_work_list_where_host_and_device_lengths_disagree(A, host_pref
     batch_of = lambda prefix: A.DeviceBatch(np.array(prefix, np.int32), batch.cu_step_lens, batch.block_tables, batch.token_ids)
     db = batch_of(device_prefix)
     db.prefix_host[:] = host_prefix
-    with pytest.raises(A.ArbError) as e:                      # host check: nothing is launched
-        A.arb_stage_attention(model, q, ks[0], vs[0], db, ws=torch.empty(16, dtype=torch.uint8, device="cuda"))
-    need = int(re.search(r"workspace 16 < (\d+) bytes", str(e.value)).group(1))
+    need = _least_attention_scratch(A, model, q, ks[0], vs[0], db)
+    if listed:      # 32 bytes for every split (at most 256 keys in so small a batch) and kv head: all steps fit one query tile
+        items = m.n_kv_heads * sum(-(-(p + s) // 256) for p, s in zip(host_prefix, steps))
+        need += -(-32 * items // 256) * 256
     buf = torch.full((need + 4096,), 255, dtype=torch.uint8, device="cuda")
     got = A.arb_stage_attention(model, q, ks[0], vs[0], db, ws=buf[:need])
     torch.cuda.synchronize()
@@ -458,6 +468,24 @@ def test_attention_work_list_where_host_and_device_lengths_disagree(A, host_pref
     if all(h >= d for h, d in zip(host_prefix, device_prefix)):
         want = A.arb_stage_attention(model, q, ks[0], vs[0], batch_of(device_prefix))
         assert rel_err(bf16_np(got), bf16_np(want)) < 1e-2    # other splits of the keys: bf16 roundings of the partial results
+
+
+@pytest.mark.parametrize("shape,prefix,steps", [
+    (W.TINY, [0], [4300]),                       # splits that start inside the step
+    (W.TINY, [100, 4500, 0], [4100, 20, 1]),
+    (W.ROUTER_1P5B, [8192, 255, 256, 257], [22, 21, 1, 64]),             # contexts at and next to a multiple of the split length
+    (W.TARGET_8B, [3000, 700, 1], [1, 1, 1]),    # one new token each
+])
+def test_attention_without_room_for_the_work_list_is_bit_identical(A, shape, prefix, steps):
+    m, model = _stage_model(A, shape, 45)
+    wl, batch = _ragged_batch(m, prefix, steps, 45)
+    db = H().device_batch(batch)
+    ks, vs = W.make_kv_pools(wl, batch, "cuda")
+    q = rand_bf16((batch.total_tokens, m.qkv_rows), 1.0, 46)
+    want = A.arb_stage_attention(model, q, ks[0], vs[0], db)
+    need = _least_attention_scratch(A, model, q, ks[0], vs[0], db)
+    got = A.arb_stage_attention(model, q, ks[0], vs[0], db, ws=torch.empty(need, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(got, want)
 
 
 @pytest.mark.parametrize("shape,prefix,steps", [(W.ROUTER_1P5B, [0, 200, 17], [150, 20, 1]), (W.TINY, [3, 0], [1, 70])])
