@@ -706,7 +706,9 @@ arb_status launch_gather_rows(const bf16 *src, const int32_t *rows, int n, int d
 // Choice of one token per row of fp32 logits [n, V], in two launches.  Greedy (temperature <= 0): the smallest
 // index of the maximum.  Otherwise the token is drawn from softmax(logits / temperature) by inversion with the
 // caller's uniform u in [0, 1): the smallest k with sum_{i<=k} w_i >= u * sum_i w_i, w_i = exp((l_i - max) / temperature);
-// every sum has a fixed order, so a call is reproducible.
+// every sum has a fixed order, so a call is reproducible.  For u > 0 a token whose weight is 0 in fp32 is never drawn: a
+// chunk, then a thread's range in it, claims the target only if its cumulative weight crosses it, and where sums of the same
+// weights in another order end short of the target the last token with a weight is taken.
 //
 // The logits are read once at memory speed: a row is cut into chunks, a workgroup reduces one chunk with
 // 16-byte loads of neighbouring lanes to (maximum, its smallest index, sum of exp relative to the chunk's maximum),
@@ -786,7 +788,7 @@ __global__ __launch_bounds__(256) void choice_join_kernel(const float *__restric
   const float inv_t = 1.0f / temperature;
   // the chunk that contains the target: the first whose cumulative weight reaches it
   __shared__ float before_s, target_s;
-  __shared__ int chunk_s, pick_s;
+  __shared__ int chunk_s, pick_s, last_s;                // last_s: last token of the chunk with a weight (else its largest logit)
   __syncthreads();
   red_v[tid] = mine.arg < V ? mine.sum * expf((mine.max - mx) * inv_t) : 0.f;
   __syncthreads();
@@ -806,12 +808,20 @@ __global__ __launch_bounds__(256) void choice_join_kernel(const float *__restric
   }
   __syncthreads();
   const int c = chunk_s;
+  if (tid == c) last_s = mine.arg;
+  __syncthreads();
   int k = amax;                                           // ... then the mode
   if (c >= 0) {
     const int lo = c * chunk_len, hi = min(lo + chunk_len, V), per = (hi - lo + 255) / 256;
     const int a = min(lo + tid * per, hi), b = min(a + per, hi);
     float part = 0.f;
-    for (int i = a; i < b; ++i) part += expf((l[i] - mx) * inv_t);
+    int last = -1;
+    for (int i = a; i < b; ++i) {
+      const float w = expf((l[i] - mx) * inv_t);
+      part += w;
+      if (w > 0.f) last = i;
+    }
+    atomicMax(&last_s, last);
     red_v[tid] = part;
     __syncthreads();
     if (tid == 0) {
@@ -823,13 +833,19 @@ __global__ __launch_bounds__(256) void choice_join_kernel(const float *__restric
       }
     }
     __syncthreads();
-    float run = red_v[tid];
-    for (int i = a; i < b; ++i) {
-      run += expf((l[i] - mx) * inv_t);
-      if (run >= target_s) { atomicMin(&pick_s, i); break; }
+    // the range that contains the target: before < target <= before + part (the row's first range also takes target == 0)
+    const float before = red_v[tid];
+    if (a < b && (target_s > before || (c == 0 && tid == 0)) && target_s <= before + part) {
+      float run = before;
+      int pick = last < 0 ? a : last;                     // rounding in the re-summation cannot leave the range
+      for (int i = a; i < b; ++i) {
+        run += expf((l[i] - mx) * inv_t);
+        if (run >= target_s) { pick = i; break; }
+      }
+      atomicMin(&pick_s, pick);
     }
     __syncthreads();
-    k = pick_s < V ? pick_s : hi - 1;                     // rounding in the re-summation cannot leave the chunk
+    k = pick_s < V ? pick_s : last_s;                     // ... nor the chunk
   }
   if (tid == 0) {
     token[row] = k;

@@ -357,6 +357,34 @@ def test_next_token_choice_at_chunk_edges(A, d, V, n):
         assert tok.tolist() == [want] * n
 
 
+@pytest.mark.parametrize("d,V", [(64, 32000), (256, 151936)])
+def test_next_token_never_draws_a_token_without_weight(A, d, V):
+    """Nine of ten logits are -200: their weights are 0 in fp32.  The uniforms aim at the boundaries of the cumulative
+    distribution between weighted tokens, at runs of tokens without weight in between, and at its end, so that sums of
+    another order or rounding land on either side; a token that has no weight may still not be drawn, and the one drawn
+    is next to the boundary (1e-4 of the total, as above)."""
+    n = 64
+    r = np.random.default_rng(V)
+    w = np.where(r.random((V, n)) < 0.9, -200.0, r.standard_normal((V, n)))
+    w[-r.integers(1, 9):] = -200.0
+    w_lm = torch.zeros(V, d, dtype=torch.bfloat16, device="cuda")
+    w_lm[:, :n] = torch.from_numpy(w).to(torch.bfloat16).cuda()
+    hidden = torch.eye(n, d, dtype=torch.bfloat16, device="cuda")          # row i's logits are column i
+    logits = w_lm[:, :n].double().cpu().numpy()
+    cum = np.cumsum(np.exp(logits), axis=0)
+    rows = torch.arange(n, dtype=torch.int32, device="cuda")
+    for trial in range(64):
+        at = r.integers(0, V, n) if trial else np.full(n, V - 1)
+        u = np.minimum((cum[at, np.arange(n)] / cum[-1]).astype(np.float32), np.float32(1 - 2.0 ** -24))
+        tok, chosen = A.arb_next_token(hidden, rows, w_lm, temperature=1.0, uniforms=torch.from_numpy(u).cuda())
+        tok = tok.cpu().numpy()
+        drawn = logits[tok, np.arange(n)]
+        assert (drawn > -100.0)[u > 0].all(), (trial, tok[(drawn <= -100.0) & (u > 0)])
+        assert np.array_equal(chosen.double().cpu().numpy(), drawn)
+        total, before = cum[-1], cum[tok, np.arange(n)] - np.exp(drawn)
+        assert (before - 1e-4 * total <= u * total).all() and (u * total <= before + np.exp(drawn) + 1e-4 * total).all()
+
+
 def test_first_stop_bit_exact(A):
     r = np.random.default_rng(8)
     toks = r.integers(3, 50, (70, 33)).astype(np.int32)
