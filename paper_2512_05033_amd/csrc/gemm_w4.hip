@@ -373,6 +373,14 @@ __global__ __launch_bounds__(128 * WM, 2) void gemm_w4_kernel(const bf16 *__rest
 // operands agree).  Weights enter the MFMAs as 24 + q (expand_nibbles_plus24); the sums start from -24 sum_k a_k,
 // computed once per group for both row tiles by MFMAs against the constant.  One fp32 multiply by the group's scale per
 // group, as in the tile kernel.
+// An unsplit launch on a narrow matrix would leave most CUs idle that way, so its workgroups are narrower and deal the
+// chunks of K to TEAMS teams of waves instead: 4 / TEAMS row blocks and two groups per team, a step of the ring holds a
+// chunk of every team, and all sums of a row block meet in LDS at the end.  Above 16 tokens two workgroups of 16 each share the
+// rows where that still is at most one workgroup per CU.  The rule (w4_stream_shape) takes the most teams that are at most one workgroup
+// per CU.  Measured at 16 / 32 tokens, fp32 output, us, with 1, 2 and 4 teams: 4096x14336 43.2 / 51.3, 24.2 / 24.1, 17.4 / 17.4;
+// 1536x8960 28.4 / 33.1, 16.4 / 16.5, 12.3 / 12.2; 6144x4096 15.1 / 17.5, 9.5 / 9.9, 7.7 / 13.2 (384 workgroups);
+// 10240x4096 15.1 / 17.7, 9.9 / 12.7 (32 tokens per workgroup), 13.4 / 19.5; 2x8960x1536 with SwiGLU 8.8 / 9.7, 10.7 / 13.4, 13.3 / 21.
+// Split launches fill the chip by their splits and keep one team.
 // Measured at 16 tokens, 8B shape, weights from memory (before: 32x32 MFMAs, half empty; weights straight to registers in half
 // lines; activations and scales per wave): gate/up 26.1 -> 18.5 us (3.3 TB/s), O and down in 8 splits 16.8 -> 10.9 on
 // average, QKV in 4 splits 12.2 -> 8.2.  What is left is the start of so short a launch and, per chunk, the expansion.
@@ -398,45 +406,57 @@ __device__ __forceinline__ void w4s_await_tiles(unsigned &s0, unsigned &s1, u32x
   asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(s0), "+v"(s1), "+v"(f0), "+v"(f1) : : "memory");
 }
 
-template <int EPI, int MT, int D>
+template <int EPI, int MT, int D, int TEAMS>
 __global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__restrict__ A, const uint32_t *__restrict__ Bq,
                                                                 const bf16 *__restrict__ Bscale, void *__restrict__ Cv,
                                                                 int M, int N, int K) {
+  const size_t part_stride = (size_t)M * N;
+  if (gridDim.z > 1) {                                   // this workgroup's tokens
+    const int m0 = blockIdx.z * 16 * MT;
+    A += (size_t)m0 * K;
+    Cv = (char *)Cv + (size_t)m0 * N * (EPI == ARB_EPI_STORE_BF16 || EPI == ARB_EPI_SWIGLU_BF16 ? sizeof(bf16) : sizeof(float));
+    M = min(M - m0, 16 * MT);
+  }
   constexpr int RT = 2;                                  // 16-row tiles of weights per wave
-  constexpr int W_BYTES = 128 * 128, X_BYTES = MT * 16 * 512, STAGE = W_BYTES + X_BYTES;
-  constexpr int S_CHUNKS = 4, S_BLOCK = 128 * 32;        // chunks whose scales are fetched together; 32 bytes per row
-  constexpr int LOADS = 2 + MT;                          // per wave and chunk: weights, activations
+  constexpr int BLOCKS = 4 / TEAMS, ROWS = 32 * BLOCKS;  // row blocks of 32 per team; weight rows of the workgroup
+  constexpr int W_TEAM = ROWS * 128, X_TEAM = MT * 16 * 512;          // bytes of a chunk
+  constexpr int W_BYTES = TEAMS * W_TEAM, X_BYTES = TEAMS * X_TEAM, STAGE = W_BYTES + X_BYTES;
+  constexpr int S_CHUNKS = 4, S_BLOCK = ROWS * 32;       // chunks whose scales are fetched together; 32 bytes per row
+  constexpr int S_BLOCKS = ((D - 1) * TEAMS + 3) / 4 + 1;             // a block is loaded again D - 1 steps before it is read, behind its last reader
+  constexpr int LOADS = 2 + MT * TEAMS;                  // per wave and step: weights, activations
   constexpr bool SWIGLU = EPI == ARB_EPI_SWIGLU_BF16;
-  static_assert(D >= 3 && D <= 6 && D * STAGE + 3 * S_BLOCK <= 160 * 1024 && (D - 2) * LOADS <= 63 && D * STAGE >= 4 * RT * MT * 1024, "ring");
-  // the chunks of a ring, at most six, lie in at most three scale blocks
-  __shared__ __attribute__((aligned(1024))) char Ring[D * STAGE + 3 * S_BLOCK];
+  static_assert(D >= 3 && D <= 6 && D * STAGE + S_BLOCKS * S_BLOCK <= 160 * 1024 && (D - 2) * LOADS <= 63 &&
+                D * STAGE >= 8 * RT * MT * 1024, "ring");
+  __shared__ __attribute__((aligned(1024))) char Ring[D * STAGE + S_BLOCKS * S_BLOCK];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c16 = lane & 15, quarter = lane >> 4, block = wave & 3, grp = wave >> 2;
+  const int c16 = lane & 15, quarter = lane >> 4, block = wave % BLOCKS, grp = wave / BLOCKS % 2, team = wave / (2 * BLOCKS);
+  const int member = wave % (2 * BLOCKS);                // of its team
 
-  // this workgroup's chunks; a last chunk of one group (K an odd multiple of 128) reads that group twice and uses it once
+  // this workgroup's chunks, dealt to the teams: step `it` is chunk it TEAMS + team of each; a last chunk of one group (K
+  // an odd multiple of 128) reads that group twice and uses it once
   const int ng_all = K / GROUP, nc_all = (ng_all + 1) / 2;
   const int c_begin = split_point(nc_all, blockIdx.y, gridDim.y);
-  const int n = split_point(nc_all, blockIdx.y + 1, gridDim.y) - c_begin, last = n - 1;
+  const int nc = split_point(nc_all, blockIdx.y + 1, gridDim.y) - c_begin, n = (nc + TEAMS - 1) / TEAMS, last = nc - 1;
 
-  auto weight_row = [&](int r) {                         // r < 128: 32-row block of a wave, 16-row tile, row
-    if (SWIGLU) return (int)blockIdx.x * 64 + (r >> 5) * 16 + (r & 15) + ((r & 16) ? N : 0);
-    return (int)blockIdx.x * 128 + r;
+  auto weight_row = [&](int r) {                         // r < ROWS: 32-row block of a wave, 16-row tile, row
+    if (SWIGLU) return (int)blockIdx.x * (ROWS / 2) + (r >> 5) * 16 + (r & 15) + ((r & 16) ? N : 0);
+    return (int)blockIdx.x * ROWS + r;
   };
   // Loads of 1 KB: 8 weight rows of 8 pieces (16 bytes), or 2 activation rows of 32.  The pieces of a row are swizzled
   // on the global side so that the fragment reads (16 rows, one piece) cover all banks.  Addresses are a uniform base
   // (every load stays inside one 16-row tile) and a 32-bit lane offset.
   const char *w_base[2];
-  unsigned w_off[2], w_off_half[2], x_off[MT], x_off_half[MT];           // _half: the second group's pieces read the first's
+  unsigned w_off[2], w_off_half[2], x_off[MT * TEAMS], x_off_half[MT * TEAMS];       // _half: the second group's pieces read the first's
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int r0 = (wave * 2 + i) * 8, piece = (lane & 7) ^ (4 * i + (lane >> 4));
+    const int r0 = (member * 2 + i) * 8, piece = (lane & 7) ^ (4 * i + (lane >> 4));
     w_base[i] = (const char *)(Bq + (size_t)weight_row(r0) * (K / 8));
     w_off[i] = (lane >> 3) * (unsigned)(K / 2) + piece * 16;
     w_off_half[i] = (lane >> 3) * (unsigned)(K / 2) + (piece & 3) * 16;
   }
 #pragma unroll
-  for (int j = 0; j < MT; ++j) {
-    const int r = (wave + 8 * j) * 2 + (lane >> 5), piece = (lane & 31) ^ (r & 15);
+  for (int j = 0; j < MT * TEAMS; ++j) {
+    const int r = (member + 2 * BLOCKS * j) * 2 + (lane >> 5), piece = (lane & 31) ^ (r & 15);
     const unsigned row = (unsigned)(r < M ? r : M - 1) * (unsigned)(K * 2);         // rows past M re-read the last one; never stored
     x_off[j] = row + piece * 16;
     x_off_half[j] = row + (piece & 15) * 16;
@@ -451,34 +471,34 @@ __global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__re
   auto first_scale = [&](int r) { return (size_t)weight_row(r) * ng_all + sc_shift + 2 * c_begin; };
   size_t sc_dword[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) sc_dword[i] = (first_scale((wave * 2 + i) * 8 + (lane >> 3)) >> 1) + (lane & 7);
-  auto load_scales = [&](int block_of_chunks) {
-    char *dst = Ring + D * STAGE + block_of_chunks % 3 * S_BLOCK;
+  for (int i = 0; i < 2; ++i) sc_dword[i] = (first_scale((member * 2 + i) * 8 + (lane >> 3)) >> 1) + (lane & 7);
+  auto load_scales = [&](int block_of_chunks) {          // the first team's members, for all teams
+    char *dst = Ring + D * STAGE + block_of_chunks % S_BLOCKS * S_BLOCK;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       size_t at = sc_dword[i] + block_of_chunks * S_CHUNKS;
       at = at < sc_last ? at : sc_last;
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(sc_base + at * 4), LDS_PTR(dst + (wave * 2 + i) * 256), 4, 0, 0);
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(sc_base + at * 4), LDS_PTR(dst + (member * 2 + i) * 256), 4, 0, 0);
     }
   };
-  auto load = [&](int s, int it) {                       // `it` past the end: the last chunk again, never used
-    if (it % S_CHUNKS == 0 && it < n) load_scales(it / S_CHUNKS);
-    const int c = c_begin + (it < last ? it : last);
+  auto load = [&](int s, int it) {                       // past the end: the last chunk again, never used
+    if (it * TEAMS % S_CHUNKS == 0 && it < n && team == 0) load_scales(it * TEAMS / S_CHUNKS);
+    const int at = it * TEAMS + team, c = c_begin + (at < last ? at : last);
     const bool half = 2 * c + 1 >= ng_all;               // a chunk of one group
-    char *dst = Ring + s * STAGE;
+    char *dst = Ring + s * STAGE + team * W_TEAM, *dst_x = Ring + s * STAGE + W_BYTES + team * X_TEAM;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
       __builtin_amdgcn_global_load_lds(GLOBAL_PTR(w_base[i] + (size_t)c * 128 + (half ? w_off_half[i] : w_off[i])),
-                                       LDS_PTR(dst + (wave * 2 + i) * 1024), 16, 0, 2 /* nt */);
+                                       LDS_PTR(dst + (member * 2 + i) * 1024), 16, 0, 2 /* nt */);
 #pragma unroll
-    for (int j = 0; j < MT; ++j)
+    for (int j = 0; j < MT * TEAMS; ++j)
       __builtin_amdgcn_global_load_lds(GLOBAL_PTR((const char *)A + (size_t)c * 512 + (half ? x_off_half[j] : x_off[j])),
-                                       LDS_PTR(dst + W_BYTES + (wave + 8 * j) * 1024), 16, 0, 0);
+                                       LDS_PTR(dst_x + (member + 2 * BLOCKS * j) * 1024), 16, 0, 0);
   };
 
   // LDS addresses of this lane's fragments in stage 0: row tile 0 of the weights; word w of the activations' token tile 0
   const unsigned ring = (unsigned)(uintptr_t)LDS_PTR(Ring);
-  const unsigned w_addr = ring + (block * 32 + c16) * 128 + (((4 * grp + quarter) ^ (c16 >> 1)) << 4);
+  const unsigned w_addr = ring + team * W_TEAM + (block * 32 + c16) * 128 + (((4 * grp + quarter) ^ (c16 >> 1)) << 4);
   unsigned x_addr[4];
   unsigned s_addr[RT], high[RT];                         // address of a scale's dword in block 0, chunk 0; is it the upper half
 #pragma unroll
@@ -489,7 +509,7 @@ __global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__re
     high[i] = h & 1;
   }
 #pragma unroll
-  for (int w = 0; w < 4; ++w) x_addr[w] = ring + W_BYTES + c16 * 512 + (((16 * grp + 4 * quarter + w) ^ c16) << 4);
+  for (int w = 0; w < 4; ++w) x_addr[w] = ring + W_BYTES + team * X_TEAM + c16 * 512 + (((16 * grp + 4 * quarter + w) ^ c16) << 4);
 
   f32x4 acc[RT][MT];
 #pragma unroll
@@ -513,7 +533,9 @@ __global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__re
     __builtin_amdgcn_sched_barrier(0);
     const unsigned stage = s * STAGE;
     s = s + 1 == D ? 0 : s + 1;
-    if (2 * (c_begin + it) + grp >= ng_all) continue;    // the missing second group of the last chunk
+    const int chunk = it * TEAMS + team;
+    // the chunks past the end of the last step, the missing second group of the last chunk
+    if ((TEAMS > 1 && chunk > last) || 2 * (c_begin + chunk) + grp >= ng_all) continue;
     u32x4 wf[RT], xf[MT][4];
     unsigned sc[RT];
 #pragma unroll
@@ -521,7 +543,7 @@ __global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__re
       w4s_read<0>(x_addr[w] + stage, xf[0][w]);
       if (MT == 2) w4s_read<16 * 512>(x_addr[w] + stage, xf[MT - 1][w]);
     }
-    const unsigned sc_at = it / S_CHUNKS % 3 * S_BLOCK + it % S_CHUNKS * 4;
+    const unsigned sc_at = chunk / S_CHUNKS % S_BLOCKS * S_BLOCK + chunk % S_CHUNKS * 4;
     w4s_read_scales(s_addr[0] + sc_at, s_addr[1] + sc_at, sc[0], sc[1]);
     w4s_read<0>(w_addr + stage, wf[0]);
     w4s_read<16 * 128>(w_addr + stage, wf[1]);
@@ -561,21 +583,24 @@ __global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__re
   }
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  // the two group sums of a row block meet in LDS: every load has landed and, past the barrier, every stage has been read
+  // the 2 TEAMS sums of a row block meet in LDS: every load has landed and, past the barrier, every stage has been read
   __syncthreads();
   f32x4 *red = (f32x4 *)Ring;
-  if (grp == 1) {
+  const int share = wave / BLOCKS;                       // 2 team + grp
+  if (share > 0) {
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int j = 0; j < MT; ++j) red[((block * RT + i) * MT + j) * 64 + lane] = acc[i][j];
+      for (int j = 0; j < MT; ++j) red[((wave * RT + i) * MT + j) * 64 + lane] = acc[i][j];
   }
   __syncthreads();
-  if (grp == 1) return;
+  if (share > 0) return;
 #pragma unroll
-  for (int i = 0; i < RT; ++i)
+  for (int o = 1; o < 2 * TEAMS; ++o)
 #pragma unroll
-    for (int j = 0; j < MT; ++j) acc[i][j] += red[((block * RT + i) * MT + j) * 64 + lane];
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int j = 0; j < MT; ++j) acc[i][j] += red[(((o * BLOCKS + block) * RT + i) * MT + j) * 64 + lane];
   // D layout of the 16x16 MFMA: lane holds column lane%16 (a weight row) and rows (tokens) 4*(lane/16) + {0..3}
 #pragma unroll
   for (int j = 0; j < MT; ++j)
@@ -585,17 +610,27 @@ __global__ __launch_bounds__(512, 2) void gemm_w4_stream_kernel(const bf16 *__re
       if (m >= M) continue;
       if (SWIGLU) {
         const float gte = acc[0][j][e], up = acc[1][j][e];
-        ((bf16 *)Cv)[(size_t)m * N + blockIdx.x * 64 + block * 16 + c16] = (bf16)(gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up);
+        ((bf16 *)Cv)[(size_t)m * N + blockIdx.x * (ROWS / 2) + block * 16 + c16] = (bf16)(gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up);
       } else {
 #pragma unroll
         for (int i = 0; i < RT; ++i) {
-          const size_t at = (size_t)m * N + blockIdx.x * 128 + block * 32 + i * 16 + c16;
+          const size_t at = (size_t)m * N + blockIdx.x * ROWS + block * 32 + i * 16 + c16;
           if (EPI == ARB_EPI_STORE_BF16) ((bf16 *)Cv)[at] = (bf16)acc[i][j][e];
-          else if (EPI == EPI_PARTIAL_F32) ((float *)Cv)[(size_t)blockIdx.y * M * N + at] = acc[i][j][e];
+          else if (EPI == EPI_PARTIAL_F32) ((float *)Cv)[blockIdx.y * part_stride + at] = acc[i][j][e];
           else ((float *)Cv)[at] += acc[i][j][e];
         }
       }
     }
+}
+
+// Teams of the streaming kernel and, for more than 16 tokens, whether its workgroups take 16 tokens each (see the kernel).
+struct W4Stream { int teams, token_tiles; };
+static W4Stream w4_stream_shape(int M, int tiles_n, int splits) {
+  const int tokens16 = M <= 16 ? 1 : 2;
+  if (splits > 1) return {1, 1};
+  if (tiles_n * 4 * tokens16 <= 256) return {4, tokens16};
+  if (tiles_n * 2 * tokens16 <= 256) return {2, tokens16};
+  return {tiles_n * 2 <= 256 ? 2 : 1, 1};
 }
 
 }  // namespace
@@ -657,13 +692,21 @@ arb_status launch_gemm_w4(const bf16 *A, const uint32_t *Bq, const bf16 *Bscale,
   const bool skinny = M <= kSkinnyRows;                // few tokens: the weight-streaming kernel
   const bool tall = !skinny && w4_tall(M, tiles_n, K, splits);
   const int tall_m = ceil_div(M, 2 * BM);
-  const dim3 grid((tall ? tall_m : tiles_m) * tiles_n, splits), block(skinny || tall ? 512 : 256);
+  const W4Stream stream = skinny ? w4_stream_shape(M, tiles_n, splits) : W4Stream{1, 1};
+  const int mt = M <= 16 || stream.token_tiles == 2 ? 1 : 2;       // 16-token tiles of a streaming workgroup
+  const dim3 grid((tall ? tall_m : tiles_m) * tiles_n * stream.teams, splits, stream.token_tiles), block(skinny || tall ? 512 : 256);
 #define ARB_W4(E)                                                                                                    \
   do {                                                                                                               \
-    if (skinny && M <= 16)                                                                                           \
-      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 1, 6>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);          \
+    if (skinny && mt == 1 && stream.teams == 4)                                                                      \
+      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 1, 3, 4>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);       \
+    else if (skinny && mt == 1 && stream.teams == 2)                                                                 \
+      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 1, 4, 2>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);       \
+    else if (skinny && mt == 1)                                                                                      \
+      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 1, 6, 1>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);       \
+    else if (skinny && stream.teams == 2)                                                                            \
+      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 2, 3, 2>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);       \
     else if (skinny)                                                                                                 \
-      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 2, 4>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);          \
+      hipLaunchKernelGGL((gemm_w4_stream_kernel<E, 2, 4, 1>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K);       \
     else if (tall)                                                                                                   \
       hipLaunchKernelGGL((gemm_w4_kernel<E, 4>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K, tall_m, tiles_n);    \
     else hipLaunchKernelGGL((gemm_w4_kernel<E, 2>), grid, block, 0, st, A, Bq, Bscale, C, M, N, K, tiles_m, tiles_n); \

@@ -964,6 +964,29 @@ def test_w4_few_tokens_at_chunk_edges(A, M, K):
     assert got.shape == (M, N // 2) and rel_err(got, O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
 
 
+@pytest.mark.parametrize("N", [128, 4096, 4224,           # 4 teams per workgroup; the last, above 16 tokens, 2
+                               8192, 8320, 16384,          # 4, 2 and 2 teams; the last two above 16 tokens with all tokens in a workgroup
+                               16512])                     # 1 team
+@pytest.mark.parametrize("K", [128, 1664, 3200])           # 1, 7 and 13 chunks (the last half a one): fewer than teams, turns of the rings and remainders
+def test_w4_few_tokens_by_teams(A, N, K):
+    """The streaming kernel's workgroup shapes at the edges of their ranges, with every epilogue (of 17 and 32 tokens
+    the last 1 and 16 may be another workgroup's).  Bounds as for the other GEMM tests."""
+    w = rand_bf16((N, K), 0.05, 58)
+    packed, scales = A.arb_w4_quantize(w)
+    deq = O.w4_dequantize(*O.w4_quantize(W.bf16_bits(w)))
+    for M in (1, 16, 17, 32):
+        a = rand_bf16((M, K), 1.0, 59 + M)
+        ref = bf16_np(a) @ deq.T
+        assert rel_err(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
+        assert rel_err(bf16_np(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_STORE_BF16)), ref) < 4e-3
+        h0 = torch.randn(M, N, device="cuda", dtype=torch.float32)
+        h = h0.clone()
+        A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_RESIDUAL_F32, out=h)
+        assert rel_err(h.cpu().numpy(), h0.cpu().numpy().astype(np.float64) + ref) < 1e-5
+        got = bf16_np(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_SWIGLU_BF16))
+        assert rel_err(got, O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
+
+
 @pytest.mark.parametrize("few_tokens,bits", [(False, 4), (True, 4), (True, 3)])
 def test_quantized_draft_forward_matches_the_oracle_on_dequantized_weights(A, few_tokens, bits):
     """The whole forward with 4-bit projection weights (C2's shape, 2 layers, so that split-K, SwiGLU
