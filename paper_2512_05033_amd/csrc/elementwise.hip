@@ -451,23 +451,29 @@ arb_status launch_final_norm_head(const float *h, const float *parts, RowParts n
 
 // ------------------------------------------------------- rotary embedding + KV append
 
-// One block per token.  A work unit is (head, two adjacent pair indices t, t+1):
-// it reads u[t..t+1] and u[t+half..t+half+1] of that head, rotates q and k heads
+// One block per token and 256 work units.  A unit is (head, UNIT adjacent pair indices t..):
+// it reads u[t..] and u[t+half..] of that head, rotates q and k heads
 // by the token's table row ((a, b) -> (a cos - b sin, b cos + a sin)), writes q
 // (bf16) to the qkv row and k, v (bf16) to the token's slot of the pool
 // [n_blocks, Hkv, 16, hd].  With PARTS the projection comes as fp32 split-K partial
 // products that are added up here (fixed order), so q and k are rounded once; a row of qkv then only holds
 // the query heads.  row_heads: heads per row of qkv.
-template <bool PARTS>
+// Many tokens are bound by memory: four pairs, 16-byte loads of the fp32 products (against two pairs and 8-byte loads, us
+// per layer: 8B shape 512 tokens 11.0 -> 10.1, 1040 tokens in several splits 13.8 -> 12.4, 4096 tokens 35.0 -> 30.2; 1.5B shape
+// 4096 tokens 15.8 -> 15.3).  Few tokens are a chain of dependent loads whose length the width of a unit does not change.
+// (With bf16 products to read, 4096 tokens of the 8B shape took 25.3.)
+template <bool PARTS, int UNIT>
 __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv, const float *__restrict__ parts,
                                                           RowParts row_parts, size_t part_stride,
                                                           const f32x2 *__restrict__ cs,
                                                           const int32_t *__restrict__ tok_slot,
                                                           bf16 *__restrict__ k_pool, bf16 *__restrict__ v_pool,
                                                           int Hq, int Hkv, int hd, float q_scale, int row_heads) {
+  typedef float vec_f __attribute__((ext_vector_type(UNIT)));
+  typedef bf16 vec_b __attribute__((ext_vector_type(UNIT)));
   const int j = blockIdx.x;
   const int n_parts = j < row_parts.row ? row_parts.head : row_parts.tail;
-  const int half = hd / 2, units_per_head = half / 2, n_heads = Hq + 2 * Hkv;
+  const int half = hd / 2, units_per_head = half / UNIT, n_heads = Hq + 2 * Hkv;
   bf16 *row = qkv + (size_t)j * row_heads * hd;
   const float *prow = PARTS ? parts + (size_t)j * n_heads * hd : nullptr;
   const int slot = tok_slot[j];
@@ -477,42 +483,49 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv
   // 6 rounds per token on the 8B shape: most of the kernel's time in small batches)
   const int u = blockIdx.y * blockDim.x + threadIdx.x;
   if (u < n_heads * units_per_head) {
-    const int head = u / units_per_head, t = (u - head * units_per_head) * 2;
+    const int head = u / units_per_head, t = (u - head * units_per_head) * UNIT;
     bf16 *src = row + head * hd;
-    float a[2], b[2];
+    vec_f a, b;
     if (PARTS) {
       // up to eight partial products are asked for together (a loop over a run-time count waits for each before it asks
       // for the next: 16 tokens of the 1.5B shape, 4 partial products, 3.9 -> 3.4 us); the sums keep the fixed order
       const float *p0 = prow + head * hd + t;
-      a[0] = a[1] = b[0] = b[1] = 0.f;
+      a = b = vec_f(0.f);
       for (int p = 0; p < n_parts; p += 8) {
-        f32x2 pa[8], pb[8];
+        vec_f pa[8], pb[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i)
           if (p + i < n_parts) {
-            pa[i] = *(const f32x2 *)(p0 + (p + i) * part_stride);
-            pb[i] = *(const f32x2 *)(p0 + (p + i) * part_stride + half);
+            pa[i] = *(const vec_f *)(p0 + (p + i) * part_stride);
+            pb[i] = *(const vec_f *)(p0 + (p + i) * part_stride + half);
           }
 #pragma unroll
         for (int i = 0; i < 8; ++i)
           if (p + i < n_parts) {
-            a[0] += pa[i][0]; a[1] += pa[i][1]; b[0] += pb[i][0]; b[1] += pb[i][1];
+            a += pa[i];
+            b += pb[i];
           }
       }
     } else {
-      const bf16x2 va = *(const bf16x2 *)(src + t), vb = *(const bf16x2 *)(src + t + half);
-      a[0] = (float)va[0]; a[1] = (float)va[1]; b[0] = (float)vb[0]; b[1] = (float)vb[1];
+      const vec_b va = *(const vec_b *)(src + t), vb = *(const vec_b *)(src + t + half);
+#pragma unroll
+      for (int e = 0; e < UNIT; ++e) { a[e] = (float)va[e]; b[e] = (float)vb[e]; }
     }
-    bf16x2 oa, ob;
+    vec_b oa, ob;
     if (head < Hq + Hkv) {
-      const f32x2 cs0 = cs[(size_t)j * half + t], cs1 = cs[(size_t)j * half + t + 1];
+      f32x4 two[UNIT / 2];                                  // (cos, sin) of two pairs each
+#pragma unroll
+      for (int e = 0; e < UNIT / 2; ++e) two[e] = *(const f32x4 *)(cs + (size_t)j * half + t + 2 * e);
       const float f = head < Hq ? q_scale : 1.0f;          // queries may carry a constant factor for the attention kernel
-      oa[0] = (bf16)((a[0] * cs0[0] - b[0] * cs0[1]) * f);
-      ob[0] = (bf16)((b[0] * cs0[0] + a[0] * cs0[1]) * f);
-      oa[1] = (bf16)((a[1] * cs1[0] - b[1] * cs1[1]) * f);
-      ob[1] = (bf16)((b[1] * cs1[0] + a[1] * cs1[1]) * f);
+#pragma unroll
+      for (int e = 0; e < UNIT; ++e) {
+        const float c = two[e / 2][e % 2 * 2], s = two[e / 2][e % 2 * 2 + 1];
+        oa[e] = (bf16)((a[e] * c - b[e] * s) * f);
+        ob[e] = (bf16)((b[e] * c + a[e] * s) * f);
+      }
     } else {
-      oa[0] = (bf16)a[0]; oa[1] = (bf16)a[1]; ob[0] = (bf16)b[0]; ob[1] = (bf16)b[1];
+#pragma unroll
+      for (int e = 0; e < UNIT; ++e) { oa[e] = (bf16)a[e]; ob[e] = (bf16)b[e]; }
     }
     bf16 *dst;
     if (head < Hq) {
@@ -522,23 +535,27 @@ __global__ __launch_bounds__(256) void rope_append_kernel(bf16 *__restrict__ qkv
     } else {
       dst = v_pool + ((blk * Hkv + (head - Hq - Hkv)) * ARB_KV_BLOCK + off) * hd;
     }
-    *(bf16x2 *)(dst + t) = oa;
-    *(bf16x2 *)(dst + t + half) = ob;
+    *(vec_b *)(dst + t) = oa;
+    *(vec_b *)(dst + t + half) = ob;
   }
 }
+
+constexpr int kRopeManyTokens = 512;        // below, the two forms are within 0.2 us of each other, two pairs ahead more often
 
 arb_status launch_rope_append(bf16 *qkv, const float *parts, RowParts n_parts, const f32x2 *cs, const int32_t *tok_slot,
                               bf16 *k_pool, bf16 *v_pool, int T, int n_q_heads, int n_kv_heads, int head_dim,
                               float q_scale, hipStream_t st) {
   if (T == 0) return ARB_OK;
   const size_t stride = (size_t)T * (n_q_heads + 2 * n_kv_heads) * head_dim;
-  const dim3 grid(T, ceil_div((n_q_heads + 2 * n_kv_heads) * (head_dim / 4), 256));
-  if (n_parts.head > 0)
-    hipLaunchKernelGGL((rope_append_kernel<true>), grid, dim3(256), 0, st, qkv, parts, n_parts, stride, cs, tok_slot,
-                       k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale, n_q_heads);
-  else
-    hipLaunchKernelGGL((rope_append_kernel<false>), grid, dim3(256), 0, st, qkv, (const float *)nullptr, RowParts{}, stride, cs,
-                       tok_slot, k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale, n_q_heads + 2 * n_kv_heads);
+  const int unit = T >= kRopeManyTokens ? 4 : 2;                      // half a head is 32 or 64 pairs
+  const dim3 grid(T, ceil_div((n_q_heads + 2 * n_kv_heads) * (head_dim / 2 / unit), 256));
+  const int row_heads = n_parts.head > 0 ? n_q_heads : n_q_heads + 2 * n_kv_heads;
+#define ARB_ROPE(PARTS, UNIT)                                                                                            \
+  hipLaunchKernelGGL((rope_append_kernel<PARTS, UNIT>), grid, dim3(256), 0, st, qkv, parts, n_parts, stride, cs, tok_slot, \
+                     k_pool, v_pool, n_q_heads, n_kv_heads, head_dim, q_scale, row_heads)
+  if (n_parts.head > 0) { if (unit == 4) ARB_ROPE(true, 4); else ARB_ROPE(true, 2); }
+  else { if (unit == 4) ARB_ROPE(false, 4); else ARB_ROPE(false, 2); }
+#undef ARB_ROPE
   ARB_CHECK_LAUNCH("rope_append");
   return ARB_OK;
 }

@@ -238,6 +238,26 @@ def test_rope_append_stage(A):
     assert rel_err(O.bf16_to_float(flat(k_got)[written]), O.bf16_to_float(flat(kp)[written])) < 4e-3
 
 
+@pytest.mark.parametrize("shape", [W.TINY, W.ROUTER_1P5B])
+def test_rope_append_of_many_tokens_is_that_of_few(A, shape):
+    """From 512 tokens on the kernel takes wider units: the same bits as for the sequences one by one."""
+    m, model = _stage_model(A, shape, 25)
+    wl, batch = _ragged_batch(m, [70, 0, 33], [56, 455, 1])
+    qkv = rand_bf16((batch.total_tokens, m.qkv_rows), 1.0, 26)
+    runs = []
+    for parts in ([[0, 1, 2]], [[0], [1], [2]]):
+        q = qkv.clone()
+        ks, vs = W.make_kv_pools(wl, batch, "cuda")
+        for rows in parts:
+            sub = batch.select(rows)
+            lo, hi = batch.cu_step_lens[rows[0]], batch.cu_step_lens[rows[-1] + 1]
+            piece = q[lo:hi].clone()
+            A.arb_stage_rope_append(model, piece, ks[0], vs[0], H().device_batch(sub))
+            q[lo:hi] = piece
+        runs.append((q, ks[0], vs[0]))
+    assert batch.total_tokens == 512 and all(torch.equal(a, b) for a, b in zip(*runs))
+
+
 def test_norm_pool_head_stage_mean_and_last(A):
     d = 1536
     _, batch = _ragged_batch(W.ROUTER_1P5B, [0, 0, 0, 0], [1, 64, 17, 128])
