@@ -118,6 +118,24 @@ def test_gemm_few_tokens(A, M, N, K):
     assert rel_err(bf16_np(got), O.silu(ref[:, :F]) * ref[:, F:]) < 5e-3
 
 
+@pytest.mark.parametrize("M", [33, 64])
+@pytest.mark.parametrize("K", [64, 256, 320, 576])         # steps of 64: fewer than the ring's five stages, as many, more
+def test_gemm_64_rows_two_workgroups_per_cu(A, M, K):
+    """33 to 64 token rows on more than 32768 weight rows (an LM head): 64x64 tiles, two workgroups per CU with the
+    shorter of the two rings.  Bounds as above."""
+    N = 33024
+    a, b = rand_bf16((M, K), 1.0, 63), rand_bf16((N, K), 0.05, 64)
+    ref = bf16_np(a) @ bf16_np(b).T
+    assert rel_err(bf16_np(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_BF16)), ref) < 4e-3
+    assert rel_err(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
+    h0 = torch.randn(M, N, device="cuda", dtype=torch.float32)
+    h = h0.clone()
+    A.arb_stage_gemm(a, b, A.ARB_EPI_RESIDUAL_F32, out=h)
+    assert rel_err(h.cpu().numpy(), h0.cpu().numpy().astype(np.float64) + ref) < 1e-5
+    got = A.arb_stage_gemm(a, b, A.ARB_EPI_SWIGLU_BF16)
+    assert rel_err(bf16_np(got), O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
+
+
 @pytest.mark.parametrize("M,N,K", [(4096, 4096, 64), (4000, 4096, 128),      # one round of 256 large tiles, one and two steps of K
                                    (4097, 4096, 192), (4111, 4096, 320),      # ... and 1 or 15 rows left for another kernel
                                    (8208, 2048, 256), (2304, 6144, 448)])     # 32 and 10 tile rows per round
@@ -1005,6 +1023,43 @@ def test_w4_few_tokens_by_teams(A, N, K):
         assert rel_err(h.cpu().numpy(), h0.cpu().numpy().astype(np.float64) + ref) < 1e-5
         got = bf16_np(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_SWIGLU_BF16))
         assert rel_err(got, O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
+
+
+# Row counts and widths at which the 256-row tile is estimated to be the faster one (one m-tile and 129 n-tiles, two and 128,
+# three and 64), with a whole last m-tile and ones of 44 and 8 rows.
+@pytest.mark.parametrize("M,N", [(256, 16512), (300, 16384), (520, 8192)])
+@pytest.mark.parametrize("K", [128, 256, 384, 640, 896])   # 2 and 4 steps: out of the first turn of six; one turn; 10 and 14
+def test_w4_256_row_tile(A, M, N, K):
+    """Every epilogue of the 256-row tile kernel and every way out of its loop.  Bounds as for the other GEMM tests."""
+    a, w = rand_bf16((M, K), 1.0, 65), rand_bf16((N, K), 0.05, 66)
+    packed, scales = A.arb_w4_quantize(w)
+    ref = bf16_np(a) @ O.w4_dequantize(*O.w4_quantize(W.bf16_bits(w))).T
+    assert rel_err(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
+    assert rel_err(bf16_np(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_STORE_BF16)), ref) < 4e-3
+    h0 = torch.randn(M, N, device="cuda", dtype=torch.float32)
+    h = h0.clone()
+    A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_RESIDUAL_F32, out=h)
+    assert rel_err(h.cpu().numpy(), h0.cpu().numpy().astype(np.float64) + ref) < 1e-5
+    got = bf16_np(A.arb_stage_gemm_w4(a, packed, scales, A.ARB_EPI_SWIGLU_BF16))
+    assert rel_err(got, O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
+
+
+def test_w4_layer_with_split_256_row_tiles(A):
+    """One 8B layer with 4-bit weights at 484 tokens: QKV in two and down in four K splits of 256-row tiles, O in 128-row
+    ones.  Every sequence of 30 tokens gets what it gets alone, on the streaming kernel; both are bf16 results well
+    within the stated 2e-2 of the exact ones, so that is what they may differ by."""
+    m = replace(W.TARGET_8B, n_layers=1, vocab=256)
+    steps = [30] * 16 + [4]
+    wl, batch = _ragged_batch(m, [0] * len(steps), steps)
+    model = H().make_model(m, A.QuantizedWeights(W.make_weights(m, 27, "cuda")))
+    ks, vs = W.make_kv_pools(wl, batch, "cuda")
+    h_in = torch.randn(batch.total_tokens, m.d_model, device="cuda", dtype=torch.float32)
+    run = lambda bt, h: A.arb_stage_layers(model, A.KVCache(ks, vs), H().device_batch(bt), 0, 1, h.contiguous()) - h
+    together = run(batch, h_in)
+    for b, (lo, hi) in enumerate(zip(batch.cu_step_lens, batch.cu_step_lens[1:])):
+        alone = run(batch.select([b]), h_in[lo:hi])
+        assert rel_err(together[lo:hi].cpu().numpy(), alone.double().cpu().numpy()) < HIDDEN_TOL
+    model.close()
 
 
 @pytest.mark.parametrize("few_tokens,bits", [(False, 4), (True, 4), (True, 3)])
