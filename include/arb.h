@@ -301,9 +301,11 @@ arb_status arb_w3_quantize(const void *W, int32_t N, int32_t K, void *packed, vo
 arb_status arb_stage_gemm_w4(const void *A, const void *packed, const void *scales, void *C, int32_t M, int32_t N,
                              int32_t K, int32_t epilogue, void *stream);
 
-/* How the projection GEMM of that shape is launched (host arithmetic only): the number of leading
- * 256-column blocks of C (128-feature blocks for SWIGLU) that one kernel computes in 256x256 tiles; the
- * remaining columns go to a second kernel in 128x128 tiles.  0 = one kernel, 128x128 tiles throughout. */
+/* How a launch that is cut by columns is laid out (host arithmetic only): the SWIGLU projection, and any epilogue with
+ * B_blocked.  The result is the number of leading 256-column blocks of C (128-feature blocks for SWIGLU) that one kernel
+ * computes in 256x256 tiles; the remaining columns go to a second kernel in smaller tiles.  0 = one kernel in smaller
+ * tiles, or, for few rows, one that streams the weights.  (Other launches are cut by rows, not columns: whole rounds of
+ * 256 large tiles and a launch of its own for the rows left over, each on the kernel that is estimated to be the fastest.) */
 int32_t arb_gemm_large_tile_columns(int32_t M, int32_t N, int32_t K, int32_t epilogue);
 
 /* Append-attention of one layer.  q: device bf16, row t at q + t*q_row_stride elements, heads contiguous

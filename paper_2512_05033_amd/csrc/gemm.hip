@@ -636,9 +636,9 @@ __global__ __launch_bounds__(256, 1) void gemm256_kernel(const bf16 *__restrict_
 // wave is done with the region refilled next.  Fragment reads and their waits are inline assembly: left to the
 // compiler, every read would wait for all direct-to-LDS loads in flight.
 //
-// The rate of a full chip is set by its clock under this load, not by the schedule: 256 tiles with K = 14336 run at
-// 1.34 PFLOP/s (1.6 us per step), 192 at 1.14 (1.3 us per step), so three quarters of a round are 85 % as fast as
-// a whole one, and a launch of 144 tiles already beats smaller tiles that fill the chip.  Measured (before: 128x128
+// The rate of a full chip is set by its clock under this load, not by the schedule: with K = 14336, 256 tiles run at
+// 1.25 to 1.34 PFLOP/s (1.6 us per step of 64), 192 at 1.1 to 1.14 (1.4 us), 128 at 0.9 (1.17 us), so three quarters of a
+// round are 85 % as fast as a whole one, and a launch of 144 tiles already beats smaller tiles that fill the chip.  Measured (before: 128x128
 // tiles): down 8208x1536x8960 193 us (262), O 8208x1536x1536 44 (55), down 3001x4096x14336 293 (407), QKV
 // 2048x6144x4096 89 (125).
 constexpr int W_TM = 256, W_TN = 256;                    // tile
@@ -1030,9 +1030,10 @@ __global__ __launch_bounds__(256) void gemm_narrow_kernel(const bf16 *__restrict
 // neighbouring lanes on four different rows) stays at 4.1 TB/s.  Weights are loaded non-temporal: each is used once.
 // 16x16x32 MFMAs with the weights as rows and 16 MT tokens as columns; a lane ends with 4 consecutive features of one
 // token.  Ring depth and rows keep a workgroup at 72 to 80 KB (two per CU) where MT allows.
-// Measured at 16 tokens, weights from memory (against the 64- and 128-row tiles): 1.5B shape QKV 3.6 us (6.6),
-// O 3.4 (6.0), gate/up 15.0 (16.8), down 7.7 (11.0), LM head 88 (100); 8B shape gate/up 41 (49), down 21 (24),
-// LM head 188 (256).
+// Measured at 16 tokens in a loop of launches, weights from memory (against the 64- and 128-row tiles): 1.5B shape QKV 3.6 us
+// (6.6), O 3.4 (6.0), gate/up 15.0 (16.8), down 7.7 (11.0), LM head 88 (100); 8B shape gate/up 41 (49), down 21 (24),
+// LM head 188 (256).  By the kernel trace of a decode step, where a launch also starts behind another kernel: 4.4, 4.1,
+// 15.5, 7.6 and 88; 8B shape at 5 tokens gate/up 40, O and down 21 on average, LM head 190 to 198.
 __device__ __forceinline__ int lds_off_stream(int row, int chunk) {   // 128-byte rows; 16 lanes read one chunk of 16 rows
   return row * 64 + ((chunk ^ ((row >> 1) & 7)) << 3);
 }
@@ -1186,9 +1187,14 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(const bf16 *__restrict
 //    201 on the 8B one; gate/up of the 8B shape 43 against 41).
 //  - From 17 to 32 tokens the activations, which every workgroup reads for itself, weigh as much as half of its weights: it
 //    still wins where the tiled kernels are short of workgroups, i.e. on small matrices (up to 16 M weights: the narrow
-//    projections of the 1.5B shape, whose forward of 20 tokens takes 453 us instead of 523), and on a very large matrix with
-//    a long K (8B LM head 204 against 238 us).  In between the tiled kernels win (1.5B gate/up 16.8 against 18.9 us, LM head 97
-//    against 121; a 4-layer pass of 30 tokens on the 8B shape 550 against 579).
+//    projections of the 1.5B shape, whose forward of 20 tokens takes 453 us instead of 523), and mostly on a very large matrix
+//    with a long K.  In between the tiled kernels win (a 4-layer pass of 30 tokens on the 8B shape 550 us against 579).
+//    Large matrices, fp32 output, us at 17 / 24 / 32 tokens, tiled against streaming: 151936 rows, K 1536 89 / 96 / 105 against
+//    109 / 117 / 123; 2560 149 / 163 / 174, 155 / 165 / 176; 3072 164 / 176 / 190, 181 / 193 / 208; 3584 187 / 198 / 213,
+//    185 / 189 / 196; 4096 236 / 244 / 254, 223 / 227 / 231; 5120 264 / 277 / 291, 281 / 278 / 292; 8192 equal within 5 %.  At 65536
+//    rows: 3584 78 / 80 / 85, 80 / 83 / 86; 4096 104 / 107 / 111, 101 / 103 / 103; 5120 114 / 119 / 127, 115 / 118 / 122; 8192 2 % ahead.
+//    At 32768 rows the tiled kernels win by 2 to 9 % for K of 1536, 2560 to 3584 and 5120 and lose by 3 to 10 % for 2048, 4096
+//    and 8192.  So the line lies between 3584 and 4096, where the two are within a few per cent.
 //  - Beyond, the 64-row tile, which shares the activations through LDS, is as fast or faster (64 tokens on the 8B
 //    shape: a 4-layer pass 506 against 648 us; 37 on the 1.5B shape: 555 both).
 static bool stream_shape(int M, int rows, int K, int *mt, int *rt) {
@@ -1243,8 +1249,8 @@ int gemm_large_cols(int M, int N, int K, int epilogue, int splits) {
 // Time estimates in us for a launch of m rows with fp32 (or bf16) output, from which the planner below chooses.  Both have
 // the form steps x time per step + fixed + what the partial products cost to write here and read in the consumer.  Time
 // per step of 64 k, measured on launches that fill one round of their kernel: 64x128 tiles 0.45, 128x128 one per CU
-// 0.67, two per CU 1.0, 256x128 0.93; 256x256 tiles 1.17 up to half of the CUs, 1.31 at three quarters, 1.59
-// with all (the clock).
+// 0.67, two per CU 1.0, 256x128 0.93; 256x256 tiles 1.17 up to half of the CUs, 1.4 at three quarters, 1.6
+// with all (the clock; the line through the two ends gives 1.38 in between).
 static double traffic_us(int m, int N, int splits, int bytes) { return (double)m * N * bytes * (2 * splits - 1) / 5.0e6; }
 static double tiled_us(int m, int N, int K, int splits, int bytes) {
   const int t128 = ceil_div(m, BM) * (N / BN) * splits, t64 = ceil_div(m, 64) * (N / BN) * splits,
