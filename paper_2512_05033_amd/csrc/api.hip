@@ -159,7 +159,7 @@ struct Workspace {
   int32_t *tok_pos, *tok_slot;
   f32x2 *cs;         // [T, hd/2] rotary table
   float *tok_dot;    // [T]
-  float *parts;      // fp32 [8, T, d] split-K partial products of the QKV and residual projections (at least [T, qkv rows])
+  float *parts;      // fp32 [8, T, d] split-K partial products of the QKV and residual projections (at least one token's qkv row)
   void *attn_ws;
   size_t attn_ws_bytes, total;
 };
@@ -184,7 +184,7 @@ static Workspace carve(const arb_model_cfg &c, int T, int attn_splits, size_t at
   w.cs = (f32x2 *)take(t * (c.head_dim / 2) * sizeof(f32x2));
   w.tok_dot = (float *)take(t * sizeof(float));
   const size_t qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
-  w.parts = (float *)take(t * (qkv_rows > 8 * (size_t)c.d_model ? qkv_rows : 8 * (size_t)c.d_model) * sizeof(float));
+  w.parts = (float *)take((8 * t * c.d_model > qkv_rows ? 8 * t * c.d_model : qkv_rows) * sizeof(float));
   w.attn_ws_bytes = attention_ws_bytes(attn_splits, attn_items, T, c.n_q_heads, c.head_dim);
   w.attn_ws = take(w.attn_ws_bytes);
   w.total = off;
@@ -312,23 +312,25 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   // bf16 projection before / fp32 products now: 8B shape 128 tokens 28.8 / 28.0, 256 40.6 / 36.0, 1024 80.3 / 74.0, 4096 215 / 238;
   // 1.5B shape 37 tokens 16.3 / 15.2, 256 19.6 / 22.0, 1024 24.4 / 25.1, 4096 50.0 / 52.9: where the projection is
   // unsplit and large, the twice as wide products cost more than the freer choice of splits and tiles gives.
+  // A model whose QKV rows are wider than that takes the tokens in ranges that fit.
   const int q_splits = 8 * d / m->qkv_rows() > 1 ? 8 * d / m->qkv_rows() : 1;
-  GemmPlan plan_q;
-  if (m->w4) {
-    int sq = 256 / (ceil_div(T, 128) * (m->qkv_rows() / 128));
+  const long long q_fit = 8LL * T * d / m->qkv_rows();
+  const int q_tokens = q_fit >= T ? T : q_fit > 1 ? (int)q_fit : 1;
+  auto qkv_plan = [&](int rows) {
+    if (!m->w4) return gemm_plan(rows, m->qkv_rows(), d, q_splits);
+    int sq = 256 / (ceil_div(rows, 128) * (m->qkv_rows() / 128));
     if (sq > d / 256) sq = d / 256;
     if (sq > q_splits) sq = q_splits;
     if (sq > 4) sq = 4;
     if (sq < 1) sq = 1;
-    if (T > 32) sq = gemm_w4_splits(T, m->qkv_rows(), d, q_splits);
-    plan_q = GemmPlan{{{0, T, sq, false}}, 1};
-  } else {
-    plan_q = gemm_plan(T, m->qkv_rows(), d, q_splits);
-  }
+    if (rows > 32) sq = gemm_w4_splits(rows, m->qkv_rows(), d, q_splits);
+    return GemmPlan{{{0, rows, sq, false}}, 1};
+  };
+  const GemmPlan plan_q = qkv_plan(q_tokens), plan_q_last = T % q_tokens ? qkv_plan(T % q_tokens) : plan_q;
   // one projection by its plan: bf16 weights, or packed 4-bit weights with their group scales
-  auto project = [&](const bf16 *a, const bf16 *wt, const bf16 *scale, void *out, int N, int K, int epi, const GemmPlan &p) {
-    if (!m->w4) return launch_gemm_plan(p, a, wt, out, T, N, K, epi, st);
-    return launch_gemm_w4(a, (const uint32_t *)wt, scale, out, T, N, K, epi, st, p.seg[0].splits);
+  auto project = [&](const bf16 *a, const bf16 *wt, const bf16 *scale, void *out, int rows, int N, int K, int epi, const GemmPlan &p) {
+    if (!m->w4) return launch_gemm_plan(p, a, wt, out, rows, N, K, epi, st);
+    return launch_gemm_w4(a, (const uint32_t *)wt, scale, out, rows, N, K, epi, st, p.seg[0].splits);
   };
   auto gate_up = [&](int l, int part) {
     if (!m->w4) return launch_gemm(w.x, m->wgu[l], w.act, T, c.d_ffn, d, ARB_EPI_SWIGLU_BF16, st, part,
@@ -358,18 +360,21 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
       pending = RowParts{};
     }
     if (s) return s;
-    {
-      TraceScope t(m, ARB_STAGE_QKV, st);
-      s = project(w.x, m->wqkv[l], scale_of(m->sqkv, l), w.parts, m->qkv_rows(), d, ARB_EPI_STORE_F32, plan_q);
-    }
-    if (s) return s;
-    {
+    for (int t0 = 0; t0 < T; t0 += q_tokens) {               // one range, unless QKV rows are wider than 8 d_model
+      const int rows = T - t0 < q_tokens ? T - t0 : q_tokens;
+      const GemmPlan &pq = rows == q_tokens ? plan_q : plan_q_last;
+      {
+        TraceScope t(m, ARB_STAGE_QKV, st);
+        s = project(w.x + (size_t)t0 * d, m->wqkv[l], scale_of(m->sqkv, l), w.parts, rows, m->qkv_rows(), d, ARB_EPI_STORE_F32, pq);
+      }
+      if (s) return s;
       TraceScope t(m, ARB_STAGE_ROPE_APPEND, st);
       // the queries leave the rotary kernel multiplied by log2(e)/sqrt(hd) (in fp32, before their one rounding)
-      s = launch_rope_append(w.q, w.parts, parts_of(plan_q), w.cs, w.tok_slot, (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], T, c.n_q_heads,
-                             c.n_kv_heads, c.head_dim, attention_q_scale(c.head_dim), st);
+      s = launch_rope_append(w.q + (size_t)t0 * hq, w.parts, parts_of(pq), w.cs + (size_t)t0 * (c.head_dim / 2), w.tok_slot + t0,
+                             (bf16 *)kv->k_pool[l], (bf16 *)kv->v_pool[l], rows, c.n_q_heads, c.n_kv_heads, c.head_dim,
+                             attention_q_scale(c.head_dim), st);
+      if (s) return s;
     }
-    if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_ATTENTION, st);
       s = launch_attention(w.q, hq, (const bf16 *)kv->k_pool[l], (const bf16 *)kv->v_pool[l],
@@ -379,7 +384,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_OPROJ, st);
-      s = project(w.attn, m->wo[l], scale_of(m->so, l), w.parts, d, hq, ARB_EPI_STORE_F32, plan_o);
+      s = project(w.attn, m->wo[l], scale_of(m->so, l), w.parts, T, d, hq, ARB_EPI_STORE_F32, plan_o);
       pending = parts_of(plan_o);
     }
     if (s) return s;
@@ -396,7 +401,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_DOWN, st);
-      s = project(w.act, m->wd[l], scale_of(m->sd, l), w.parts, d, c.d_ffn, ARB_EPI_STORE_F32, plan_d);
+      s = project(w.act, m->wd[l], scale_of(m->sd, l), w.parts, T, d, c.d_ffn, ARB_EPI_STORE_F32, plan_d);
       pending = parts_of(plan_d);
     }
     if (s) return s;

@@ -163,6 +163,30 @@ def test_workspace_size_grows_with_every_argument(lib):
     lib.arb_model_destroy(h)
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,F", [(1536, 12, 2, 128, 8960), (4096, 32, 8, 128, 14336),
+                                           (128, 16, 4, 128, 256), (128, 64, 64, 64, 128)])      # QKV rows 24 and 96 times d_model wide
+def test_scratch_of_a_call_per_token(lib, d, hq, hkv, hd, F):
+    """What a call needs per step token does not grow with the width of the QKV projection beyond its bf16 row: h, x, q, k and
+    v, attention output, SwiGLU output, position, slot, rotary row, head dot, splits, eight fp32 partial products."""
+    from paper_2512_05033_amd import binding as B
+    w, _keep = _weights()
+    st, h = _create(lib, _cfg(d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=F), w)
+    assert st == B.ARB_OK
+    pools = (C.c_void_p * 2)(0x1000, 0x1000)
+    kv = B._KV(pools, pools, 8)
+
+    def need(T):                        # one sequence, nothing cached: a single key split; refused on the host
+        p, c = np.zeros(1, np.int32), np.array([0, T], np.int32)
+        bt = B._Batch(1, T, 16, 0x1000, 0x1000, 0x1000, 0x1000, p.ctypes.data, c.ctypes.data)
+        assert lib.arb_score_steps(h, C.byref(kv), C.byref(bt), 0.0, 0x1000, None, None, 0x1000, 16, None) == B.ARB_ECAPACITY
+        return int(re.search(rb"workspace 16 < (\d+) bytes", lib.arb_last_error()).group(1))
+
+    token = 4 * d + 2 * d + 2 * (hq + 2 * hkv) * hd + 2 * hq * hd + 2 * F + 4 + 4 + 4 * hd + 4 + 4 + 32 * d
+    for T in (200, 256):
+        assert need(T) <= T * token + 12 * 256
+    lib.arb_model_destroy(h)
+
+
 def test_binding_refuses_to_run_without_the_library(tmp_path):
     from paper_2512_05033_amd import binding
     with pytest.raises(RuntimeError, match="no fallback"):

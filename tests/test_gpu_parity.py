@@ -659,6 +659,18 @@ def test_c1_with_large_weights_exercises_attention(A):
     _assert_scores(sess.batch, scores, esc, s_ref, e_ref)
 
 
+@pytest.mark.parametrize("batch,step", [(4, 32), (1, 3), (3, 1)])          # 128 tokens in ranges of 42; ranges of one token
+def test_qkv_rows_wider_than_their_scratch(A, batch, step):
+    """Heads that make a QKV row 24 times as wide as d_model: the tokens' fp32 products take turns in the scratch."""
+    w = replace(W.scaled(W.C1, batch=batch), step=("fixed", step, step),
+                model=replace(W.TINY, d_model=128, n_q_heads=16, n_kv_heads=4, head_dim=128, d_ffn=256))
+    sess, (scores, esc, hidden), (s_ref, e_ref, y_ref), (kp, vp, kp_before) = _end_to_end(A, w, gain_jitter=0.1)
+    assert rel_err(bf16_np(hidden), y_ref) < HIDDEN_TOL
+    _assert_scores(sess.batch, scores, esc, s_ref, e_ref)
+    slots = O.slot_mapping(sess.batch.prefix_lens, sess.batch.cu_step_lens, sess.batch.block_tables, 16)
+    _assert_cache(sess, kp, vp, kp_before, slots)
+
+
 @pytest.mark.parametrize("pool_mode", ["mean", "last"])
 def test_c1_two_class_head_scores_are_probabilities(A, pool_mode):
     """The two-way classification head of Section 4.2: scores are class-1 probabilities, tau is a probability."""
