@@ -49,8 +49,11 @@ __device__ __forceinline__ int attention_item_count(int p, int s, int c, int G, 
 __device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, const int32_t *__restrict__ cu, int batch,
                                       int G, int Hkv, int kv_chunk, int max_splits, AttnItem *__restrict__ items,
                                       int n_items, int part, int n_parts) {
-  __shared__ int key[kListSeqs], first[kListSeqs], prefix[kListSeqs], step[kListSeqs], order[kListSeqs];
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  __shared__ i32x4 key4[kListSeqs / 4];
+  __shared__ int first[kListSeqs], prefix[kListSeqs], step[kListSeqs], order[kListSeqs];
   __shared__ int ends[kListSeqs], wave_total[4];           // ends: inclusive sums of the ordered item counts
+  int *key = (int *)key4;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int written = 0;
   for (int base = 0; base < batch; base += kListSeqs) {
@@ -62,11 +65,19 @@ __device__ void write_attention_items(const int32_t *__restrict__ prefix_lens, c
       step[i] = s;
       key[i] = s > 0 ? attn_seq_chunk(p + s, kv_chunk) : ATTN_KT;        // without a step: no items
     }
+    if (tid < 16 && n + tid < kListSeqs) key[n + tid] = 0;               // below every key: the ranks are counted sixteen at a time
     __syncthreads();
     for (int i = tid; i < n; i += 256) {
       const int k = key[i];
       int rank = 0;
-      for (int j = 0; j < n; ++j) rank += key[j] > k || (key[j] == k && j < i);
+      // (one key per LDS read, each waited for, made this loop the longest part of the opening launch: 200 sequences 13 us)
+      for (int j = 0; j < n; j += 16) {
+        i32x4 other[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) other[q] = key4[j / 4 + q];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) rank += other[e / 4][e % 4] > k || (other[e / 4][e % 4] == k && j + e < i);
+      }
       order[rank] = i;
     }
     __syncthreads();
