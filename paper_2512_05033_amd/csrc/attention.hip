@@ -226,11 +226,11 @@ __global__ __launch_bounds__(256, 2) void attention_kernel(
   const int G = Hq / Hkv;
   AttnItem item;
   if (items == nullptr) {
-    // No room for a list: the product of sequences, most splits, heads and most query tiles; a workgroup whose place holds
-    // no visible key returns.  The items, and with them the results, are the list's, bit for bit.
+    // No list: the product of sequences, most splits, heads and most query tiles (the last ones, which see most keys, first);
+    // a workgroup whose place holds no visible key returns.  The items, and with them the results, are the list's, bit for bit.
     const int hq = Hkv * max_qtiles, group = index / hq, rest = index - group * hq;
     const int seq = SPLIT ? group / max_splits : group, part = SPLIT ? group - seq * max_splits : 0;
-    const int p0 = prefix_lens[seq], t0 = cu[seq], len = cu[seq + 1] - t0, r0 = rest % max_qtiles * QROWS;
+    const int p0 = prefix_lens[seq], t0 = cu[seq], len = cu[seq + 1] - t0, r0 = (max_qtiles - 1 - rest % max_qtiles) * QROWS;
     if (r0 >= len * G) return;
     const int chunk = SPLIT ? attn_seq_chunk(p0 + len, kv_chunk) : p0 + len, begin = part * chunk;
     const int visible = p0 + (min(len * G, r0 + QROWS) - 1) / G + 1;          // keys any row of the tile may see

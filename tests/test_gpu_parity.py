@@ -516,6 +516,8 @@ def test_attention_where_host_and_device_lengths_disagree(A, host_prefix, device
     which as a work item would point far outside of every buffer.)"""
     m, model = _stage_model(A, W.TINY, 61)
     steps = [20, 5, 1]
+    if listed:      # short contexts beside them: a call lists its work where most places of the launch would be empty
+        host_prefix, device_prefix, steps = host_prefix + [7] * 16, device_prefix + [7] * 16, steps + [2] * 16
     longest = [max(p) for p in zip(host_prefix, device_prefix)]
     wl, batch = _ragged_batch(m, longest, steps, 61)          # blocks for the longer of the two
     ks, vs = W.make_kv_pools(wl, batch, "cuda")
@@ -542,16 +544,36 @@ def test_attention_where_host_and_device_lengths_disagree(A, host_prefix, device
     (W.ROUTER_1P5B, [8192, 255, 256, 257], [22, 21, 1, 64]),             # contexts at and next to a multiple of the split length
     (W.TARGET_8B, [3000, 700, 1], [1, 1, 1]),    # one new token each
 ])
-def test_attention_without_room_for_the_work_list_is_bit_identical(A, shape, prefix, steps):
+def test_without_room_for_the_attention_work_list_a_layer_is_bit_identical(A, shape, prefix, steps):
+    """A forward lists the attention's work if the workspace has room for the list; with the least workspace that it
+    takes there is none."""
     m, model = _stage_model(A, shape, 45)
     wl, batch = _ragged_batch(m, prefix, steps, 45)
     db = H().device_batch(batch)
-    ks, vs = W.make_kv_pools(wl, batch, "cuda")
-    q = rand_bf16((batch.total_tokens, m.qkv_rows), 1.0, 46)
-    want = A.arb_stage_attention(model, q, ks[0], vs[0], db)
-    need = _least_attention_scratch(A, model, q, ks[0], vs[0], db)
-    got = A.arb_stage_attention(model, q, ks[0], vs[0], db, ws=torch.empty(need, dtype=torch.uint8, device="cuda"))
-    assert torch.equal(got, want)
+    h_in = torch.randn(batch.total_tokens, m.d_model, device="cuda", dtype=torch.float32)
+    def run(ws):
+        ks, vs = W.make_kv_pools(wl, batch, "cuda")
+        return A.arb_stage_layers(model, A.KVCache(ks, vs), db, 0, 1, h_in.clone(), ws=ws)
+    with pytest.raises(A.ArbError) as e:                      # a host check: nothing is launched
+        run(torch.empty(16, dtype=torch.uint8, device="cuda"))
+    need = int(re.search(r"workspace 16 < (\d+) bytes", str(e.value)).group(1))
+    assert need < model.workspace_bytes(batch.batch, batch.total_tokens, db.max_ctx)
+    assert torch.equal(run(torch.empty(need, dtype=torch.uint8, device="cuda")), run(None))
+
+
+@pytest.mark.parametrize("shape,prefix,steps", [
+    (W.TINY, [0] + [3] * 9, [4300] + [1] * 9),   # splits that start inside the step: they have its last query tiles only
+    (W.TINY, [100, 4500] + [9] * 9, [4100, 20] + [2] * 9),               # ... next to a sequence whose splits all start in its prefix
+    (W.TINY, [2000] + [3 * (i % 7) for i in range(513)], [2] + [1 + i % 3 for i in range(513)]),    # more sequences than are ordered at a time
+    (W.TINY, [3 * (i % 7) for i in range(511)] + [2000], [1 + i % 3 for i in range(511)] + [2]),    # ... and as many
+    (W.ROUTER_1P5B, [8192] + [255, 256, 257] * 3, [22] + [21, 1, 64] * 3),        # contexts at and next to a multiple of the split length
+])
+def test_attention_stage_with_a_work_list(A, shape, prefix, steps):
+    """Batches with more than two places of the launch per piece of work, which an attention call lists."""
+    got, ref = _attention_case(A, shape, prefix, steps, False, 37)
+    assert rel_err(got, ref) < 1e-2
+    row_err = np.abs(got - ref).max(axis=-1) / (np.abs(ref).max(axis=-1) + 1e-3)
+    assert row_err.max() < 3e-2
 
 
 @pytest.mark.parametrize("shape,prefix,steps", [(W.ROUTER_1P5B, [0, 200, 17], [150, 20, 1]), (W.TINY, [3, 0], [1, 70])])
