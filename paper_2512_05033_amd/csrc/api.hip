@@ -620,7 +620,7 @@ extern "C" arb_status arb_stage_attention(const arb_model *m, const void *q, int
   AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host, G, c.n_kv_heads);
   hipStream_t st = (hipStream_t)stream;
   // Writing the work list costs a single call 2 to 8 us (a forward writes it once for all layers), and it pays where it leaves out
-  // many empty places: 64 contexts of 100 to 6400 keys with steps of 16 to 79 tokens (more than four places per item) 46 us with
+  // many empty places: 64 contexts of 100 to 6400 keys with steps of 16 to 79 tokens (2.7 and 2.2 places per item) 46 us with
   // it and 56 without on the tiny shape, 123 and 130 on the 1.5B one; where most places hold work (fewer than two per item) it does
   // not: one token against 100 keys 10.1 and 6.7, 200 against 300 33 and 26, 32 steps of 1 and 64 against 12000 164 and 153 (1.5B shape).
   const long long places = (long long)batch->batch * plan.max_splits * c.n_kv_heads * plan.max_qtiles;
