@@ -96,6 +96,25 @@ int gemm_large_cols(int M, int N, int K, int epilogue, int splits);   // in unit
 int gemm_residual_splits(int M, int N, int K);
 int gemm_stream_splits(int M, int N, int K);   // K splits of an fp32 projection on the few-token kernel; 0: another kernel takes it
 
+// gemm_few.hip
+// What a projection of few token rows does beyond its product; all pointers null for the product alone.
+struct FewFusion {
+  const float *squares;                  // SwiGLU: partial sums of squares [n_squares][padded tokens] of unscaled rows (null: rows are scaled)
+  int n_squares;
+  float eps;
+  float *h, *squares_out;                // O projection: the residual stream, and where the sums of squares of its rows go
+  const float *gain;
+  const f32x2 *cs;                       // QKV: rotary table, pool slots, pools, and the factor on the queries
+  const int32_t *tok_slot;
+  bf16 *k_pool, *v_pool;
+  int n_q_heads, n_kv_heads, head_dim, head_shift;         // head_dim = 8 << head_shift
+  float q_scale;
+};
+bool gemm_few_takes(int M, int rows, int K, int splits);         // rows: weight rows
+int gemm_few_splits(int M, int N, int K, int max_splits);
+arb_status launch_gemm_few(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, int splits,
+                           size_t part_stride, hipStream_t st);
+
 // attention.hip
 constexpr int ATTN_QROWS = 128;     // query rows (step tokens x query heads of one kv head) per workgroup
 constexpr int ATTN_KT = 64;         // keys per tile

@@ -1030,10 +1030,9 @@ __global__ __launch_bounds__(256) void gemm_narrow_kernel(const bf16 *__restrict
 // neighbouring lanes on four different rows) stays at 4.1 TB/s.  Weights are loaded non-temporal: each is used once.
 // 16x16x32 MFMAs with the weights as rows and 16 MT tokens as columns; a lane ends with 4 consecutive features of one
 // token.  Ring depth and rows keep a workgroup at 72 to 80 KB (two per CU) where MT allows.
-// Measured at 16 tokens in a loop of launches, weights from memory (against the 64- and 128-row tiles): 1.5B shape QKV 3.6 us
-// (6.6), O 3.4 (6.0), gate/up 15.0 (16.8), down 7.7 (11.0), LM head 88 (100); 8B shape gate/up 41 (49), down 21 (24),
-// LM head 188 (256).  By the kernel trace of a decode step, where a launch also starts behind another kernel: 4.4, 4.1,
-// 15.5, 7.6 and 88; 8B shape at 5 tokens gate/up 40, O and down 21 on average, LM head 190 to 198.
+// Large matrices with a K that fits are the resident-activation kernel's (gemm_few.hip); what is left here are small ones, where the
+// start of a launch is all there is (QKV and O of the 1.5B shape at 16 tokens in four K splits 4.3 and 4.2 us by the kernel trace of
+// a decode step, 4.8 and 4.6 there, unsplit), and unsplit products of a very long K.
 __device__ __forceinline__ int lds_off_stream(int row, int chunk) {   // 128-byte rows; 16 lanes read one chunk of 16 rows
   return row * 64 + ((chunk ^ ((row >> 1) & 7)) << 3);
 }
@@ -1181,22 +1180,15 @@ __global__ __launch_bounds__(256) void gemm_stream_kernel(const bf16 *__restrict
 }  // namespace
 
 // Whether a launch runs on the weight-streaming kernel, and in which shape: mt = 16-token tiles, rt = 16-row
-// tiles of weights per workgroup.  rows = weight rows (2 F for SwiGLU).
-//  - Up to 16 tokens it beats the tiled kernels at every size measured (figures at the kernel).  Four row tiles instead
-//    of two pay where there are still two workgroups per CU (LM heads: 88 against 95 us on the 1.5B shape, 188 against
-//    201 on the 8B one; gate/up of the 8B shape 43 against 41).
+// tiles of weights per workgroup.  rows = weight rows (2 F for SwiGLU).  (What gemm_few_takes is asked about first.)
+//  - Up to 16 tokens it beats the tiled kernels at every size measured.  Four row tiles instead of two pay where there are still
+//    two workgroups per CU.
 //  - From 17 to 32 tokens the activations, which every workgroup reads for itself, weigh as much as half of its weights: it
 //    still wins where the tiled kernels are short of workgroups, i.e. on small matrices (up to 16 M weights: the narrow
-//    projections of the 1.5B shape, whose forward of 20 tokens takes 453 us instead of 523), and mostly on a very large matrix
-//    with a long K.  In between the tiled kernels win (a 4-layer pass of 30 tokens on the 8B shape 550 us against 579).
-//    Large matrices, fp32 output, us at 17 / 24 / 32 tokens, tiled against streaming: 151936 rows, K 1536 89 / 96 / 105 against
-//    109 / 117 / 123; 2560 149 / 163 / 174, 155 / 165 / 176; 3072 164 / 176 / 190, 181 / 193 / 208; 3584 187 / 198 / 213,
-//    185 / 189 / 196; 4096 236 / 244 / 254, 223 / 227 / 231; 5120 264 / 277 / 291, 281 / 278 / 292; 8192 equal within 5 %.  At 65536
-//    rows: 3584 78 / 80 / 85, 80 / 83 / 86; 4096 104 / 107 / 111, 101 / 103 / 103; 5120 114 / 119 / 127, 115 / 118 / 122; 8192 2 % ahead.
-//    At 32768 rows the tiled kernels win by 2 to 9 % for K of 1536, 2560 to 3584 and 5120 and lose by 3 to 10 % for 2048, 4096
-//    and 8192.  So the line lies between 3584 and 4096, where the two are within a few per cent.
-//  - Beyond, the 64-row tile, which shares the activations through LDS, is as fast or faster (64 tokens on the 8B
-//    shape: a 4-layer pass 506 against 648 us; 37 on the 1.5B shape: 555 both).
+//    projections of the 1.5B shape, whose forward of 20 tokens takes 453 us instead of 523), and on a very large matrix with a K that
+//    no other few-token kernel holds: 65536 rows, us at 17 / 24 / 32 tokens, tiled against streaming, K 5120 114 / 119 / 127,
+//    115 / 118 / 122; 8192 2 % ahead; 151936 rows equal within 5 %.
+//  - Beyond, the 64-row tile, which shares the activations through LDS, is as fast or faster.
 static bool stream_shape(int M, int rows, int K, int *mt, int *rt) {
   if (M <= 0 || M > 32) return false;
   const bool wide = rows / 64 >= 512 && rows % 64 == 0;
@@ -1271,7 +1263,8 @@ static double wide_us(int m, int N, int K, int splits, int bytes) {
 // eight-wave kernel unsplit.  The rows left over (all of them, where there is no whole round) are a launch of their own,
 // because what suits them is another kernel or another split of K: it goes to the eight-wave kernel with the number of
 // splits that fills its round best, or to the tiled kernels, or (a few rows) to the weight-streaming kernel, whichever is
-// estimated to be the fastest.  max_splits > 0: fp32 output that may come as that many partial products; 0: unsplit.  (Down 6144x4096x14336:
+// estimated to be the fastest, or at most 64 rows to the kernel with resident activations.  max_splits > 0: fp32 output that may come
+// as that many partial products; 0: unsplit.  (Down 6144x4096x14336:
 // one launch of 384 tiles 635 us; 256 + 128 tiles in two K splits 550.  4943x4096x14336: 619 us in 320 tiles, 568 in
 // 128x128 tiles; 256 + 64 in four splits 465.)
 GemmPlan gemm_plan(int M, int N, int K, int max_splits) {
@@ -1290,7 +1283,9 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits) {
   const int m = M - row;
   if (m <= 0) return p;
   GemmSeg rest{row, m, 1, false};
-  if (stream_shape(m, N, K, &mt, &rt)) {
+  if (gemm_few_takes(m, N, K, 1) || (partials && gemm_few_splits(m, N, K, max_splits))) {
+    if (partials) rest.splits = gemm_few_splits(m, N, K, max_splits);
+  } else if (stream_shape(m, N, K, &mt, &rt)) {
     if (partials) rest.splits = std::min(gemm_stream_splits(m, N, K), max_splits);
   } else {
     double best = tiled_us(m, N, K, 1, bytes);
@@ -1340,6 +1335,8 @@ static arb_status launch_tiles(const bf16 *A, const bf16 *B, void *C, int M, int
   const int tiles_m = ceil_div(M, BM);
   int tiles_n = epilogue == ARB_EPI_SWIGLU_BF16 ? N / 64 : N / BN;
   const int rows = epilogue == ARB_EPI_SWIGLU_BF16 ? 2 * N : N;
+  if (gemm_few_takes(M, rows, K, splits))
+    return part == GEMM_PART_LARGE ? ARB_OK : launch_gemm_few(A, B, C, M, N, K, epilogue, splits, part_stride, st);
   int mt, rt;
   if (stream_shape(M, rows, K, &mt, &rt)) {
     if (part == GEMM_PART_LARGE) return ARB_OK;
@@ -1371,8 +1368,8 @@ static arb_status launch_tiles(const bf16 *A, const bf16 *B, void *C, int M, int
   // At most 64 token rows: 64 weight rows per workgroup where 128 of them would leave half of the CUs idle, or would make
   // more than one round of one workgroup per CU (two of these share a CU).  Measured at 37 tokens against 64x128 tiles: down
   // of the 1.5B shape (96 workgroups of 128 weight rows) 12.7 -> 9.8 us, QKV and O (96, 72) 6.3 -> 6.2 and 6.1 -> 6.0, LM head
-  // (1187, in large tiles before) 117 -> 106, of the 8B shape 248 -> 213.  In between 128 weight rows stay the better
-  // ones: gate/up (140) 16.3 against 18.5.
+  // of the 8B shape (1002, in large tiles before) 248 -> 213.  In between 128 weight rows stay the better ones: gate/up (140) 16.3
+  // against 18.5.
   const int wgs128 = rows / BN * splits;
   if (M <= 64 && (wgs128 <= 128 || wgs128 > 256)) {
     if (part == GEMM_PART_LARGE) return ARB_OK;

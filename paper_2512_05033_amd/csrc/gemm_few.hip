@@ -1,0 +1,399 @@
+// Projections of few token rows (drafting token by token, one short step): C[M,N] = A[M,K] * B[N,K]^T with M <= 64, and
+// the two fusions that such a pass wants, because its launches of a few microseconds each cost more than their bytes:
+// the QKV projection that rotates and appends, and the O projection that completes the residual stream and hands the norm
+// on as unscaled rows with their sums of squares.
+//
+// Such a launch reads every weight once, so what bounds it is the memory: how many bytes of weights are in flight, and that
+// nothing else is.  One workgroup of eight waves per CU; a wave owns one eighth of the workgroup's K and keeps the
+// activations of that slice in registers, as MFMA operands, for the whole launch, so that the LDS holds little but weights: a
+// private ring of D stages of 16 rows by 64 k (2 KB) per wave, up to 112 KB per CU in flight, filled by non-temporal direct-to-LDS
+// loads of whole 128-byte lines.  The activations come first through the same ring, and the ring runs on across the 16-row tiles that the workgroup
+// walks through; at the end of a tile the eight partial sums meet in one of two LDS buffers (one barrier per tile, no drain), and
+// the waves take turns in adding them up and storing.  (The kernel before it, gemm_stream_kernel, fetches the activations
+// again for every 32 weight rows, drains at the end of each of its short workgroups, and its launches were 1.09 or 1.75 rounds of them.)
+// By the kernel trace of a pass, us, before and now: 1.5B shape, 16 tokens: gate/up 15.5 -> 13.3, LM head 87.8 -> 81.8; 37 tokens:
+// gate/up 16.8 -> 15.0, down (5 splits) 10.0 -> 9.3; 8B shape, 5 tokens: QKV 12.4 -> 10.5, down 30 -> 20.6, gate/up 39.9 -> 37.2, LM
+// head 193 -> 157 (6.7 TB/s); 40 tokens: O and down together 34.2 -> 34.8 in 4 and 8 splits, QKV 13.6 -> 11.8.
+#include "common.h"
+
+#include <algorithm>
+
+namespace {
+
+#define GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void *)(p))
+#define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+
+// s_waitcnt immediates (vmcnt in bits 3:0 and 15:14, lgkmcnt in 11:8, expcnt 6:4 left at "no wait")
+constexpr int waitcnt_vm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 0xF70; }
+constexpr int kWaitLgkm0 = 0xC07F;
+
+constexpr int FW = 8;                                    // waves
+constexpr int kFewGrid = 256;                            // one workgroup per CU
+constexpr long long kFewWeights = 8 << 20;               // fewest weights of an unfused launch
+constexpr int kSquarePieces = 16;                        // most partial sums of squares a thread adds up
+
+// How a launch divides its units and its chunks of 64 k among the workgroups: so many each, one more for the first few.
+struct FewSplit {
+  int units, units_left, chunks, chunks_left;
+};
+// chunks per wave
+inline int few_chunks(int K, int splits) { return ceil_div(ceil_div(K / 64, splits), FW); }
+
+enum { FEW_BF16, FEW_RESIDUAL, FEW_F32, FEW_SWIGLU, FEW_SCALED_SWIGLU, FEW_ROPE, FEW_NORM };
+
+template <int OFF>
+__device__ __forceinline__ void few_read(unsigned addr, bf16x8 &f) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(f) : "v"(addr), "n"(OFF) : "memory");
+}
+// Register loads (uniform base, lane offset in bytes) whose landing the code below counts itself: the compiler, which does not
+// count the direct-to-LDS loads behind them across a loop, would wait for those as well.
+template <int OFF = 0>
+__device__ __forceinline__ void few_load(const void *base, unsigned off, uint32_t &v) {
+  asm volatile("global_load_dword %0, %1, %2 offset:%3" : "=&v"(v) : "v"(off), "s"(base), "n"(OFF) : "memory");
+}
+template <int OFF = 0, typename T>
+__device__ __forceinline__ void few_load16(const void *base, unsigned off, T &v) {
+  static_assert(sizeof(T) == 16, "16 bytes");
+  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=&v"(v) : "v"(off), "s"(base), "n"(OFF) : "memory");
+}
+// named behind the wait that covers their loads, the registers have no reader in front of it
+__device__ __forceinline__ void few_landed(uint32_t &v) { asm volatile("" : "+v"(v) : : "memory"); }
+template <typename T>
+__device__ __forceinline__ void few_landed(T &v0, T &v1) { asm volatile("" : "+v"(v0), "+v"(v1) : : "memory"); }
+__device__ __forceinline__ void few_await(bf16x8 &f0, bf16x8 &f1) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f0), "+v"(f1) : : "memory");
+}
+
+// Weight rows come in units of eight: eight consecutive rows, or (SwiGLU) four gate rows and their four up rows, or (QKV) four
+// rows of the first half of a head and the four that the rotation pairs them with.  A tile is two units.  In the result of
+// the 16x16 MFMA lane quarter q holds rows 4 q .. 4 q + 3 of the tile for the token lane % 16, so that the two
+// partners of a pair come to lie in neighbouring quarters of the same token.
+template <int EPI, int MT, int NC, int D>
+__global__ __launch_bounds__(64 * FW, 2) void gemm_few_kernel(const bf16 *__restrict__ A, const bf16 *__restrict__ B,
+                                                           void *__restrict__ Cv, int M, int N, int K, FewSplit split,
+                                                           size_t part_stride, FewFusion fu) {
+  constexpr bool SCALED = EPI == FEW_SCALED_SWIGLU, SWIGLU = EPI == FEW_SWIGLU || SCALED, ROPE = EPI == FEW_ROPE, NORM = EPI == FEW_NORM, PAIRED = SWIGLU || ROPE;
+  constexpr int P = 16 * MT, NP = 64 * FW / P;             // padded tokens; threads per token that add up sums of squares
+  __shared__ __attribute__((aligned(1024))) char Ring[FW * D * 2048];
+  __shared__ __attribute__((aligned(16))) f32x4 Red[2][FW][MT][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, quarter = lane >> 4, bx = blockIdx.x, by = blockIdx.y;
+
+  // units of this workgroup, K range of this wave (in chunks of 64; a short launch is a chain of few instructions, so no divisions)
+  const int u0 = bx * split.units + min(bx, split.units_left), nu = split.units + (bx < split.units_left);
+  const int tiles = (nu + 1) / 2;
+  const int kt0 = by * split.chunks + min(by, split.chunks_left), kn = split.chunks + (by < split.chunks_left);
+  const int c0 = kn * wave / FW, nc = kn * (wave + 1) / FW - c0;
+  const unsigned k_bytes = (unsigned)K * 2;
+  const char *a_base = (const char *)A + (size_t)(kt0 + c0) * 128, *b_base = (const char *)B + (size_t)(kt0 + c0) * 128;
+
+  // Everything that is not a weight is asked for first: loads return in order, so it has landed when the first stage has.
+  uint32_t square[kSquarePieces];
+  if (SCALED) {
+#pragma unroll
+    for (int i = 0; i < kSquarePieces; ++i)
+      few_load(fu.squares, (min(tid / P + i * NP, fu.n_squares - 1) * P + tid % P) * 4, square[i]);
+  }
+  // the one item (tile, 16 tokens) that this wave finishes: residual stream and gain, or cosines, sines and pool slot
+  f32x4 item[2];
+  uint32_t slot;
+  if (NORM) {
+    const unsigned f = u0 * 8 + quarter * 4;
+    few_load16(fu.h, (min(wave * 16 + r16, M - 1) * N + f) * 4, item[0]);
+    few_load16(fu.gain, f * 4, item[1]);
+  }
+  if (ROPE) {
+    const int t = min(wave / MT, tiles - 1), m = min(wave % MT * 16 + r16, M - 1), half = fu.head_dim / 2;
+    const int u = u0 + min(2 * t + (lane >> 4 & 1), nu - 1);
+    const unsigned cs = (m * half + (u * 4 & (half - 1))) * 8;
+    few_load16(fu.cs, cs, item[0]);
+    few_load16<16>(fu.cs, cs, item[1]);
+    few_load(fu.tok_slot, m * 4, slot);
+  }
+  // A stage is 16 rows by 64 k: load i of it rows 8 i + lane / 8, lane l piece l % 8 (16 bytes), swizzled by the row / 2
+  // on the global side.  The first stages of a wave are its activations, 16 tokens each (rows past M repeat the last one and are never
+  // stored), the others weights, a unit per load.  A workgroup's last tile may hold one unit, which it then holds twice.  (Activations
+  // loaded straight into registers, in half lines: QKV at 16 / 37 tokens 5.7 / 8.0 us instead of 4.8 / 5.8.)
+  const int lr = lane >> 3;
+  const unsigned piece0 = ((lane & 7) ^ ((lr >> 1) & 7)) * 16, piece1 = ((lane & 7) ^ (((lr + 8) >> 1) & 7)) * 16;
+  const unsigned unit_rows = (PAIRED ? (lr & 3) + (lr >> 2) * (SWIGLU ? N : fu.head_dim / 2) : lr) * k_bytes;
+  const int head_shift = ROPE ? fu.head_shift : 0;
+  // first row of a unit: 8 u, 4 u, or 4 u and the second halves of the heads before it
+  auto unit_row = [&](int u) { return (unsigned)(PAIRED ? 4 * u + (ROPE ? u >> head_shift << (head_shift + 2) : 0) : 8 * u); };
+  char *ring = Ring + wave * D * 2048;
+  const int total = (MT + tiles) * nc;                      // stages of this wave
+  int issued = 0, ls = 0, lc = nc, lt = -MT;                // stages asked for; ring offset, chunks left and tile (of tokens: negative) of the next
+  const char *base;                                         // addresses: a uniform base and a 32-bit lane offset
+  unsigned off0, off1;
+  auto aim = [&]() {
+    if (lt < 0) {
+      base = a_base;
+      off0 = min((lt + MT) * 16 + lr, M - 1) * k_bytes + piece0;
+      off1 = min((lt + MT) * 16 + 8 + lr, M - 1) * k_bytes + piece1;
+    } else {
+      const unsigned row = unit_row(u0 + 2 * lt);
+      base = b_base + (size_t)row * k_bytes;
+      off0 = unit_rows + piece0;
+      off1 = unit_rows + piece1 + (unit_row(u0 + min(2 * lt + 1, nu - 1)) - row) * k_bytes;
+    }
+  };
+  aim();
+  auto request = [&]() {
+    if (lt < 0) {                                           // every workgroup reads them: they have to stay in L2 (non-temporal: QKV 5.8 -> 6.9 us)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(base + off0), LDS_PTR(ring + ls), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(base + off1), LDS_PTR(ring + ls + 1024), 16, 0, 0);
+    } else {
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(base + off0), LDS_PTR(ring + ls), 16, 0, 2 /* nt */);
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(base + off1), LDS_PTR(ring + ls + 1024), 16, 0, 2 /* nt */);
+    }
+    base += 128;
+    ls = ls == (D - 1) * 2048 ? 0 : ls + 2048;
+    ++issued;
+    if (__builtin_expect(--lc == 0, 0)) {
+      lc = nc;
+      ++lt;
+      aim();
+    }
+  };
+#pragma unroll 1
+  for (int i = min(D - 1, total); i > 0; --i) request();
+
+  unsigned addr[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    addr[h] = (unsigned)(uintptr_t)LDS_PTR(ring) + r16 * 128 + (((h * 4 + quarter) ^ ((r16 >> 1) & 7)) << 4);
+  int s = 0, done = 0;                                      // ring slot and number of the stage to be read
+  // The next stage, as MFMA operands.  It has landed when no more than the stages behind it are in flight (a store in between
+  // only makes the wait longer); near the end, where nothing is asked for any more, fewer may be.
+  auto take = [&](bf16x8 &f0, bf16x8 &f1) {
+    if (issued < total) request();                          // into the slot that was read last
+    __builtin_amdgcn_sched_barrier(0);
+    const int behind = issued - 1 - done;
+    if (behind >= D - 1) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * (D - 1)));
+    else if (behind >= 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm(6));
+    else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    __builtin_amdgcn_sched_barrier(0);
+    few_read<0>(addr[0] + s, f0);
+    few_read<0>(addr[1] + s, f1);
+    few_await(f0, f1);
+    ++done;
+    s = s == (D - 1) * 2048 ? 0 : s + 2048;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  bf16x8 act[NC][2][MT];
+#pragma unroll
+  for (int j = 0; j < MT; ++j)
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c < nc) take(act[c][0][j], act[c][1][j]);
+  if (ROPE || NORM) few_landed(item[0], item[1]);
+  if (ROPE) few_landed(slot);
+
+  // 1 / rms of each token's row, from the partial sums of squares that the O projection left (fixed order)
+  float inv_rms[MT];
+#pragma unroll
+  for (int j = 0; j < MT; ++j) inv_rms[j] = 1.0f;
+  if (SCALED) {
+    float *sums = (float *)Red;                             // [P][NP]
+    float sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < kSquarePieces; ++i) {
+      few_landed(square[i]);
+      sq += tid / P + i * NP < fu.n_squares ? __uint_as_float(square[i]) : 0.f;
+    }
+    if (tid / P < NP) sums[tid % P * NP + tid / P] = sq;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+      float all = 0.f;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) all += sums[(j * 16 + r16) * NP + i];
+      inv_rms[j] = 1.0f / sqrtf(all / (float)K + fu.eps);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    __builtin_amdgcn_s_barrier();                           // read by all before a tile's sums go there
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  for (int t = 0; t < tiles; ++t) {
+    f32x4 acc[MT];
+#pragma unroll
+    for (int j = 0; j < MT; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (c < nc) {
+        bf16x8 wf[2];
+        take(wf[0], wf[1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int j = 0; j < MT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h], act[c][h][j], acc[j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    // Two buffers: one is written again two tiles on, behind the next tile's barrier, which its readers reach after reading.
+    f32x4(*red)[MT][64] = Red[t & 1];
+#pragma unroll
+    for (int j = 0; j < MT; ++j) red[wave][j][lane] = acc[j];
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    const int units = min(2, nu - 2 * t);                    // units of this tile
+#pragma unroll
+    for (int j = 0; j < MT; ++j) {
+      if (((t * MT + j) & (FW - 1)) != wave) continue;
+      const int m = j * 16 + r16;
+      auto sum = [&](int l) {
+        f32x4 v = red[0][j][l];
+#pragma unroll
+        for (int w = 1; w < FW; ++w) v += red[w][j][l];
+        return v;
+      };
+      if (PAIRED) {
+        const int i = lane >> 4, u = u0 + 2 * t + i;
+        if (i >= units || m >= M) continue;                  // half of the lanes: an item is a token and a unit
+        f32x4 a = sum(i * 32 + r16), b = sum(i * 32 + 16 + r16);
+        if (SWIGLU) {
+          bf16x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float gte = SCALED ? a[e] * inv_rms[j] : a[e], up = SCALED ? b[e] * inv_rms[j] : b[e];
+            o[e] = (bf16)(gte * __builtin_amdgcn_rcpf(1.0f + __expf(-gte)) * up);
+          }
+          *(bf16x4 *)((bf16 *)Cv + (size_t)m * N + (size_t)u * 4) = o;
+        } else {
+          const int head = u >> head_shift, f = u * 4 & (fu.head_dim / 2 - 1);
+          bf16x4 oa, ob;
+          if (head < fu.n_q_heads + fu.n_kv_heads) {
+            const float q = head < fu.n_q_heads ? fu.q_scale : 1.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float cosv = item[e / 2][e % 2 * 2], sinv = item[e / 2][e % 2 * 2 + 1];
+              oa[e] = (bf16)((a[e] * cosv - b[e] * sinv) * q);
+              ob[e] = (bf16)((b[e] * cosv + a[e] * sinv) * q);
+            }
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              oa[e] = (bf16)a[e];
+              ob[e] = (bf16)b[e];
+            }
+          }
+          bf16 *dst;
+          if (head < fu.n_q_heads) {
+            dst = (bf16 *)Cv + ((size_t)m * fu.n_q_heads + head) * fu.head_dim;
+          } else {
+            const int kv = head - fu.n_q_heads, hk = kv < fu.n_kv_heads ? kv : kv - fu.n_kv_heads;
+            dst = (kv < fu.n_kv_heads ? fu.k_pool : fu.v_pool) +
+                  (((size_t)(slot / ARB_KV_BLOCK) * fu.n_kv_heads + hk) * ARB_KV_BLOCK + slot % ARB_KV_BLOCK) * fu.head_dim;
+          }
+          *(bf16x4 *)(dst + f) = oa;
+          *(bf16x4 *)(dst + f + fu.head_dim / 2) = ob;
+        }
+      } else {
+        f32x4 v = sum(lane);
+        const bool mine = m < M && quarter / 2 < units;
+        const size_t at = (size_t)m * N + (size_t)(u0 + 2 * t) * 8 + quarter * 4;
+        if (NORM) {
+          // The residual stream is complete here; its norm needs the whole row.  The row goes on times the gain, unscaled
+          // (rounded to bf16 as the scaled one would be), with this tile's share of its sum of squares.
+          v += item[0];
+          float sq = mine ? v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3] : 0.f;
+          sq += __shfl_xor(sq, 16, 64);
+          sq += __shfl_xor(sq, 32, 64);
+          if (lane < 16) fu.squares_out[(size_t)blockIdx.x * P + m] = sq;
+          if (mine) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)(v[e] * item[1][e]);
+            *(f32x4 *)(fu.h + at) = v;
+            *(bf16x4 *)((bf16 *)Cv + at) = o;
+          }
+        } else if (mine) {
+          if (EPI == FEW_BF16) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)v[e];
+            *(bf16x4 *)((bf16 *)Cv + at) = o;
+          } else if (EPI == FEW_F32) {
+            *(f32x4 *)((float *)Cv + blockIdx.y * part_stride + at) = v;
+          } else {
+            *(f32x4 *)((float *)Cv + at) += v;
+          }
+        }
+      }
+    }
+  }
+}
+
+template <int EPI>
+arb_status launch_few(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, const dim3 &grid, size_t part_stride,
+                      const FewFusion &fu, hipStream_t st) {
+  const int mt = ceil_div(M, 16), nc = few_chunks(K, grid.y), units = (EPI == FEW_SWIGLU || EPI == FEW_SCALED_SWIGLU ? 2 * N : N) / 8, gx = grid.x, gy = grid.y;
+  const FewSplit split{units / gx, units % gx, K / 64 / gy, K / 64 % gy};
+#define ARB_FEW(MT, NC, D)                                                                                              \
+  hipLaunchKernelGGL((gemm_few_kernel<EPI, MT, NC, D>), grid, dim3(64 * FW), 0, st, A, B, C, M, N, K, split, part_stride, fu)
+  // the ring and the two buffers of sums together fill 144 KB
+  if (mt == 1) { if (nc <= 4) ARB_FEW(1, 4, 8); else if (nc <= 8) ARB_FEW(1, 8, 8); else ARB_FEW(1, 16, 8); }
+  else if (mt == 2) { if (nc <= 4) ARB_FEW(2, 4, 7); else ARB_FEW(2, 8, 7); }
+  else if (mt == 3) ARB_FEW(3, 4, 6);
+  else ARB_FEW(4, 4, 5);
+#undef ARB_FEW
+  ARB_CHECK_LAUNCH("gemm_few");
+  return ARB_OK;
+}
+
+}  // namespace
+
+// Whether a launch of M rows against `rows` weight rows (2 F for SwiGLU), K in so many splits, can run on this kernel.
+//  - A wave's slice of the activations has to fit its registers (8 per chunk and 16 tokens): at most 128 of them.
+//  - Every wave needs work: at least two of the chunks of K.
+//  - A lane's offset from its unit's first row is kept in 32 bits.
+static bool few_fits(int M, int rows, int K, int splits) {
+  if (M <= 0 || M > 64 || K / 64 / splits < 2 * FW || (long long)(rows + 8) * K * 2 >= (1LL << 32)) return false;
+  const int nc = few_chunks(K, splits);
+  return nc <= 16 && ceil_div(M, 16) * (nc <= 4 ? 4 : nc <= 8 ? 8 : 16) <= 16;
+}
+
+// ... and should.  On small matrices the start of a launch is all there is, and a split K is the faster start.
+bool gemm_few_takes(int M, int rows, int K, int splits) {
+  return few_fits(M, rows, K, splits) && (long long)rows * K >= kFewWeights;
+}
+
+// K splits of a projection with fp32 partial products, 0 if this kernel does not take it.  The time of a launch goes with the
+// number of 16 KB stages (all waves together) per workgroup, activations included, of which a CU takes one in about 0.55 us; every
+// split costs its consumer another row to read.
+int gemm_few_splits(int M, int N, int K, int max_splits) {
+  int best = 0;
+  double best_us = 0;
+  for (int s = 1; s <= max_splits; ++s) {
+    if (!gemm_few_takes(M, N, K, s)) continue;
+    const int per = std::max(2, ceil_div(N / 8, kFewGrid / s));          // units of a workgroup
+    const double us = 0.55 * (ceil_div(M, 16) + ceil_div(per, 2)) * K / 64 / s / FW + s * (0.4 + (double)M * N * 8 / 5.0e6);
+    if (best == 0 || us < best_us) {
+      best = s;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+arb_status launch_gemm_few(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, int splits,
+                           size_t part_stride, hipStream_t st) {
+  const int units = (epilogue == ARB_EPI_SWIGLU_BF16 ? 2 * N : N) / 8;
+  const dim3 grid(std::min(kFewGrid / splits, ceil_div(units, 2)), splits);       // whole tiles, one workgroup per CU
+  const FewFusion none{};
+  switch (epilogue) {
+    case ARB_EPI_STORE_BF16: return launch_few<FEW_BF16>(A, B, C, M, N, K, grid, part_stride, none, st);
+    case ARB_EPI_RESIDUAL_F32:
+      if (splits > 1) return launch_few<FEW_F32>(A, B, C, M, N, K, grid, part_stride, none, st);
+      return launch_few<FEW_RESIDUAL>(A, B, C, M, N, K, grid, part_stride, none, st);
+    case ARB_EPI_STORE_F32: return launch_few<FEW_F32>(A, B, C, M, N, K, grid, part_stride, none, st);
+    case ARB_EPI_SWIGLU_BF16: return launch_few<FEW_SWIGLU>(A, B, C, M, N, K, grid, part_stride, none, st);
+  }
+  return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
+}

@@ -118,6 +118,27 @@ def test_gemm_few_tokens(A, M, N, K):
     assert rel_err(bf16_np(got), O.silu(ref[:, :F]) * ref[:, F:]) < 5e-3
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 8192, 1024),         # two chunks of k per wave, four whole tiles per workgroup
+                                   (16, 8320, 1088),        # 17 chunks: waves with two and with three; 1040 units, four or five per workgroup
+                                   (17, 4224, 2112), (32, 2176, 4096),       # two token tiles, up to eight chunks per wave
+                                   (33, 8192, 1600), (48, 8192, 2048),       # three, rings of six stages
+                                   (49, 8192, 1536), (64, 8320, 2048),       # four
+                                   (16, 1280, 8192), (15, 1152, 8000)])      # sixteen chunks per wave; 125 chunks in all
+def test_gemm_resident_activations(A, M, N, K):
+    """The few-token kernel that keeps the activations in registers, at the edges of its token tiles, uneven K slices and
+    workgroups whose last tile is half a tile.  Bounds as above."""
+    a, b = rand_bf16((M, K), 1.0, 19), rand_bf16((N, K), 0.05, 20)
+    ref = bf16_np(a) @ bf16_np(b).T
+    assert rel_err(bf16_np(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_BF16)), ref) < 4e-3
+    assert rel_err(A.arb_stage_gemm(a, b, A.ARB_EPI_STORE_F32).cpu().numpy(), ref) < 1e-5
+    h0 = torch.randn(M, N, device="cuda", dtype=torch.float32)
+    h = h0.clone()
+    A.arb_stage_gemm(a, b, A.ARB_EPI_RESIDUAL_F32, out=h)
+    assert rel_err(h.cpu().numpy(), h0.cpu().numpy().astype(np.float64) + ref) < 1e-5
+    got = A.arb_stage_gemm(a, b, A.ARB_EPI_SWIGLU_BF16)
+    assert rel_err(bf16_np(got), O.silu(ref[:, :N // 2]) * ref[:, N // 2:]) < 5e-3
+
+
 @pytest.mark.parametrize("M", [33, 64])
 @pytest.mark.parametrize("K", [64, 256, 320, 576])         # steps of 64: fewer than the ring's five stages, as many, more
 def test_gemm_64_rows_two_workgroups_per_cu(A, M, K):
