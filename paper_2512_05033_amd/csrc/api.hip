@@ -338,6 +338,16 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (part == GEMM_PART_SMALL) return (arb_status)ARB_OK;            // the 4-bit kernel is one launch
     return launch_gemm_w4(w.x, (const uint32_t *)m->wgu[l], m->sgu[l], w.act, T, c.d_ffn, d, ARB_EPI_SWIGLU_BF16, st, 1);
   };
+  // Few tokens: the projection rotates and appends by itself (launch_gemm_few_qkv).
+  const bool rotates = !m->w4 && gemm_few_rotates(T, m->qkv_rows(), d);
+  FewFusion few{};
+  few.cs = w.cs;
+  few.tok_slot = w.tok_slot;
+  few.n_q_heads = c.n_q_heads;
+  few.n_kv_heads = c.n_kv_heads;
+  few.head_dim = c.head_dim;
+  few.head_shift = c.head_dim == 64 ? 3 : 4;
+  few.q_scale = attention_q_scale(c.head_dim);
   auto scale_of = [&](const std::vector<const bf16 *> &v, int l) { return m->w4 ? v[l] : (const bf16 *)nullptr; };
   RowParts pending{};
   arb_status s;
@@ -360,7 +370,17 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
       pending = RowParts{};
     }
     if (s) return s;
-    for (int t0 = 0; t0 < T; t0 += q_tokens) {               // one range, unless QKV rows are wider than 8 d_model
+    if (rotates) {
+      few.k_pool = (bf16 *)kv->k_pool[l];
+      few.v_pool = (bf16 *)kv->v_pool[l];
+      {
+        TraceScope t(m, ARB_STAGE_QKV, st);
+        s = launch_gemm_few_qkv(w.x, m->wqkv[l], w.q, T, m->qkv_rows(), d, few, st);
+      }
+      if (s) return s;
+      TraceScope t(m, ARB_STAGE_ROPE_APPEND, st);            // nothing is left of this stage
+    }
+    for (int t0 = 0; t0 < T && !rotates; t0 += q_tokens) {   // one range, unless QKV rows are wider than 8 d_model
       const int rows = T - t0 < q_tokens ? T - t0 : q_tokens;
       const GemmPlan &pq = rows == q_tokens ? plan_q : plan_q_last;
       {

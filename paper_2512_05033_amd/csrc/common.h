@@ -114,6 +114,8 @@ bool gemm_few_takes(int M, int rows, int K, int splits);         // rows: weight
 int gemm_few_splits(int M, int N, int K, int max_splits);
 arb_status launch_gemm_few(const bf16 *A, const bf16 *B, void *C, int M, int N, int K, int epilogue, int splits,
                            size_t part_stride, hipStream_t st);
+bool gemm_few_rotates(int M, int rows, int K);                   // whether launch_gemm_few_qkv takes a projection
+arb_status launch_gemm_few_qkv(const bf16 *A, const bf16 *B, bf16 *q, int M, int rows, int K, const FewFusion &fu, hipStream_t st);
 
 // attention.hip
 constexpr int ATTN_QROWS = 128;     // query rows (step tokens x query heads of one kv head) per workgroup

@@ -397,3 +397,17 @@ arb_status launch_gemm_few(const bf16 *A, const bf16 *B, void *C, int M, int N, 
   }
   return arb_fail(ARB_EINVAL, "gemm: unknown epilogue %d", epilogue);
 }
+
+// ---- the fused launches of a pass ----
+
+// QKV: the epilogue holds both partners of a rotary pair, rotates them and writes q, and k and v to their pool slots, so that neither
+// the fp32 products nor the launch that would read them back exist.  Sums are fp32 and q, k are rounded once, after the rotation.  A wave
+// fetches what its one item needs (cosines, sines, slot) at the start; that is the limit on tiles.
+bool gemm_few_rotates(int M, int rows, int K) {
+  if (!few_fits(M, rows, K, 1)) return false;
+  const int units = rows / 8, per = ceil_div(units, std::min(kFewGrid, ceil_div(units, 2)));
+  return ceil_div(per, 2) * ceil_div(M, 16) <= FW;
+}
+arb_status launch_gemm_few_qkv(const bf16 *A, const bf16 *B, bf16 *q, int M, int rows, int K, const FewFusion &fu, hipStream_t st) {
+  return launch_few<FEW_ROPE>(A, B, q, M, rows, K, dim3(std::min(kFewGrid, ceil_div(rows / 8, 2)), 1), 0, fu, st);
+}

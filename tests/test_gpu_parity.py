@@ -714,6 +714,25 @@ def test_qkv_rows_wider_than_their_scratch(A, batch, step):
     _assert_cache(sess, kp, vp, kp_before, slots)
 
 
+@pytest.mark.parametrize("d,hq,hkv,hd,F", [(1024, 8, 2, 128, 1024),      # two chunks of K per wave; one unit pair per workgroup
+                                           (1152, 18, 6, 64, 1280),      # 18 chunks: waves with two and three
+                                           (1024, 32, 8, 128, 1024)])    # QKV: three units per workgroup, tiles across heads; O: K = 4096
+@pytest.mark.parametrize("batch,step", [(1, 1), (16, 1), (3, 6), (4, 8), (3, 11), (7, 7), (64, 1)])        # 1 to 64 tokens
+def test_pass_of_few_tokens(A, d, hq, hkv, hd, F, batch, step):
+    """Passes of at most 64 tokens on models whose projections run on the kernel with resident activations, at the edges of
+    its token tiles.  Held to the bars of the hidden states and the cache.  (The score bar is one of means over steps: a single
+    token's score has a standard deviation of 0.02 |y| times the relative error of y, 0.02 * 34 * 0.5 % = 0.0034 at d = 1152,
+    of which the largest among 64 is about 0.011.)"""
+    w = replace(W.scaled(W.C1, batch=batch), step=("fixed", step, step), prefix=(20, 90), kv_source="synthetic", kv_sigma=0.8,
+                model=replace(W.TINY, d_model=d, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=F, vocab=512))
+    sess, (scores, esc, hidden), (s_ref, e_ref, y_ref), (kp, vp, kp_before) = _end_to_end(A, w, gain_jitter=0.1)
+    assert rel_err(bf16_np(hidden), y_ref) < HIDDEN_TOL
+    slots = O.slot_mapping(sess.batch.prefix_lens, sess.batch.cu_step_lens, sess.batch.block_tables, 16)
+    _assert_cache(sess, kp, vp, kp_before, slots)
+    again = A.arb_score_steps(sess.model, sess.kv, sess.dbatch, sess.batch.tau, want_hidden=True, ws=sess.ws)
+    assert torch.equal(again[0], scores) and torch.equal(again[2], hidden)
+
+
 @pytest.mark.parametrize("pool_mode", ["mean", "last"])
 def test_c1_two_class_head_scores_are_probabilities(A, pool_mode):
     """The two-way classification head of Section 4.2: scores are class-1 probabilities, tau is a probability."""
