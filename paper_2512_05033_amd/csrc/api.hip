@@ -338,7 +338,8 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (part == GEMM_PART_SMALL) return (arb_status)ARB_OK;            // the 4-bit kernel is one launch
     return launch_gemm_w4(w.x, (const uint32_t *)m->wgu[l], m->sgu[l], w.act, T, c.d_ffn, d, ARB_EPI_SWIGLU_BF16, st, 1);
   };
-  // Few tokens: the projection rotates and appends by itself (launch_gemm_few_qkv).
+  // Few tokens: QKV rotates and appends by itself, O completes the residual stream, and gate/up applies the norm between the two.
+  const bool norms = !m->w4 && gemm_few_norms(T, d, hq, c.d_ffn);
   const bool rotates = !m->w4 && gemm_few_rotates(T, m->qkv_rows(), d);
   FewFusion few{};
   few.cs = w.cs;
@@ -348,6 +349,10 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
   few.head_dim = c.head_dim;
   few.head_shift = c.head_dim == 64 ? 3 : 4;
   few.q_scale = attention_q_scale(c.head_dim);
+  few.h = w.h;
+  few.squares = few.squares_out = w.parts;                 // [d / 16][padded tokens]; free between QKV and down
+  few.n_squares = d / 16;
+  few.eps = c.rms_eps;
   auto scale_of = [&](const std::vector<const bf16 *> &v, int l) { return m->w4 ? v[l] : (const bf16 *)nullptr; };
   RowParts pending{};
   arb_status s;
@@ -404,13 +409,19 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (s) return s;
     {
       TraceScope t(m, ARB_STAGE_OPROJ, st);
-      s = project(w.attn, m->wo[l], scale_of(m->so, l), w.parts, T, d, hq, ARB_EPI_STORE_F32, plan_o);
-      pending = parts_of(plan_o);
+      if (norms) {
+        few.gain = m->g_mlp[l];
+        s = launch_gemm_few_o(w.attn, m->wo[l], w.x, T, d, hq, few, st);
+      } else {
+        s = project(w.attn, m->wo[l], scale_of(m->so, l), w.parts, T, d, hq, ARB_EPI_STORE_F32, plan_o);
+      }
     }
     if (s) return s;
-    if ((s = launch_rmsnorm(w.h, w.parts, pending, m->g_mlp[l], c.rms_eps, T, d, w.x, st))) return s;
-    pending = RowParts{};
-    {
+    if (!norms && (s = launch_rmsnorm(w.h, w.parts, parts_of(plan_o), m->g_mlp[l], c.rms_eps, T, d, w.x, st))) return s;
+    if (norms) {
+      TraceScope t(m, ARB_STAGE_GATE_UP, st);
+      s = launch_gemm_few_gate_up(w.x, m->wgu[l], w.act, T, c.d_ffn, d, few, st);
+    } else {
       TraceScope t(m, ARB_STAGE_GATE_UP, st);
       {
         TraceScope large(m, ARB_STAGE_GATE_UP_LARGE, st);

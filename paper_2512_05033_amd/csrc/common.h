@@ -116,6 +116,9 @@ arb_status launch_gemm_few(const bf16 *A, const bf16 *B, void *C, int M, int N, 
                            size_t part_stride, hipStream_t st);
 bool gemm_few_rotates(int M, int rows, int K);                   // whether launch_gemm_few_qkv takes a projection
 arb_status launch_gemm_few_qkv(const bf16 *A, const bf16 *B, bf16 *q, int M, int rows, int K, const FewFusion &fu, hipStream_t st);
+bool gemm_few_norms(int M, int d, int hq, int F);                // whether the next two take the projections of a layer
+arb_status launch_gemm_few_o(const bf16 *A, const bf16 *B, bf16 *x, int M, int d, int hq, const FewFusion &fu, hipStream_t st);
+arb_status launch_gemm_few_gate_up(const bf16 *x, const bf16 *B, bf16 *act, int M, int F, int d, const FewFusion &fu, hipStream_t st);
 
 // attention.hip
 constexpr int ATTN_QROWS = 128;     // query rows (step tokens x query heads of one kv head) per workgroup

@@ -411,3 +411,18 @@ bool gemm_few_rotates(int M, int rows, int K) {
 arb_status launch_gemm_few_qkv(const bf16 *A, const bf16 *B, bf16 *q, int M, int rows, int K, const FewFusion &fu, hipStream_t st) {
   return launch_few<FEW_ROPE>(A, B, q, M, rows, K, dim3(std::min(kFewGrid, ceil_div(rows / 8, 2)), 1), 0, fu, st);
 }
+
+// O, the norm and gate/up: the O epilogue adds its sums to the residual stream and stores the new row times the gain, unscaled, with each
+// 16-feature tile's share of the row's sum of squares; every gate/up workgroup adds those up and scales its sums by 1 / rms before the
+// activation.  W (r x) = r (W x) row by row, and x is rounded to bf16 once with or without r, so nothing is rounded more than it was.
+// A workgroup of the O launch has one tile, so that each wave can fetch the stream and the gain of its one item at the start.
+bool gemm_few_norms(int M, int d, int hq, int F) {
+  const int pieces = 64 * FW / (16 * ceil_div(M, 16)) * kSquarePieces;     // partial sums that a gate/up workgroup can add up per token
+  return few_fits(M, d, hq, 1) && few_fits(M, 2 * F, d, 1) && d / 16 <= pieces;
+}
+arb_status launch_gemm_few_o(const bf16 *A, const bf16 *B, bf16 *x, int M, int d, int hq, const FewFusion &fu, hipStream_t st) {
+  return launch_few<FEW_NORM>(A, B, x, M, d, hq, dim3(d / 16, 1), 0, fu, st);
+}
+arb_status launch_gemm_few_gate_up(const bf16 *x, const bf16 *B, bf16 *act, int M, int F, int d, const FewFusion &fu, hipStream_t st) {
+  return launch_few<FEW_SCALED_SWIGLU>(x, B, act, M, F, d, dim3(std::min(kFewGrid, ceil_div(F / 4, 2)), 1), 0, fu, st);
+}
