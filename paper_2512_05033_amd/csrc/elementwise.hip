@@ -329,8 +329,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const f
         const float *src = h_in + (size_t)row * d + c;
         f32x4 a = *(const f32x4 *)src, b = *(const f32x4 *)(src + 4);
         if (n_parts > 0) {
-          // For the usual split counts the loads of all partial products go out together (a loop over a
-          // run-time count waits for each before it asks for the next); the sums keep the fixed order.
+          // The loads of all partial products go out together (a loop over a run-time count waits for each before it asks for
+          // the next); the sums keep the fixed order.
           const float *p0 = parts + (size_t)row * d + c;
 #define ARB_ADD_PARTS(NP)                                                      \
   {                                                                            \
@@ -347,6 +347,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float *h_in, const f
             case 3: ARB_ADD_PARTS(3) break;
             case 4: ARB_ADD_PARTS(4) break;
             case 5: ARB_ADD_PARTS(5) break;
+            case 6: ARB_ADD_PARTS(6) break;
+            case 7: ARB_ADD_PARTS(7) break;
             case 8: ARB_ADD_PARTS(8) break;
             default:
               for (int sp = 0; sp < n_parts; ++sp) {

@@ -1239,24 +1239,28 @@ int gemm_large_cols(int M, int N, int K, int epilogue, int splits) {
 }
 
 // Time estimates in us for a launch of m rows with fp32 (or bf16) output, from which the planner below chooses.  Both have
-// the form steps x time per step + fixed + what the partial products cost to write here and read in the consumer.  Time
-// per step of 64 k, measured on launches that fill one round of their kernel: 64x128 tiles 0.45, 128x128 one per CU
-// 0.67, two per CU 1.0, 256x128 0.93; 256x256 tiles 1.17 up to half of the CUs, 1.4 at three quarters, 1.6
-// with all (the clock; the line through the two ends gives 1.38 in between).
-static double traffic_us(int m, int N, int splits, int bytes) { return (double)m * N * bytes * (2 * splits - 1) / 5.0e6; }
+// the form steps x time per step + fixed + what each split's product costs to write here and read in the consumer.  The constants
+// are a fit to 8 matrices (QKV, O and down of the 1.5B and 8B shapes, two in between) x 29 row counts from 70 to 8208 x every
+// kernel and split, weights from memory, plus each split's products read once at 12 TB/s (they come from the memory-side cache: a norm
+// behind 3 and behind 7 of them, 768 rows of 1536: 5.9 and 7.3 us, a rotary kernel behind 1 and 2: 5.1 and 5.2).  Per step of 64 k:
+// 64x128 tiles 0.355, 128x128 one per CU 0.53, two per CU 0.83, 256x128 0.9; 256x256 tiles 1.1 up to half of the CUs, 1.33 with
+// all (the clock).  What the estimates choose is 0.9 % slower than the best of each (the worst 14 %); with times per step taken at full
+// launches of long K, and one split per kernel to choose from, it was 5 % (30 %): 8B O at 160 rows 22 -> 17 us with its share of the
+// consumer; passes of 200 / 384 / 512 rows of the 1.5B shape 765 -> 715, 897 -> 821, 1104 -> 1060 us.
+static double split_us(int m, int N, int splits, int bytes) { return (double)m * N * bytes * splits / 2.9e6; }
 static double tiled_us(int m, int N, int K, int splits, int bytes) {
   const int t128 = ceil_div(m, BM) * (N / BN) * splits, t64 = ceil_div(m, 64) * (N / BN) * splits,
             t256 = ceil_div(m, 256) * (N / BN) * splits;
   double step;
-  if (t128 <= 128 || m <= 64) step = 0.45 * ceil_div(t64, 256);
-  else if (t128 <= 256) step = 0.67;
-  else if (t256 >= 192 && t256 <= 256) step = 0.93;
-  else step = (t128 / 512) * 1.0 + (t128 % 512 == 0 ? 0.0 : t128 % 512 <= 256 ? 0.67 : 0.95);
-  return step * (K / BK) / splits + 5.0 + traffic_us(m, N, splits, bytes);
+  if (t128 <= 128 || m <= 64) step = 0.355 * ceil_div(t64, 256);
+  else if (t128 <= 256) step = 0.53;
+  else if (t256 >= 192 && t256 <= 256) step = 0.9;
+  else step = (t128 / 512) * 0.83 + (t128 % 512 == 0 ? 0.0 : t128 % 512 <= 256 ? 0.53 : 0.98);
+  return step * (K / BK) / splits + 3.9 + split_us(m, N, splits, bytes);
 }
 static double wide_us(int m, int N, int K, int splits, int bytes) {
   const double f = ceil_div(m, W_TM) * (N / W_TN) * splits / 256.0;          // at most one round
-  return (f <= 0.5 ? 1.17 : 1.17 + 0.85 * (f - 0.5)) * (K / BK) / splits + 5.0 + traffic_us(m, N, splits, bytes);
+  return (f <= 0.5 ? 1.1 : 1.1 + 0.46 * (f - 0.5)) * (K / BK) / splits + 3.9 + split_us(m, N, splits, bytes);
 }
 
 // How a projection without the SwiGLU epilogue is launched.  Rows that make up whole rounds of 256 large tiles go to the
@@ -1289,11 +1293,11 @@ GemmPlan gemm_plan(int M, int N, int K, int max_splits) {
     if (partials) rest.splits = std::min(gemm_stream_splits(m, N, K), max_splits);
   } else {
     double best = tiled_us(m, N, K, 1, bytes);
-    if (partials) {
-      const int s = std::min(gemm_residual_splits(m, N, K), max_splits);
-      if (s > 1 && tiled_us(m, N, K, s, bytes) < best) {
+    for (int s = 2; partials && s <= max_splits && K / BK / s >= 4; ++s) {
+      const double t = tiled_us(m, N, K, s, bytes);
+      if (t < best) {
+        best = t;
         rest.splits = s;
-        best = tiled_us(m, N, K, s, bytes);
       }
     }
     const int tiles = N % W_TN == 0 ? ceil_div(m, W_TM) * (N / W_TN) : 0;
