@@ -258,7 +258,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (!kv->k_pool[l] || !kv->v_pool[l]) return arb_fail(ARB_EINVAL, "null kv pool in layer %d", l);
   const int T = bt->total_tokens, B = bt->batch, d = c.d_model;
   const int G = c.n_q_heads / c.n_kv_heads;
-  AttnPlan plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads);
+  AttnPlan plan = plan_attention(B, bt->prefix_lens_host, bt->cu_step_lens_host, G, c.n_kv_heads, c.head_dim);
   // the attention part is sized by this call's own split count (never above what arb_workspace_bytes assumed)
   Workspace w = carve(c, T, plan.max_splits, plan.n_items, ws);
   // Scratch that has no room for the attention work list (the static buffer's size does not follow from the batch) is used
@@ -648,7 +648,7 @@ extern "C" arb_status arb_stage_attention(const arb_model *m, const void *q, int
   if (q_row_stride < c.n_q_heads * c.head_dim || q_row_stride % 8 != 0)
     return arb_fail(ARB_EINVAL, "arb_stage_attention: q_row_stride %d", q_row_stride);
   const int G = c.n_q_heads / c.n_kv_heads, T = batch->total_tokens;
-  AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host, G, c.n_kv_heads);
+  AttnPlan plan = plan_attention(batch->batch, batch->prefix_lens_host, batch->cu_step_lens_host, G, c.n_kv_heads, c.head_dim);
   hipStream_t st = (hipStream_t)stream;
   // Writing the work list costs a single call 2 to 8 us (a forward writes it once for all layers), and it pays where it leaves out
   // many empty places: 64 contexts of 100 to 6400 keys with steps of 16 to 79 tokens (2.7 and 2.2 places per item) 46 us with

@@ -456,7 +456,45 @@ int attention_splits_cap(int max_ctx) {
   return n < kMaxSplits ? n : kMaxSplits;
 }
 
-AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads) {
+// Estimated time of an attention launch and its merge with parts of at most `chunk` keys.  A 64-key tile of 128 rows takes 1.4 us
+// alone on a CU and 1.15 us of the CU's time when two workgroups share it, one of a few rows (one wave works) 2.3 and 1.5; an item costs 4 us
+// more, half of it not hidden by its neighbour.  With more items than places the launch ends half an item after the average place.  Between three
+// quarters and all of the places a launch takes up to a fifth longer than that: CUs that got two of the long items hold it up.
+// Fitted to 43 batches (1 to 64 sequences, 50 to 32 K keys, steps of 1 to 128, three shapes) x up to 17 chunks.
+static double plan_us(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int head_dim, int chunk) {
+  const double f = head_dim == 128 ? 1.0 : 0.6, item = 4.0, places = kTargetWorkgroups, cus = kTargetWorkgroups / 2;
+  double n = 0, work = 0, tiles_all = 0, parts = 0, bytes = 0, shortest = 1e30, alone = 0, shared = 0;
+  int max_ctx = 0;
+  bool decode = true;
+  for (int b = 0; b < batch; ++b) {
+    const int s = cu_host[b + 1] - cu_host[b], ctx = prefix_host[b] + s, k = attn_seq_chunk(ctx, chunk), ns = ceil_div(ctx, k);
+    const bool few = (long long)s * G <= 32;
+    const double count = (double)ns * ceil_div(s * G, QROWS) * n_kv_heads, tiles = k / KT, per = few ? 1.5 : 1.15;
+    n += count;
+    work += count * (tiles * per * f + item / 2);
+    tiles_all += count * tiles;
+    parts += (double)ns * s * G * n_kv_heads;
+    bytes += (double)ctx * n_kv_heads * head_dim * 4;
+    shortest = tiles < shortest ? tiles : shortest;
+    alone = fmax(alone, tiles * (few ? 2.3 : 1.4) * f);
+    shared = fmax(shared, tiles * per * f);
+    decode = decode && few;
+    max_ctx = ctx > max_ctx ? ctx : max_ctx;
+  }
+  const double second = n <= cus ? 0 : (decode ? 1.5 : 1.15) * f * (shortest + (tiles_all / n - shortest) * fmin(1.0, (n - cus) / cus));
+  double us;
+  if (n <= places) {
+    us = item + fmax(alone, shared + second);
+    if (n > 0.75 * places && n < 0.98 * places) us *= 1 + 0.22 * (n - 0.75 * places) / (0.25 * places);
+  } else {
+    us = fmax(item + alone, work / cus + 0.5 * work / n);
+  }
+  us = fmax(us, item + bytes / 5.0e6);
+  const int splits = ceil_div(max_ctx, chunk);
+  return splits > 1 ? us + 5.0 + 1.3 * ceil_div(splits, 8) + parts * head_dim * 4e-7 : us;
+}
+
+AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int head_dim) {
   long long keys_streamed = 0;          // sum over (sequence, kv head, query tile) of the context length
   int max_ctx = 0, max_step = 0;
   for (int b = 0; b < batch; ++b) {
@@ -465,18 +503,35 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
     max_ctx = ctx > max_ctx ? ctx : max_ctx;
     max_step = s > max_step ? s : max_step;
   }
-  // Keys per split: about kTargetWorkgroups workgroups (one resident round) when contexts are short,
-  // so that few partial states have to be merged; never more than kMaxChunk keys, so that long
-  // ragged contexts become several rounds of similar-sized workgroups instead of one unbalanced round
-  // (measured on the ragged workloads: 3072, 4096 and 6144 tie within 2 %, 2048 loses 4 %).  A batch whose steps all
-  // fit one wave (32 query rows: drafting token by token) only streams the cache: there a longer
-  // chunk wins (4096 / 6144 / 8192 keys: 406 / 400 / 418 us on 32 contexts of 4 K to 32 K of the 8B shape).
-  // A sequence is cut into equal parts of at most that many keys (attn_seq_chunk).
+  // Keys per split, a first choice: about kTargetWorkgroups workgroups, never more than kMaxChunk keys (a batch whose steps all fit one
+  // wave only streams the cache: there a longer chunk wins).  A sequence is cut into equal parts of at most that many keys
+  // (attn_seq_chunk).  It bounds the splits, and with them the scratch of a call.
   const int cap = max_step * G <= 32 ? kMaxChunkDecode : kMaxChunk;
   long long chunk = (keys_streamed / kTargetWorkgroups + KT - 1) / KT * KT;
   if (chunk > cap) chunk = cap;
   if (chunk < kMinChunk) chunk = kMinChunk;
   while (max_ctx > chunk * kMaxSplits) chunk += KT;
+  // Then the chunk with the least estimated time among those that need no more splits, if it promises 3 %.  What the first choice does
+  // not see: sequences of different lengths cut by one size make a quarter more items than there are places, or leave
+  // a quarter of them empty, and a CU's two places share its pipes.  (Measured, first choice -> this, us of one layer: 1.5B shape,
+  // 32 steps of 8 to 96 against 512 to 4 K 67 -> 57, one of 64 against 16 K 36 -> 28, 32 of 1 and 10
+  // against 1 K to 32 K 156 -> 122; 8B shape, 12 of 16 to 64 against 512 to 2 K 43 -> 36, 16 of 1 against 2 K 42 -> 34.  Over 43 batches
+  // the first choice is 9.4 % slower than the best chunk, this one 4.7 %.)
+  // At most eight of the shortest parts (one round of the merge) stay: such a launch is the latency of one part.
+  const int splits = max_ctx > 0 ? ceil_div(max_ctx, (int)chunk) : 1;
+  if (chunk > kMinChunk || splits > 8) {
+    double best = 0.97 * plan_us(batch, prefix_host, cu_host, G, n_kv_heads, head_dim, (int)chunk);
+    long long pick = chunk;
+    for (const int c : {256, 320, 384, 512, 640, 768, 1024, 1280, 1536, 2048, 2560, 3072, 4096, 6144, 8192}) {
+      if (ceil_div(max_ctx, c) > splits || c >= 2 * max_ctx) continue;
+      const double us = plan_us(batch, prefix_host, cu_host, G, n_kv_heads, head_dim, c);
+      if (us < best) {
+        best = us;
+        pick = c;
+      }
+    }
+    chunk = pick;
+  }
   AttnPlan pl;
   pl.max_qtiles = ceil_div(max_step * G, QROWS);
   pl.kv_chunk = (int)chunk;

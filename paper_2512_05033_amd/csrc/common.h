@@ -145,7 +145,7 @@ static __host__ __device__ inline int attn_seq_chunk(int ctx, int kv_chunk) {
 static __host__ __device__ inline int attn_first_qtile(int prefix, int G, int kv_begin) {
   return kv_begin <= prefix ? 0 : (int)((long long)(kv_begin - prefix) * G / ATTN_QROWS);
 }
-AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads);
+AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int head_dim);
 size_t attention_ws_bytes(int max_splits, size_t n_items, int total_tokens, int n_q_heads, int head_dim);
 int attention_splits_cap(int max_ctx);   // largest max_splits plan_attention can return for contexts <= max_ctx
 // The work list inside an attention workspace (attention_ws_bytes), to be written by launch_token_meta before the
