@@ -1032,7 +1032,7 @@ __global__ __launch_bounds__(256) void gemm_narrow_kernel(const bf16 *__restrict
 // token.  Ring depth and rows keep a workgroup at 72 to 80 KB (two per CU) where MT allows.
 // Large matrices with a K that fits are the resident-activation kernel's (gemm_few.hip); what is left here are small ones, where the
 // start of a launch is all there is (QKV and O of the 1.5B shape at 16 tokens in four K splits 4.3 and 4.2 us by the kernel trace of
-// a decode step, 4.8 and 4.6 there, unsplit), and unsplit products of a very long K.
+// a decode step, 4.8 and 4.6 there, unsplit; a pass takes them there all the same, fused with what follows), and unsplit products of a very long K.
 __device__ __forceinline__ int lds_off_stream(int row, int chunk) {   // 128-byte rows; 16 lanes read one chunk of 16 rows
   return row * 64 + ((chunk ^ ((row >> 1) & 7)) << 3);
 }

@@ -6,14 +6,15 @@
 // Such a launch reads every weight once, so what bounds it is the memory: how many bytes of weights are in flight, and that
 // nothing else is.  One workgroup of eight waves per CU; a wave owns one eighth of the workgroup's K and keeps the
 // activations of that slice in registers, as MFMA operands, for the whole launch, so that the LDS holds little but weights: a
-// private ring of D stages of 16 rows by 64 k (2 KB) per wave, up to 112 KB per CU in flight, filled by non-temporal direct-to-LDS
+// private ring of D stages of 16 rows by 64 k (2 KB) per wave, 48 to 80 KB per CU in flight, filled by non-temporal direct-to-LDS
 // loads of whole 128-byte lines.  The activations come first through the same ring, and the ring runs on across the 16-row tiles that the workgroup
 // walks through; at the end of a tile the eight partial sums meet in one of two LDS buffers (one barrier per tile, no drain), and
 // the waves take turns in adding them up and storing.  (The kernel before it, gemm_stream_kernel, fetches the activations
 // again for every 32 weight rows, drains at the end of each of its short workgroups, and its launches were 1.09 or 1.75 rounds of them.)
-// By the kernel trace of a pass, us, before and now: 1.5B shape, 16 tokens: gate/up 15.5 -> 13.3, LM head 87.8 -> 81.8; 37 tokens:
-// gate/up 16.8 -> 15.0, down (5 splits) 10.0 -> 9.3; 8B shape, 5 tokens: QKV 12.4 -> 10.5, down 30 -> 20.6, gate/up 39.9 -> 37.2, LM
-// head 193 -> 157 (6.7 TB/s); 40 tokens: O and down together 34.2 -> 34.8 in 4 and 8 splits, QKV 13.6 -> 11.8.
+// By the kernel trace of a pass, us, before and now: 1.5B shape, 16 tokens: gate/up 15.5 -> 13.6, down (5 splits) 7.6 -> 7.0, LM head
+// 87.8 -> 82.7, QKV and the rotary kernel 4.3 + 3.3 -> 5.3, O and the norm 4.2 + 3.5 -> 5.0; 37 tokens: gate/up 16.8 -> 15.0, down
+// 10.0 -> 9.3, QKV 6.2 + 3.5 -> 6.2, O 6.0 + 4.8 -> 6.1; 8B shape, 5 tokens: QKV 12.4 + 4.6 -> 11.9, O 12 + 4.6 -> 8.8, down
+// 30 -> 20.3, gate/up 39.9 -> 39.1, LM head 193 -> 159 (6.6 TB/s).
 #include "common.h"
 
 #include <algorithm>
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(64 * FW, 2) void gemm_few_kernel(const bf16 *__rest
   // A stage is 16 rows by 64 k: load i of it rows 8 i + lane / 8, lane l piece l % 8 (16 bytes), swizzled by the row / 2
   // on the global side.  The first stages of a wave are its activations, 16 tokens each (rows past M repeat the last one and are never
   // stored), the others weights, a unit per load.  A workgroup's last tile may hold one unit, which it then holds twice.  (Activations
-  // loaded straight into registers, in half lines: QKV at 16 / 37 tokens 5.7 / 8.0 us instead of 4.8 / 5.8.)
+  // loaded straight into registers, in half lines: QKV alone at 16 / 37 tokens 5.7 / 8.0 us instead of 4.8 / 5.8.)
   const int lr = lane >> 3;
   const unsigned piece0 = ((lane & 7) ^ ((lr >> 1) & 7)) * 16, piece1 = ((lane & 7) ^ (((lr + 8) >> 1) & 7)) * 16;
   const unsigned unit_rows = (PAIRED ? (lr & 3) + (lr >> 2) * (SWIGLU ? N : fu.head_dim / 2) : lr) * k_bytes;
@@ -337,11 +338,13 @@ arb_status launch_few(const bf16 *A, const bf16 *B, void *C, int M, int N, int K
   const FewSplit split{units / gx, units % gx, K / 64 / gy, K / 64 % gy};
 #define ARB_FEW(MT, NC, D)                                                                                              \
   hipLaunchKernelGGL((gemm_few_kernel<EPI, MT, NC, D>), grid, dim3(64 * FW), 0, st, A, B, C, M, N, K, split, part_stride, fu)
-  // the ring and the two buffers of sums together fill 144 KB
-  if (mt == 1) { if (nc <= 4) ARB_FEW(1, 4, 8); else if (nc <= 8) ARB_FEW(1, 8, 8); else ARB_FEW(1, 16, 8); }
-  else if (mt == 2) { if (nc <= 4) ARB_FEW(2, 4, 7); else ARB_FEW(2, 8, 7); }
-  else if (mt == 3) ARB_FEW(3, 4, 6);
-  else ARB_FEW(4, 4, 5);
+  // Depth of the ring: what covers the memory's latency (a long K: six stages), and no more: the requests in front of the first wait
+  // hold up a short launch.  Passes with nine stages (160 KB with the sums) / eight / six / five, us: 1.5B shape, one token 353 / 350 / 344 / 339,
+  // 16 sequences 520 / 517 / 510 / 507; 8B shape, one token 391 / 387 / 382 / 383, 32 tokens 431 / 432 / 429 / 432.
+  if (mt == 1) { if (nc <= 4) ARB_FEW(1, 4, 5); else if (nc <= 8) ARB_FEW(1, 8, 6); else ARB_FEW(1, 16, 6); }
+  else if (mt == 2) { if (nc <= 4) ARB_FEW(2, 4, 5); else ARB_FEW(2, 8, 6); }
+  else if (mt == 3) ARB_FEW(3, 4, 4);
+  else ARB_FEW(4, 4, 4);
 #undef ARB_FEW
   ARB_CHECK_LAUNCH("gemm_few");
   return ARB_OK;
