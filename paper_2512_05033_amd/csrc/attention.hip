@@ -446,6 +446,7 @@ __global__ __launch_bounds__(256) void attention_merge_kernel(const bf16 *__rest
 
 static const int kTargetWorkgroups = 512;    // two resident workgroups per CU on 256 CUs
 static const int kMinChunk = 256, kMaxChunk = 4096, kMaxChunkDecode = 6144, kMaxSplits = 64;
+static const double kReplanUs = 20;
 static const int kMaxRun = 16;                // longest run of work items on one XCD when there are few runs per XCD
 
 float attention_q_scale(int head_dim) { return (float)(1.4426950408889634 / sqrt((double)head_dim)); }
@@ -464,12 +465,13 @@ int attention_splits_cap(int max_ctx) {
 static double plan_us(int batch, const int32_t *prefix_host, const int32_t *cu_host, int G, int n_kv_heads, int head_dim, int chunk) {
   const double f = head_dim == 128 ? 1.0 : 0.6, item = 4.0, places = kTargetWorkgroups, cus = kTargetWorkgroups / 2;
   double n = 0, work = 0, tiles_all = 0, parts = 0, bytes = 0, shortest = 1e30, alone = 0, shared = 0;
+  const double per_chunk = 1.0 / chunk;
   int max_ctx = 0;
   bool decode = true;
-  for (int b = 0; b < batch; ++b) {
-    const int s = cu_host[b + 1] - cu_host[b], ctx = prefix_host[b] + s, k = attn_seq_chunk(ctx, chunk), ns = ceil_div(ctx, k);
+  for (int b = 0; b < batch; ++b) {                        // without integer divisions: some hundred of these per call
+    const int s = cu_host[b + 1] - cu_host[b], ctx = prefix_host[b] + s, ns = 1 + (int)((ctx - 1) * per_chunk);
     const bool few = (long long)s * G <= 32;
-    const double count = (double)ns * ceil_div(s * G, QROWS) * n_kv_heads, tiles = k / KT, per = few ? 1.5 : 1.15;
+    const double count = (double)ns * ceil_div(s * G, QROWS) * n_kv_heads, tiles = 1 + (int)((ctx - 1) / (double)(ns * KT)), per = few ? 1.5 : 1.15;
     n += count;
     work += count * (tiles * per * f + item / 2);
     tiles_all += count * tiles;
@@ -519,8 +521,10 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
   // the first choice is 9.4 % slower than the best chunk, this one 4.7 %.)
   // At most eight of the shortest parts (one round of the merge) stay: such a launch is the latency of one part.
   const int splits = max_ctx > 0 ? ceil_div(max_ctx, (int)chunk) : 1;
-  if (chunk > kMinChunk || splits > 8) {
-    double best = 0.97 * plan_us(batch, prefix_host, cu_host, G, n_kv_heads, head_dim, (int)chunk);
+  // So does a choice of less than kReplanUs: the estimates themselves take some microseconds of the host, which a short pass waits for.
+  const double first = chunk > kMinChunk || splits > 8 ? plan_us(batch, prefix_host, cu_host, G, n_kv_heads, head_dim, (int)chunk) : 0.0;
+  if (first >= kReplanUs) {
+    double best = 0.97 * first;
     long long pick = chunk;
     for (const int c : {256, 320, 384, 512, 640, 768, 1024, 1280, 1536, 2048, 2560, 3072, 4096, 6144, 8192}) {
       if (ceil_div(max_ctx, c) > splits || c >= 2 * max_ctx) continue;
