@@ -27,7 +27,7 @@ PEAK_HBM_GBS = 8000.0
 # Counter runs of the dominant kernel on workload C2 (profiles/score_steps_C2_hbm_traffic.txt): scaled
 # FETCH_SIZE + WRITE_SIZE bytes per launch, and the SHA-256 of the csrc/gemm.hip they were taken with.
 COUNTED_GATE_UP_BYTES = 75778048 + 16777216
-COUNTED_GEMM_SHA256 = "a3b7b247d9ebeb480a1bed26bc8cb19da6520dd96b6cd32d76dd02fa6fb22347"
+COUNTED_GEMM_SHA256 = "0cf8a2a2f92d87f4bf4e344c3b3f49687e61ffc09375e2a1d23913fbe3b73002"
 
 # Which sequences the CPU oracle recomputes per workload (the rungs of the stated ladder): the whole batch
 # where that takes seconds, else a seeded sub-batch at full depth that includes the extremes.
