@@ -350,7 +350,8 @@ arb_status arb_stage_layers(arb_model *m, const arb_kv *kv, const arb_batch *bat
  * number of launches recorded since arming.  n == 0 disarms. */
 typedef enum {
   ARB_STAGE_QKV = 0, ARB_STAGE_ATTENTION = 1, ARB_STAGE_OPROJ = 2, ARB_STAGE_GATE_UP = 3, ARB_STAGE_DOWN = 4,
-  ARB_STAGE_NORM = 5, ARB_STAGE_ROPE_APPEND = 6,
+  ARB_STAGE_NORM = 5,
+  ARB_STAGE_ROPE_APPEND = 6,  /* an empty interval where the QKV projection rotates and appends itself (few tokens) */
   ARB_STAGE_GATE_UP_LARGE = 7 /* the 256x256-tile kernel of the gate/up projection alone (an empty interval
                                  when arb_gemm_large_tile_columns is 0) */
 } arb_trace_stage;

@@ -420,6 +420,7 @@ static arb_status forward(arb_model *m, const arb_kv *kv, const arb_batch *bt, b
     if (!norms && (s = launch_rmsnorm(w.h, w.parts, parts_of(plan_o), m->g_mlp[l], c.rms_eps, T, d, w.x, st))) return s;
     if (norms) {
       TraceScope t(m, ARB_STAGE_GATE_UP, st);
+      { TraceScope large(m, ARB_STAGE_GATE_UP_LARGE, st); }  // an empty interval, as wherever no large tile runs
       s = launch_gemm_few_gate_up(w.x, m->wgu[l], w.act, T, c.d_ffn, d, few, st);
     } else {
       TraceScope t(m, ARB_STAGE_GATE_UP, st);
