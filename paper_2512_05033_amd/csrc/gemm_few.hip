@@ -42,27 +42,23 @@ inline int few_chunks(int K, int splits) { return ceil_div(ceil_div(K / 64, spli
 
 enum { FEW_BF16, FEW_RESIDUAL, FEW_F32, FEW_SWIGLU, FEW_SCALED_SWIGLU, FEW_ROPE, FEW_NORM };
 
-template <int OFF>
-__device__ __forceinline__ void few_read(unsigned addr, bf16x8 &f) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(f) : "v"(addr), "n"(OFF) : "memory");
-}
-// Register loads (uniform base, lane offset in bytes) whose landing the code below counts itself: the compiler, which does not
-// count the direct-to-LDS loads behind them across a loop, would wait for those as well.
-template <int OFF = 0>
-__device__ __forceinline__ void few_load(const void *base, unsigned off, uint32_t &v) {
-  asm volatile("global_load_dword %0, %1, %2 offset:%3" : "=&v"(v) : "v"(off), "s"(base), "n"(OFF) : "memory");
-}
-template <int OFF = 0, typename T>
-__device__ __forceinline__ void few_load16(const void *base, unsigned off, T &v) {
-  static_assert(sizeof(T) == 16, "16 bytes");
-  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=&v"(v) : "v"(off), "s"(base), "n"(OFF) : "memory");
-}
-// named behind the wait that covers their loads, the registers have no reader in front of it
-__device__ __forceinline__ void few_landed(uint32_t &v) { asm volatile("" : "+v"(v) : : "memory"); }
+// LDS reads that the compiler must not order behind the direct-to-LDS loads in flight (it would wait for all of them); each block
+// waits for its own reads, so that no register is named before it holds its value.
 template <typename T>
-__device__ __forceinline__ void few_landed(T &v0, T &v1) { asm volatile("" : "+v"(v0), "+v"(v1) : : "memory"); }
-__device__ __forceinline__ void few_await(bf16x8 &f0, bf16x8 &f1) {
-  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f0), "+v"(f1) : : "memory");
+__device__ __forceinline__ void few_read(unsigned a0, unsigned a1, T &v0, T &v1) {
+  static_assert(sizeof(T) == 16, "16 bytes");
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v0), "=&v"(v1) : "v"(a0), "v"(a1) : "memory");
+}
+template <typename T>
+__device__ __forceinline__ void few_read(unsigned a0, unsigned a1, unsigned a2, T &v0, T &v1, uint32_t &v2) {
+  static_assert(sizeof(T) == 16, "16 bytes");
+  asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %4\n\tds_read_b32 %2, %5\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(v0), "=&v"(v1), "=&v"(v2) : "v"(a0), "v"(a1), "v"(a2) : "memory");
+}
+__device__ __forceinline__ void few_read4(unsigned a, uint32_t (&v)[4]) {     // 256 bytes apart
+  asm volatile("ds_read_b32 %0, %4\n\tds_read_b32 %1, %4 offset:256\n\tds_read_b32 %2, %4 offset:512\n\t"
+               "ds_read_b32 %3, %4 offset:768\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(a) : "memory");
 }
 
 // Weight rows come in units of eight: eight consecutive rows, or (SwiGLU) four gate rows and their four up rows, or (QKV) four
@@ -77,6 +73,8 @@ __global__ __launch_bounds__(64 * FW, 2) void gemm_few_kernel(const bf16 *__rest
   constexpr int P = 16 * MT, NP = 64 * FW / P;             // padded tokens; threads per token that add up sums of squares
   __shared__ __attribute__((aligned(1024))) char Ring[FW * D * 2048];
   __shared__ __attribute__((aligned(16))) f32x4 Red[2][FW][MT][64];
+  constexpr int SIDE = SCALED ? kSquarePieces * 256 : ROPE ? 2 * 1024 + 256 : NORM ? 2 * 1024 : 0;      // bytes per wave
+  __shared__ __attribute__((aligned(1024))) char Side[SIDE ? FW * SIDE : 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, quarter = lane >> 4, bx = blockIdx.x, by = blockIdx.y;
 
@@ -88,28 +86,30 @@ __global__ __launch_bounds__(64 * FW, 2) void gemm_few_kernel(const bf16 *__rest
   const unsigned k_bytes = (unsigned)K * 2;
   const char *a_base = (const char *)A + (size_t)(kt0 + c0) * 128, *b_base = (const char *)B + (size_t)(kt0 + c0) * 128;
 
-  // Everything that is not a weight is asked for first: loads return in order, so it has landed when the first stage has.
-  uint32_t square[kSquarePieces];
+  // Everything that is not a weight is asked for first, to a place of this wave's in LDS: loads return in order, so it has landed when the
+  // first stage has.
+  char *side = Side + wave * SIDE;
+  const unsigned side_addr = (unsigned)(uintptr_t)LDS_PTR(side);
   if (SCALED) {
-#pragma unroll
-    for (int i = 0; i < kSquarePieces; ++i)
-      few_load(fu.squares, (min(tid / P + i * NP, fu.n_squares - 1) * P + tid % P) * 4, square[i]);
+#pragma unroll 1
+    for (int i = 0; i * NP < fu.n_squares; ++i)             // at most kSquarePieces (gemm_few_norms)
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(fu.squares + min(tid / P + i * NP, fu.n_squares - 1) * P + tid % P), LDS_PTR(side + i * 256), 4, 0, 0);
   }
   // the one item (tile, 16 tokens) that this wave finishes: residual stream and gain, or cosines, sines and pool slot
   f32x4 item[2];
   uint32_t slot;
   if (NORM) {
     const unsigned f = u0 * 8 + quarter * 4;
-    few_load16(fu.h, (min(wave * 16 + r16, M - 1) * N + f) * 4, item[0]);
-    few_load16(fu.gain, f * 4, item[1]);
+    __builtin_amdgcn_global_load_lds(GLOBAL_PTR(fu.h + min(wave * 16 + r16, M - 1) * N + f), LDS_PTR(side), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(GLOBAL_PTR(fu.gain + f), LDS_PTR(side + 1024), 16, 0, 0);
   }
   if (ROPE) {
     const int t = min(wave / MT, tiles - 1), m = min(wave % MT * 16 + r16, M - 1), half = fu.head_dim / 2;
     const int u = u0 + min(2 * t + (lane >> 4 & 1), nu - 1);
-    const unsigned cs = (m * half + (u * 4 & (half - 1))) * 8;
-    few_load16(fu.cs, cs, item[0]);
-    few_load16<16>(fu.cs, cs, item[1]);
-    few_load(fu.tok_slot, m * 4, slot);
+    const f32x2 *cs = fu.cs + m * half + (u * 4 & (half - 1));
+    __builtin_amdgcn_global_load_lds(GLOBAL_PTR(cs), LDS_PTR(side), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(GLOBAL_PTR(cs + 2), LDS_PTR(side + 1024), 16, 0, 0);
+    __builtin_amdgcn_global_load_lds(GLOBAL_PTR(fu.tok_slot + m), LDS_PTR(side + 2048), 4, 0, 0);
   }
   // A stage is 16 rows by 64 k: load i of it rows 8 i + lane / 8, lane l piece l % 8 (16 bytes), swizzled by the row / 2
   // on the global side.  The first stages of a wave are its activations, 16 tokens each (rows past M repeat the last one and are never
@@ -174,9 +174,7 @@ __global__ __launch_bounds__(64 * FW, 2) void gemm_few_kernel(const bf16 *__rest
     else if (behind >= 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm(6));
     else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     __builtin_amdgcn_sched_barrier(0);
-    few_read<0>(addr[0] + s, f0);
-    few_read<0>(addr[1] + s, f1);
-    few_await(f0, f1);
+    few_read(addr[0] + s, addr[1] + s, f0, f1);
     ++done;
     s = s == (D - 1) * 2048 ? 0 : s + 2048;
     __builtin_amdgcn_sched_barrier(0);
@@ -187,8 +185,8 @@ __global__ __launch_bounds__(64 * FW, 2) void gemm_few_kernel(const bf16 *__rest
 #pragma unroll
     for (int c = 0; c < NC; ++c)
       if (c < nc) take(act[c][0][j], act[c][1][j]);
-  if (ROPE || NORM) few_landed(item[0], item[1]);
-  if (ROPE) few_landed(slot);
+  if (NORM) few_read(side_addr + lane * 16, side_addr + 1024 + lane * 16, item[0], item[1]);
+  if (ROPE) few_read(side_addr + lane * 16, side_addr + 1024 + lane * 16, side_addr + 2048 + lane * 4, item[0], item[1], slot);
 
   // 1 / rms of each token's row, from the partial sums of squares that the O projection left (fixed order)
   float inv_rms[MT];
@@ -197,10 +195,12 @@ __global__ __launch_bounds__(64 * FW, 2) void gemm_few_kernel(const bf16 *__rest
   if (SCALED) {
     float *sums = (float *)Red;                             // [P][NP]
     float sq = 0.f;
+#pragma unroll 1
+    for (int i = 0; i * NP < fu.n_squares; i += 4) {        // (of four, the ones past the last hold nothing and are not added)
+      uint32_t square[4];
+      few_read4(side_addr + i * 256 + lane * 4, square);
 #pragma unroll
-    for (int i = 0; i < kSquarePieces; ++i) {
-      few_landed(square[i]);
-      sq += tid / P + i * NP < fu.n_squares ? __uint_as_float(square[i]) : 0.f;
+      for (int k = 0; k < 4; ++k) sq += tid / P + (i + k) * NP < fu.n_squares ? __uint_as_float(square[k]) : 0.f;
     }
     if (tid / P < NP) sums[tid % P * NP + tid / P] = sq;
     __builtin_amdgcn_sched_barrier(0);

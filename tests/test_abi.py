@@ -200,3 +200,15 @@ def test_product_path_does_not_import_the_oracle():
             if f.endswith((".py", ".hip", ".h")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.lower(), f
+
+
+def test_few_token_kernel_names_no_register_before_its_load_has_landed():
+    """The compiler takes the outputs of an asm statement as written when it ends.  A load that is still in flight then can fill a
+    register that has been copied, spilled or given to something else: each asm load of this kernel waits in its own statement."""
+    text = open(os.path.join(ROOT, "paper_2512_05033_amd", "csrc", "gemm_few.hip")).read()
+    loads = [a for a in re.findall(r"asm volatile\((.*?)\);", text, flags=re.S)
+             if re.search(r"(ds_read|ds_load|global_load|buffer_load|flat_load)", a)]
+    assert loads
+    for a in loads:
+        code = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', a.split(": \"=")[0]))
+        assert re.search(r"s_waitcnt [a-z]+cnt\(0\)$", code), a
