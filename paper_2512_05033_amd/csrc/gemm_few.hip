@@ -32,6 +32,7 @@ constexpr int FW = 8;                                    // waves
 constexpr int kFewGrid = 256;                            // one workgroup per CU
 constexpr long long kFewWeights = 8 << 20;               // fewest weights of an unfused launch
 constexpr int kSquarePieces = 16;                        // most partial sums of squares a thread adds up
+constexpr double kStageUs = 0.55;                        // of a CU, for one 16 KB stage (all waves together)
 
 // How a launch divides its units and its chunks of 64 k among the workgroups: so many each, one more for the first few.
 struct FewSplit {
@@ -368,7 +369,7 @@ bool gemm_few_takes(int M, int rows, int K, int splits) {
 }
 
 // K splits of a projection with fp32 partial products, 0 if this kernel does not take it.  The time of a launch goes with the
-// number of 16 KB stages (all waves together) per workgroup, activations included, of which a CU takes one in about 0.55 us; every
+// number of 16 KB stages (all waves together) per workgroup, activations included, of which a CU takes one in about kStageUs; every
 // split costs its consumer another row to read.
 int gemm_few_splits(int M, int N, int K, int max_splits) {
   int best = 0;
@@ -376,7 +377,7 @@ int gemm_few_splits(int M, int N, int K, int max_splits) {
   for (int s = 1; s <= max_splits; ++s) {
     if (!gemm_few_takes(M, N, K, s)) continue;
     const int per = std::max(2, ceil_div(N / 8, kFewGrid / s));          // units of a workgroup
-    const double us = 0.55 * (ceil_div(M, 16) + ceil_div(per, 2)) * K / 64 / s / FW + s * (0.4 + (double)M * N * 8 / 5.0e6);
+    const double us = kStageUs * (ceil_div(M, 16) + ceil_div(per, 2)) * K / 64 / s / FW + s * (0.4 + (double)M * N * 8 / 5.0e6);
     if (best == 0 || us < best_us) {
       best = s;
       best_us = us;
@@ -406,10 +407,15 @@ arb_status launch_gemm_few(const bf16 *A, const bf16 *B, void *C, int M, int N, 
 // QKV: the epilogue holds both partners of a rotary pair, rotates them and writes q, and k and v to their pool slots, so that neither
 // the fp32 products nor the launch that would read them back exist.  Sums are fp32 and q, k are rounded once, after the rotation.  A wave
 // fetches what its one item needs (cosines, sines, slot) at the start; that is the limit on tiles.
+// K is not split here, so a workgroup with a whole tile more than its even share costs that tile's stages.  The alternative, K splits
+// that divide evenly and a rotary kernel, costs a launch: where the uneven share takes more than 4 us of stages, it is the faster one.
+// Passes of 1 / 8 / 16 tokens, us per layer, fused against split: 2.2 us (4096 wide, 6144 QKV rows) 98.1 / 102.3 / 104.1, 99.5 / 104.0 /
+// 104.6; 3.3 us (8192, 2560) 59.7 / 62.6 / 63.5, 59.8 / 63.7 / 64.7; 4.4 us (8192, 10240) 304.4 / 308.3 / 313.2, 303.0 / 307.2 /
+// 312.1; 5.0 us (6144, 5120) 63.3 / 66.0 / 67.1, 61.2 / 65.0 / 66.4; 7.2 us (7680, 8704) 90.9 / 94.8 / 97.1, 89.4 / 93.5 / 94.5.
 bool gemm_few_rotates(int M, int rows, int K) {
   if (!few_fits(M, rows, K, 1)) return false;
-  const int units = rows / 8, per = ceil_div(units, std::min(kFewGrid, ceil_div(units, 2)));
-  return ceil_div(per, 2) * ceil_div(M, 16) <= FW;
+  const int units = rows / 8, tiles = ceil_div(ceil_div(units, std::min(kFewGrid, ceil_div(units, 2))), 2);
+  return tiles * ceil_div(M, 16) <= FW && kStageUs * (tiles - units / (2.0 * kFewGrid)) * K / 64 / FW <= 4.0;
 }
 arb_status launch_gemm_few_qkv(const bf16 *A, const bf16 *B, bf16 *q, int M, int rows, int K, const FewFusion &fu, hipStream_t st) {
   return launch_few<FEW_ROPE>(A, B, q, M, rows, K, dim3(std::min(kFewGrid, ceil_div(rows / 8, 2)), 1), 0, fu, st);
@@ -418,10 +424,21 @@ arb_status launch_gemm_few_qkv(const bf16 *A, const bf16 *B, bf16 *q, int M, int
 // O, the norm and gate/up: the O epilogue adds its sums to the residual stream and stores the new row times the gain, unscaled, with each
 // 16-feature tile's share of the row's sum of squares; every gate/up workgroup adds those up and scales its sums by 1 / rms before the
 // activation.  W (r x) = r (W x) row by row, and x is rounded to bf16 once with or without r, so nothing is rounded more than it was.
-// A workgroup of the O launch has one tile, so that each wave can fetch the stream and the gain of its one item at the start.
+// A workgroup of the O launch has one tile, so that each wave can fetch the stream and the gain of its one item at the start.  So the launch
+// is d / 16 workgroups, each over the whole K, one per CU.  Where they leave CUs idle, in the only round or in the second, K splits
+// and a norm kernel can be faster; by the stages that an even division would save, the line lies at 3.1 us in one round (from 96 workgroups
+// on the launch has the memory's rate all the same) and at 2.1 us with a second.  Passes of 1 / 8 / 16 tokens, us per layer, fused against split:
+// one round, 3.0 us (1280 wide, 4096 of attention) 31.0 / 32.9 / 34.7, 30.5 / 33.6 / 35.4; 3.3 us (1024, 4096) 30.0 / 31.8 / 33.4,
+// 29.0 / 30.9 / 32.8; 6.6 us (1024, 8192) 35.3 / 37.1 / 39.3, 32.4 / 34.5 / 37.0; 96 workgroups, 2.8 us (1536, 4096) 31.0 / 33.2 / 35.2,
+// 32.8 / 35.4 / 37.5; two rounds, 1.4 us (6144, 2560) 54.1 / 56.2 / 57.7, 54.5 / 56.8 / 58.0; 2.5 us (5120, 3072) 51.1 / 52.7 /
+// 55.0, 50.3 / 52.4 / 54.7; 4.1 us (5120, 5120) 62.2 / 65.3 / 66.8, 59.9 / 63.8 / 64.5; 0 us (8192, 8192) 304.4 / 308.3 / 313.2,
+// 305.9 / 309.6 / 313.4.
 bool gemm_few_norms(int M, int d, int hq, int F) {
   const int pieces = 64 * FW / (16 * ceil_div(M, 16)) * kSquarePieces;     // partial sums that a gate/up workgroup can add up per token
-  return few_fits(M, d, hq, 1) && few_fits(M, 2 * F, d, 1) && d / 16 <= pieces;
+  if (!few_fits(M, d, hq, 1) || !few_fits(M, 2 * F, d, 1) || d / 16 > pieces) return false;
+  const int workgroups = d / 16, rounds = ceil_div(workgroups, kFewGrid);
+  const double idle_us = kStageUs * (rounds - workgroups / (double)kFewGrid) * hq / 64 / FW;
+  return rounds == 1 ? workgroups >= 96 || idle_us <= 3.1 : idle_us <= 2.1;
 }
 arb_status launch_gemm_few_o(const bf16 *A, const bf16 *B, bf16 *x, int M, int d, int hq, const FewFusion &fu, hipStream_t st) {
   return launch_few<FEW_NORM>(A, B, x, M, d, hq, dim3(d / 16, 1), 0, fu, st);

@@ -212,3 +212,30 @@ def test_few_token_kernel_names_no_register_before_its_load_has_landed():
     for a in loads:
         code = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', a.split(": \"=")[0]))
         assert re.search(r"s_waitcnt [a-z]+cnt\(0\)$", code), a
+
+
+def _internal(lib, mangled, argtypes, restype=C.c_bool):
+    """A host function of the library that the header does not declare."""
+    f = getattr(lib, mangled)
+    f.argtypes, f.restype = argtypes, restype
+    return f
+
+
+@pytest.mark.parametrize("tokens", [1, 8, 16])
+@pytest.mark.parametrize("d,hq,fused", [(1024, 1024, True), (1024, 3072, True), (1024, 4096, False), (1024, 8192, False),      # 64 workgroups
+                                        (1280, 4096, True), (1408, 8192, False), (1536, 4096, True), (2048, 8192, True),       # 80, 88, 96, 128
+                                        (4096, 4096, True), (4096, 8192, True),                    # one full round
+                                        (4224, 4224, False), (5120, 2560, True), (5120, 5120, False), (6144, 1024, True),
+                                        (6144, 6144, False), (7168, 4096, True), (8192, 8192, True)])
+def test_fused_o_projection_only_where_it_is_the_faster_one(lib, tokens, d, hq, fused):
+    """One workgroup per 16 features and CU, each over the whole K: not where idle CUs cost more than a norm kernel."""
+    assert _internal(lib, "_Z14gemm_few_normsiiii", [C.c_int] * 4)(tokens, d, hq, 2048) == fused
+
+
+@pytest.mark.parametrize("tokens", [1, 8, 16])
+@pytest.mark.parametrize("d,rows,fused", [(1024, 1280, True), (1024, 10240, True), (1536, 2048, True), (4096, 6144, True), (4096, 10240, True),
+                                          (6144, 8192, True), (6144, 5120, False), (6656, 7680, True), (7168, 2560, True),
+                                          (7168, 9216, False), (8192, 2560, True), (8192, 1280, False), (8192, 10240, False)])
+def test_fused_qkv_projection_only_where_it_is_the_faster_one(lib, tokens, d, rows, fused):
+    """K is not split there: not where the workgroups' uneven shares of the rows cost more than a rotary kernel."""
+    assert _internal(lib, "_Z16gemm_few_rotatesiii", [C.c_int] * 3)(tokens, rows, d) == fused
