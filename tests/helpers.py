@@ -1,6 +1,8 @@
 """Glue between the seeded workloads and the oracle's plain-array interface."""
 from __future__ import annotations
 
+import ctypes as C
+
 import numpy as np
 
 import workloads as W
@@ -74,3 +76,36 @@ def rel_err(got: np.ndarray, ref: np.ndarray) -> float:
 def rms_err(got: np.ndarray, ref: np.ndarray) -> float:
     """sqrt(mean (got - ref)^2 / mean ref^2)."""
     return float(np.sqrt(np.mean((got.astype(np.float64) - ref) ** 2) / np.mean(ref ** 2)))
+
+
+class AttentionPlan(C.Structure):
+    _fields_ = [("kv_chunk", C.c_int), ("max_splits", C.c_int), ("max_qtiles", C.c_int), ("n_items", C.c_int)]
+
+
+def attention_plan(lib, m: W.ModelShape, prefix, steps) -> AttentionPlan:
+    """What the library plans for an attention launch over this batch (a host function that the header does not declare)."""
+    f = lib._Z14plan_attentioniPKiS0_iii
+    f.restype, f.argtypes = AttentionPlan, [C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int]
+    p, cu = np.asarray(prefix, np.int32), np.concatenate([[0], np.cumsum(steps)]).astype(np.int32)
+    return f(len(p), p.ctypes.data, cu.ctypes.data, m.group, m.n_kv_heads, m.head_dim)
+
+
+def first_attention_chunk(m: W.ModelShape, prefix, steps) -> int:
+    """Keys per split before any estimate: about 512 workgroups, between 256 keys and 4096 (6144 where every step is one wave)."""
+    keys = sum(-(-s * m.group // 128) * m.n_kv_heads * (p + s) for p, s in zip(prefix, steps))
+    chunk = -(-(keys // 512) // 64) * 64
+    chunk = max(256, min(chunk, 6144 if max(steps) * m.group <= 32 else 4096))
+    longest = max(p + s for p, s in zip(prefix, steps))
+    while longest > 64 * chunk:
+        chunk += 64
+    return chunk
+
+
+# Batches for which the planner leaves that choice.
+REPLANNED = [
+    (W.ROUTER_1P5B, [16384], [64]),                          # one long context
+    (W.TARGET_8B, [2048] * 16, [1] * 16),                    # one token each: a full round instead of a round and a quarter
+    (W.ROUTER_1P5B, [2048] * 16, [1] * 16),
+    (W.ROUTER_1P5B, [3119, 4555, 5707, 305, 950, 4955], [94, 25, 31, 87, 42, 28]),       # ragged
+    (W.TARGET_8B, [5002, 3954, 2229], [9, 70, 35]),
+    (W.TINY, [3060, 1467, 3282, 4631, 901, 1897, 1907, 4806, 3517, 2456, 4768], [97, 15, 89, 23, 64, 94, 40, 66, 36, 76, 49])]

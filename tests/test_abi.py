@@ -8,6 +8,9 @@ import re
 import numpy as np
 import pytest
 
+import workloads as W
+from helpers import REPLANNED, attention_plan, first_attention_chunk
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -239,3 +242,41 @@ def test_fused_o_projection_only_where_it_is_the_faster_one(lib, tokens, d, hq, 
 def test_fused_qkv_projection_only_where_it_is_the_faster_one(lib, tokens, d, rows, fused):
     """K is not split there: not where the workgroups' uneven shares of the rows cost more than a rotary kernel."""
     assert _internal(lib, "_Z16gemm_few_rotatesiii", [C.c_int] * 3)(tokens, rows, d) == fused
+
+
+def _items(m, plan, prefix, steps):
+    """(sequence, split, kv head, query tile) with at least one visible key, as the work list counts them."""
+    n = 0
+    for p, s in zip(prefix, steps):
+        parts = -(-(p + s) // plan.kv_chunk)
+        part = -(-(-(-(p + s) // parts)) // 64) * 64
+        tiles = -(-s * m.group // 128)
+        for begin in range(0, p + s, part):
+            n += (tiles - (max(0, begin - p) * m.group) // 128) * m.n_kv_heads
+    return n
+
+
+@pytest.mark.parametrize("m,prefix,steps", REPLANNED)
+def test_the_attention_planner_leaves_its_first_choice(lib, m, prefix, steps):
+    """Each of these batches is cut otherwise than the number of places alone would have it."""
+    plan, first = attention_plan(lib, m, prefix, steps), first_attention_chunk(m, prefix, steps)
+    assert plan.kv_chunk != first
+
+
+def test_the_attention_planner_never_needs_more_scratch_than_its_first_choice(lib):
+    """Whatever the estimates say: whole tiles of keys, no more splits than the first choice needs (a caller's scratch is sized by them),
+    and the items that belong to the chunk."""
+    r = np.random.default_rng(17)
+    moved = 0
+    for m in (W.TINY, W.ROUTER_1P5B, W.TARGET_8B):
+        for _ in range(150):
+            n = int(r.integers(1, 40))
+            prefix = [int(v) for v in r.integers(0, int(np.exp(r.uniform(3, 10.5))), n)]
+            steps = [int(v) for v in r.integers(1, int(r.choice([2, 9, 129])), n)]
+            plan, first = attention_plan(lib, m, prefix, steps), first_attention_chunk(m, prefix, steps)
+            longest = max(p + s for p, s in zip(prefix, steps))
+            moved += plan.kv_chunk != first
+            assert plan.kv_chunk % 64 == 0 and plan.max_splits == -(-longest // plan.kv_chunk) <= -(-longest // first)
+            assert plan.max_splits <= _internal(lib, "_Z20attention_splits_capi", [C.c_int], C.c_int)(longest)
+            assert plan.n_items == _items(m, plan, prefix, steps)
+    assert moved >= 20
