@@ -518,7 +518,9 @@ AttnPlan plan_attention(int batch, const int32_t *prefix_host, const int32_t *cu
   // a quarter of them empty, and a CU's two places share its pipes.  (Measured, first choice -> this, us of one layer: 1.5B shape,
   // 32 steps of 8 to 96 against 512 to 4 K 67 -> 57, one of 64 against 16 K 36 -> 28, 32 of 1 and 10
   // against 1 K to 32 K 156 -> 122; 8B shape, 12 of 16 to 64 against 512 to 2 K 43 -> 36, 16 of 1 against 2 K 42 -> 34.  Over 43 batches
-  // the first choice is 9.4 % slower than the best chunk, this one 4.7 %.)
+  // the first choice is 9.4 % slower than the best chunk, this one 4.7 %.  Estimates miss: of 161 other batches that they move, 110 got faster by
+  // more than 2 % and at best 32, 23 slower by more than 2 % and at worst 14, most of those many one-token steps on ragged contexts; 7 %
+  // on the geometric mean.)
   // At most eight of the shortest parts (one round of the merge) stay: such a launch is the latency of one part.
   const int splits = max_ctx > 0 ? ceil_div(max_ctx, (int)chunk) : 1;
   // So does a choice of less than kReplanUs: the estimates themselves take some microseconds of the host, which a short pass waits for.

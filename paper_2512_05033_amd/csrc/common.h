@@ -94,12 +94,12 @@ arb_status launch_gemm(const bf16 *A, const bf16 *B, void *C, int M, int N, int 
 arb_status launch_pack_k_blocked(const bf16 *W, size_t rows, int K, bf16 *packed, hipStream_t st);
 int gemm_large_cols(int M, int N, int K, int epilogue, int splits);   // in units of 256 columns (128 SwiGLU features)
 int gemm_residual_splits(int M, int N, int K);
-int gemm_stream_splits(int M, int N, int K);   // K splits of an fp32 projection on the few-token kernel; 0: another kernel takes it
+int gemm_stream_splits(int M, int N, int K);   // K splits of an fp32 projection on the weight-streaming kernel; 0: another kernel takes it
 
 // gemm_few.hip
-// What a projection of few token rows does beyond its product; all pointers null for the product alone.
+// What a projection of few token rows does beyond its product.  Which of these a launch uses follows from its launcher; the others are not looked at.
 struct FewFusion {
-  const float *squares;                  // SwiGLU: partial sums of squares [n_squares][padded tokens] of unscaled rows (null: rows are scaled)
+  const float *squares;                  // launch_gemm_few_gate_up: partial sums of squares [n_squares][padded tokens] of its unscaled rows
   int n_squares;
   float eps;
   float *h, *squares_out;                // O projection: the residual stream, and where the sums of squares of its rows go

@@ -4,17 +4,18 @@
 // on as unscaled rows with their sums of squares.
 //
 // Such a launch reads every weight once, so what bounds it is the memory: how many bytes of weights are in flight, and that
-// nothing else is.  One workgroup of eight waves per CU; a wave owns one eighth of the workgroup's K and keeps the
+// nothing else is.  One workgroup of eight waves per CU at a time (the O launch of a model wider than 4096 is two
+// rounds of them); a wave owns one eighth of the workgroup's K and keeps the
 // activations of that slice in registers, as MFMA operands, for the whole launch, so that the LDS holds little but weights: a
 // private ring of D stages of 16 rows by 64 k (2 KB) per wave, 48 to 80 KB per CU in flight, filled by non-temporal direct-to-LDS
 // loads of whole 128-byte lines.  The activations come first through the same ring, and the ring runs on across the 16-row tiles that the workgroup
-// walks through; at the end of a tile the eight partial sums meet in one of two LDS buffers (one barrier per tile, no drain), and
-// the waves take turns in adding them up and storing.  (The kernel before it, gemm_stream_kernel, fetches the activations
+// walks through; at the end of a tile the eight partial sums meet in one of two LDS buffers (one barrier per tile, behind which the others
+// go on), and the waves take turns in adding them up and storing (the compiler has that wave wait for its own ring first).  (The kernel before it, gemm_stream_kernel, fetches the activations
 // again for every 32 weight rows, drains at the end of each of its short workgroups, and its launches were 1.09 or 1.75 rounds of them.)
-// By the kernel trace of a pass, us, before and now: 1.5B shape, 16 tokens: gate/up 15.5 -> 13.6, down (5 splits) 7.6 -> 7.0, LM head
-// 87.8 -> 82.7, QKV and the rotary kernel 4.3 + 3.3 -> 5.3, O and the norm 4.2 + 3.5 -> 5.0; 37 tokens: gate/up 16.8 -> 15.0, down
-// 10.0 -> 9.3, QKV 6.2 + 3.5 -> 6.2, O 6.0 + 4.8 -> 6.1; 8B shape, 5 tokens: QKV 12.4 + 4.6 -> 11.9, O 12 + 4.6 -> 8.8, down
-// 30 -> 20.3, gate/up 39.9 -> 39.1, LM head 193 -> 159 (6.6 TB/s).
+// By the kernel trace of a pass, us, with that kernel and now: 1.5B shape, 16 tokens: gate/up 15.5 -> 13.7, down (5 splits) 7.6 -> 7.1, LM head
+// 87.8 -> 82.2, QKV and the rotary kernel 4.3 + 3.3 -> 5.4, O and the norm 4.2 + 3.5 -> 5.0; 37 tokens: gate/up 16.8 -> 15.2, down
+// 10.0 -> 9.1, QKV 6.2 + 3.5 -> 6.3, O 6.0 + 4.8 -> 6.1; 8B shape, 5 tokens: QKV 12.4 + 4.6 -> 11.7, O 12 + 4.6 -> 8.7, down
+// 30 -> 20.3, gate/up 39.9 -> 38.7, LM head 193 -> 165 (6.4 TB/s).
 #include "common.h"
 
 #include <algorithm>
